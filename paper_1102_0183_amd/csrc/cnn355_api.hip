@@ -45,7 +45,6 @@ hipError_t launch_batch_outputs(hipStream_t stream, const float* logits, float* 
                                 int n_classes, int out_units);
 hipError_t launch_batch_pack(hipStream_t stream, const BatchPack& q, long long wt_floats);
 hipError_t launch_deform(hipStream_t stream, const DeformJob& J);
-size_t deform_lds_bytes(const DeformJob& J);
 }  // namespace cnn355
 
 using namespace cnn355;
@@ -1989,9 +1988,12 @@ int cnn_deform_images(void* hip_stream, const float* d_src, size_t n_src, float*
   J.n = (long long)n; J.n_src = (long long)n_src; J.C = C; J.H = H; J.W = W;
   J.max_tx = (double)p->max_translation * W;
   J.max_ty = (double)p->max_translation * H;
-  J.max_rot = (double)p->max_rotation * 3.14159265358979323846 / 180.0;
+  J.max_rot = (double)p->max_rotation / 180.0;
   J.max_shear = p->max_shear; J.max_scale = p->max_scaling; J.alpha = p->alpha; J.fill = p->fill;
   J.seed = seed; J.first_index = first_index;
+  // |A - I| is at most 3 and 2 (1 + max_shear), the smoothed fields stay within [-1, 1]
+  const double reach = 2.0 * (1.0 + J.max_shear) + 3.0;
+  J.fixed = J.max_tx + J.max_ty + reach * (H + W) + std::fabs((double)J.alpha) < (double)(1 << 18);
   J.R = -1;
   for (float& t : J.taps) t = 0.f;
   if (p->sigma > 0.f && p->alpha != 0.f) {

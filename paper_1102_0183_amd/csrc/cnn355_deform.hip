@@ -27,7 +27,11 @@ __device__ __forceinline__ unsigned long long mix64(unsigned long long z) {
 }
 
 // 32 random bits -> [-1, 1) in steps of 2^-23
-__device__ __forceinline__ float sym(unsigned int bits) { return (float)(bits >> 8) * (2.0f / 16777216.0f) - 1.0f; }
+// (the bits opaque: half of a 64-bit number, they would be converted as 64 bits)
+__device__ __forceinline__ float sym(unsigned int bits) {
+  asm("" : "+v"(bits));
+  return (float)(bits >> 8) * (2.0f / 16777216.0f) - 1.0f;
+}
 
 constexpr int SW = 4;    // outputs of one lane along the line being smoothed
 
@@ -59,8 +63,148 @@ __device__ __forceinline__ void blur_strip(const float* ax, const float* ay, int
   }
 }
 
+// The affine part of presentation k: displacement = (A - I) (u, v) + (tx, ty), A = Rot . Shear . Scale.
+// (In double: the products reach tens of pixels on large maps, where a float keeps 1e-5 of a pixel at best.)
+struct Affine {
+  double a00, a01, a10, a11, tx, ty;
+};
+__device__ __forceinline__ unsigned long long presentation_key(const DeformJob& J, long long k) {
+  return mix64(J.seed + GOLDEN * (J.first_index + (unsigned long long)k + 1ull));
+}
+__device__ __forceinline__ Affine draw_affine(const DeformJob& J, unsigned long long key) {
+  const unsigned long long d0 = mix64(key + GOLDEN * 1ull), d1 = mix64(key + GOLDEN * 2ull), d2 = mix64(key + GOLDEN * 3ull);
+  const double theta = sym((unsigned int)(d1 >> 32)) * J.max_rot, sh = sym((unsigned int)d1) * J.max_shear;
+  const double sx = 1.0 + sym((unsigned int)(d2 >> 32)) * J.max_scale, sy = 1.0 + sym((unsigned int)d2) * J.max_scale;
+  double sn, cs;
+  sincospi(theta, &sn, &cs);
+  Affine A;
+  A.tx = sym((unsigned int)(d0 >> 32)) * J.max_tx;
+  A.ty = sym((unsigned int)d0) * J.max_ty;
+  A.a00 = cs * sx - 1.0;
+  A.a01 = (cs * sh - sn) * sy;
+  A.a10 = sn * sx;
+  A.a11 = (sn * sh + cs) * sy - 1.0;
+  return A;
+}
+
+// The affine parts of a workgroup's next AFF images (blockIdx.x + gridDim.x i), one a lane: a sine and cosine in double
+// cost more than a wavefront's share of a small image's pixels, and 64 lanes would work out the same ones.
+constexpr int AFF = 16;
+__device__ __forceinline__ const Affine& affine_of(const DeformJob& J, Affine* ring, long long k, int i) {
+  if ((i & (AFF - 1)) == 0) {
+    __syncthreads();  // the previous ones have been read
+    const long long q = k + (long long)threadIdx.x * gridDim.x;
+    if (threadIdx.x < AFF && q < J.n) ring[threadIdx.x] = draw_affine(J, presentation_key(J, q));
+    __syncthreads();
+  }
+  return ring[i & (AFF - 1)];
+}
+
+// Where presentation k reads and writes; an index that names no source image gives an image of `fill`.
+struct Image {
+  const CNN_GLOBAL char* src;
+  CNN_GLOBAL char* dst;
+  long long k;
+  bool known;
+};
+__device__ __forceinline__ Image image_of(const DeformJob& J, long long k) {
+  const long long sz = (long long)J.C * (J.H * J.W);
+  long long s = J.src_index ? (long long)__builtin_amdgcn_readfirstlane(J.src_index[k]) : k;
+  const bool known = s >= 0 && s < J.n_src;
+  if (!known) s = 0;
+  return Image{(const CNN_GLOBAL char*)(J.src + s * sz), (CNN_GLOBAL char*)(J.dst + k * sz), k, known};
+}
+
+// N pixels (x[i], y[i]) of a lane, displaced by ax[i] + ex[i] and ay[i] + ey[i] (the affine map's share and the elastic
+// part); fax = ax + FIX, fay = ay + FIX; pixels with !ok[i] are worked out and not written.  All loads of a map are in flight together, then the stores
+// (a load behind a store waits for the store too).  A neighbour outside reads the image's first pixel and takes `fill`.
+// The source position's whole part and fraction come out of one addition: below 2^19 pixels (J.fixed: the host has
+// bounded every term) the sum plus 1.5 * 2^20 has the fraction as the low word of the double, in steps of 2^-32,
+// and the whole part, floored, in the high word.  RARE: the caller wants the displacements, or they are unbounded.
+constexpr double FIX = 1572864.0;          // 1.5 * 2^20
+constexpr int FIX_HI = 0x41380000;         // its high word
+template <int N, bool ELASTIC, bool RARE>
+__device__ __forceinline__ void sample_pixels(const DeformJob& J, const Image& im, const int (&x)[N], const int (&y)[N],
+                                              const bool (&ok)[N], const double (&fax)[N], const double (&fay)[N],
+                                              const double (&ax)[N], const double (&ay)[N], const float (&ex)[N], const float (&ey)[N]) {
+  const int H = J.H, W = J.W;
+  float fx[N], fy[N];
+  int x0[N], y0[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (!RARE || J.fixed) {
+      double px = fax[i], py = fay[i];
+      if (ELASTIC) { px += (double)ex[i]; py += (double)ey[i]; }
+      x0[i] = x[i] + (__double2hiint(px) - FIX_HI);
+      y0[i] = y[i] + (__double2hiint(py) - FIX_HI);
+      fx[i] = (float)(unsigned int)__double2loint(px) * 2.3283064365386963e-10f;   // 2^-32
+      fy[i] = (float)(unsigned int)__double2loint(py) * 2.3283064365386963e-10f;
+    }
+    if (RARE) {
+      double dx = ax[i], dy = ay[i];
+      if (ELASTIC) { dx += (double)ex[i]; dy += (double)ey[i]; }
+      if (!J.fixed) {
+        // far outside in any direction reads the fill value only; the clamp keeps the integers small
+        const double fdx = floor(fmin(fmax(dx, -(double)(W + 2)), (double)(W + 2)));
+        const double fdy = floor(fmin(fmax(dy, -(double)(H + 2)), (double)(H + 2)));
+        fx[i] = fminf(fmaxf((float)(dx - fdx), 0.f), 1.f);
+        fy[i] = fminf(fmaxf((float)(dy - fdy), 0.f), 1.f);
+        x0[i] = x[i] + (int)fdx;
+        y0[i] = y[i] + (int)fdy;
+      }
+      if (J.disp && ok[i]) {
+        J.disp[(im.k * 2) * (H * W) + y[i] * W + x[i]] = (float)dx;
+        J.disp[(im.k * 2 + 1) * (H * W) + y[i] * W + x[i]] = (float)dy;
+      }
+    }
+  }
+  bool in00[N], in01[N], in10[N], in11[N];
+  unsigned int o00[N], o01[N], o10[N], o11[N], od[N];  // bytes
+  float w00[N], w01[N], w10[N], w11[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const bool in_x0 = (unsigned int)x0[i] < (unsigned int)W, in_x1 = (unsigned int)(x0[i] + 1) < (unsigned int)W;
+    const bool in_y0 = (unsigned int)y0[i] < (unsigned int)H, in_y1 = (unsigned int)(y0[i] + 1) < (unsigned int)H;
+    in00[i] = in_y0 && in_x0; in01[i] = in_y0 && in_x1; in10[i] = in_y1 && in_x0; in11[i] = in_y1 && in_x1;
+    const unsigned int at = (unsigned int)(__mul24(y0[i], W) + x0[i]) * 4u, row = (unsigned int)W * 4u;
+    o00[i] = in00[i] ? at : 0u; o01[i] = in01[i] ? at + 4u : 0u;
+    o10[i] = in10[i] ? at + row : 0u; o11[i] = in11[i] ? at + row + 4u : 0u;
+    od[i] = (unsigned int)(__mul24(y[i], W) + x[i]) * 4u;
+    w00[i] = (1.f - fy[i]) * (1.f - fx[i]); w01[i] = (1.f - fy[i]) * fx[i]; w10[i] = fy[i] * (1.f - fx[i]); w11[i] = fy[i] * fx[i];
+  }
+  const unsigned int map_bytes = (unsigned int)(H * W) * 4u;
+  const CNN_GLOBAL char* m = im.src;
+  CNN_GLOBAL char* o = im.dst;
+  for (int c = 0; c < J.C; ++c, m += map_bytes, o += map_bytes) {
+    float v00[N], v01[N], v10[N], v11[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      // (opaque here, so that the address stays a uniform base and a 32-bit offset and no 64-bit sum per lane)
+      asm("" : "+v"(o00[i]), "+v"(o01[i]), "+v"(o10[i]), "+v"(o11[i]), "+v"(od[i]));
+      v00[i] = *(const CNN_GLOBAL float*)(m + o00[i]);
+      v01[i] = *(const CNN_GLOBAL float*)(m + o01[i]);
+      v10[i] = *(const CNN_GLOBAL float*)(m + o10[i]);
+      v11[i] = *(const CNN_GLOBAL float*)(m + o11[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const float a = in00[i] ? v00[i] : J.fill, b = in01[i] ? v01[i] : J.fill;
+      const float d = in10[i] ? v10[i] : J.fill, e = in11[i] ? v11[i] : J.fill;
+      v00[i] = im.known ? fmaf(w00[i], a, fmaf(w01[i], b, fmaf(w10[i], d, w11[i] * e))) : J.fill;
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (ok[i]) *(CNN_GLOBAL float*)(o + od[i]) = v00[i];
+  }
+}
+
+// A lane PXL pixels at a time (all their loads in flight: bound by latency without smoothing, 60000 translated 1x29x29
+// images 240 -> 148 us, 2.7 TB/s; one where a map has no more pixels than lanes).  The smoothing (ELASTIC) as sums over a
+// line, a strip of outputs a lane: for maps k_deform_mx would be mostly padding on.
+template <int PXL, bool ELASTIC, bool RARE>
 __global__ void __launch_bounds__(DT) k_deform(const DeformJob J) {
   extern __shared__ float lds[];
+  __shared__ Affine ring[AFF];
   const int H = J.H, W = J.W, HW = H * W, R = J.R;
   const int Wp = W | 1;       // odd row pitch: lanes on consecutive rows fall on different LDS banks
   float* rx = lds;            // [H][Wp] random fields, then the smoothed ones
@@ -70,27 +214,20 @@ __global__ void __launch_bounds__(DT) k_deform(const DeformJob J) {
   float* taps = lds + 4 * H * Wp; // [R + SW zeros][2R + 1 taps][R + SW zeros]
   const float* tp = taps + 2 * R + SW;  // the centre tap
   const int tid = threadIdx.x;
-  const bool elastic = R >= 0;
-  if (elastic) {
+  if constexpr (ELASTIC) {
     for (int i = tid; i < 4 * R + 2 * SW + 1; i += DT) {
       const int q = i - (R + SW);
       taps[i] = q >= 0 && q <= 2 * R ? J.taps[q] : 0.f;
     }
   }
-  const float cx = 0.5f * (float)(W - 1), cy = 0.5f * (float)(H - 1);
-  for (long long k = blockIdx.x; k < J.n; k += gridDim.x) {
-    const unsigned long long key = mix64(J.seed + GOLDEN * (J.first_index + (unsigned long long)k + 1ull));
-    // ---- the affine part: displacement = (A - I) (u, v) + (tx, ty), A = Rot . Shear . Scale
-    const unsigned long long d0 = mix64(key + GOLDEN * 1ull), d1 = mix64(key + GOLDEN * 2ull), d2 = mix64(key + GOLDEN * 3ull);
-    // (in double: the products reach tens of pixels on large maps, where a float keeps 1e-5 of a pixel at best)
-    const double tx = sym((unsigned int)(d0 >> 32)) * J.max_tx, ty = sym((unsigned int)d0) * J.max_ty;
-    const double theta = sym((unsigned int)(d1 >> 32)) * J.max_rot, sh = sym((unsigned int)d1) * J.max_shear;
-    const double sx = 1.0 + sym((unsigned int)(d2 >> 32)) * J.max_scale, sy = 1.0 + sym((unsigned int)d2) * J.max_scale;
-    double sn, cs;
-    sincos(theta, &sn, &cs);
-    const double a00 = cs * sx - 1.0, a01 = (cs * sh - sn) * sy, a10 = sn * sx, a11 = (sn * sh + cs) * sy - 1.0;
+  const double cx = 0.5 * (double)(W - 1), cy = 0.5 * (double)(H - 1);
+  const int step_y = DT / W, step_x = DT - step_y * W, first_y = tid / W, first_x = tid - first_y * W;
+  int i = 0;
+  for (long long k = blockIdx.x; k < J.n; k += gridDim.x, ++i) {
+    const unsigned long long key = presentation_key(J, k);
+    const Affine A = affine_of(J, ring, k, i);
     // ---- the elastic part: two random fields, smoothed along rows, then along columns
-    if (elastic) {
+    if constexpr (ELASTIC) {
       __syncthreads();  // the previous image's fields have been read
       unsigned long long ctr = key + GOLDEN * (unsigned long long)(tid + 4);
       for (int p = tid; p < HW; p += DT, ctr += GOLDEN * (unsigned long long)DT) {
@@ -127,40 +264,153 @@ __global__ void __launch_bounds__(DT) k_deform(const DeformJob J) {
       __syncthreads();
     }
     // ---- sample the source
-    long long s = J.src_index ? (long long)J.src_index[k] : k;
-    const bool known = s >= 0 && s < J.n_src;  // an index that names no source image gives an image of `fill`
-    if (!known) s = 0;
-    const CNN_GLOBAL float* src = J.src + s * J.C * HW;
-    CNN_GLOBAL float* dst = J.dst + k * J.C * HW;
-    for (int p = tid; p < HW; p += DT) {
-      const int y = p / W, x = p - y * W;
-      const double u = (double)x - (double)cx, v = (double)y - (double)cy;
-      double dx = fma(a00, u, fma(a01, v, tx)), dy = fma(a10, u, fma(a11, v, ty));
-      if (elastic) {
-        dx += (double)(J.alpha * rx[y * Wp + x]);
-        dy += (double)(J.alpha * ry[y * Wp + x]);
+    const Image im = image_of(J, k);
+    int x = first_x, y = first_y;
+    for (int p = tid; p < HW; p += PXL * DT) {
+      int px[PXL], py[PXL];
+      bool ok[PXL];
+      double ax[PXL], ay[PXL], fax[PXL], fay[PXL];
+      float ex[PXL], ey[PXL];
+#pragma unroll
+      for (int q = 0; q < PXL; ++q) {
+        px[q] = x;
+        py[q] = y;
+        ok[q] = p + q * DT < HW;
+        const double u = (double)x - cx, v = (double)y - cy;
+        ax[q] = fma(A.a00, u, fma(A.a01, v, A.tx));
+        ay[q] = fma(A.a10, u, fma(A.a11, v, A.ty));
+        fax[q] = fma(A.a00, u, fma(A.a01, v, A.tx + FIX));
+        fay[q] = fma(A.a10, u, fma(A.a11, v, A.ty + FIX));
+        const int at = ok[q] ? y * Wp + x : 0;
+        ex[q] = ELASTIC ? J.alpha * rx[at] : 0.f;
+        ey[q] = ELASTIC ? J.alpha * ry[at] : 0.f;
+        x += step_x;
+        y += step_y;
+        if (x >= W) { x -= W; ++y; }
       }
-      if (J.disp) {
-        J.disp[(k * 2) * HW + p] = (float)dx;
-        J.disp[(k * 2 + 1) * HW + p] = (float)dy;
+      sample_pixels<PXL, ELASTIC, RARE>(J, im, px, py, ok, fax, fay, ax, ay, ex, ey);
+    }
+  }
+}
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// The same deformation with the Gaussian on the matrix cores: smoothing along a row is a product with the banded
+// matrix G[j][x] = tap[j - x], smoothing along a column one with its transpose, both in tiles of 16 x 16
+// (v_mfma_f32_16x16x4_f32: fp32 in, fp32 sums).  A wavefront takes a strip of 16 columns and walks down it:
+//   rows:    Hx[yt][xt]  = sum over d of  Rand[yt][xt + d] . G_d
+//   columns: V[yt - d]  += G_d' . Hx[yt]                          |d| <= D (further tiles are all zero or outside)
+// Lane l = 16 g + c holds element k = 4 g + v of an operand's contraction at step v = 0 .. 3.  With that order a tile of
+// Hx leaves the first product in the very registers the second one reads it from, and G_d is the same four registers in
+// both (a tap depends on j - x alone), loaded once per workgroup.  Only the random fields pass through LDS: every one of
+// the 2 D + 1 strips that read a tile would have to draw it again.  V[-D .. D] of the walk are 2 D + 1 tiles of sums.
+// The fields lie in LDS with zeros around them up to whole tiles, at a row pitch of 4 x odd floats (a lane's four
+// elements are one 128-bit read, 16 rows fall on different banks).
+// Bound by vector-ALU issue (1870 instructions a 29 x 29 image: 37 a draw, 60 a sampled pixel), matrix pipes a quarter
+// busy.  Sums by fmaf over a line -> this, line form also without its draws' and samples' slack: 60000 of 1x29x29
+// 648 -> 556 -> 377 us (1.07 TB/s), 1000 of 2x96x96 373 -> 340 -> 138 us, 10000 of 3x32x32 127 -> 113 -> 99 us.
+constexpr int PX = 2;   // pixels of a lane in flight together (4: registers of the wide Gaussians spill)
+template <int D, bool RARE>
+__global__ void __launch_bounds__(512, 4) k_deform_mx(const DeformJob J) {
+  extern __shared__ float lds[];
+  __shared__ Affine ring[AFF];
+  const int H = J.H, W = J.W, HW = H * W, R = J.R;
+  const int nxt = (W + 15) >> 4, nyt = (H + 15) >> 4;
+  const int pitch = 16 * nxt + 4, plane = 16 * nyt * pitch;
+  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63;
+  const int c = lane & 15, g4 = (lane >> 4) * 4;
+  v4f G[2 * D + 1];
+#pragma unroll
+  for (int d = 0; d <= 2 * D; ++d)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int off = 16 * (d - D) + g4 + v - c;
+      const float t = J.taps[min(max(off + R, 0), 2 * DEFORM_MAX_R)];
+      G[d][v] = off >= -R && off <= R ? t : 0.f;
+    }
+  for (int q = tid; q < 2 * plane; q += nt) lds[q] = 0.f;
+  const double cx = 0.5 * (double)(W - 1), cy = 0.5 * (double)(H - 1);
+  const int step_y = nt / W, step_x = nt - step_y * W;
+  const int first_y = tid / W, first_x = tid - first_y * W;
+  int n_done = 0;
+  for (long long k = blockIdx.x; k < J.n; k += gridDim.x, ++n_done) {
+    const unsigned long long key = presentation_key(J, k);
+    const Affine& A = affine_of(J, ring, k, n_done);
+    __syncthreads();  // the previous image's fields have been read
+    {
+      unsigned long long ctr = key + GOLDEN * (unsigned long long)(tid + 4);
+      int x = first_x, at = first_y * pitch + first_x;
+      for (int p = tid; p < HW; p += nt, ctr += GOLDEN * (unsigned long long)nt) {
+        const unsigned long long d = mix64(ctr);
+        lds[at] = sym((unsigned int)(d >> 32));
+        lds[at + plane] = sym((unsigned int)d);
+        x += step_x;
+        at += step_y * pitch + step_x;
+        if (x >= W) { x -= W; at += pitch - W; }
       }
-      // far outside in any direction reads the fill value only; the clamp keeps the integers small
-      const double fdx = floor(fmin(fmax(dx, -(double)(W + 2)), (double)(W + 2)));
-      const double fdy = floor(fmin(fmax(dy, -(double)(H + 2)), (double)(H + 2)));
-      const float fx = fminf(fmaxf((float)(dx - fdx), 0.f), 1.f), fy = fminf(fmaxf((float)(dy - fdy), 0.f), 1.f);
-      const int x0 = x + (int)fdx, y0 = y + (int)fdy;
-      const bool in_x0 = x0 >= 0 && x0 < W, in_x1 = x0 + 1 >= 0 && x0 + 1 < W;
-      const bool in_y0 = y0 >= 0 && y0 < H, in_y1 = y0 + 1 >= 0 && y0 + 1 < H;
-      const int xa = min(max(x0, 0), W - 1), xb = min(max(x0 + 1, 0), W - 1);
-      const int ya = min(max(y0, 0), H - 1), yb = min(max(y0 + 1, 0), H - 1);
-      const float w00 = (1.f - fy) * (1.f - fx), w01 = (1.f - fy) * fx, w10 = fy * (1.f - fx), w11 = fy * fx;
-      for (int c = 0; c < J.C; ++c) {
-        const CNN_GLOBAL float* m = src + (long long)c * HW;
-        const float v00 = in_y0 && in_x0 ? m[ya * W + xa] : J.fill;
-        const float v01 = in_y0 && in_x1 ? m[ya * W + xb] : J.fill;
-        const float v10 = in_y1 && in_x0 ? m[yb * W + xa] : J.fill;
-        const float v11 = in_y1 && in_x1 ? m[yb * W + xb] : J.fill;
-        dst[(long long)c * HW + p] = known ? fmaf(w00, v00, fmaf(w01, v01, fmaf(w10, v10, w11 * v11))) : J.fill;
+    }
+    const Image im = image_of(J, k);
+    __syncthreads();
+    for (int xt = __builtin_amdgcn_readfirstlane(tid >> 6); xt < nxt; xt += nt >> 6) {
+      const int x = 16 * xt + c;
+      const double u = (double)x - cx;
+      const double ax = fma(A.a00, u, A.tx), ay = fma(A.a10, u, A.ty);
+      v4f vx[2 * D + 1], vy[2 * D + 1];  // the tile of rows yt + D - i, i = 0 .. 2 D
+#pragma unroll
+      for (int i = 0; i <= 2 * D; ++i) { vx[i] = v4f{0.f, 0.f, 0.f, 0.f}; vy[i] = vx[i]; }
+      for (int yt = 0; yt < nyt + D; ++yt) {
+        if (yt < nyt) {
+          v4f hx = v4f{0.f, 0.f, 0.f, 0.f}, hy = hx;
+          const float* f = lds + (16 * yt + c) * pitch + 16 * xt + g4;
+#pragma unroll
+          for (int d = 0; d <= 2 * D; ++d) {
+            if (xt + d - D < 0 || xt + d - D >= nxt) continue;
+            const v4f fx = *(const v4f*)(f + 16 * (d - D)), fy = *(const v4f*)(f + plane + 16 * (d - D));
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              hx = __builtin_amdgcn_mfma_f32_16x16x4f32(fx[v], G[d][v], hx, 0, 0, 0);
+              hy = __builtin_amdgcn_mfma_f32_16x16x4f32(fy[v], G[d][v], hy, 0, 0, 0);
+            }
+          }
+#pragma unroll
+          for (int i = 0; i <= 2 * D; ++i) {
+            const int yo = yt + D - i;
+            if (yo < 0 || yo >= nyt) continue;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              vx[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(G[i][v], hx[v], vx[i], 0, 0, 0);
+              vy[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(G[i][v], hy[v], vy[i], 0, 0, 0);
+            }
+          }
+        }
+        if (yt >= D) {   // tile yt - D has all its sums
+          const double v0 = (double)(16 * (yt - D) + g4) - cy;
+          const double bx = A.a01, by = A.a11, ax0 = fma(bx, v0, ax), ay0 = fma(by, v0, ay);
+#pragma unroll
+          for (int v = 0; v < 4; v += PX) {
+            int px[PX], py[PX];
+            bool ok[PX];
+            double dx[PX], dy[PX], fdx[PX], fdy[PX];
+            float ex[PX], ey[PX];
+#pragma unroll
+            for (int q = 0; q < PX; ++q) {
+              px[q] = x;
+              py[q] = 16 * (yt - D) + g4 + v + q;
+              ok[q] = x < W && py[q] < H;
+              dx[q] = fma(bx, (double)(v + q), ax0);
+              dy[q] = fma(by, (double)(v + q), ay0);
+              fdx[q] = fma(bx, (double)(v + q), ax0 + FIX);
+              fdy[q] = fma(by, (double)(v + q), ay0 + FIX);
+              ex[q] = J.alpha * vx[2 * D][v + q];
+              ey[q] = J.alpha * vy[2 * D][v + q];
+            }
+            sample_pixels<PX, true, RARE>(J, im, px, py, ok, fdx, fdy, dx, dy, ex, ey);
+          }
+        }
+#pragma unroll
+        for (int i = 2 * D; i > 0; --i) { vx[i] = vx[i - 1]; vy[i] = vy[i - 1]; }
+        vx[0] = v4f{0.f, 0.f, 0.f, 0.f};
+        vy[0] = vx[0];
       }
     }
   }
@@ -168,18 +418,49 @@ __global__ void __launch_bounds__(DT) k_deform(const DeformJob J) {
 
 }  // namespace
 
-size_t deform_lds_bytes(const DeformJob& J) {
-  return J.R >= 0 ? ((size_t)4 * J.H * (J.W | 1) + 4 * J.R + 2 * SW + 1) * sizeof(float) : 0;
+template <int PXL, bool ELASTIC, bool RARE>
+static hipError_t launch_deform_px(hipStream_t stream, const DeformJob& J, unsigned int grid) {
+  const size_t lds = ELASTIC ? ((size_t)4 * J.H * (J.W | 1) + 4 * J.R + 2 * SW + 1) * sizeof(float) : 0;
+  hipError_t e = hipFuncSetAttribute((const void*)k_deform<PXL, ELASTIC, RARE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_deform<PXL, ELASTIC, RARE>), dim3(grid), dim3(DT), lds, stream, J);
+  return hipGetLastError();
+}
+
+template <int D, bool RARE>
+static hipError_t launch_deform_mx(hipStream_t stream, const DeformJob& J, unsigned int grid) {
+  const int nxt = (J.W + 15) / 16, nyt = (J.H + 15) / 16;
+  const size_t lds = (size_t)2 * 16 * nyt * (16 * nxt + 4) * sizeof(float);
+  hipError_t e = hipFuncSetAttribute((const void*)k_deform_mx<D, RARE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_deform_mx<D, RARE>), dim3(grid), dim3(64u * (nxt < 8 ? nxt : 8)), lds, stream, J);
+  return hipGetLastError();
+}
+
+template <bool RARE>
+static hipError_t launch_deform_any(hipStream_t stream, const DeformJob& J, unsigned int grid) {
+  if (J.R < 0) return J.H * J.W > DT ? launch_deform_px<4, false, RARE>(stream, J, grid) : launch_deform_px<1, false, RARE>(stream, J, grid);
+  // The matrix form works on whole tiles: it is the faster one where they are at least half full and the map is not a
+  // thin band of them (whose few strips are a long chain each), and for a map of one tile.  us, matrix form / line form:
+  // 30000 of 6x6 30 / 59, 16x16 38 / 102, 17x17 137 / 120, 20x20 144 / 133, 24x24 149 / 167; 10000 of 24x64 159 / 131,
+  // 32x64 167 / 190, 48x48x2 (5000) 126 / 156; 1000 of 2x96x96 138 / 340; 3000 of 200x20 285 / 185, 200x32 301 / 597.
+  const int tx = (J.W + 15) / 16, ty = (J.H + 15) / 16, tiles = tx > ty ? tx : ty;
+  const bool full = J.H > 24 && J.W > 24 && 2 * J.H * J.W >= 256 * tx * ty;
+  if (tiles > 1 && !full) return launch_deform_px<1, true, RARE>(stream, J, grid);
+  const int d = (J.R + 15) / 16;   // neighbouring tiles a tap reaches, as far as there are any
+  switch (d < tiles ? d : tiles - 1) {
+    case 0: return launch_deform_mx<0, RARE>(stream, J, grid);
+    case 1: return launch_deform_mx<1, RARE>(stream, J, grid);
+    case 2: return launch_deform_mx<2, RARE>(stream, J, grid);
+    case 3: return launch_deform_mx<3, RARE>(stream, J, grid);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 hipError_t launch_deform(hipStream_t stream, const DeformJob& J) {
   if (J.n <= 0) return hipSuccess;
-  const size_t lds = deform_lds_bytes(J);
-  hipError_t e = hipFuncSetAttribute((const void*)k_deform, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
   const unsigned int grid = (unsigned int)(J.n < 8192 ? J.n : 8192);
-  hipLaunchKernelGGL(k_deform, dim3(grid), dim3(DT), lds, stream, J);
-  return hipGetLastError();
+  return J.disp || !J.fixed ? launch_deform_any<true>(stream, J, grid) : launch_deform_any<false>(stream, J, grid);
 }
 
 }  // namespace cnn355

@@ -61,6 +61,45 @@ def test_deformed_images_match_the_oracle(C, H, W, n, kw):
     assert e_d <= TOL and e_i <= TOL
 
 
+@pytest.mark.parametrize("H,W", [(6, 6), (16, 16), (16, 17), (25, 25), (31, 33), (32, 48), (49, 40), (80, 26), (26, 90), (96, 96)])
+@pytest.mark.parametrize("sigma", [0.3, 5.5, 16.0])
+def test_smoothing_at_the_edges_of_tiles(H, W, sigma):
+    """Maps of one tile, of whole tiles and one pixel more or less, under Gaussians that reach no, the next and three tiles
+    away; the images are the same bits whether the displacements are asked for or not."""
+    print("case", H, W, sigma, flush=True)
+    src = np.random.default_rng(SEED + 11).uniform(-1, 1, (5, 2, H, W)).astype(np.float32)
+    gp, op = params(**dict(ALL, sigma=sigma, alpha=6.0 * sigma))
+    got, disp = run(src, 5, gp, SEED, 77)
+    want, want_disp = DO.deform_images(src, SEED, 77, op)
+    assert float(np.abs(disp - want_disp).max() / max(np.abs(want_disp).max(), 1.0)) <= TOL
+    assert rel(got, want) <= TOL
+    assert np.array_equal(run(src, 5, gp, SEED, 77, want_disp=False)[0], got)
+
+
+@pytest.mark.parametrize("kw", [dict(max_translation=20000.0), dict(max_shear=1e7, max_rotation=10.0), dict(sigma=2.0, alpha=1e9),
+                                dict(ALL, max_translation=1e5)])
+def test_displacements_beyond_the_fixed_point_range(kw):
+    """Source positions of 2^18 pixels and more: far outside, as the oracle has them."""
+    src = np.random.default_rng(SEED + 12).uniform(-1, 1, (40, 1, 28, 30)).astype(np.float32)
+    gp, op = params(**dict(kw, fill=0.75))
+    got, disp = run(src, 40, gp, SEED, 5)
+    want, want_disp = DO.deform_images(src, SEED, 5, op)
+    assert np.abs(disp - want_disp).max() <= TOL * np.abs(want_disp).max()
+    # (a position among the pixels is a difference of numbers of that size: none is, but for a few of the sheared ones)
+    assert np.mean(np.abs(got - want) > TOL) < 0.002
+    assert np.array_equal(run(src, 40, gp, SEED, 5, want_disp=False)[0], got)
+
+
+def test_many_images_a_workgroup():
+    """More than sixteen images for every workgroup of the largest launch: its next affine maps are drawn again."""
+    n = 8192 * 16 + 3
+    src = np.random.default_rng(SEED + 13).uniform(-1, 1, (n, 1, 6, 6)).astype(np.float32)
+    gp, op = params(**dict(ALL, sigma=1.0, alpha=2.0))
+    got, _ = run(src, n, gp, SEED, 0, want_disp=False)
+    for k in (0, 8191, 8192, 8192 * 15 + 7, 8192 * 16 - 1, 8192 * 16, n - 1):
+        assert rel(got[k], DO.deform_image(src[k], SEED, k, op)[0]) <= TOL
+
+
 def test_no_ranges_is_a_bit_exact_copy_and_the_draws_do_not_depend_on_the_call():
     import torch
     rng = np.random.default_rng(SEED)

@@ -40,6 +40,9 @@ hipError_t launch_resident(int static_id, int grid, size_t lds_bytes, hipStream_
 int resident_static_id(const FlowSpec& z);
 size_t batch_gemm_lds_bytes(const BatchGemm& g);
 hipError_t launch_batch_gemm(hipStream_t stream, const BatchGemm& g);
+size_t batch_conv_lds_bytes(const BatchConv& g);
+int batch_conv_fit(int MT, int TR, size_t lds_bytes);
+hipError_t launch_batch_conv(hipStream_t stream, const BatchConv& g);
 hipError_t launch_batch_pool(hipStream_t stream, const BatchPool& q);
 hipError_t launch_batch_outputs(hipStream_t stream, const float* logits, float* probs, long long n_images,
                                 int n_classes, int out_units);
@@ -1140,7 +1143,8 @@ namespace {
 
 struct BatchStep {
   BatchGemm g;
-  BatchPool pool;     // used when g.fuse == 0
+  BatchConv c;        // used instead of g when c.MT != 0
+  BatchPool pool;     // used when the sums come raw (g.fuse or c.fuse 0)
   BatchPack pack;
   size_t wt_off = 0;  // floats from the start of the scratch
   size_t wt_floats = 0;
@@ -1155,6 +1159,74 @@ struct BatchPlan {
 };
 
 size_t up64(size_t x) { return (x + 63) / 64 * 64; }
+
+FastDiv fast_div_of(int d) {
+  FastDiv f = {0, 0};
+  while ((1ll << f.s) < d) ++f.s;
+  f.m = (unsigned)(((1ull << (31 + f.s)) + (unsigned)d - 1) / (unsigned)d);
+  return f;
+}
+
+// The plan of k_batch_conv for a convolutional layer whose k_batch_gemm plan is g: tile, chunk and slices by a small time
+// model, in clocks of a compute unit.  Never more scratch memory than g takes: no more padded maps, no more k slices.
+// Leaves c.MT = 0 where a chunk of one input map does not fit.
+void conv_plan(const LayerDev& L, const BatchGemm& g, size_t batch, BatchConv& c) {
+  constexpr size_t LDS_HALF = 80 * 1024, LDS_WHOLE = 158 * 1024;   // two workgroups a compute unit, or one
+  std::memset(&c, 0, sizeof(c));
+  BatchConv t;
+  std::memset(&t, 0, sizeof(t));
+  t.Mi = L.Mi; t.Hi = L.Hi; t.Wi = L.Wi; t.K = L.K; t.Kx = L.Kx; t.stride = L.S + 1; t.stride_x = L.Sx + 1; t.Mo = L.Mo;
+  t.in_stride = g.in_stride; t.bias = L.bias; t.k_total = L.Mi * L.K * L.Kx;
+  const int KK = L.K * L.Kx, HiWi = L.Hi * L.Wi, members = L.Kp * L.Kpx;
+  const size_t limit = (size_t)1 << 31;
+  if ((size_t)HiWi * 4 * L.Mi >= limit || (size_t)t.k_total * 160 * 4 >= limit) return;   // (32-bit offsets of a chunk)
+  double best = 0;
+  for (int slices = 1; slices <= g.KS; slices += slices < 4 ? 1 : slices / 2) {
+    // pooling inside, unless the k range is sliced or whole windows leave more than a quarter of the 128 columns empty
+    const bool inside = slices == 1 && (members == 1 || (members <= 128 && 128 / members * members >= 96));
+    t.Kp = inside ? L.Kp : 1; t.Kpx = inside ? L.Kpx : 1;
+    if (!inside && members > 1 && g.fuse != 0) continue;         // (g has no room for raw sums)
+    t.Wp = inside ? L.Wp : L.Wo;
+    t.win_img = inside ? L.Hp * L.Wp : L.Ho * L.Wo;
+    t.wins = inside ? 128 / members : 128;
+    t.fuse = slices > 1 || (!inside && members > 1) ? 0 : (L.is_output ? 2 : 1);
+    const size_t n_cb = (batch * t.win_img + t.wins - 1) / t.wins;
+    t.n_img_max = (int)std::min<size_t>(std::max<size_t>(batch, 1), (size_t)((t.wins - 1 + t.win_img - 1) / t.win_img + 1));
+    for (int tr : {32, 16})
+      for (int mt = tr == 32 ? 5 : 7; mt >= 1; --mt) {
+        const int rows = mt * tr, groups = (t.Mo + rows - 1) / rows;
+        if (groups * rows > g.MoPad) continue;
+        t.TR = tr; t.MT = mt;
+        const int kg = tr == 32 ? 8 : 16;
+        for (size_t budget : {LDS_HALF, LDS_WHOLE}) {
+          bool any = false;
+          const int whole = (t.Mi + slices - 1) / slices;   // a slice in one chunk
+          for (int ic = 1; ic <= whole; ++ic) {
+            int chunks = (t.Mi + ic - 1) / ic, cps = (chunks + slices - 1) / slices;
+            t.IC = ic; t.slot = (int)up64((size_t)ic * HiWi); t.n_slices = slices;
+            t.chunks_per_slice = cps; t.resident = cps == 1;
+            if (batch_conv_lds_bytes(t) > budget) {
+              if (ic == whole) break;
+              ic = whole - 1;      // the longest chunk may fit again: it needs its weights once
+              continue;
+            }
+            if ((chunks + cps - 1) / cps != slices) continue;
+            any = true;
+            // a block's time: k padded to whole groups, a few hundred clocks a chunk, a few thousand a block; a
+            // workgroup takes its blocks one after the other, the workgroups of a compute unit share its matrix cores
+            const int kc = ic * KK, fit = batch_conv_fit(mt, tr, batch_conv_lds_bytes(t));
+            const double block = (double)cps * ((kc + kg - 1) / kg * kg * (double)rows + 500.0) + 2500.0 + 16.0 * rows;
+            const size_t lines = (size_t)groups * slices, gx = std::min(n_cb, std::max<size_t>(1, 256 * fit / lines));
+            const size_t side = (gx * lines + 255) / 256, rounds = (n_cb + gx - 1) / gx;
+            const double est = (double)(side * rounds) * block * (side > 1 ? 1.0 : 1.5) + (t.fuse == 0 ? 12000.0 : 0.0);
+            if (best == 0 || est < best) { best = est; c = t; }
+          }
+          if (any) break;
+        }
+      }
+  }
+  if (c.MT) { c.by_win_img = fast_div_of(c.win_img); c.by_wp = fast_div_of(c.Wp); }
+}
 
 // Shape of every layer's matrix product, tile choice and LDS budget.  Returns 0 or an error code.
 int batch_plan(cnn* net, size_t batch, BatchPlan& B) {
@@ -1239,14 +1311,18 @@ int batch_plan(cnn* net, size_t batch, BatchPlan& B) {
     g.bias = L.bias;
     g.in_stride = (long long)g.Mi * HiWi;
     g.out_stride = (long long)g.Mo * g.P;
-    st.wt_floats = up64((size_t)g.Mi * KK * g.MoPad);
+    std::memset(&st.c, 0, sizeof(st.c));
+    if (L.kind == L_CONV) conv_plan(L, g, batch, st.c);
+    const BatchConv& c = st.c;
+    const int KSl = c.MT ? c.n_slices : g.KS, fuse = c.MT ? c.fuse : g.fuse;
+    st.wt_floats = up64((size_t)g.Mi * KK * (c.MT ? (size_t)(c.Mo + c.MT * c.TR - 1) / (c.MT * c.TR) * (c.MT * c.TR) : (size_t)g.MoPad));
     st.wt_off = B.wt_total;
     B.wt_total += st.wt_floats;
     BatchPack& k = st.pack;
     std::memset(&k, 0, sizeof(k));
     k.w = L.w; k.csr_ptr = L.csr_ptr; k.csr_idx = L.csr_idx;
     k.is_fc = L.kind != L_CONV; k.full_table = L.full_table; k.Mi = g.Mi; k.Mo = g.Mo; k.K = g.K; k.Kx = g.Kx; k.n_in = L.n_in;
-    k.MoPad = g.MoPad;
+    k.row = c.MT ? c.MT * c.TR : g.MoPad; k.k_total = g.Mi * KK;
     if (L.kind == L_CONV) {
       int ci = 0;
       for (int q = 0; q < l; ++q) ci += P.layers[q].kind == L_CONV;
@@ -1257,10 +1333,11 @@ int batch_plan(cnn* net, size_t batch, BatchPlan& B) {
     BatchPool& q = st.pool;
     std::memset(&q, 0, sizeof(q));
     q.bias = L.bias; q.Mo = g.Mo; q.Ho = Ho; q.Wo = (L.kind == L_CONV) ? L.Wo : 1; q.Kp = Kp; q.Kpx = Kpx; q.Hp = Hp; q.Wp = Wp;
-    q.n_slices = g.KS; q.slice_stride = g.slice_stride; q.act = L.is_output ? 0 : 1;
+    q.n_slices = KSl; q.slice_stride = c.MT ? (long long)(batch * L.Mo * L.Ho * L.Wo) : g.slice_stride; q.act = L.is_output ? 0 : 1;
     st.out_per_image = pooled ? (size_t)g.Mo * Hp * Wp : (size_t)g.Mo * g.P;
-    if (g.fuse == 0) B.sums_per_image = std::max(B.sums_per_image, up64((size_t)g.KS * g.Mo * g.P));
-    // (g.P is Ho * Wo whenever fuse == 0 with pooling: pooling inside the product always has fuse != 0)
+    if (c.MT) { st.c.slice_stride = q.slice_stride; st.c.out_stride = (long long)c.Mo * c.win_img; }
+    if (fuse == 0) B.sums_per_image = std::max(B.sums_per_image, up64((size_t)KSl * g.Mo * (c.MT ? c.win_img : g.P)));
+    // (the columns are the layer's pixels whenever fuse == 0 with pooling: pooling inside the product has fuse != 0)
     B.act_per_image = std::max(B.act_per_image, up64(st.out_per_image));
     B.steps.push_back(st);
   }
@@ -2056,18 +2133,23 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
     int cur = 0;
     for (size_t s = 0; s < B.steps.size(); ++s) {
       BatchStep& st = B.steps[s];
-      BatchGemm g = st.g;
-      g.in = in; g.in_stride = in_stride; g.wt = base + st.wt_off; g.N = (long long)nb * g.P;
       float* out = d_act[cur];
-      if (g.fuse == 0) {
-        g.out = d_sums;
+      const bool raw = (st.c.MT ? st.c.fuse : st.g.fuse) == 0;
+      if (st.c.MT) {
+        BatchConv c = st.c;
+        c.in = in; c.in_stride = in_stride; c.wt = base + st.wt_off; c.out = raw ? d_sums : out;
+        c.vec = ((uintptr_t)in & 15u) == 0 && in_stride % 4 == 0 && (c.IC * c.Hi * c.Wi) % 4 == 0;
+        c.n_win = (int)(nb * c.win_img); c.n_cb = (c.n_win + c.wins - 1) / c.wins;
+        HIP_TRY(net, launch_batch_conv(net->stream, c));
+      } else {
+        BatchGemm g = st.g;
+        g.in = in; g.in_stride = in_stride; g.wt = base + st.wt_off; g.N = (long long)nb * g.P; g.out = raw ? d_sums : out;
         HIP_TRY(net, launch_batch_gemm(net->stream, g));
+      }
+      if (raw) {
         BatchPool q = st.pool;
         q.sums = d_sums; q.out = out; q.total = (long long)nb * q.Mo * q.Hp * q.Wp;
         HIP_TRY(net, launch_batch_pool(net->stream, q));
-      } else {
-        g.out = out;
-        HIP_TRY(net, launch_batch_gemm(net->stream, g));
       }
       in = out;
       in_stride = (long long)st.out_per_image;

@@ -9,6 +9,7 @@
 // tolerance of the one-image path.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #define CNN_GLOBAL __attribute__((address_space(1)))
@@ -300,6 +301,269 @@ __global__ void __launch_bounds__(BT) k_batch_gemm(BatchGemm g) {
   }
 }
 
+// ---- a convolutional layer of a whole batch -------------------------------------------------------------------
+// The same product with everything between the arithmetic taken out of its way:
+//  * The next chunk (input maps, rows of Wt) goes straight to the other half of LDS (global_load_lds: no registers, no
+//    instructions to store it) while the matrix cores work on the present one; one barrier a chunk.
+//  * A workgroup is persistent: it takes column blocks blockIdx.x, + gridDim.x, ..., and fetches the next block's first
+//    chunk during the last of this one.  Where the k range is one chunk the weights are staged once and stay.
+//  * Up to 160 maps a workgroup (MT tiles of TR): one operand of the staged images feeds MT matrix instructions.
+//  * Pooling: the columns are (image, window, member of the window), so a window's sums lie side by side in one
+//    accumulator register of adjacent lanes.  2 x 2 windows are four lanes, reduced by DPP, each lane going on with one
+//    row in four (bias, tanh and store at full lanes); others pass through LDS tile by tile.  The full-resolution sums
+//    never reach memory, however long the k range.
+// Bound by the matrix pipes: 70-80 % busy at the 2.1 GHz the chip keeps here where the blocks divide evenly; staging is
+// hidden (without it the products take as long).  Per 512 images of 300 maps: 300C3 on 3 maps 206 -> 185 us, 300C2 on
+// 300 maps with its pooling 1286 + 45 -> 794 us (91 TFLOP/s), 300C4 405 -> 237 us; 4096 digits: 20C4 83 -> 76 us, 40C5
+// 243 + 24 -> 187 us (71 TFLOP/s).  Tried and not kept: the next group's operands in a second set of registers (300C2 852
+// us), all of a group's LDS reads before its first product (833), three or four workgroups a compute unit (795, 791).
+// Layout of dynamic LDS: [1 or 2][KC][MT * TR] weights, [2][n_img_max][slot] images, koff, biases, [TR][EP] sums of one tile.
+constexpr int EP = 132;
+
+__device__ __forceinline__ int fast_div(int n, FastDiv d) { return (int)(__umulhi(2u * (unsigned)n, d.m) >> d.s); }
+
+// Lane l's 4 or 16 bytes at base + off go to lds_byte + 4 l or 16 l; the wavefront has them after s_waitcnt vmcnt(0).
+// (Not the builtin: the compiler then waits for the load before every LDS read that it cannot tell apart from its
+// destination.  m0 holds nothing else here: no LDS instruction of gfx950 but these needs it.)
+__device__ __forceinline__ void lds_dma4(unsigned lds_byte, const CNN_GLOBAL char* base, unsigned off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_byte), "v"(off), "s"(base) : "memory");
+}
+__device__ __forceinline__ void lds_dma16(unsigned lds_byte, const CNN_GLOBAL char* base, unsigned off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_byte), "v"(off), "s"(base) : "memory");
+}
+
+template <int MT, int TR>
+__global__ void __launch_bounds__(BT, MT * TR > 96 ? 2 : 3) k_batch_conv(BatchConv g) {
+  extern __shared__ __align__(16) float lds[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int KS = TR == 32 ? 2 : 4;             // k values one instruction takes, one per group of 64 / KS lanes
+  constexpr int CT = 32 / TR;                      // column tiles of a wavefront
+  constexpr int AV = TR == 32 ? 16 : 4;            // accumulator floats per lane and tile
+  constexpr int WROW = MT * TR;
+  const int lrow = lane & (TR - 1), lk = lane / TR;
+  const int HiWi = g.Hi * g.Wi, KK = g.K * g.Kx, KC = g.IC * KK;
+  const int w_size = (KC * WROW + 255) & ~255, in_size = g.n_img_max * g.slot;
+  float* lds_w = lds;
+  float* lds_in = lds_w + (g.resident ? 1 : 2) * w_size;
+  const int KH = (((KC + KS - 1) / KS) + 3) & ~3;
+  int* koff = (int*)(lds_in + 2 * in_size);        // [KS][KH] byte offset of k inside a staged image
+  float* lds_b = (float*)(koff + KS * KH);         // [MT * TR] biases
+  float* ep = lds_b + WROW;
+  const unsigned w_byte = (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)lds_w;
+  const unsigned in_byte = (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)lds_in;
+  for (int x = tid; x < KS * KH; x += BT) {
+    const int par = x / KH, h = x - par * KH;
+    const int k = min(KS * h + par, KC - 1);
+    const int c = k / KK, t = k - c * KK;
+    const int ky = t / g.Kx, kx = t - ky * g.Kx;
+    koff[x] = (c * HiWi + ky * g.Wi + kx) * 4;
+  }
+  const int j0 = blockIdx.y * WROW;
+  for (int x = tid; x < WROW; x += BT) lds_b[x] = g.fuse && j0 + x < g.Mo ? g.bias[j0 + x] : 0.f;
+  const int ic_first = blockIdx.z * g.chunks_per_slice * g.IC;
+  const int ic_end = min(g.Mi, ic_first + g.chunks_per_slice * g.IC);
+  const int M = g.Kp * g.Kpx;
+  // a column block's first and last image
+  auto first_image = [&](int cb) { return fast_div(cb * g.wins, g.by_win_img); };
+  auto last_image = [&](int cb) { return fast_div(min((cb + 1) * g.wins, g.n_win) - 1, g.by_win_img); };
+  // A wavefront takes every fourth run of 64 lanes, of a float each, or of four where every image and chunk starts on 16
+  // bytes (g.vec); lanes behind the last element of a map or group fetch nothing.
+  auto fetch = [&](int b0, int b1, int ic0, int buf, bool with_w) {
+    const int n_ic = min(g.IC, ic_end - ic0), cnt = n_ic * HiWi;
+    const int run = g.vec ? 256 : 64;
+    const CNN_GLOBAL char* base = (const CNN_GLOBAL char*)(g.in + (long long)b0 * g.in_stride + ic0 * HiWi + wave * run);
+    unsigned dst = in_byte + (unsigned)(buf * in_size + wave * run) * 4u;
+    const unsigned whole = (unsigned)lane * 4u;
+    for (int s = b0; s <= b1; ++s, base += g.in_stride * 4, dst += (unsigned)g.slot * 4u) {
+      const CNN_GLOBAL char* p = base;
+      unsigned d = dst;
+      int left = cnt - wave * run;
+      if (g.vec) {
+        for (; left >= 256; left -= 4 * BT, p += BT * 16, d += BT * 16u) lds_dma16(d, p, whole * 4u);
+        if (left > 0) {
+          if (lane * 4 + 4 <= left) lds_dma16(d, p, whole * 4u);
+          const unsigned q = (unsigned)(left & ~3) * 4u;
+          if (lane < (left & 3)) lds_dma4(d + q, p, q + whole);
+        }
+      } else {
+        for (; left >= 64; left -= BT, p += BT * 4, d += BT * 4u) lds_dma4(d, p, whole);
+        if (lane < left) lds_dma4(d, p, whole);
+      }
+    }
+    if (!with_w) return;
+    const CNN_GLOBAL char* wb = (const CNN_GLOBAL char*)(g.wt + ((long long)blockIdx.y * g.k_total + ic0 * KK) * WROW + wave * 256);
+    const int n_w = n_ic * KK * WROW;   // a multiple of 16
+    unsigned wdst = w_byte + (unsigned)((g.resident ? 0 : buf) * w_size + wave * 256) * 4u;
+    int x = wave * 256;
+    for (; x + 256 <= n_w; x += 4 * BT, wb += 16 * BT, wdst += 16u * BT) lds_dma16(wdst, wb, whole * 4u);
+    if (lane * 4 < n_w - x) lds_dma16(wdst, wb, whole * 4u);
+  };
+
+  typedef float accv __attribute__((ext_vector_type(AV)));
+  int buf = 0;
+  int b0 = first_image(blockIdx.x), b1 = last_image(blockIdx.x);
+  fetch(b0, b1, ic_first, 0, true);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  for (int cb = blockIdx.x; cb < g.n_cb; cb += gridDim.x) {
+    // the lane's column in each of the wavefront's column tiles
+    int pbase[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      const int c = wave * 32 + ct * TR + lrow;
+      const int wl = c / M, d = c - wl * M, w = cb * g.wins + wl;
+      pbase[ct] = 0;
+      if (wl < g.wins && w < g.n_win) {
+        const int b = fast_div(w, g.by_win_img), wi = w - b * g.win_img;
+        const int wy = fast_div(wi, g.by_wp), wx = wi - wy * g.Wp, dy = d / g.Kpx, dx = d - dy * g.Kpx;
+        pbase[ct] = ((b - b0) * g.slot + (wy * g.Kp + dy) * g.stride * g.Wi + (wx * g.Kpx + dx) * g.stride_x) * 4;
+      }
+    }
+    accv acc[MT][CT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int v = 0; v < AV; ++v) acc[m][ct][v] = 0.f;
+    const int cb_b0 = b0;
+    for (int ic0 = ic_first; ic0 < ic_end; ic0 += g.IC, buf ^= 1) {
+      // the chunk has arrived (every wavefront has waited for its own loads), and nobody reads the other half any more
+      __syncthreads();
+      if (ic0 + g.IC < ic_end) {
+        fetch(b0, b1, ic0 + g.IC, buf ^ 1, true);
+      } else if (cb + (int)gridDim.x < g.n_cb) {
+        b0 = first_image(cb + gridDim.x);
+        b1 = last_image(cb + gridDim.x);
+        fetch(b0, b1, ic_first, buf ^ 1, !g.resident);
+      }
+      const int kc = min(g.IC, ic_end - ic0) * KK;
+      const char* in_b[CT];
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) in_b[ct] = (const char*)(lds_in + buf * in_size) + pbase[ct];
+      const float* w_b = lds_w + (g.resident ? 0 : buf) * w_size;
+#define CNN355_MAC(a, bv)                                                                                            \
+  _Pragma("unroll") for (int u = 0; u < 4; ++u)                                                                      \
+  _Pragma("unroll") for (int m = 0; m < MT; ++m)                                                                     \
+  _Pragma("unroll") for (int ct = 0; ct < CT; ++ct) {                                                                \
+    if constexpr (TR == 32) acc[m][ct] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][m], bv[u][ct], acc[m][ct], 0, 0, 0); \
+    else acc[m][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][m], bv[u][ct], acc[m][ct], 0, 0, 0);                  \
+  }
+      constexpr int KG = 4 * KS;
+      const int kcg = kc - kc % KG;
+      for (int kk = 0; kk < kcg; kk += KG) {
+        const int4 ko = *(const int4*)(koff + lk * KH + kk / KS);
+        const float* wr = w_b + (kk + lk) * WROW + lrow;
+        float a[4][MT], bv[4][CT];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int m = 0; m < MT; ++m) a[u][m] = wr[KS * u * WROW + m * TR];
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          bv[0][ct] = *(const float*)(in_b[ct] + ko.x);
+          bv[1][ct] = *(const float*)(in_b[ct] + ko.y);
+          bv[2][ct] = *(const float*)(in_b[ct] + ko.z);
+          bv[3][ct] = *(const float*)(in_b[ct] + ko.w);
+        }
+        CNN355_MAC(a, bv)
+      }
+      if (kcg < kc) {   // the rest of the chunk: k beyond it counts as zero on both sides
+        float a[4][MT], bv[4][CT];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int k = kcg + KS * u + lk, kr = min(k, kc - 1);
+          const int ko = koff[lk * KH + min(k / KS, KH - 1)];
+#pragma unroll
+          for (int m = 0; m < MT; ++m) {
+            const float t = w_b[kr * WROW + m * TR + lrow];
+            a[u][m] = k < kc ? t : 0.f;
+          }
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) {
+            const float t = *(const float*)(in_b[ct] + (k < kc ? ko : 0));
+            bv[u][ct] = k < kc ? t : 0.f;
+          }
+        }
+        CNN355_MAC(a, bv)
+      }
+#undef CNN355_MAC
+      // here and not behind the barrier: the wait would take in the stores of the results (and those read no memory
+      // themselves, biases are in LDS: a load's wait takes in the stores before it too)
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    // element v of a lane, 32-row tiles: row (v / 4) * 8 + (lane / 32) * 4 + v % 4 of the tile, column lane % 32;
+    // 16-row tiles: row (lane / 16) * 4 + v, column lane % 16
+    gf dst = g.out + (long long)blockIdx.z * g.slice_stride;
+    auto finish = [&](float sv, int j) {
+      if (g.fuse) sv += lds_b[j - j0];
+      return g.fuse == 1 ? b_act(sv) : sv;
+    };
+    if (M == 1 || M == 4) {
+      const int q = M == 4 ? lane & 3 : 0;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        const int c = wave * 32 + ct * TR + lrow;
+        const int w = cb * g.wins + (M == 4 ? c >> 2 : c);
+        const bool ok = w < g.n_win;
+        const int b = ok ? fast_div(w, g.by_win_img) : cb_b0, wi = ok ? w - b * g.win_img : 0;
+        const unsigned o0 = (unsigned)b * (unsigned)g.out_stride + (unsigned)wi;
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+          if (M == 4) {
+#pragma unroll
+            for (int v4 = 0; v4 < AV; v4 += 4) {
+              if (j0 + m * TR + v4 * 2 >= g.Mo) break;   // (TR = 16: v4 is 0)
+              float r[4];
+#pragma unroll
+              for (int u = 0; u < 4; ++u) {
+                float x = acc[m][ct][v4 + u];
+                x = fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xf, 0xf, true)));   // lanes 1 0 3 2
+                r[u] = fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xf, 0xf, true)));  // 2 3 0 1
+              }
+              const float mine = fmaxf(q < 2 ? (q == 0 ? r[0] : r[1]) : (q == 2 ? r[2] : r[3]), -INFINITY);  // (no number at all: -inf)
+              const int j = j0 + m * TR + (TR == 32 ? (v4 >> 2) * 8 : 0) + lk * 4 + q;
+              if (ok && j < g.Mo) dst[o0 + (unsigned)j * (unsigned)g.win_img] = finish(mine, j);
+            }
+          } else {
+#pragma unroll
+            for (int v = 0; v < AV; ++v) {
+              const int j = j0 + m * TR + (TR == 32 ? (v >> 2) * 8 + lk * 4 + (v & 3) : lk * 4 + v);
+              if (ok && j < g.Mo) dst[o0 + (unsigned)j * (unsigned)g.win_img] = finish(acc[m][ct][v], j);
+            }
+          }
+        }
+      }
+    } else {
+      // a thread's window stays its own for all rows it takes
+      const int rows = BT / g.wins, jr = tid / g.wins, wl = tid - jr * g.wins;
+      const int w = cb * g.wins + wl;
+      const bool ok = jr < rows && w < g.n_win;
+      const int b = ok ? fast_div(w, g.by_win_img) : cb_b0, wi = ok ? w - b * g.win_img : 0;
+      const unsigned o0 = (unsigned)b * (unsigned)g.out_stride + (unsigned)wi;
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        __syncthreads();   // the previous tile has been read
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+          for (int v = 0; v < AV; ++v)
+            ep[(TR == 32 ? (v >> 2) * 8 + lk * 4 + (v & 3) : lk * 4 + v) * EP + wave * 32 + ct * TR + lrow] = acc[m][ct][v];
+        __syncthreads();
+        if (ok)
+          for (int r = jr; r < TR; r += rows) {
+            const int j = j0 + m * TR + r;
+            if (j >= g.Mo) break;
+            const float* win = ep + r * EP + wl * M;
+            float best = -INFINITY;
+            for (int d = 0; d < M; ++d) best = fmaxf(best, win[d]);
+            dst[o0 + (unsigned)j * (unsigned)g.win_img] = finish(best, j);
+          }
+      }
+    }
+  }
+}
+
 // bias + scaled tanh + max-pooling (Sec. 2.2, 2.3) of the raw sums of a whole batch; the sums may
 // come as several planes (slices of the k range), added here in a fixed order.  The activation
 // function is increasing, so the maximum is taken first: one tanh per window.  act 0: none (the
@@ -343,14 +607,14 @@ __global__ void __launch_bounds__(256) k_batch_outputs(cgf logits, gf probs, lon
   for (int k = 0; k < n_classes; ++k) o[k] = expf(a[k] - mx) / z;
 }
 
-// Wt[k][j] of one layer from the canonical weights: k = (input map, ky, kx), j = output map;
+// Wt[group of `row` maps][k][map] of one layer from the canonical weights: k = (input map, ky, kx), j = output map;
 // absent connections and the padding maps stay zero (the buffer is cleared first).
 __global__ void __launch_bounds__(256) k_batch_pack(BatchPack q) {
   const long long x = (long long)blockIdx.x * 256 + threadIdx.x;
   if (x >= q.total) return;
   if (q.is_fc) {  // W[n_out][n_in]
     const int j = (int)(x / q.n_in), m = (int)(x - (long long)j * q.n_in);
-    q.wt[(long long)m * q.MoPad + j] = q.w[x];
+    q.wt[((long long)(j / q.row) * q.k_total + m) * q.row + j % q.row] = q.w[x];
     return;
   }
   const int KK = q.K * q.Kx;
@@ -370,12 +634,31 @@ __global__ void __launch_bounds__(256) k_batch_pack(BatchPack q) {
     j = lo;
     i = q.csr_idx[slot];
   }
-  q.wt[((long long)i * KK + t) * q.MoPad + j] = q.w[x];
+  q.wt[((long long)(j / q.row) * q.k_total + i * KK + t) * q.row + j % q.row] = q.w[x];
 }
 
 __global__ void __launch_bounds__(256) k_batch_zero(gf p, long long n) {
   const long long x = (long long)blockIdx.x * 256 + threadIdx.x;
   if (x < n) p[x] = 0.f;
+}
+
+}  // namespace
+// workgroups of k_batch_conv a compute unit holds at once (registers, LDS)
+int batch_conv_fit(int MT, int TR, size_t lds_bytes) {
+  const int regs = (MT * (TR == 32 ? 16 : 8) + 64 + 7) & ~7;
+  return std::max(1, std::min({512 / regs, (int)(160 * 1024 / lds_bytes), 8}));
+}
+namespace {
+
+template <int MT, int TR>
+hipError_t launch_conv_mt(hipStream_t stream, const BatchConv& g, size_t lds_bytes) {
+  hipError_t e = hipFuncSetAttribute((const void*)k_batch_conv<MT, TR>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+  if (e != hipSuccess) return e;
+  const int groups = (g.Mo + MT * TR - 1) / (MT * TR) * g.n_slices;
+  const int gx = (int)std::min<long long>(g.n_cb, std::max(1, 256 * batch_conv_fit(MT, TR, lds_bytes) / groups));
+  hipLaunchKernelGGL((k_batch_conv<MT, TR>), dim3((unsigned)gx, (unsigned)(groups / g.n_slices), (unsigned)g.n_slices), dim3(BT),
+                     lds_bytes, stream, g);
+  return hipGetLastError();
 }
 
 template <int MT, int TR>
@@ -395,6 +678,40 @@ size_t batch_gemm_lds_bytes(const BatchGemm& g) {
   const size_t KS = g.TR == 32 ? 2 : 4;
   const size_t KH = ((((size_t)KC + KS - 1) / KS) + 3) & ~(size_t)3;
   return ((((size_t)g.n_img_max * g.IC * g.Hi * g.Wi + 3) & ~(size_t)3) + (size_t)(KC + 1) * g.MT * g.TR + KS * KH) * sizeof(float);
+}
+
+size_t batch_conv_lds_bytes(const BatchConv& g) {
+  const size_t KC = (size_t)g.IC * g.K * g.Kx, KS = g.TR == 32 ? 2 : 4, M = (size_t)g.Kp * g.Kpx;
+  const size_t KH = (((KC + KS - 1) / KS) + 3) & ~(size_t)3;
+  const size_t w_size = (KC * g.MT * g.TR + 255) & ~(size_t)255;
+  return ((g.resident ? 1 : 2) * w_size + 2 * (size_t)g.n_img_max * g.slot + KS * KH + g.MT * g.TR +
+          (M == 1 || M == 4 ? 0 : (size_t)g.TR * EP)) * sizeof(float);
+}
+
+hipError_t launch_batch_conv(hipStream_t stream, const BatchConv& g) {
+  if (g.n_win <= 0) return hipSuccess;
+  const size_t lds_bytes = batch_conv_lds_bytes(g);
+  if (g.TR == 32) {
+    switch (g.MT) {
+      case 1: return launch_conv_mt<1, 32>(stream, g, lds_bytes);
+      case 2: return launch_conv_mt<2, 32>(stream, g, lds_bytes);
+      case 3: return launch_conv_mt<3, 32>(stream, g, lds_bytes);
+      case 4: return launch_conv_mt<4, 32>(stream, g, lds_bytes);
+      case 5: return launch_conv_mt<5, 32>(stream, g, lds_bytes);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  if (g.TR != 16) return hipErrorInvalidValue;
+  switch (g.MT) {
+    case 1: return launch_conv_mt<1, 16>(stream, g, lds_bytes);
+    case 2: return launch_conv_mt<2, 16>(stream, g, lds_bytes);
+    case 3: return launch_conv_mt<3, 16>(stream, g, lds_bytes);
+    case 4: return launch_conv_mt<4, 16>(stream, g, lds_bytes);
+    case 5: return launch_conv_mt<5, 16>(stream, g, lds_bytes);
+    case 6: return launch_conv_mt<6, 16>(stream, g, lds_bytes);
+    case 7: return launch_conv_mt<7, 16>(stream, g, lds_bytes);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 hipError_t launch_batch_gemm(hipStream_t stream, const BatchGemm& g) {

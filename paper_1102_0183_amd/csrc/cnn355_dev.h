@@ -246,6 +246,30 @@ struct BatchGemm {
   int prefetch;                  // the next chunk is fetched into registers during the arithmetic
   int fuse;                      // 0: raw sums (pooling follows); 1: bias + scaled tanh; 2: bias only (output layer)
 };
+// n / d for 0 <= n < 2^31 as a product: floor(2 n m / 2^(32 + s)), m = ceil(2^(31 + s) / d), s = ceil(log2 d)
+struct FastDiv {
+  unsigned m;
+  int s;
+};
+// A convolutional layer over a whole batch with its pooling (k_batch_conv).  Columns: (image, window, member of the
+// window); without pooling inside (Kp = Kpx = 1) a window is a pixel.
+struct BatchConv {
+  const CNN_GLOBAL float* in;    // [batch] images of [Mi][Hi][Wi], in_stride floats apart
+  const CNN_GLOBAL float* wt;    // [group of MT * TR maps][Mi*K*Kx][MT * TR]
+  const CNN_GLOBAL float* bias;  // [Mo]
+  CNN_GLOBAL float* out;         // [batch][Mo][windows], out_stride floats per image
+  long long in_stride, out_stride;
+  long long slice_stride;        // floats between the planes of partial sums of the k slices
+  int Mi, Hi, Wi, K, Kx, stride, stride_x, Mo;
+  int Kp, Kpx, Wp, win_img;      // pooling window; windows of one row of an image, of an image
+  FastDiv by_win_img, by_wp;
+  int wins, n_win, n_cb;         // windows of a column block, of the whole batch; column blocks
+  int IC, slot, n_img_max;       // input maps of a chunk; floats of one staged image (whole runs of 64); images a block can touch
+  int MT, TR;                    // tiles of TR maps a workgroup: TR 32 (v_mfma_f32_32x32x2_f32) or 16 (v_mfma_f32_16x16x4_f32)
+  int n_slices, chunks_per_slice, resident, k_total;  // resident: the k range is one chunk, its weights are staged once
+  int vec;                       // images and chunks start on 16 bytes: staged 16 bytes a lane
+  int fuse;                      // 0: raw sums; 1: bias + scaled tanh; 2: bias only
+};
 struct BatchPool {
   const CNN_GLOBAL float* sums;  // [batch][Mo][Ho][Wo] raw sums
   const CNN_GLOBAL float* bias;
@@ -257,11 +281,12 @@ struct BatchPool {
 };
 struct BatchPack {
   const CNN_GLOBAL float* w;     // conv: [n_conn][K*Kx] in table order; fc: [n_out][n_in]
-  CNN_GLOBAL float* wt;          // [Kdim][MoPad]
+  CNN_GLOBAL float* wt;          // [group][Kdim][row]
   const CNN_GLOBAL int* csr_ptr;
   const CNN_GLOBAL int* csr_idx;
   long long total;               // weights of the layer (biases apart)
-  int is_fc, full_table, Mi, Mo, K, Kx, n_in, MoPad;
+  int is_fc, full_table, Mi, Mo, K, Kx, n_in;
+  int row, k_total;              // maps of a group of Wt, rows of it
 };
 
 // ---- on-line deformation of training images ---------------------------------------------------

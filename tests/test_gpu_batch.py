@@ -162,3 +162,36 @@ def test_every_layer_of_the_batched_pass_matches_the_oracle(name, n):
     with pytest.raises(binding.CnnError):
         g.debug_forward_batch_layer(d_imgs, n, len(layers), scratch)
     g.close()
+
+
+@pytest.mark.parametrize("arch,batch", [
+    ("1x9x9-1C2-MP2-3N", 1),                    # one map, one image
+    ("1x9x9-17C2-MP4-33C1-MP1-3N", 7),          # one map beyond a tile of 16 and of 32; 4 x 4 windows; 1 x 1 kernels
+    ("3x13x13-33C2-MP3-40C3-MP2-4N", 40),       # 3 x 3 windows, blocks of 14 of them that straddle images
+    ("2x12x15-20C3-MP2x1-48C2-MP2x3-4N", 65),   # 2- and 6-member windows
+    ("1x27x27-5C3-MP5-9C2-4N", 33),             # 25-member windows, an unpooled layer behind them
+    ("1x25x25-6C4-MP11-3N", 9),                 # 121 members: one window a block
+    ("1x26x26-6C3-MP12-3N", 9),                 # 144 members: pooled outside the product
+    ("2x11x11-161C2-MP2-161C2-MP2-3N", 3),      # one map beyond 160, k range in slices
+    ("5x8x8-80C3S1-MP3-3N", 200),               # skipping factor; more blocks than workgroups
+    ("4x10x10-48C3-MP2-48C2-3N", 700),          # images staged four floats a lane
+    ("3x9x9-48C2-MP2-48C2-3N", 700),            # odd images: a float a lane
+])
+def test_convolutional_layers_at_the_edges_of_tiles_and_windows(arch, batch):
+    """Every layer of a batch and a ragged second one against the one-image path and the oracle."""
+    import torch
+    print("case", arch, batch, flush=True)
+    n = batch + (batch + 1) // 2
+    g, o = build_pair(arch=arch, wscale=0.2)
+    imgs = (np.random.default_rng(5).random((n, g.image_size)) * 2 - 1).astype(np.float32)
+    d_imgs = to_dev(imgs)
+    probs = torch.full((n * g.num_classes,), -1.0, dtype=torch.float32, device="cuda:0")
+    g.forward_batch(d_imgs, n, probs, _scratch(g, batch), batch)
+    one = torch.empty(n * g.num_classes, dtype=torch.float32, device="cuda:0")
+    g.forward_many(d_imgs, n, one)
+    g.synchronize()
+    assert (probs - one).abs().max().item() <= 1e-5
+    for i in {0, batch - 1, n - 1}:
+        want = o.forward(imgs[i])
+        assert np.abs(probs.cpu().numpy().reshape(n, -1)[i] - want).max() <= 1e-5
+    g.close()

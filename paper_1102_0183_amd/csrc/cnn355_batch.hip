@@ -44,6 +44,8 @@ __device__ __forceinline__ float b_act(float a) {
 constexpr int PRE_IN = 16;     // floats per thread a prefetched chunk may hold: staged images ...
 constexpr int PRE_W = 48;      // ... and rows of Wt
 
+__host__ __device__ __forceinline__ int batch_slot(int IC, int HiWi) { return HiWi == 1 ? IC | 1 : IC * HiWi; }
+
 // Workgroup (x, y): columns [128 x, 128 x + 128) and map tiles [MT y, MT y + MT) of TR maps each.  TR = 32:
 // v_mfma_f32_32x32x2_f32, a wavefront's 32 columns are one tile wide, a lane takes the even or the odd k.  TR = 16:
 // v_mfma_f32_16x16x4_f32, the 32 columns are two tiles of 16, a lane takes one k in four; it is chosen where 16-row
@@ -63,7 +65,9 @@ __global__ void __launch_bounds__(BT) k_batch_gemm(BatchGemm g) {
   constexpr int AV = TR == 32 ? 16 : 4;            // accumulator floats per lane and tile
   const int lrow = lane & (TR - 1), lk = lane / TR;
   const int HiWi = g.Hi * g.Wi, KK = g.K * g.Kx;
-  const int slot_sz = g.IC * HiWi;
+  // floats of a staged image; odd for one-pixel maps (fully connected layers), whose IC is a power of two: the 32 columns
+  // of an operand, an image each, would all lie in one bank (360 -> 150 units of 4096 images 30.5 -> 25 us)
+  const int slot_sz = batch_slot(g.IC, HiWi);
   const int KC = g.IC * KK;                        // k per full chunk
   constexpr int WROW = MT * TR;
   float* lds_in = lds;                              // [n_img_max][IC][Hi*Wi]
@@ -677,7 +681,7 @@ size_t batch_gemm_lds_bytes(const BatchGemm& g) {
   const int KC = g.IC * g.K * g.Kx;
   const size_t KS = g.TR == 32 ? 2 : 4;
   const size_t KH = ((((size_t)KC + KS - 1) / KS) + 3) & ~(size_t)3;
-  return ((((size_t)g.n_img_max * g.IC * g.Hi * g.Wi + 3) & ~(size_t)3) + (size_t)(KC + 1) * g.MT * g.TR + KS * KH) * sizeof(float);
+  return ((((size_t)g.n_img_max * batch_slot(g.IC, g.Hi * g.Wi) + 3) & ~(size_t)3) + (size_t)(KC + 1) * g.MT * g.TR + KS * KH) * sizeof(float);
 }
 
 size_t batch_conv_lds_bytes(const BatchConv& g) {

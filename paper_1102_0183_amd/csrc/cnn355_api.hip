@@ -44,9 +44,9 @@ size_t batch_conv_lds_bytes(const BatchConv& g);
 int batch_conv_fit(int MT, int TR, size_t lds_bytes);
 hipError_t launch_batch_conv(hipStream_t stream, const BatchConv& g);
 hipError_t launch_batch_pool(hipStream_t stream, const BatchPool& q);
-hipError_t launch_batch_outputs(hipStream_t stream, const float* logits, float* probs, long long n_images,
-                                int n_classes, int out_units);
-hipError_t launch_batch_pack(hipStream_t stream, const BatchPack& q, long long wt_floats);
+hipError_t launch_batch_outputs(hipStream_t stream, const float* sums, int n_slices, long long slice_stride, const float* bias,
+                                float* probs, long long n_images, int n_classes, int out_units);
+hipError_t launch_batch_pack(hipStream_t stream, const BatchPackAll& all);
 hipError_t launch_deform(hipStream_t stream, const DeformJob& J);
 }  // namespace cnn355
 
@@ -1321,15 +1321,8 @@ int batch_plan(cnn* net, size_t batch, BatchPlan& B) {
     BatchPack& k = st.pack;
     std::memset(&k, 0, sizeof(k));
     k.w = L.w; k.csr_ptr = L.csr_ptr; k.csr_idx = L.csr_idx;
-    k.is_fc = L.kind != L_CONV; k.full_table = L.full_table; k.Mi = g.Mi; k.Mo = g.Mo; k.K = g.K; k.Kx = g.Kx; k.n_in = L.n_in;
+    k.full_table = L.kind != L_CONV || L.full_table; k.Mo = g.Mo; k.K = g.K; k.Kx = g.Kx;
     k.row = c.MT ? c.MT * c.TR : g.MoPad; k.k_total = g.Mi * KK;
-    if (L.kind == L_CONV) {
-      int ci = 0;
-      for (int q = 0; q < l; ++q) ci += P.layers[q].kind == L_CONV;
-      k.total = (long long)net->host_tables[ci].csr_idx.size() * KK;
-    } else {
-      k.total = (long long)L.n_in * L.n_out;
-    }
     BatchPool& q = st.pool;
     std::memset(&q, 0, sizeof(q));
     q.bias = L.bias; q.Mo = g.Mo; q.Ho = Ho; q.Wo = (L.kind == L_CONV) ? L.Wo : 1; q.Kp = Kp; q.Kpx = Kpx; q.Hp = Hp; q.Wp = Wp;
@@ -2116,10 +2109,13 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
   float* d_act[2] = {d_sums + batch * B.sums_per_image, d_sums + batch * (B.sums_per_image + B.act_per_image)};
   float* d_fe = d_act[1] + batch * B.act_per_image;
   // the weights as the products read them: one [k][map] matrix per layer, from their present values
-  for (BatchStep& st : B.steps) {
-    st.pack.wt = base + st.wt_off;
-    HIP_TRY(net, launch_batch_pack(net->stream, st.pack, (long long)st.wt_floats));
+  BatchPackAll pack;
+  pack.n = (int)B.steps.size();
+  for (int l = 0; l < pack.n; ++l) {
+    pack.l[l] = B.steps[l].pack;
+    pack.l[l].wt = base + B.steps[l].wt_off;
   }
+  HIP_TRY(net, launch_batch_pack(net->stream, pack));
   const size_t fe_sz = P.has_frontend ? (size_t)P.fe.n_filters * P.fe.H * P.fe.W : 0;
   for (size_t t0 = 0; t0 < n; t0 += batch) {
     const size_t nb = std::min(batch, n - t0);
@@ -2131,6 +2127,7 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
       in_stride = (long long)fe_sz;
     }
     int cur = 0;
+    const BatchPool* last_raw = nullptr;
     for (size_t s = 0; s < B.steps.size(); ++s) {
       BatchStep& st = B.steps[s];
       float* out = d_act[cur];
@@ -2145,6 +2142,12 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
         BatchGemm g = st.g;
         g.in = in; g.in_stride = in_stride; g.wt = base + st.wt_off; g.N = (long long)nb * g.P; g.out = raw ? d_sums : out;
         HIP_TRY(net, launch_batch_gemm(net->stream, g));
+      }
+      // (the output units add the planes of their own layer's sums)
+      if (raw && s + 1 == B.steps.size() && tap_step < 0) {
+        last_raw = &st.pool;
+        in = d_sums;
+        break;
       }
       if (raw) {
         BatchPool q = st.pool;
@@ -2161,7 +2164,9 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
         return CNN_OK;
       }
     }
-    HIP_TRY(net, launch_batch_outputs(net->stream, in, d_probs + t0 * P.n_classes, (long long)nb, P.n_classes, net->out_units));
+    HIP_TRY(net, launch_batch_outputs(net->stream, in, last_raw ? last_raw->n_slices : 1, last_raw ? last_raw->slice_stride : 0,
+                                      last_raw ? (const float*)last_raw->bias : nullptr, d_probs + t0 * P.n_classes, (long long)nb,
+                                      P.n_classes, net->out_units));
   }
   return CNN_OK;
 }

@@ -568,6 +568,20 @@ __global__ void __launch_bounds__(BT, MT * TR > 96 ? 2 : 3) k_batch_conv(BatchCo
   }
 }
 
+// the planes of partial sums of one output, added in their order, eight loads in flight (one: 50 planes took 14 us)
+__device__ __forceinline__ float add_planes(cgf p, int n, long long stride) {
+  float v = 0.f;
+  for (int s0 = 0; s0 < n; s0 += 8) {
+    float t[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t[u] = p[(long long)min(s0 + u, n - 1) * stride];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (s0 + u < n) v += t[u];
+  }
+  return v;
+}
+
 // bias + scaled tanh + max-pooling (Sec. 2.2, 2.3) of the raw sums of a whole batch; the sums may
 // come as several planes (slices of the k range), added here in a fixed order.  The activation
 // function is increasing, so the maximum is taken first: one tanh per window.  act 0: none (the
@@ -584,66 +598,74 @@ __global__ void __launch_bounds__(256) k_batch_pool(BatchPool q) {
   float best = -INFINITY;
   for (int dy = 0; dy < q.Kp; ++dy)
     for (int dx = 0; dx < q.Kpx; ++dx) {
-      float v = 0.f;
-      for (int sl = 0; sl < q.n_slices; ++sl) v += src[(long long)sl * q.slice_stride + dy * q.Wo + dx];
+      const float v = add_planes(src + dy * q.Wo + dx, q.n_slices, q.slice_stride);
       best = fmaxf(best, v);
     }
   best += q.bias[j];
   q.out[x] = q.act ? b_act(best) : best;
 }
 
-// Output units of a whole batch: soft-max of the output layer's sums (bias included), or the
-// scaled tanh for the variant with tanh output neurons.  One thread per image.
-__global__ void __launch_bounds__(256) k_batch_outputs(cgf logits, gf probs, long long n_images, int n_classes,
-                                                       int out_units) {
+// Output units of a whole batch: soft-max of the output layer's sums (as n_slices planes without the bias, or one with
+// it: bias null), or the scaled tanh for the variant with tanh output neurons.  One thread per image.
+__global__ void __launch_bounds__(256) k_batch_outputs(cgf sums, int n_slices, long long slice_stride, cgf bias, gf probs,
+                                                       long long n_images, int n_classes, int out_units) {
   const long long b = (long long)blockIdx.x * 256 + threadIdx.x;
   if (b >= n_images) return;
-  cgf a = logits + b * n_classes;
+  cgf a = sums + b * n_classes;
   gf o = probs + b * n_classes;
-  if (out_units == 1) {
-    for (int k = 0; k < n_classes; ++k) o[k] = b_act(a[k]);
-    return;
+  float mx = -INFINITY;
+  for (int k = 0; k < n_classes; ++k) {
+    float v = bias ? fmaxf(add_planes(a + k, n_slices, slice_stride), -INFINITY) + bias[k] : a[k];
+    if (out_units == 1) v = b_act(v);
+    o[k] = v;
+    mx = k ? fmaxf(mx, v) : v;
   }
-  float mx = a[0];
-  for (int k = 1; k < n_classes; ++k) mx = fmaxf(mx, a[k]);
+  if (out_units == 1) return;
   float z = 0.f;
-  for (int k = 0; k < n_classes; ++k) z += expf(a[k] - mx);
-  for (int k = 0; k < n_classes; ++k) o[k] = expf(a[k] - mx) / z;
+  for (int k = 0; k < n_classes; ++k) z += expf(o[k] - mx);
+  for (int k = 0; k < n_classes; ++k) o[k] = expf(o[k] - mx) / z;
 }
 
-// Wt[group of `row` maps][k][map] of one layer from the canonical weights: k = (input map, ky, kx), j = output map;
-// absent connections and the padding maps stay zero (the buffer is cleared first).
-__global__ void __launch_bounds__(256) k_batch_pack(BatchPack q) {
-  const long long x = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (x >= q.total) return;
-  if (q.is_fc) {  // W[n_out][n_in]
-    const int j = (int)(x / q.n_in), m = (int)(x - (long long)j * q.n_in);
-    q.wt[((long long)(j / q.row) * q.k_total + m) * q.row + j % q.row] = q.w[x];
-    return;
-  }
-  const int KK = q.K * q.Kx;
-  const long long slot = x / KK;
-  const int t = (int)(x - slot * KK);
-  int j, i;
-  if (q.full_table) {
-    j = (int)(slot / q.Mi);
-    i = (int)(slot - (long long)j * q.Mi);
-  } else {
-    // row j with csr_ptr[j] <= slot < csr_ptr[j + 1]
-    int lo = 0, hi = q.Mo;
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (q.csr_ptr[mid] <= slot) lo = mid; else hi = mid;
+// Wt[group of `row` maps][k][map] of every layer (blockIdx.y) from the canonical weights: k = (input map, ky, kx), j =
+// output map; absent connections and the padding maps are zero.  Tiles of 64 k x 32 maps, turned round in LDS: rows of
+// the canonical weights are read, rows of Wt written.  Two launches a layer (clear, scatter) before: 10000 digits 38 us
+// of launches -> 5.
+constexpr int PK = 64, PJ = 32;
+__global__ void __launch_bounds__(256) k_batch_pack(BatchPackAll all) {
+  __shared__ float t[PJ][PK + 1];
+  const BatchPack q = all.l[blockIdx.y];
+  const int KK = q.K * q.Kx, tk = (q.k_total + PK - 1) / PK;
+  const int rows = (q.Mo + q.row - 1) / q.row * q.row, tiles = tk * ((rows + PJ - 1) / PJ);
+  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int j0 = tile / tk * PJ, k0 = tile % tk * PK;
+    const int k = k0 + (threadIdx.x & (PK - 1));
+    const int i = k / KK;
+    for (int r = threadIdx.x / PK; r < PJ; r += 256 / PK) {
+      const int j = j0 + r;
+      float v = 0.f;
+      if (j < q.Mo && k < q.k_total) {
+        if (q.full_table) {
+          v = q.w[(long long)j * q.k_total + k];
+        } else {   // the slot of input map i among the row's connections, which ascend
+          int lo = q.csr_ptr[j], hi = q.csr_ptr[j + 1];
+          const int end = hi;
+          while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (q.csr_idx[mid] < i) lo = mid + 1; else hi = mid;
+          }
+          if (lo < end && q.csr_idx[lo] == i) v = q.w[(long long)lo * KK + (k - i * KK)];
+        }
+      }
+      t[r][k - k0] = v;
     }
-    j = lo;
-    i = q.csr_idx[slot];
+    __syncthreads();
+    const int j = j0 + (threadIdx.x & (PJ - 1));
+    if (j < rows) {
+      const gf dst = q.wt + (long long)(j / q.row) * q.k_total * q.row + j % q.row;
+      for (int c = threadIdx.x / PJ; c < PK && k0 + c < q.k_total; c += 256 / PJ) dst[(long long)(k0 + c) * q.row] = t[j - j0][c];
+    }
+    __syncthreads();
   }
-  q.wt[((long long)(j / q.row) * q.k_total + i * KK + t) * q.row + j % q.row] = q.w[x];
-}
-
-__global__ void __launch_bounds__(256) k_batch_zero(gf p, long long n) {
-  const long long x = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (x < n) p[x] = 0.f;
 }
 
 }  // namespace
@@ -746,17 +768,22 @@ hipError_t launch_batch_pool(hipStream_t stream, const BatchPool& q) {
   return hipGetLastError();
 }
 
-hipError_t launch_batch_outputs(hipStream_t stream, const float* logits, float* probs, long long n_images,
-                                int n_classes, int out_units) {
+hipError_t launch_batch_outputs(hipStream_t stream, const float* sums, int n_slices, long long slice_stride, const float* bias,
+                                float* probs, long long n_images, int n_classes, int out_units) {
   if (n_images <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_batch_outputs, dim3((unsigned)((n_images + 255) / 256)), dim3(256), 0, stream, (cgf)logits,
-                     (gf)probs, n_images, n_classes, out_units);
+  hipLaunchKernelGGL(k_batch_outputs, dim3((unsigned)((n_images + 255) / 256)), dim3(256), 0, stream, (cgf)sums, n_slices,
+                     slice_stride, (cgf)bias, (gf)probs, n_images, n_classes, out_units);
   return hipGetLastError();
 }
 
-hipError_t launch_batch_pack(hipStream_t stream, const BatchPack& q, long long wt_floats) {
-  hipLaunchKernelGGL(k_batch_zero, dim3((unsigned)((wt_floats + 255) / 256)), dim3(256), 0, stream, q.wt, wt_floats);
-  hipLaunchKernelGGL(k_batch_pack, dim3((unsigned)((q.total + 255) / 256)), dim3(256), 0, stream, q);
+hipError_t launch_batch_pack(hipStream_t stream, const BatchPackAll& all) {
+  long long most = 1;
+  for (int l = 0; l < all.n; ++l) {
+    const BatchPack& q = all.l[l];
+    const long long rows = (q.Mo + q.row - 1) / q.row * (long long)q.row;
+    most = std::max(most, (q.k_total + PK - 1) / PK * ((rows + PJ - 1) / PJ));
+  }
+  hipLaunchKernelGGL(k_batch_pack, dim3((unsigned)std::min(most, 4096ll), (unsigned)all.n), dim3(256), 0, stream, all);
   return hipGetLastError();
 }
 

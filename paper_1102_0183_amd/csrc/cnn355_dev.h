@@ -281,12 +281,15 @@ struct BatchPool {
 };
 struct BatchPack {
   const CNN_GLOBAL float* w;     // conv: [n_conn][K*Kx] in table order; fc: [n_out][n_in]
-  CNN_GLOBAL float* wt;          // [group][Kdim][row]
-  const CNN_GLOBAL int* csr_ptr;
+  CNN_GLOBAL float* wt;          // [group][k_total][row]
+  const CNN_GLOBAL int* csr_ptr; // used where the table is not full
   const CNN_GLOBAL int* csr_idx;
-  long long total;               // weights of the layer (biases apart)
-  int is_fc, full_table, Mi, Mo, K, Kx, n_in;
+  int full_table, Mo, K, Kx;     // (a fully connected layer: full, K = Kx = 1)
   int row, k_total;              // maps of a group of Wt, rows of it
+};
+struct BatchPackAll {
+  int n;
+  BatchPack l[MAX_LAYERS];
 };
 
 // ---- on-line deformation of training images ---------------------------------------------------

@@ -42,6 +42,7 @@ size_t batch_gemm_lds_bytes(const BatchGemm& g);
 hipError_t launch_batch_gemm(hipStream_t stream, const BatchGemm& g);
 size_t batch_conv_lds_bytes(const BatchConv& g);
 int batch_conv_fit(int MT, int TR, size_t lds_bytes);
+int batch_conv_grid_x(const BatchConv& g);
 hipError_t launch_batch_conv(hipStream_t stream, const BatchConv& g);
 hipError_t launch_batch_pool(hipStream_t stream, const BatchPool& q);
 hipError_t launch_batch_outputs(hipStream_t stream, const float* sums, int n_slices, long long slice_stride, const float* bias,
@@ -1167,9 +1168,12 @@ FastDiv fast_div_of(int d) {
   return f;
 }
 
-// The plan of k_batch_conv for a convolutional layer whose k_batch_gemm plan is g: tile, chunk and slices by a small time
-// model, in clocks of a compute unit.  Never more scratch memory than g takes: no more padded maps, no more k slices.
-// Leaves c.MT = 0 where a chunk of one input map does not fit.
+// The plan of k_batch_conv for a convolutional layer whose k_batch_gemm plan is g: tile and chunk by a small time model,
+// in clocks of a compute unit.  Never more scratch memory than g takes: no more padded maps.  The slices of the k range are
+// g's own, so that a running sum is no longer than there (fewer slices are faster for 33 stereo pairs, 77 us instead of 96,
+// but the error of 128 maps of 450 terms in one sum instead of three is 3.6e-7 instead of 2.3e-7, that of 100 maps of 2500
+// terms in one instead of five 8.3e-7 instead of 4.1e-7; and ten and ten input maps instead of sixteen and four already
+// 2.9e-7 instead of 2.8e-7).  Leaves c.MT = 0 where a chunk of one input map does not fit.
 void conv_plan(const LayerDev& L, const BatchGemm& g, size_t batch, BatchConv& c) {
   constexpr size_t LDS_HALF = 80 * 1024, LDS_WHOLE = 158 * 1024;   // two workgroups a compute unit, or one
   std::memset(&c, 0, sizeof(c));
@@ -1181,50 +1185,47 @@ void conv_plan(const LayerDev& L, const BatchGemm& g, size_t batch, BatchConv& c
   const size_t limit = (size_t)1 << 31;
   if ((size_t)HiWi * 4 * L.Mi >= limit || (size_t)t.k_total * 160 * 4 >= limit) return;   // (32-bit offsets of a chunk)
   double best = 0;
-  for (int slices = 1; slices <= g.KS; slices += slices < 4 ? 1 : slices / 2) {
-    // pooling inside, unless the k range is sliced or whole windows leave more than a quarter of the 128 columns empty
-    const bool inside = slices == 1 && (members == 1 || (members <= 128 && 128 / members * members >= 96));
-    t.Kp = inside ? L.Kp : 1; t.Kpx = inside ? L.Kpx : 1;
-    if (!inside && members > 1 && g.fuse != 0) continue;         // (g has no room for raw sums)
-    t.Wp = inside ? L.Wp : L.Wo;
-    t.win_img = inside ? L.Hp * L.Wp : L.Ho * L.Wo;
-    t.wins = inside ? 128 / members : 128;
-    t.fuse = slices > 1 || (!inside && members > 1) ? 0 : (L.is_output ? 2 : 1);
-    const size_t n_cb = (batch * t.win_img + t.wins - 1) / t.wins;
-    t.n_img_max = (int)std::min<size_t>(std::max<size_t>(batch, 1), (size_t)((t.wins - 1 + t.win_img - 1) / t.win_img + 1));
-    for (int tr : {32, 16})
-      for (int mt = tr == 32 ? 5 : 7; mt >= 1; --mt) {
-        const int rows = mt * tr, groups = (t.Mo + rows - 1) / rows;
-        if (groups * rows > g.MoPad) continue;
-        t.TR = tr; t.MT = mt;
-        const int kg = tr == 32 ? 8 : 16;
-        for (size_t budget : {LDS_HALF, LDS_WHOLE}) {
-          bool any = false;
-          const int whole = (t.Mi + slices - 1) / slices;   // a slice in one chunk
-          for (int ic = 1; ic <= whole; ++ic) {
-            int chunks = (t.Mi + ic - 1) / ic, cps = (chunks + slices - 1) / slices;
-            t.IC = ic; t.slot = (int)up64((size_t)ic * HiWi); t.n_slices = slices;
-            t.chunks_per_slice = cps; t.resident = cps == 1;
-            if (batch_conv_lds_bytes(t) > budget) {
-              if (ic == whole) break;
-              ic = whole - 1;      // the longest chunk may fit again: it needs its weights once
-              continue;
-            }
-            if ((chunks + cps - 1) / cps != slices) continue;
-            any = true;
-            // a block's time: k padded to whole groups, a few hundred clocks a chunk, a few thousand a block; a
-            // workgroup takes its blocks one after the other, the workgroups of a compute unit share its matrix cores
-            const int kc = ic * KK, fit = batch_conv_fit(mt, tr, batch_conv_lds_bytes(t));
-            const double block = (double)cps * ((kc + kg - 1) / kg * kg * (double)rows + 500.0) + 2500.0 + 16.0 * rows;
-            const size_t lines = (size_t)groups * slices, gx = std::min(n_cb, std::max<size_t>(1, 256 * fit / lines));
-            const size_t side = (gx * lines + 255) / 256, rounds = (n_cb + gx - 1) / gx;
-            const double est = (double)(side * rounds) * block * (side > 1 ? 1.0 : 1.5) + (t.fuse == 0 ? 12000.0 : 0.0);
-            if (best == 0 || est < best) { best = est; c = t; }
+  const int slices = g.KS;
+  t.n_slices = slices; t.run = std::min(t.Mi, g.chunks_per_slice * g.IC);
+  // pooling inside, unless the k range is sliced or whole windows leave more than a quarter of the 128 columns empty
+  const bool inside = slices == 1 && (members == 1 || (members <= 128 && 128 / members * members >= 96));
+  if (!inside && members > 1 && g.fuse != 0) return;           // (g has no room for raw sums)
+  t.Kp = inside ? L.Kp : 1; t.Kpx = inside ? L.Kpx : 1;
+  t.Wp = inside ? L.Wp : L.Wo;
+  t.win_img = inside ? L.Hp * L.Wp : L.Ho * L.Wo;
+  t.wins = inside ? 128 / members : 128;
+  t.fuse = slices > 1 || (!inside && members > 1) ? 0 : (L.is_output ? 2 : 1);
+  const size_t n_cb = (batch * t.win_img + t.wins - 1) / t.wins;
+  t.n_img_max = (int)std::min<size_t>(std::max<size_t>(batch, 1), (size_t)((t.wins - 1 + t.win_img - 1) / t.win_img + 1));
+  for (int tr : {32, 16})
+    for (int mt = tr == 32 ? 5 : 7; mt >= 1; --mt) {
+      const int rows = mt * tr, groups = (t.Mo + rows - 1) / rows;
+      if (groups * rows > g.MoPad) continue;
+      t.TR = tr; t.MT = mt;
+      const int kg = tr == 32 ? 8 : 16;
+      for (size_t budget : {LDS_HALF, LDS_WHOLE}) {
+        bool any = false;
+        for (int ic = 1; ic <= t.run; ++ic) {
+          const int cps = (t.run + ic - 1) / ic;         // chunks of a slice, the last may be short
+          t.IC = ic; t.slot = (int)up64((size_t)ic * HiWi); t.resident = cps == 1;
+          if (batch_conv_lds_bytes(t) > budget) {
+            if (ic == t.run) break;
+            ic = t.run - 1;      // the longest chunk may fit again: it needs its weights once
+            continue;
           }
-          if (any) break;
+          any = true;
+          // a block's time: k padded to whole groups, a few hundred clocks a chunk, a few thousand a block; a
+          // workgroup takes its blocks one after the other, the workgroups of a compute unit share its matrix cores
+          const int kc = ic * KK, fit = batch_conv_fit(mt, tr, batch_conv_lds_bytes(t));
+          const double block = (double)cps * ((kc + kg - 1) / kg * kg * (double)rows + 500.0) + 2500.0 + 16.0 * rows;
+          const size_t lines = (size_t)groups * slices, gx = std::min(n_cb, std::max<size_t>(1, 256 * fit / lines));
+          const size_t side = (gx * lines + 255) / 256, rounds = (n_cb + gx - 1) / gx;
+          const double est = (double)(side * rounds) * block * (side > 1 ? 1.0 : 1.5) + (t.fuse == 0 ? 12000.0 : 0.0);
+          if (best == 0 || est < best) { best = est; c = t; }
         }
+        if (any) break;
       }
-  }
+    }
   if (c.MT) { c.by_win_img = fast_div_of(c.win_img); c.by_wp = fast_div_of(c.Wp); }
 }
 
@@ -1789,6 +1790,45 @@ int cnn355_resident_plan_text(const char* arch, int fan_in, int n_ranks, int xcd
   return CNN_OK;
 }
 
+// development aid, host only: the plan of the batched forward pass of `arch` at `batch` images (tables as in
+// cnn355_resident_plan_text), a line per trainable layer of "name value" pairs, then the scratch floats a call takes.
+// run: input maps (of KK terms each) of the longest running sum; gemm_run, gemm_KS: of k_batch_gemm's plan of the layer.
+int cnn355_batch_plan_text(const char* arch, int fan_in, size_t batch, char* buf, size_t n) {
+  if (!arch || !buf || n == 0 || batch == 0) return fail(nullptr, CNN_E_ARG, "NULL argument or batch of 0");
+  cnn tmp;
+  int rc = plan_only(tmp, arch, fan_in, 0, 0);
+  if (rc) return rc;
+  BatchPlan B;
+  rc = batch_plan(&tmp, batch, B);
+  if (rc) { g_err = tmp.err; return rc; }
+  std::string t;
+  for (const BatchStep& st : B.steps) {
+    const BatchGemm& g = st.g;
+    BatchConv c = st.c;
+    std::vector<std::pair<const char*, long long>> f = {
+        {"conv", c.MT != 0}, {"Mi", g.Mi}, {"KK", g.K * g.Kx}, {"gemm_KS", g.KS}, {"gemm_run", std::min(g.Mi, g.chunks_per_slice * g.IC)},
+        {"wt_floats", (long long)st.wt_floats}};
+    if (c.MT) {
+      c.n_win = (int)(batch * c.win_img); c.n_cb = (c.n_win + c.wins - 1) / c.wins;
+      f.insert(f.end(), {{"MT", c.MT}, {"TR", c.TR}, {"IC", c.IC}, {"n_slices", c.n_slices}, {"run", c.run}, {"resident", c.resident},
+                         {"members", c.Kp * c.Kpx}, {"fuse", c.fuse}, {"wins", c.wins}, {"n_cb", c.n_cb}, {"gx", batch_conv_grid_x(c)},
+                         {"groups", (c.Mo + c.MT * c.TR - 1) / (c.MT * c.TR)}, {"chunk_floats", c.IC * c.Hi * c.Wi},
+                         {"lds_bytes", (long long)batch_conv_lds_bytes(c)}});
+    } else {
+      f.insert(f.end(), {{"MT", g.MT}, {"TR", g.TR}, {"IC", g.IC}, {"n_slices", g.KS},
+                         {"run", std::min(g.Mi, g.chunks_per_slice * g.IC)}, {"members", g.Kp * g.Kpx}, {"fuse", g.fuse},
+                         {"lds_bytes", (long long)batch_gemm_lds_bytes(g)}});
+    }
+    t += "layer";
+    for (const auto& kv : f) t += std::string(" ") + kv.first + " " + std::to_string(kv.second);
+    t += "\n";
+  }
+  t += "floats " + std::to_string(B.floats(batch)) + "\n";
+  if (t.size() + 1 > n) return fail(nullptr, CNN_E_ARG, "buffer too small for the plan text");
+  std::memcpy(buf, t.c_str(), t.size() + 1);
+  return CNN_OK;
+}
+
 // development aid: how many ranks share the delta pull into one input map of the resident plan's conv layer l
 int cnn355_resident_pull_shares(const cnn_t* net, int l) {
   if (!net || !net->flow_ok || l < 0 || l >= net->flow.n_conv) return -1;
@@ -2135,7 +2175,8 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
       if (st.c.MT) {
         BatchConv c = st.c;
         c.in = in; c.in_stride = in_stride; c.wt = base + st.wt_off; c.out = raw ? d_sums : out;
-        c.vec = ((uintptr_t)in & 15u) == 0 && in_stride % 4 == 0 && (c.IC * c.Hi * c.Wi) % 4 == 0;
+        c.vec = ((uintptr_t)in & 15u) == 0 && in_stride % 4 == 0 && (c.IC * c.Hi * c.Wi) % 4 == 0 &&
+                (c.n_slices == 1 || (c.run * c.Hi * c.Wi) % 4 == 0);
         c.n_win = (int)(nb * c.win_img); c.n_cb = (c.n_win + c.wins - 1) / c.wins;
         HIP_TRY(net, launch_batch_conv(net->stream, c));
       } else {

@@ -374,8 +374,8 @@ __global__ void __launch_bounds__(BT, MT * TR > 96 ? 2 : 3) k_batch_conv(BatchCo
   }
   const int j0 = blockIdx.y * WROW;
   for (int x = tid; x < WROW; x += BT) lds_b[x] = g.fuse && j0 + x < g.Mo ? g.bias[j0 + x] : 0.f;
-  const int ic_first = blockIdx.z * g.chunks_per_slice * g.IC;
-  const int ic_end = min(g.Mi, ic_first + g.chunks_per_slice * g.IC);
+  const int ic_first = blockIdx.z * g.run;
+  const int ic_end = min(g.Mi, ic_first + g.run);
   const int M = g.Kp * g.Kpx;
   // a column block's first and last image
   auto first_image = [&](int cb) { return fast_div(cb * g.wins, g.by_win_img); };
@@ -678,10 +678,16 @@ __global__ void __launch_bounds__(256) k_batch_pack(BatchPackAll all) {
 }
 
 }  // namespace
+size_t batch_conv_lds_bytes(const BatchConv& g);
 // workgroups of k_batch_conv a compute unit holds at once (registers, LDS)
 int batch_conv_fit(int MT, int TR, size_t lds_bytes) {
   const int regs = (MT * (TR == 32 ? 16 : 8) + 64 + 7) & ~7;
   return std::max(1, std::min({512 / regs, (int)(160 * 1024 / lds_bytes), 8}));
+}
+// workgroups along the column blocks: as many as the chip holds at once, over all groups of maps and slices
+int batch_conv_grid_x(const BatchConv& g) {
+  const int groups = (g.Mo + g.MT * g.TR - 1) / (g.MT * g.TR) * g.n_slices;
+  return (int)std::min<long long>(g.n_cb, std::max(1, 256 * batch_conv_fit(g.MT, g.TR, batch_conv_lds_bytes(g)) / groups));
 }
 namespace {
 
@@ -689,9 +695,8 @@ template <int MT, int TR>
 hipError_t launch_conv_mt(hipStream_t stream, const BatchConv& g, size_t lds_bytes) {
   hipError_t e = hipFuncSetAttribute((const void*)k_batch_conv<MT, TR>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
   if (e != hipSuccess) return e;
-  const int groups = (g.Mo + MT * TR - 1) / (MT * TR) * g.n_slices;
-  const int gx = (int)std::min<long long>(g.n_cb, std::max(1, 256 * batch_conv_fit(MT, TR, lds_bytes) / groups));
-  hipLaunchKernelGGL((k_batch_conv<MT, TR>), dim3((unsigned)gx, (unsigned)(groups / g.n_slices), (unsigned)g.n_slices), dim3(BT),
+  const int groups = (g.Mo + MT * TR - 1) / (MT * TR);
+  hipLaunchKernelGGL((k_batch_conv<MT, TR>), dim3((unsigned)batch_conv_grid_x(g), (unsigned)groups, (unsigned)g.n_slices), dim3(BT),
                      lds_bytes, stream, g);
   return hipGetLastError();
 }

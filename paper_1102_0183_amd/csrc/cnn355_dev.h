@@ -266,7 +266,8 @@ struct BatchConv {
   int wins, n_win, n_cb;         // windows of a column block, of the whole batch; column blocks
   int IC, slot, n_img_max;       // input maps of a chunk; floats of one staged image (whole runs of 64); images a block can touch
   int MT, TR;                    // tiles of TR maps a workgroup: TR 32 (v_mfma_f32_32x32x2_f32) or 16 (v_mfma_f32_16x16x4_f32)
-  int n_slices, chunks_per_slice, resident, k_total;  // resident: the k range is one chunk, its weights are staged once
+  int n_slices, run;             // the k range in slices of `run` input maps, one per blockIdx.z
+  int resident, k_total;         // resident: a slice is one chunk, its weights are staged once
   int vec;                       // images and chunks start on 16 bytes: staged 16 bytes a lane
   int fuse;                      // 0: raw sums; 1: bias + scaled tanh; 2: bias only
 };

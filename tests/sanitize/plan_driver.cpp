@@ -11,6 +11,7 @@
 
 #include "../../include/cnn355.h"
 extern "C" int cnn355_resident_plan_text(const char* arch, int fan_in, int n_ranks, int xcd_stride, char* buf, size_t n);
+extern "C" int cnn355_batch_plan_text(const char* arch, int fan_in, size_t batch, char* buf, size_t n);
 
 static int fails = 0;
 #define EXPECT(c) do { if (!(c)) { std::printf("FAILED line %d: %s\n", __LINE__, #c); ++fails; } } while (0)
@@ -48,6 +49,10 @@ static void walk(const std::string& arch, int fan, int ranks, int stride) {
     EXPECT(rp == 0 && std::strlen(buf.data()) > 0 && bytes > 0);
     const int rr = cnn355_resident_plan_text(arch.c_str(), fan, ranks, stride, buf.data(), buf.size());
     EXPECT(rr == 0 && std::strlen(buf.data()) > 0);
+    for (size_t batch : {(size_t)1, (size_t)33, (size_t)4096}) {   // (maps beyond the batched pass's LDS are refused)
+      const int rb = cnn355_batch_plan_text(arch.c_str(), fan, batch, buf.data(), buf.size());
+      EXPECT(rb == 0 || std::strlen(cnn_last_error(nullptr)) > 0);
+    }
     EXPECT(cnn_plan_text(arch.c_str(), buf.data(), 8) != 0 || std::strlen(buf.data()) < 8);   // a buffer too small is refused or cut
   } else {
     EXPECT(std::strlen(cnn_last_error(nullptr)) > 0);

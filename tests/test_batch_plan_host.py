@@ -1,0 +1,48 @@
+"""Host logic of the batched forward pass (no GPU): the plan of every layer -- kernel, tile, chunks, slices of the k
+range -- against rules restated here, over the benchmark networks, the paper's and seeded random ones, from one image
+to thousands."""
+import numpy as np
+import pytest
+
+from paper_1102_0183_amd import binding, synth
+
+LDS = 160 * 1024
+BATCHES = (1, 2, 7, 16, 33, 64, 128, 300, 512, 1000, 4096)
+
+
+def random_archs(n, seed):
+    rng = np.random.default_rng(seed)
+    out = []
+    while len(out) < n:
+        c, h = int(rng.integers(1, 5)), int(rng.integers(8, 50))
+        s, layers = "%dx%dx%d" % (c, h, h), 0
+        for _ in range(int(rng.integers(1, 5))):
+            k, skip = int(rng.integers(1, 6)), int(rng.integers(0, 4) == 0)
+            if h < k + 1:
+                break
+            h = (h - k) // (skip + 1) + 1
+            pool = int(rng.choice([q for q in (1, 2, 3, 4, 5) if h % q == 0]))
+            h //= pool
+            s += "-%dC%d%s-MP%d" % (int(rng.choice([3, 16, 17, 33, 80, 100, 150, 161, 300])), k, "S1" if skip else "", pool)
+            layers += 1
+        if layers:
+            out.append(s + "-%dN-5N" % int(rng.integers(5, 300)))
+    return out
+
+
+ARCHS = sorted({w.arch for w in synth.WORKLOADS.values()}) + random_archs(40, 21)
+
+
+@pytest.mark.parametrize("arch", ARCHS)
+def test_partial_sums_are_those_of_the_general_product(arch):
+    """k_batch_conv takes a layer over from k_batch_gemm: its partial sums are those of the k slices there (rounding of
+    a sum in 32 bits grows with its length), and its planes no more (the caller's scratch memory)."""
+    for batch in BATCHES:
+        layers, _ = binding.batch_plan(arch, batch)
+        for l, p in enumerate(layers):
+            where = (batch, l, p)
+            assert p["run"] == p["gemm_run"], where
+            assert p["n_slices"] == p["gemm_KS"], where
+            assert (p["n_slices"] - 1) * p["run"] < p["Mi"] <= p["n_slices"] * p["run"], where
+            assert 1 <= p["IC"] <= p["Mi"], where
+            assert p["lds_bytes"] <= LDS, where

@@ -577,13 +577,15 @@ __global__ void __launch_bounds__(BT, MT * TR > 96 ? 2 : 3) k_batch_conv(BatchCo
   }
 }
 
-// the planes of partial sums of one output, added in their order, eight loads in flight (one: 50 planes took 14 us)
+// the planes of partial sums of one output, added in their order, up to eight loads in flight
 __device__ __forceinline__ float add_planes(cgf p, int n, long long stride) {
+  if (n == 1) return 0.f + p[0];
   float v = 0.f;
   for (int s0 = 0; s0 < n; s0 += 8) {
     float t[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) t[u] = p[(long long)min(s0 + u, n - 1) * stride];
+    for (int u = 0; u < 8; ++u)
+      if (s0 + u < n) t[u] = p[(long long)(s0 + u) * stride];
 #pragma unroll
     for (int u = 0; u < 8; ++u)
       if (s0 + u < n) v += t[u];

@@ -203,7 +203,7 @@ def resident_plan(arch, fan_in=0, n_ranks=0, xcd_stride=0):
 
 def batch_plan(arch, batch, fan_in=0):
     """Development aid, host-only: the plan of the batched forward pass of an architecture at `batch` images in flight,
-    parsed: ([{field: value} per trainable layer], scratch floats).  fan_in as for resident_plan()."""
+    parsed: ([{field: value} per trainable layer], {field: value} of the whole pass).  fan_in as for resident_plan()."""
     f = lib().cnn355_batch_plan_text
     f.restype = C.c_int
     f.argtypes = [C.c_char_p, C.c_int, C.c_size_t, C.c_char_p, C.c_size_t]
@@ -211,14 +211,14 @@ def batch_plan(arch, batch, fan_in=0):
     rc = f(arch.encode(), fan_in, batch, buf, len(buf))
     if rc:
         raise CnnError(rc, "cnn355_batch_plan_text(%r)" % arch, _err())
-    layers, floats = [], 0
+    layers, whole = [], {}
     for line in buf.value.decode().splitlines():
         w = line.split()
         if w[0] == "layer":
             layers.append({w[k]: int(w[k + 1]) for k in range(1, len(w), 2)})
         else:
-            floats = int(w[1])
-    return layers, floats
+            whole[w[0]] = int(w[1])
+    return layers, whole
 
 
 def resident_spec_source_for(arch, fan_in=0, n_ranks=0, xcd_stride=0):

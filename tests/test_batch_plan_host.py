@@ -46,3 +46,14 @@ def test_partial_sums_are_those_of_the_general_product(arch):
             assert (p["n_slices"] - 1) * p["run"] < p["Mi"] <= p["n_slices"] * p["run"], where
             assert 1 <= p["IC"] <= p["Mi"], where
             assert p["lds_bytes"] <= LDS, where
+
+
+@pytest.mark.parametrize("classes", [2, 5, 10, 47, 1000])
+@pytest.mark.parametrize("hidden", ["", "-300N", "-1200N"])
+def test_output_units_add_planes_only_where_they_are_few(classes, hidden):
+    """One thread adds an image's planes, class after class: a handful of rounds of eight loads, no more."""
+    arch = "1x24x24-40C3-MP2%s-%dN" % (hidden, classes)
+    for batch in BATCHES:
+        layers, whole = binding.batch_plan(arch, batch)
+        rounds = classes * -(-layers[-1]["n_slices"] // 8)
+        assert whole["outputs_add"] == (layers[-1]["fuse"] == 0 and rounds <= 8), (batch, layers[-1], whole)

@@ -1173,12 +1173,55 @@ FastDiv fast_div_of(int d) {
   return f;
 }
 
-// The plan of k_batch_conv for a convolutional layer whose k_batch_gemm plan is g: tile and chunk by a small time model,
-// in clocks of a compute unit.  Never more scratch memory than g takes: no more padded maps.  The slices of the k range are
-// g's own, so that a running sum is no longer than there (fewer slices are faster for 33 stereo pairs, 77 us instead of 96,
-// but the error of 128 maps of 450 terms in one sum instead of three is 3.6e-7 instead of 2.3e-7, that of 100 maps of 2500
-// terms in one instead of five 8.3e-7 instead of 4.1e-7; and ten and ten input maps instead of sixteen and four already
-// 2.9e-7 instead of 2.8e-7).  Leaves c.MT = 0 where a chunk of one input map does not fit.
+// Time models of the two kernels for a convolutional layer, in clocks of a compute unit: coefficients fitted to the
+// difference of the two kernels over 12700 layers, random ones and those of the benchmark's nets (1 to 300 maps of 1 to 96
+// pixels, kernels 1 to 7, pooling to 12, batches to 10000).  k_batch_conv is the slower one by more than 3 % in 683 of
+// them, in 143 of those that conv_plan gives it, which does without 0.4 % of what the kernel gains over all of them.  The
+// more workgroups work side by side on a compute unit (1, 2, up to 4, more), the more of a workgroup's waits is hidden.
+int side_by_side(double workgroups, int fit) {
+  const double n = std::min((double)fit, workgroups);
+  return n < 2 ? 0 : n < 3 ? 1 : n < 5 ? 2 : 3;
+}
+// k_batch_gemm: per chunk the products (k padded to whole groups) and the rounds of eight loads a thread that stage it
+double gemm_clocks(const BatchGemm& g, size_t batch) {
+  constexpr double ROUND[4] = {810, 850, 530, 90};
+  const int rows = g.MT * g.TR, kc = g.IC * g.K * g.Kx, kg = g.TR == 32 ? 8 : 16, members = g.Kp * g.Kpx;
+  const int regs = g.MT * (g.TR == 32 ? 16 : 8) * (members > 1 ? 2 : 1) + 80;
+  const int fit = std::max(1, std::min({512 / regs, (int)(160 * 1024 / batch_gemm_lds_bytes(g)), 8}));
+  const double side = std::ceil(std::ceil((double)batch * g.P / 128) * (g.MoPad / rows) * g.KS / 256);
+  const int s = side_by_side(side, fit);
+  const double images = std::min<double>((double)batch, 1.0 + 127.0 / g.P);
+  const double rounds = std::ceil(images * g.IC * g.Hi * g.Wi / 2048) + std::ceil((kc + 1.0) * rows / 4096);
+  const double chunk = 1600.0 + 0.82 * ((kc + kg - 1) / kg * kg) * rows * members + (g.prefetch ? 310.0 : ROUND[s]) * rounds;
+  return side * (g.chunks_per_slice * chunk + 81.0 * rows) * (s ? 1.0 : 1.5) + (g.fuse == 0 ? 6400.0 : 0.0);
+}
+// k_batch_conv: per chunk the products and a wavefront's staging loads (a run of every image the block touches); per block
+// a constant and the stores of its rows, or the tiles that pass through LDS.  A workgroup takes its blocks one after the
+// other, the workgroups of a compute unit share its matrix cores.
+double conv_clocks(const BatchConv& t, size_t batch, size_t n_cb) {
+  constexpr double LOAD16[4] = {139, 126, 104, 104}, LOAD4[4] = {87, 78, 62, 66}, BLOCK[4] = {1930, 1290, 1220, 970};
+  const int rows = t.MT * t.TR, kc = t.IC * t.K * t.Kx, kg = t.TR == 32 ? 8 : 16, HiWi = t.Hi * t.Wi, M = t.Kp * t.Kpx;
+  const int fit = batch_conv_fit(t.MT, t.TR, batch_conv_lds_bytes(t));
+  const size_t lines = (size_t)((t.Mo + rows - 1) / rows) * t.n_slices, gx = std::min(n_cb, std::max<size_t>(1, 256 * fit / lines));
+  const size_t side = (gx * lines + 255) / 256, rounds = (n_cb + gx - 1) / gx;
+  const int s = side_by_side((double)side, fit);
+  const bool vec = (t.IC * HiWi) % 4 == 0 && t.in_stride % 4 == 0 && (t.n_slices == 1 || (t.run * HiWi) % 4 == 0);
+  const double images = std::min<double>((double)batch, 1.0 + (t.wins - 1.0) / t.win_img);
+  const int runs = (t.IC * HiWi + (vec ? 255 : 63)) / (vec ? 256 : 64);
+  const double chunk = 0.78 * ((kc + kg - 1) / kg * kg) * rows + (vec ? LOAD16 : LOAD4)[s] * images * ((runs + 3) / 4);
+  const double block = (t.run + t.IC - 1) / t.IC * chunk + BLOCK[s] + (M == 1 ? 49.0 * rows : M == 4 ? 0.0 : 285.0 * t.MT);
+  return (double)(side * rounds) * block * (s ? 1.0 : 1.5) + (t.fuse == 0 ? 9700.0 : 0.0);
+}
+
+// The plan of k_batch_conv for a convolutional layer whose k_batch_gemm plan is g: the tile and chunk of the fewest clocks.
+// Never more scratch memory than g takes: no more padded maps.  The slices of the k range are g's own, so that a running
+// sum is no longer than there (fewer slices are faster for 33 stereo pairs, 77 us instead of 96, but the error of 128 maps
+// of 450 terms in one sum instead of three is 3.6e-7 instead of 2.3e-7, that of 100 maps of 2500 terms in one instead of
+// five 8.3e-7 instead of 4.1e-7; and ten and ten input maps instead of sixteen and four already 2.9e-7 instead of 2.8e-7).
+// Leaves c.MT = 0 where a chunk of one input map does not fit, and where the models have k_batch_gemm as fast (or a tenth
+// slower; sliced sums, where they err most, 5 % faster): this kernel stages image by image, so that blocks of many small
+// images (layers of one output pixel) or of a small part of a large one leave its matrix cores waiting (5000 images, 100C4
+// on 100 maps of 4 x 4: k_batch_gemm 118 us, k_batch_conv 223; 1289 of 1x81x81-4C6-MP2 433 and 704).
 void conv_plan(const LayerDev& L, const BatchGemm& g, size_t batch, BatchConv& c) {
   constexpr size_t LDS_HALF = 80 * 1024, LDS_WHOLE = 158 * 1024;   // two workgroups a compute unit, or one
   std::memset(&c, 0, sizeof(c));
@@ -1186,7 +1229,7 @@ void conv_plan(const LayerDev& L, const BatchGemm& g, size_t batch, BatchConv& c
   std::memset(&t, 0, sizeof(t));
   t.Mi = L.Mi; t.Hi = L.Hi; t.Wi = L.Wi; t.K = L.K; t.Kx = L.Kx; t.stride = L.S + 1; t.stride_x = L.Sx + 1; t.Mo = L.Mo;
   t.in_stride = g.in_stride; t.bias = L.bias; t.k_total = L.Mi * L.K * L.Kx;
-  const int KK = L.K * L.Kx, HiWi = L.Hi * L.Wi, members = L.Kp * L.Kpx;
+  const int HiWi = L.Hi * L.Wi, members = L.Kp * L.Kpx;
   const size_t limit = (size_t)1 << 31;
   if ((size_t)HiWi * 4 * L.Mi >= limit || (size_t)t.k_total * 160 * 4 >= limit) return;   // (32-bit offsets of a chunk)
   double best = 0;
@@ -1207,30 +1250,23 @@ void conv_plan(const LayerDev& L, const BatchGemm& g, size_t batch, BatchConv& c
       const int rows = mt * tr, groups = (t.Mo + rows - 1) / rows;
       if (groups * rows > g.MoPad) continue;
       t.TR = tr; t.MT = mt;
-      const int kg = tr == 32 ? 8 : 16;
       for (size_t budget : {LDS_HALF, LDS_WHOLE}) {
         bool any = false;
-        for (int ic = 1; ic <= t.run; ++ic) {
-          const int cps = (t.run + ic - 1) / ic;         // chunks of a slice, the last may be short
-          t.IC = ic; t.slot = (int)up64((size_t)ic * HiWi); t.resident = cps == 1;
+        for (int ic = 1; ic <= t.run; ++ic) {   // (the last chunk of a slice may be short)
+          t.IC = ic; t.slot = (int)up64((size_t)ic * HiWi); t.resident = ic == t.run;
           if (batch_conv_lds_bytes(t) > budget) {
             if (ic == t.run) break;
             ic = t.run - 1;      // the longest chunk may fit again: it needs its weights once
             continue;
           }
           any = true;
-          // a block's time: k padded to whole groups, a few hundred clocks a chunk, a few thousand a block; a
-          // workgroup takes its blocks one after the other, the workgroups of a compute unit share its matrix cores
-          const int kc = ic * KK, fit = batch_conv_fit(mt, tr, batch_conv_lds_bytes(t));
-          const double block = (double)cps * ((kc + kg - 1) / kg * kg * (double)rows + 500.0) + 2500.0 + 16.0 * rows;
-          const size_t lines = (size_t)groups * slices, gx = std::min(n_cb, std::max<size_t>(1, 256 * fit / lines));
-          const size_t side = (gx * lines + 255) / 256, rounds = (n_cb + gx - 1) / gx;
-          const double est = (double)(side * rounds) * block * (side > 1 ? 1.0 : 1.5) + (t.fuse == 0 ? 12000.0 : 0.0);
+          const double est = conv_clocks(t, batch, n_cb);
           if (best == 0 || est < best) { best = est; c = t; }
         }
         if (any) break;
       }
     }
+  if (best >= (c.fuse ? 1.1 : 0.95) * gemm_clocks(g, batch)) c.MT = 0;
   if (c.MT) { c.by_win_img = fast_div_of(c.win_img); c.by_wp = fast_div_of(c.Wp); }
 }
 

@@ -57,3 +57,17 @@ def test_output_units_add_planes_only_where_they_are_few(classes, hidden):
         layers, whole = binding.batch_plan(arch, batch)
         rounds = classes * -(-layers[-1]["n_slices"] // 8)
         assert whole["outputs_add"] == (layers[-1]["fuse"] == 0 and rounds <= 8), (batch, layers[-1], whole)
+
+
+@pytest.mark.parametrize("arch,batch", [("100x4x4-100C4-10N", 5000), ("128x3x3-100C3-10N", 5000), ("64x2x2-64C2-10N", 700),
+                                        ("300x1x1-300C1-10N", 5000), ("36x6x6-72C6-5N", 4837), ("1x81x81-4C6-MP2-5N", 1289),
+                                        ("1x63x63-1C4-MP4-5N", 2882)])
+def test_blocks_of_many_small_images_or_of_a_small_part_of_one_stay_with_the_general_product(arch, batch):
+    """Measured 1.2 to 4.5 times as slow in k_batch_conv."""
+    assert not binding.batch_plan(arch, batch)[0][0]["conv"]
+
+
+@pytest.mark.parametrize("name,batch,layers", [("cfg2a", 4096, 2), ("cfg3", 33, 2), ("cfg4a", 512, 3), ("cfg4b", 512, 3), ("cfg5", 1024, 2)])
+def test_the_benchmark_networks_convolutional_layers_run_in_the_persistent_kernel(name, batch, layers):
+    plan, _ = binding.batch_plan(synth.WORKLOADS[name].arch, batch)
+    assert [p["conv"] for p in plan[:layers]] == [1] * layers

@@ -438,13 +438,20 @@ void build_tables(int Mo, int Mi, const std::vector<uint8_t>& table, cnn::HostTa
     T.csr_ptr[j + 1] = (int)T.csr_idx.size();
     T.max_conn = std::max(T.max_conn, T.csr_ptr[j + 1] - T.csr_ptr[j]);
   }
+  for (int i : T.csr_idx) ++T.csc_ptr[i + 1];
   for (int i = 0; i < Mi; ++i) {
-    for (int j = 0; j < Mo; ++j)
-      for (int s = T.csr_ptr[j]; s < T.csr_ptr[j + 1]; ++s)
-        if (T.csr_idx[s] == i) { T.csc_j.push_back(j); T.csc_slot.push_back(s); }
-    T.csc_ptr[i + 1] = (int)T.csc_j.size();
-    T.max_back = std::max(T.max_back, T.csc_ptr[i + 1] - T.csc_ptr[i]);
+    T.max_back = std::max(T.max_back, T.csc_ptr[i + 1]);
+    T.csc_ptr[i + 1] += T.csc_ptr[i];
   }
+  T.csc_j.resize(T.csr_idx.size());
+  T.csc_slot.resize(T.csr_idx.size());
+  std::vector<int> at(T.csc_ptr.begin(), T.csc_ptr.end() - 1);
+  for (int j = 0; j < Mo; ++j)
+    for (int s = T.csr_ptr[j]; s < T.csr_ptr[j + 1]; ++s) {
+      const int q = at[T.csr_idx[s]]++;
+      T.csc_j[q] = j;
+      T.csc_slot[q] = s;
+    }
 }
 
 // Every size a kernel relies on, re-derived from the finished plan: a stage whose operands do

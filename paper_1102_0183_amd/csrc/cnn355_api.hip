@@ -2154,7 +2154,7 @@ int cnn_deform_images(void* hip_stream, const float* d_src, size_t n_src, float*
   J.seed = seed; J.first_index = first_index;
   // |A - I| is at most 3 and 2 (1 + max_shear), the smoothed fields stay within [-1, 1]
   const double reach = 2.0 * (1.0 + J.max_shear) + 3.0;
-  J.fixed = J.max_tx + J.max_ty + reach * (H + W) + std::fabs((double)J.alpha) < (double)(1 << 18);
+  J.bounded = J.max_tx + J.max_ty + reach * (H + W) + std::fabs((double)J.alpha) < (double)(1 << 18);
   J.R = -1;
   for (float& t : J.taps) t = 0.f;
   if (p->sigma > 0.f && p->alpha != 0.f) {

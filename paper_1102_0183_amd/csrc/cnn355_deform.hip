@@ -116,47 +116,34 @@ __device__ __forceinline__ Image image_of(const DeformJob& J, long long k) {
 }
 
 // N pixels (x[i], y[i]) of a lane, displaced by ax[i] + ex[i] and ay[i] + ey[i] (the affine map's share and the elastic
-// part); fax = ax + FIX, fay = ay + FIX; pixels with !ok[i] are worked out and not written.  All loads of a map are in flight together, then the stores
+// part); pixels with !ok[i] are worked out and not written.  All loads of a map are in flight together, then the stores
 // (a load behind a store waits for the store too).  A neighbour outside reads the image's first pixel and takes `fill`.
-// The source position's whole part and fraction come out of one addition: below 2^19 pixels (J.fixed: the host has
-// bounded every term) the sum plus 1.5 * 2^20 has the fraction as the low word of the double, in steps of 2^-32,
-// and the whole part, floored, in the high word.  RARE: the caller wants the displacements, or they are unbounded.
-constexpr double FIX = 1572864.0;          // 1.5 * 2^20
-constexpr int FIX_HI = 0x41380000;         // its high word
+// Positions are floored in double, as they are worked out.  RARE: the
+// caller wants the displacements, or they are unbounded.
 template <int N, bool ELASTIC, bool RARE>
 __device__ __forceinline__ void sample_pixels(const DeformJob& J, const Image& im, const int (&x)[N], const int (&y)[N],
-                                              const bool (&ok)[N], const double (&fax)[N], const double (&fay)[N],
-                                              const double (&ax)[N], const double (&ay)[N], const float (&ex)[N], const float (&ey)[N]) {
+                                              const bool (&ok)[N], const double (&ax)[N], const double (&ay)[N],
+                                              const float (&ex)[N], const float (&ey)[N]) {
   const int H = J.H, W = J.W;
   float fx[N], fy[N];
   int x0[N], y0[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    if (!RARE || J.fixed) {
-      double px = fax[i], py = fay[i];
-      if (ELASTIC) { px += (double)ex[i]; py += (double)ey[i]; }
-      x0[i] = x[i] + (__double2hiint(px) - FIX_HI);
-      y0[i] = y[i] + (__double2hiint(py) - FIX_HI);
-      fx[i] = (float)(unsigned int)__double2loint(px) * 2.3283064365386963e-10f;   // 2^-32
-      fy[i] = (float)(unsigned int)__double2loint(py) * 2.3283064365386963e-10f;
+    double dx = ax[i], dy = ay[i];
+    if (ELASTIC) { dx += (double)ex[i]; dy += (double)ey[i]; }
+    if (RARE && J.disp && ok[i]) {
+      J.disp[(im.k * 2) * (H * W) + y[i] * W + x[i]] = (float)dx;
+      J.disp[(im.k * 2 + 1) * (H * W) + y[i] * W + x[i]] = (float)dy;
     }
-    if (RARE) {
-      double dx = ax[i], dy = ay[i];
-      if (ELASTIC) { dx += (double)ex[i]; dy += (double)ey[i]; }
-      if (!J.fixed) {
-        // far outside in any direction reads the fill value only; the clamp keeps the integers small
-        const double fdx = floor(fmin(fmax(dx, -(double)(W + 2)), (double)(W + 2)));
-        const double fdy = floor(fmin(fmax(dy, -(double)(H + 2)), (double)(H + 2)));
-        fx[i] = fminf(fmaxf((float)(dx - fdx), 0.f), 1.f);
-        fy[i] = fminf(fmaxf((float)(dy - fdy), 0.f), 1.f);
-        x0[i] = x[i] + (int)fdx;
-        y0[i] = y[i] + (int)fdy;
-      }
-      if (J.disp && ok[i]) {
-        J.disp[(im.k * 2) * (H * W) + y[i] * W + x[i]] = (float)dx;
-        J.disp[(im.k * 2 + 1) * (H * W) + y[i] * W + x[i]] = (float)dy;
-      }
+    if (RARE) {   // far outside in any direction reads the fill value only; the clamp keeps the integers small
+      dx = fmin(fmax(dx, -(double)(W + 2)), (double)(W + 2));
+      dy = fmin(fmax(dy, -(double)(H + 2)), (double)(H + 2));
     }
+    const double fdx = floor(dx), fdy = floor(dy);
+    fx[i] = (float)(dx - fdx);
+    fy[i] = (float)(dy - fdy);
+    x0[i] = x[i] + (int)fdx;
+    y0[i] = y[i] + (int)fdy;
   }
   bool in00[N], in01[N], in10[N], in11[N];
   unsigned int o00[N], o01[N], o10[N], o11[N], od[N];  // bytes
@@ -269,7 +256,7 @@ __global__ void __launch_bounds__(DT) k_deform(const DeformJob J) {
     for (int p = tid; p < HW; p += PXL * DT) {
       int px[PXL], py[PXL];
       bool ok[PXL];
-      double ax[PXL], ay[PXL], fax[PXL], fay[PXL];
+      double ax[PXL], ay[PXL];
       float ex[PXL], ey[PXL];
 #pragma unroll
       for (int q = 0; q < PXL; ++q) {
@@ -279,8 +266,6 @@ __global__ void __launch_bounds__(DT) k_deform(const DeformJob J) {
         const double u = (double)x - cx, v = (double)y - cy;
         ax[q] = fma(A.a00, u, fma(A.a01, v, A.tx));
         ay[q] = fma(A.a10, u, fma(A.a11, v, A.ty));
-        fax[q] = fma(A.a00, u, fma(A.a01, v, A.tx + FIX));
-        fay[q] = fma(A.a10, u, fma(A.a11, v, A.ty + FIX));
         const int at = ok[q] ? y * Wp + x : 0;
         ex[q] = ELASTIC ? J.alpha * rx[at] : 0.f;
         ey[q] = ELASTIC ? J.alpha * ry[at] : 0.f;
@@ -288,7 +273,7 @@ __global__ void __launch_bounds__(DT) k_deform(const DeformJob J) {
         y += step_y;
         if (x >= W) { x -= W; ++y; }
       }
-      sample_pixels<PXL, ELASTIC, RARE>(J, im, px, py, ok, fax, fay, ax, ay, ex, ey);
+      sample_pixels<PXL, ELASTIC, RARE>(J, im, px, py, ok, ax, ay, ex, ey);
     }
   }
 }
@@ -390,7 +375,7 @@ __global__ void __launch_bounds__(512, 4) k_deform_mx(const DeformJob J) {
           for (int v = 0; v < 4; v += PX) {
             int px[PX], py[PX];
             bool ok[PX];
-            double dx[PX], dy[PX], fdx[PX], fdy[PX];
+            double dx[PX], dy[PX];
             float ex[PX], ey[PX];
 #pragma unroll
             for (int q = 0; q < PX; ++q) {
@@ -399,12 +384,10 @@ __global__ void __launch_bounds__(512, 4) k_deform_mx(const DeformJob J) {
               ok[q] = x < W && py[q] < H;
               dx[q] = fma(bx, (double)(v + q), ax0);
               dy[q] = fma(by, (double)(v + q), ay0);
-              fdx[q] = fma(bx, (double)(v + q), ax0 + FIX);
-              fdy[q] = fma(by, (double)(v + q), ay0 + FIX);
               ex[q] = J.alpha * vx[2 * D][v + q];
               ey[q] = J.alpha * vy[2 * D][v + q];
             }
-            sample_pixels<PX, true, RARE>(J, im, px, py, ok, fdx, fdy, dx, dy, ex, ey);
+            sample_pixels<PX, true, RARE>(J, im, px, py, ok, dx, dy, ex, ey);
           }
         }
 #pragma unroll
@@ -460,7 +443,7 @@ static hipError_t launch_deform_any(hipStream_t stream, const DeformJob& J, unsi
 hipError_t launch_deform(hipStream_t stream, const DeformJob& J) {
   if (J.n <= 0) return hipSuccess;
   const unsigned int grid = (unsigned int)(J.n < 8192 ? J.n : 8192);
-  return J.disp || !J.fixed ? launch_deform_any<true>(stream, J, grid) : launch_deform_any<false>(stream, J, grid);
+  return J.disp || !J.bounded ? launch_deform_any<true>(stream, J, grid) : launch_deform_any<false>(stream, J, grid);
 }
 
 }  // namespace cnn355

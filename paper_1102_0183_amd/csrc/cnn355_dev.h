@@ -309,7 +309,7 @@ struct DeformJob {
   double max_rot;                   // half turns
   double max_shear, max_scale;      // (the affine part of a source position is worked out in double: in float
                                     // its rounding error grows with the displacement and with the map size)
-  int fixed;                        // every displacement stays below 2^18 pixels
+  int bounded;                      // every displacement stays below 2^18 pixels
   float alpha, fill;
   unsigned long long seed, first_index;
   float taps[2 * DEFORM_MAX_R + 1]; // normalised to sum 1

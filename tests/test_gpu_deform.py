@@ -90,6 +90,21 @@ def test_displacements_beyond_the_fixed_point_range(kw):
     assert np.array_equal(run(src, 40, gp, SEED, 5, want_disp=False)[0], got)
 
 
+def test_a_small_shift_keeps_its_digits():
+    """Translations of 1e-10 of the width: the shifted share of a pixel is some 1e-9, and keeps a float's digits (positions
+    are worked out and floored in double; fixed point in steps of 2^-32 would leave one digit of it)."""
+    src = np.zeros((64, 1, 12, 30), np.float32)
+    src[..., 1::2] = 1.0
+    gp, op = params(max_translation=1e-10)
+    got, disp = run(src, 64, gp, SEED, 9)
+    _, want_disp = DO.deform_images(src, SEED, 9, op)
+    right = (want_disp[:, 0, 0, 0] > 0) & (want_disp[:, 1, 0, 0] > 0)   # (to the left a fraction rounds to one)
+    assert 5 < right.sum() < 30
+    for k in np.nonzero(right)[0]:
+        share = want_disp[k, 0, 0, 0]   # of the neighbour on the right, at every pixel of an even column but in the last row
+        assert np.abs(got[k, 0, :-1, 0:28:2] / share - 1.0).max() <= 1e-6
+
+
 def test_many_images_a_workgroup():
     """More than sixteen images for every workgroup of the largest launch: its next affine maps are drawn again."""
     n = 8192 * 16 + 3

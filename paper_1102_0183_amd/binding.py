@@ -144,6 +144,14 @@ def deform_images(d_src, d_dst, n, params, seed, first_index, d_src_index=None, 
         raise CnnError(rc, "cnn_deform_images", _err())
 
 
+def deform_on_matrix_cores(maps, rows, cols, sigma):
+    """Development aid, host-only: whether deform_images smooths the fields of such images on the matrix cores."""
+    f = lib().cnn355_deform_form
+    f.restype = C.c_int
+    f.argtypes = [C.c_int, C.c_int, C.c_int, C.c_float]
+    return bool(f(maps, rows, cols, sigma))
+
+
 def arch_info(arch):
     """Host-only: list of dicts {kind, maps, h, w, K, S, Kx, Sx} (K, S: the y values), layer 0 = input."""
     n = C.c_int32()

@@ -49,6 +49,7 @@ hipError_t launch_batch_outputs(hipStream_t stream, const float* sums, int n_sli
                                 float* probs, long long n_images, int n_classes, int out_units);
 hipError_t launch_batch_pack(hipStream_t stream, const BatchPackAll& all);
 hipError_t launch_deform(hipStream_t stream, const DeformJob& J);
+bool deform_mx_is_faster(const DeformJob& J);
 }  // namespace cnn355
 
 using namespace cnn355;
@@ -2168,6 +2169,13 @@ int cnn_deform_images(void* hip_stream, const float* d_src, size_t n_src, float*
   hipError_t e = launch_deform((hipStream_t)hip_stream, J);
   if (e != hipSuccess) return fail(nullptr, CNN_E_HIP, std::string("cnn_deform_images: ") + hipGetErrorString(e));
   return CNN_OK;
+}
+
+// development aid, host only: 1 where the smoothing of such a call runs on the matrix cores, 0 where as sums over a line
+int cnn355_deform_form(int C, int H, int W, float sigma) {
+  DeformJob J;
+  J.C = C; J.H = H; J.W = W; J.R = (int)std::ceil(3.0 * (double)sigma);
+  return deform_mx_is_faster(J);
 }
 
 // tap_step >= 0 (parity tap): the pass stops behind that trainable layer and its outputs for the n <= batch

@@ -9,6 +9,8 @@
 // numbers of 24 bits each, so the same values exist exactly in float and in double.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 // device pointers of the job descriptor are global-address-space pointers in this translation unit
 #define CNN_GLOBAL __attribute__((address_space(1)))
 #include "cnn355_dev.h"
@@ -117,8 +119,10 @@ __device__ __forceinline__ Image image_of(const DeformJob& J, long long k) {
 
 // N pixels (x[i], y[i]) of a lane, displaced by ax[i] + ex[i] and ay[i] + ey[i] (the affine map's share and the elastic
 // part); pixels with !ok[i] are worked out and not written.  All loads of a map are in flight together, then the stores
-// (a load behind a store waits for the store too).  A neighbour outside reads the image's first pixel and takes `fill`.
-// Positions are floored in double, as they are worked out.  RARE: the
+// (a load behind a store waits for the store too).  A neighbour outside takes `fill`; what it reads is the nearest pixel
+// inside, in a cache line that other lanes want too (a pixel at a time: 10000 turned 3x32x32 images 63 us, 67 with the
+// image's first pixel), or, several pixels at a time, the image's first, which takes fewer instructions (60000 of 1x29x29
+// translated 134 us, 145; in matrix form 331, 335).  Positions are floored in double, as they are worked out.  RARE: the
 // caller wants the displacements, or they are unbounded.
 template <int N, bool ELASTIC, bool RARE>
 __device__ __forceinline__ void sample_pixels(const DeformJob& J, const Image& im, const int (&x)[N], const int (&y)[N],
@@ -153,9 +157,16 @@ __device__ __forceinline__ void sample_pixels(const DeformJob& J, const Image& i
     const bool in_x0 = (unsigned int)x0[i] < (unsigned int)W, in_x1 = (unsigned int)(x0[i] + 1) < (unsigned int)W;
     const bool in_y0 = (unsigned int)y0[i] < (unsigned int)H, in_y1 = (unsigned int)(y0[i] + 1) < (unsigned int)H;
     in00[i] = in_y0 && in_x0; in01[i] = in_y0 && in_x1; in10[i] = in_y1 && in_x0; in11[i] = in_y1 && in_x1;
-    const unsigned int at = (unsigned int)(__mul24(y0[i], W) + x0[i]) * 4u, row = (unsigned int)W * 4u;
-    o00[i] = in00[i] ? at : 0u; o01[i] = in01[i] ? at + 4u : 0u;
-    o10[i] = in10[i] ? at + row : 0u; o11[i] = in11[i] ? at + row + 4u : 0u;
+    if (N == 1) {
+      const int xa = min(max(x0[i], 0), W - 1), xb = min(max(x0[i] + 1, 0), W - 1);
+      const int ya = __mul24(min(max(y0[i], 0), H - 1), W), yb = __mul24(min(max(y0[i] + 1, 0), H - 1), W);
+      o00[i] = (unsigned int)(ya + xa) * 4u; o01[i] = (unsigned int)(ya + xb) * 4u;
+      o10[i] = (unsigned int)(yb + xa) * 4u; o11[i] = (unsigned int)(yb + xb) * 4u;
+    } else {
+      const unsigned int at = (unsigned int)(__mul24(y0[i], W) + x0[i]) * 4u, row = (unsigned int)W * 4u;
+      o00[i] = in00[i] ? at : 0u; o01[i] = in01[i] ? at + 4u : 0u;
+      o10[i] = in10[i] ? at + row : 0u; o11[i] = in11[i] ? at + row + 4u : 0u;
+    }
     od[i] = (unsigned int)(__mul24(y[i], W) + x[i]) * 4u;
     w00[i] = (1.f - fy[i]) * (1.f - fx[i]); w01[i] = (1.f - fy[i]) * fx[i]; w10[i] = fy[i] * (1.f - fx[i]); w11[i] = fy[i] * fx[i];
   }
@@ -185,9 +196,8 @@ __device__ __forceinline__ void sample_pixels(const DeformJob& J, const Image& i
   }
 }
 
-// A lane PXL pixels at a time (all their loads in flight: bound by latency without smoothing, 60000 translated 1x29x29
-// images 240 -> 148 us, 2.7 TB/s; one where a map has no more pixels than lanes).  The smoothing (ELASTIC) as sums over a
-// line, a strip of outputs a lane: for maps k_deform_mx would be mostly padding on.
+// A lane PXL pixels at a time, all their loads in flight.  The smoothing (ELASTIC) as sums over a line, a strip of outputs
+// a lane.
 template <int PXL, bool ELASTIC, bool RARE>
 __global__ void __launch_bounds__(DT) k_deform(const DeformJob J) {
   extern __shared__ float lds[];
@@ -401,9 +411,49 @@ __global__ void __launch_bounds__(512, 4) k_deform_mx(const DeformJob J) {
 
 }  // namespace
 
+static size_t line_lds_bytes(const DeformJob& J) { return ((size_t)4 * J.H * (J.W | 1) + 4 * J.R + 2 * SW + 1) * sizeof(float); }
+static size_t mx_lds_bytes(const DeformJob& J) {
+  return (size_t)2 * 16 * ((J.H + 15) / 16) * (16 * ((J.W + 15) / 16) + 4) * sizeof(float);
+}
+
+// Whether the matrix form smooths such images (J.R >= 0): the shape of the images and the width of the Gaussian decide, not
+// how many there are, so that a stream gives the same bits however it is cut into calls.  Time models of the two forms in
+// microseconds, fitted to 2900 random calls (1 to 16 maps of 1x1 to 200x47, sigma 0.3 to 16, 1 to 60000 images; 12 and 15 %
+// off): draws, multiply-adds along lines or products of tiles, sampled pixels with the loads of their maps, in steps of a
+// workgroup's lanes; first their share of a compute unit's issue slots, then their latency, once for every time the images
+// fill the chip.  Matrix form where it costs many images at most 5 % and few at most 15 % more than sums over a line (which
+// have become 8 % faster themselves).  Of the calls above 9 us 1 % are slower by it than with every map in line form
+// before; with maps of more than 24 pixels and half full tiles, and of one tile, in matrix form 12 % were, by up to 50 %
+// (narrow Gaussians on maps of two or three tiles, many maps an image).  Both sides, us, matrix form / line form: sigma 6,
+// 60000 of 1x29x29 331 / 447, 1000 of 2x96x96 131 / 340, 10000 of 3x32x32 94 / 103, 877 of 16x29x29 59 / 54, 30000 of 16x16
+// 39 / 100, 17x17 139 / 118, 24x24 150 / 168, 10000 of 24x64 156 / 132; sigma 0.8, 9773 of 36x36 136 / 84; sigma 1.3, 14 of
+// 4x27x30 12.0 / 9.6.
+bool deform_mx_is_faster(const DeformJob& J) {
+  auto up = [](long long x, long long d) { return (x + d - 1) / d; };
+  const size_t lds = mx_lds_bytes(J);
+  if (lds > 150 * 1024) return false;   // (thin maps)
+  const int H = J.H, W = J.W, R = J.R;
+  const double C = J.C;
+  const double rounds = (double)up((long long)H * W, DT);
+  const double taps = (double)up(H * up(W, SW), DT) * (std::min(W, 2 * R + SW) + 4) + (double)up(W * up(H, SW), DT) * (std::min(H, 2 * R + SW) + 4);
+  const int line_fit = std::max(1, std::min(6, (int)(160 * 1024 / line_lds_bytes(J))));
+  const int nxt = (W + 15) / 16, nyt = (H + 15) / 16, D = std::min((R + 15) / 16, std::max(nxt, nyt) - 1), waves = std::min(nxt, 8);
+  const double draws = (double)up((long long)H * W, 64 * waves), strips = (double)up(nxt, waves);
+  const double steps = strips * (nyt + D) * (2 * D + 1), rows = strips * nyt;
+  const int mx_fit = std::max(1, std::min(16 / waves, (int)(160 * 1024 / (lds + sizeof(Affine) * AFF))));
+  auto within = [&](int n, double share) {
+    const double line = 5.25 + n / 256.0 * (0.176 * rounds + 0.0036 * taps + 0.0161 * rounds * C) +
+                        (double)up(n, 256 * line_fit) * (0.285 * rounds + 0.0509 * taps + 0.168 * rounds * C);
+    const double mx = 5.19 + n / 256.0 * (waves / 4.0) * (0.173 * draws + 0.062 * steps + 0.166 * rows * C) +
+                      (double)up(n, 256 * mx_fit) * (0.267 * draws + 0.104 * steps + 0.705 * rows + 0.412 * rows * C);
+    return mx < share * line;
+  };
+  return within(1, 1.15) && within(256, 1.15) && within(1024, 1.15) && within(60000, 1.05);
+}
+
 template <int PXL, bool ELASTIC, bool RARE>
 static hipError_t launch_deform_px(hipStream_t stream, const DeformJob& J, unsigned int grid) {
-  const size_t lds = ELASTIC ? ((size_t)4 * J.H * (J.W | 1) + 4 * J.R + 2 * SW + 1) * sizeof(float) : 0;
+  const size_t lds = ELASTIC ? line_lds_bytes(J) : 0;
   hipError_t e = hipFuncSetAttribute((const void*)k_deform<PXL, ELASTIC, RARE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_deform<PXL, ELASTIC, RARE>), dim3(grid), dim3(DT), lds, stream, J);
@@ -412,8 +462,8 @@ static hipError_t launch_deform_px(hipStream_t stream, const DeformJob& J, unsig
 
 template <int D, bool RARE>
 static hipError_t launch_deform_mx(hipStream_t stream, const DeformJob& J, unsigned int grid) {
-  const int nxt = (J.W + 15) / 16, nyt = (J.H + 15) / 16;
-  const size_t lds = (size_t)2 * 16 * nyt * (16 * nxt + 4) * sizeof(float);
+  const int nxt = (J.W + 15) / 16;
+  const size_t lds = mx_lds_bytes(J);
   hipError_t e = hipFuncSetAttribute((const void*)k_deform_mx<D, RARE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_deform_mx<D, RARE>), dim3(grid), dim3(64u * (nxt < 8 ? nxt : 8)), lds, stream, J);
@@ -422,14 +472,14 @@ static hipError_t launch_deform_mx(hipStream_t stream, const DeformJob& J, unsig
 
 template <bool RARE>
 static hipError_t launch_deform_any(hipStream_t stream, const DeformJob& J, unsigned int grid) {
-  if (J.R < 0) return J.H * J.W > DT ? launch_deform_px<4, false, RARE>(stream, J, grid) : launch_deform_px<1, false, RARE>(stream, J, grid);
-  // The matrix form works on whole tiles: it is the faster one where they are at least half full and the map is not a
-  // thin band of them (whose few strips are a long chain each), and for a map of one tile.  us, matrix form / line form:
-  // 30000 of 6x6 30 / 59, 16x16 38 / 102, 17x17 137 / 120, 20x20 144 / 133, 24x24 149 / 167; 10000 of 24x64 159 / 131,
-  // 32x64 167 / 190, 48x48x2 (5000) 126 / 156; 1000 of 2x96x96 138 / 340; 3000 of 200x20 285 / 185, 200x32 301 / 597.
+  if (J.R < 0) {
+    // Two pixels a lane keep more loads in flight: 60000 translated 1x29x29 images 133 us, one 159.  Turned images of
+    // several maps lose by it (1559 of 8x48x48 85 us with one, 91 with two; 1000 of 2x96x96 70, 68), small maps leave the
+    // second pixels idle.
+    return J.C == 1 && J.H * J.W > 2 * DT ? launch_deform_px<2, false, RARE>(stream, J, grid) : launch_deform_px<1, false, RARE>(stream, J, grid);
+  }
+  if (!deform_mx_is_faster(J)) return launch_deform_px<1, true, RARE>(stream, J, grid);
   const int tx = (J.W + 15) / 16, ty = (J.H + 15) / 16, tiles = tx > ty ? tx : ty;
-  const bool full = J.H > 24 && J.W > 24 && 2 * J.H * J.W >= 256 * tx * ty;
-  if (tiles > 1 && !full) return launch_deform_px<1, true, RARE>(stream, J, grid);
   const int d = (J.R + 15) / 16;   // neighbouring tiles a tap reaches, as far as there are any
   switch (d < tiles ? d : tiles - 1) {
     case 0: return launch_deform_mx<0, RARE>(stream, J, grid);

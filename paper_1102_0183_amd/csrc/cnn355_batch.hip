@@ -328,7 +328,7 @@ __device__ __forceinline__ int fast_div(int n, FastDiv d) { return (int)(__umulh
 
 // Lane l's 4 or 16 bytes at base + off go to lds_byte + 4 l or 16 l; the wavefront has them after s_waitcnt vmcnt(0).
 // (Not the builtin: the compiler then waits for the load before every LDS read that it cannot tell apart from its
-// destination.  m0 holds nothing else here: no LDS instruction of gfx950 but these needs it.)
+// destination.)
 // lds_byte and base are the same for the whole wavefront; the wait in front is what an address fresh from a vector
 // instruction needs.
 __device__ __forceinline__ const CNN_GLOBAL char* uniform(const CNN_GLOBAL char* p) {
@@ -336,14 +336,17 @@ __device__ __forceinline__ const CNN_GLOBAL char* uniform(const CNN_GLOBAL char*
   const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
   return (const CNN_GLOBAL char*)(((unsigned long long)hi << 32) | lo);
 }
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // (m0 is a reserved register: nothing else would say that it is written)
 __device__ __forceinline__ void lds_dma4(unsigned lds_byte, const CNN_GLOBAL char* base, unsigned off) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dword %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(lds_byte)),
-               "v"(off), "s"(uniform(base)) : "memory");
+               "v"(off), "s"(uniform(base)) : "memory", "m0");
 }
 __device__ __forceinline__ void lds_dma16(unsigned lds_byte, const CNN_GLOBAL char* base, unsigned off) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(lds_byte)),
-               "v"(off), "s"(uniform(base)) : "memory");
+               "v"(off), "s"(uniform(base)) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 template <int MT, int TR>
 __global__ void __launch_bounds__(BT, MT * TR > 96 ? 2 : 3) k_batch_conv(BatchConv g) {

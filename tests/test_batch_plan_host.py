@@ -71,3 +71,12 @@ def test_blocks_of_many_small_images_or_of_a_small_part_of_one_stay_with_the_gen
 def test_the_benchmark_networks_convolutional_layers_run_in_the_persistent_kernel(name, batch, layers):
     plan, _ = binding.batch_plan(synth.WORKLOADS[name].arch, batch)
     assert [p["conv"] for p in plan[:layers]] == [1] * layers
+
+
+def test_the_gpu_test_of_the_tiles_reaches_every_one():
+    from tests.test_gpu_batch import TILES
+    for arch, batch, MT, TR, members, raw, sliced, resident, several in TILES:
+        p = binding.batch_plan(arch, batch)[0][0]
+        assert p["conv"] and (p["MT"], p["TR"], p["members"]) == (MT, TR, members), (arch, batch, p)
+        assert (p["fuse"] == 0, p["n_slices"] > 1, bool(p["resident"]), p["n_cb"] > p["gx"]) == (raw, sliced, resident, several), (arch, p)
+    assert {t[2:4] for t in TILES} == {(m, 16) for m in range(1, 8)} | {(m, 32) for m in range(1, 6)}

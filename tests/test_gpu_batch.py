@@ -164,27 +164,48 @@ def test_every_layer_of_the_batched_pass_matches_the_oracle(name, n):
     g.close()
 
 
+def _trainable(o):
+    return [l for l in range(1, o.num_layers) if o.layer_info(l)["kind"] in (1, 3)]
+
+
+def _check_layers(g, o, d_imgs, imgs, n, sample, layers):
+    """Outputs of the trainable layers `layers` for n images run as one batch against the oracle's on a sample."""
+    scratch = _scratch(g, n)
+    got = {k: g.debug_forward_batch_layer(d_imgs, n, k, scratch).astype(np.float64) for k in layers}
+    for i in sample:
+        o.forward(imgs[i])
+        for k in layers:
+            l = _trainable(o)[k]
+            pooled = l + 1 < o.num_layers and o.layer_info(l + 1)["kind"] == 2
+            w = np.asarray(o.activation(l + 1 if pooled else l), dtype=np.float64).ravel()
+            assert got[k][i].shape == w.shape
+            assert np.abs(got[k][i] - w).max() <= 1e-5 * max(np.abs(w).max(), 1e-3), (i, k)
+
+
 @pytest.mark.parametrize("arch,batch", [
     ("1x9x9-1C2-MP2-3N", 1),                    # one map, one image
-    ("1x9x9-17C2-MP4-33C1-MP1-3N", 7),          # one map beyond a tile of 16 and of 32; 4 x 4 windows; 1 x 1 kernels
+    ("1x9x9-17C2-MP4-33C1-MP1-3N", 7),          # one map beyond a tile of 16; 4 x 4 windows; 1 x 1 kernels
     ("3x13x13-33C2-MP3-40C3-MP2-4N", 40),       # 3 x 3 windows, blocks of 14 of them that straddle images
     ("2x12x15-20C3-MP2x1-48C2-MP2x3-4N", 65),   # 2- and 6-member windows
     ("1x27x27-5C3-MP5-9C2-4N", 33),             # 25-member windows, an unpooled layer behind them
     ("1x25x25-6C4-MP11-3N", 9),                 # 121 members: one window a block
-    ("1x26x26-6C3-MP12-3N", 9),                 # 144 members: pooled outside the product
-    ("2x11x11-161C2-MP2-161C2-MP2-3N", 3),      # one map beyond 160, k range in slices
-    ("5x8x8-80C3S1-MP3-3N", 200),               # skipping factor; more blocks than workgroups
+    ("1x26x26-6C3-MP12-3N", 9),                 # 144 members: the general product, pooling inside
+    ("1x26x26-6C3-MP12-3N", 64),                # the same, sums pooled outside the product
+    ("2x11x11-161C2-MP2-161C2-MP2-3N", 3),      # one map beyond a multiple of 32, k range in slices
+    ("5x8x8-80C3S1-MP3-3N", 200),               # skipping factor
     ("4x10x10-48C3-MP2-48C2-3N", 700),          # images staged four floats a lane
     ("3x9x9-48C2-MP2-48C2-3N", 700),            # odd images: a float a lane
 ])
 def test_convolutional_layers_at_the_edges_of_tiles_and_windows(arch, batch):
-    """Every layer of a batch and a ragged second one against the one-image path and the oracle."""
+    """The convolutional layers of a batch against the oracle, the outputs of it and of a ragged second one against the
+    one-image path and the oracle."""
     import torch
     print("case", arch, batch, flush=True)
     n = batch + (batch + 1) // 2
     g, o = build_pair(arch=arch, wscale=0.2)
     imgs = (np.random.default_rng(5).random((n, g.image_size)) * 2 - 1).astype(np.float32)
     d_imgs = to_dev(imgs)
+    _check_layers(g, o, d_imgs, imgs, batch, sorted({0, batch // 2, batch - 1}), range(arch.count("C")))
     probs = torch.full((n * g.num_classes,), -1.0, dtype=torch.float32, device="cuda:0")
     g.forward_batch(d_imgs, n, probs, _scratch(g, batch), batch)
     one = torch.empty(n * g.num_classes, dtype=torch.float32, device="cuda:0")
@@ -194,4 +215,61 @@ def test_convolutional_layers_at_the_edges_of_tiles_and_windows(arch, batch):
     for i in {0, batch - 1, n - 1}:
         want = o.forward(imgs[i])
         assert np.abs(probs.cpu().numpy().reshape(n, -1)[i] - want).max() <= 1e-5
+    g.close()
+
+
+# every tile of the persistent kernel; (arch, batch, tiles a workgroup, maps a tile, members of a window inside the product,
+# whether sums come raw, whether the k range is sliced, whether a slice is one chunk, more blocks than workgroups)
+TILES = [
+    ("2x26x26-3C1-MP1-3N", 600, 1, 16, 1, False, False, False, True),
+    ("4x29x29-16C2-MP7-3N", 130, 1, 16, 49, False, False, True, True),
+    ("4x26x26-1C3-MP12-3N", 300, 1, 16, 1, True, False, True, True),       # 144 members: pooled outside the product
+    ("17x28x28-16C1-MP2-3N", 64, 1, 16, 1, True, True, False, True),
+    ("33x28x28-32C1-MP2-3N", 130, 1, 32, 4, False, False, False, True),
+    ("5x23x23-17C1-MP1-3N", 600, 1, 32, 1, False, False, False, True),
+    ("1x23x23-17C3-MP7-3N", 600, 2, 16, 49, False, False, True, True),
+    ("2x26x26-32C2-MP5-3N", 300, 2, 16, 25, False, False, False, False),
+    ("2x23x23-128C2-MP2-3N", 300, 2, 32, 4, False, False, True, True),
+    ("48x20x20-64C1-MP5-3N", 130, 2, 32, 1, True, True, False, True),
+    ("17x24x24-129C1-MP2-3N", 64, 3, 16, 4, False, False, False, True),
+    ("1x25x25-129C1-MP5-3N", 130, 3, 16, 25, False, False, True, True),
+    ("17x22x22-96C1-MP2-3N", 300, 3, 32, 4, False, False, False, True),
+    ("4x27x27-161C1-MP9-3N", 130, 3, 32, 1, True, False, True, True),      # 81 members leave too many columns empty
+    ("5x26x26-161C3-MP3-3N", 33, 4, 16, 9, False, False, True, False),
+    ("5x10x10-128C1-MP1-3N", 600, 4, 32, 1, False, False, True, False),
+    ("2x28x28-97C1-MP7-3N", 130, 4, 32, 49, False, False, True, True),
+    ("1x29x29-80C2-MP2-3N", 300, 5, 16, 4, False, False, True, True),
+    ("33x20x20-80C1-MP2-3N", 130, 5, 16, 1, True, True, False, True),
+    ("2x14x14-150C1-MP2-3N", 600, 5, 32, 4, False, False, True, True),
+    ("17x24x24-150C1-MP3-3N", 130, 5, 32, 9, False, False, False, True),
+    ("3x26x26-90C3-MP8-3N", 130, 6, 16, 64, False, False, True, False),
+    ("4x29x29-97C2-MP2-3N", 130, 7, 16, 4, False, False, True, True),
+]
+
+
+@pytest.mark.parametrize("arch,batch,MT,TR,members,raw,sliced,resident,several", TILES)
+def test_every_tile_of_the_persistent_kernel(arch, batch, MT, TR, members, raw, sliced, resident, several):
+    """The convolutional layer, as planned (a planner that no longer picks the tile fails here first), against the oracle;
+    the outputs with a ragged second batch against the one-image path; the same bits from images off 16 bytes."""
+    import torch
+    print("case", arch, batch, flush=True)
+    p = binding.batch_plan(arch, batch)[0][0]
+    assert p["conv"] and (p["MT"], p["TR"], p["members"]) == (MT, TR, members), p
+    assert (p["fuse"] == 0, p["n_slices"] > 1, bool(p["resident"]), p["n_cb"] > p["gx"]) == (raw, sliced, resident, several), p
+    n = batch + batch // 2 + 1
+    g, o = build_pair(arch=arch, wscale=0.2)
+    imgs = (np.random.default_rng(6).random((n, g.image_size)) * 2 - 1).astype(np.float32)
+    d_imgs = to_dev(imgs)
+    _check_layers(g, o, d_imgs, imgs, batch, sorted({0, 1, batch // 2, batch - 1}), [0])
+    probs = torch.full((n * g.num_classes,), -1.0, dtype=torch.float32, device="cuda:0")
+    g.forward_batch(d_imgs, n, probs, _scratch(g, batch), batch)
+    one = torch.empty(n * g.num_classes, dtype=torch.float32, device="cuda:0")
+    g.forward_many(d_imgs, n, one)
+    shifted = torch.empty(d_imgs.numel() + 1, dtype=torch.float32, device="cuda:0")[1:]
+    shifted.copy_(d_imgs.view(-1))
+    again = torch.empty_like(probs)
+    g.forward_batch(shifted, n, again, _scratch(g, batch), batch)
+    g.synchronize()
+    assert (probs - one).abs().max().item() <= 1e-5
+    assert torch.equal(probs, again)
     g.close()

@@ -316,10 +316,12 @@ __global__ void __launch_bounds__(BT) k_batch_gemm(BatchGemm g) {
 //    accumulator register of adjacent lanes.  2 x 2 windows are four lanes, reduced by DPP, each lane going on with one
 //    row in four (bias, tanh and store at full lanes); others pass through LDS tile by tile.  The full-resolution sums
 //    never reach memory, however long the k range.
-// Bound by the matrix pipes: 70-80 % busy at the 2.1 GHz the chip keeps here where the blocks divide evenly; staging is
-// hidden (without it the products take as long).  Per 512 images of 300 maps: 300C3 on 3 maps 206 -> 185 us, 300C2 on
-// 300 maps with its pooling 1286 + 45 -> 794 us (91 TFLOP/s), 300C4 405 -> 237 us; 4096 digits: 20C4 83 -> 76 us, 40C5
-// 243 + 24 -> 187 us (71 TFLOP/s).  Tried and not kept: the next group's operands in a second set of registers (300C2 852
+// Bound by the matrix pipes in layers with a long k range: busy 73 % of the time in 300C2, 78 in 300C4, 66 in 40C5 (at the
+// 2.1 GHz the chip keeps there); staging is hidden in them (without it the products take as long), the rest is blocks that
+// do not divide evenly.  First layers (k of 16 or 27) by the epilogue's vector instructions: 300C3 38 % and 42 % of the
+// vector issue, 20C4 27 and 61.  Per 512 images of 300 maps, under the tracer: 300C3 on 3 maps 206 -> 183 us, 300C2 on 300
+// maps with its pooling 1286 + 45 -> 772 us (94 TFLOP/s), 300C4 405 -> 235 us; 4096 digits: 20C4 83 -> 76 us, 40C5 243 + 24
+// -> 183 us (73 TFLOP/s).  Tried and not kept: the next group's operands in a second set of registers (300C2 794 -> 852
 // us), all of a group's LDS reads before its first product (833), three or four workgroups a compute unit (795, 791).
 // Layout of dynamic LDS: [1 or 2][KC][MT * TR] weights, [2][n_img_max][slot] images, koff, biases, [TR][EP] sums of one tile.
 constexpr int EP = 132;
@@ -688,12 +690,16 @@ __global__ void __launch_bounds__(256) k_batch_pack(BatchPackAll all) {
 
 }  // namespace
 size_t batch_conv_lds_bytes(const BatchConv& g);
-// workgroups of k_batch_conv a compute unit holds at once (registers, LDS)
+// workgroups of k_batch_conv a compute unit holds at once, estimated: accumulators and 64 more registers, LDS.  By the
+// compiler's registers two to five tiles of 32 maps fit one workgroup less (4, 3, 2, 2), seven of 16 too, one of 32 and two
+// of 16 one more; where LDS does not bind, the surplus workgroups of a launch start as the first ones end.  With the
+// compiler's counts here and in the time models fitted with these, 10000 digits took 756 us instead of 746, 777 images of
+// the widest net 1887 instead of 1877, 300 of them 772 instead of 733.
 int batch_conv_fit(int MT, int TR, size_t lds_bytes) {
   const int regs = (MT * (TR == 32 ? 16 : 8) + 64 + 7) & ~7;
   return std::max(1, std::min({512 / regs, (int)(160 * 1024 / lds_bytes), 8}));
 }
-// workgroups along the column blocks: as many as the chip holds at once, over all groups of maps and slices
+// workgroups along the column blocks: about as many as the chip holds at once, over all groups of maps and slices
 int batch_conv_grid_x(const BatchConv& g) {
   const int groups = (g.Mo + g.MT * g.TR - 1) / (g.MT * g.TR) * g.n_slices;
   return (int)std::min<long long>(g.n_cb, std::max(1, 256 * batch_conv_fit(g.MT, g.TR, batch_conv_lds_bytes(g)) / groups));

@@ -301,10 +301,13 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 // the 2 D + 1 strips that read a tile would have to draw it again.  V[-D .. D] of the walk are 2 D + 1 tiles of sums.
 // The fields lie in LDS with zeros around them up to whole tiles, at a row pitch of 4 x odd floats (a lane's four
 // elements are one 128-bit read, 16 rows fall on different banks).
-// Bound by vector-ALU issue (1870 instructions a 29 x 29 image: 37 a draw, 60 a sampled pixel), matrix pipes a quarter
-// busy.  Sums by fmaf over a line -> this, line form also without its draws' and samples' slack: 60000 of 1x29x29
-// 648 -> 556 -> 377 us (1.07 TB/s), 1000 of 2x96x96 373 -> 340 -> 138 us, 10000 of 3x32x32 127 -> 113 -> 99 us.
-constexpr int PX = 2;   // pixels of a lane in flight together (4: registers of the wide Gaussians spill)
+// Bound by vector-ALU issue (1930 instructions a 29 x 29 image: 37 a draw, 64 a sampled pixel), matrix pipes a quarter
+// busy.  Before, sums by fmaf over a line, in a chain of passes: 60000 of 1x29x29 541 -> 331 us (1.2 TB/s; 358 under the
+// profiler), 1000 of 2x96x96 380 -> 134 us.
+// Pixels of a lane in flight together.  The bound of four wavefronts a SIMD leaves 128 registers; 16 of D = 2 and 43 of
+// D = 3 lie in scratch memory as it is (8, 36 and 71 of D = 1, 2, 3 where the displacements are asked for), with four
+// pixels more.
+constexpr int PX = 2;
 template <int D, bool RARE>
 __global__ void __launch_bounds__(512, 4) k_deform_mx(const DeformJob J) {
   extern __shared__ float lds[];

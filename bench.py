@@ -6,7 +6,9 @@
 
 One "step" is one cnn_train_many call: B consecutive images of the headline workload's seeded stream trained
 on-line -- forward pass, delta pass, weight gradients and an SGD update after every image.  The stream is
-resident in HBM before the timed region starts.  Prints ONE JSON line.
+resident in HBM before the timed region starts.  Prints ONE JSON line, short enough for readers that keep the end
+of an output only (8 KB): the rows of per_config with their rates and fractions, no phases.  The whole of it, every
+field described here, goes to stderr as a line of its own before.
 
 value        = images trained per second over the K timed steps (wall clock, synchronised).
 roofline     = the dominant kernel's algorithmic bytes per launch / its mean launch duration, measured with HIP
@@ -52,6 +54,25 @@ PAPER_NETS = [
      "Table 1, 20M-40M-60M-80M-100M-120M-150N with random partial connectivity: no time given; kernel sizes and the "
      "share of connections kept (here half, in a regular pattern) are not given either", -2),
 ]
+
+
+def short(out):
+    """What the JSON line on stdout keeps of everything measured."""
+    out = dict(out)
+    if "roofline" in out:
+        out["roofline"] = {k: v for k, v in out["roofline"].items() if k != "per_layer"}
+    rows = []
+    for r in out.get("per_config", []):
+        row = {k: r[k] for k in ("name", "mode", "bound", "frac", "achieved_tflops", "achieved_gbs", "traffic") if k in r}
+        for k in ("train", "forward_only"):
+            if k in r:
+                row[k + "_images_per_s"] = r[k]["images_per_s"]
+        if "cpu_baseline" in r:
+            row["cpu_images_per_s"] = r["cpu_baseline"]["value"]
+        rows.append(row)
+    if rows:
+        out["per_config"] = rows
+    return out
 
 
 def measured_traffic(kernel, cfg, batch):
@@ -593,7 +614,9 @@ def main():
         oracle.set_threads(0)
     for net in list(nets):
         net.close()
-    print(json.dumps(out))
+    print(json.dumps(out), file=sys.stderr)
+    sys.stderr.flush()
+    print(json.dumps(short(out)))
     sys.stdout.flush()
 
 

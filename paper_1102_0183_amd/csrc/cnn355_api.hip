@@ -1223,7 +1223,7 @@ double conv_clocks(const BatchConv& t, size_t batch, size_t n_cb) {
 
 // The plan of k_batch_conv for a convolutional layer whose k_batch_gemm plan is g: the tile and chunk of the fewest clocks.
 // Never more scratch memory than g takes: no more padded maps.  The slices of the k range are g's own, so that a running
-// sum is no longer than there (fewer slices are faster for 33 stereo pairs, 77 us instead of 96, but the error of 128 maps
+// sum is no longer than there (fewer slices are faster for 33 stereo pairs, 77 us instead of 88, but the error of 128 maps
 // of 450 terms in one sum instead of three is 3.6e-7 instead of 2.3e-7, that of 100 maps of 2500 terms in one instead of
 // five 8.3e-7 instead of 4.1e-7; and ten and ten input maps instead of sixteen and four already 2.9e-7 instead of 2.8e-7).
 // Leaves c.MT = 0 where a chunk of one input map does not fit, and where the models have k_batch_gemm as fast (or a tenth

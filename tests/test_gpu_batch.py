@@ -273,3 +273,24 @@ def test_every_tile_of_the_persistent_kernel(arch, batch, MT, TR, members, raw, 
     assert (probs - one).abs().max().item() <= 1e-5
     assert torch.equal(probs, again)
     g.close()
+
+
+@pytest.mark.parametrize("classes,hidden,adds", [(5, "-300N", 1), (2, "-1200N", 1), (10, "-300N", 0), (300, "-60N", 0)])
+@pytest.mark.parametrize("units", [binding.OUTPUT_SOFTMAX_XENT, binding.OUTPUT_TANH_SQERR])
+def test_output_units_that_add_their_planes_and_that_do_not(classes, hidden, adds, units):
+    import torch
+    arch, n = "1x16x16-8C3-MP2%s-%dN" % (hidden, classes), 200
+    print("case", arch, units, flush=True)
+    assert binding.batch_plan(arch, n)[1]["outputs_add"] == adds
+    g, o = build_pair(arch=arch, wscale=0.1)
+    g.set_output_units(units)
+    o.set_output_units(int(units == binding.OUTPUT_TANH_SQERR))
+    imgs = (np.random.default_rng(8).random((n, g.image_size)) * 2 - 1).astype(np.float32)
+    out = torch.full((n * classes,), -9.0, dtype=torch.float32, device="cuda:0")
+    g.forward_batch(to_dev(imgs), n, out, _scratch(g, n), n)
+    g.synchronize()
+    got = out.cpu().numpy().reshape(n, -1)
+    for i in (0, 63, 64, n - 1):
+        want = o.forward(imgs[i])
+        assert np.abs(got[i] - want).max() <= 1e-5 * np.abs(want).max()
+    g.close()

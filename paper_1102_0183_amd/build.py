@@ -10,8 +10,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libcnn355.so")
-SOURCES = ["cnn355_kernels.hip", "cnn355_flow.hip", "cnn355_batch.hip", "cnn355_deform.hip", "cnn355_api.hip"]
+SOURCES = ["cnn355_kernels.hip", "cnn355_winners.hip", "cnn355_flow.hip", "cnn355_batch.hip", "cnn355_deform.hip", "cnn355_api.hip"]
 HEADERS = [os.path.join(CSRC, "cnn355_dev.h"), os.path.join(CSRC, "cnn355_flowspec.h"),
+           os.path.join(CSRC, "cnn355_stage.h"), os.path.join(CSRC, "cnn355_winners.h"),
            os.path.join(HERE, "..", "include", "cnn355.h")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-FP32 instructions are switched off on purpose: some of their forms have given wrong
@@ -22,6 +23,10 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-mllvm", "-instcombine-max-copied-from-constant-users=100000",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function", "-Wno-pass-failed"]
+
+
+# (a wavefront's uniform branches stay jumps, and the sums they choose among stay in their registers)
+SOURCE_FLAGS = {"cnn355_winners.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions=1"]}
 
 
 def sources():
@@ -51,7 +56,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
     jobs = []
     for src in sources():
         if force or _older(_obj(src), [src] + HEADERS):
-            cmd = [HIPCC] + FLAGS + extra + ["-c", "-o", _obj(src), src]
+            cmd = [HIPCC] + FLAGS + SOURCE_FLAGS.get(os.path.basename(src), []) + extra + ["-c", "-o", _obj(src), src]
             if verbose:
                 print(" ".join(cmd))
             jobs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))

@@ -17,14 +17,15 @@
 #include "cnn355_flowspec.h"
 
 namespace cnn355 {
-hipError_t launch_stage(int kind, int n_items, hipStream_t stream, const ProgramDev* d_prog, int s,
+hipError_t launch_stage(const Stage& st, const LayerDev& L, hipStream_t stream, const ProgramDev* d_prog, int s,
                         StatusDev* d_status, const RunArgs& a);
 hipError_t launch_stage_pair(int kind_a, int n_a, int kind_b, int n_b, hipStream_t stream, const ProgramDev* d_prog,
                              int s, StatusDev* d_status, const RunArgs& a, bool* done);
 hipError_t launch_reset_status(hipStream_t stream, StatusDev* d_status, int clear_label_flag);
 hipError_t launch_call_set(hipStream_t stream, CallArgs* d_call, const CallArgs& v);
 const void* call_advance_kernel();
-const void* stage_kernel(int kind);
+const void* stage_kernel(const Stage& st, const LayerDev& L, int* threads);
+int conv_bwd_win_group(int K, int KP);
 const void* stage_pair_kernel(int kind_a, int kind_b);
 hipError_t launch_persistent(int grid, bool with_matrix_stages, hipStream_t stream, const ProgramDev* d_prog,
                              StatusDev* d_status, const RunArgs& a);
@@ -200,6 +201,22 @@ bool mfma_wgrad_shape_ok(int Mi, int K, int Mo, int Hi, int Wi, int Ho, int Wo) 
   // (measured: below some 300 000 weights the vector kernel, which visits the winners only, is as fast)
   return Mo >= 64 && cols >= 256 && Mo * cols >= 300000 && P >= 4 && 32 * (P + 2) + P + (long long)Hi * Wi + 64 <= LDS_FLOATS;
 }
+// The same over the pooling winners, a lane per input map (cnn355_winners.h).  64 input maps lie in LDS pixel by pixel;
+// below 32 input maps most lanes idle, below 9 winners a map the matrix product multiplies few zeros and stays (300C4 with
+// its four winners: 11 us either way), without pooling there are none to skip (126 maps -> 208C4: 62.7 us an image with
+// the dense product, 68.4 so).
+bool win_wgrad_shape_ok(int Mi, int K, int Hi, int Wi, int Kp, int HW) {
+  return Mi >= 32 && K >= 2 && K <= 5 && Kp >= 2 && HW >= 9 && (long long)Hi * Wi * 65 <= LDS_FLOATS;
+}
+// The delta pull over the winners (cnn355_winners.hip): kernels are compiled for these kernel sizes and pooling windows.
+// Measured over 90 nets, an image's whole step against the matrix product: 64 and more input maps and 2^20 terms 0.70 to
+// 1.0 of the time; fewer maps leave lanes idle (42 -> 235C4: 54.2 us, 57.1 so), five by five filters over 2 x 2 windows
+// keep 240 registers and gain from 2^23 terms (93 -> 111C5: 57.5, 59.3; 94 -> 487C5: 112, 103), two by two ones have four
+// terms a branch and win and lose by turns (282 -> 416C2 93 and 78, 381 -> 383C2 114 and 116).
+bool win_bwd_shape_ok(int Mi, int K, int S, int Kp, int Mo, int HW) {
+  const long long terms = (long long)Mi * Mo * HW * K * K;
+  return S == 0 && Mi >= 64 && K >= 3 && K <= 5 && Kp >= 2 && Kp <= 4 && terms >= (K == 5 && Kp == 2 ? 1 << 23 : 1 << 20);
+}
 int ceil_log2(int v) {
   int l = 0;
   while ((1 << l) < v) ++l;
@@ -247,6 +264,7 @@ struct cnn {
   float* d_fe_out = nullptr;
   float* d_fe_batch = nullptr;  // resident mode: front-end outputs of FE_BATCH images at a time
   float* d_mm_part = nullptr;   // partial sums of the matrix-core forward pass (one layer at a time)
+  size_t mm_part_floats = 0;
   int use_mfma = 1;
   int out_units = CNN_OUTPUT_SOFTMAX_XENT;
   struct ConvBuf {
@@ -331,6 +349,7 @@ size_t carve(cnn* net, void* base) {
           mm = std::max(mm, (size_t)MFMA_MAX_SLICES * A[l - 1].maps * A[l - 1].h * A[l - 1].w);
       }
     net->d_mm_part = c.take<float>(mm);
+    net->mm_part_floats = mm;
   }
   net->d_flow_ptrs = c.take<FlowPtrs>(1);
   {  // resident mode: tagged exchange buffers, sized for any team (see plan_flow for the split)
@@ -547,6 +566,27 @@ int check_plan(cnn* net) {
         if (st.n_tiles * st.chunk < L.Mi || (st.n_tiles - 1) * st.chunk >= L.Mi || st.n_items != ((L.Mo + 31) / 32) * st.n_tiles) return bad(s, "chunks do not cover the input maps");
         break;
       }
+      case ST_CONV_WGRAD_WIN:
+        if (net->mode != CNN_MODE_STAGES) return bad(s, "the gradient over the winners is planned for the stage-launch mode only");
+        if (L.rect || !L.full_table || !win_wgrad_shape_ok(L.Mi, L.K, L.Hi, L.Wi, L.Kp, L.Hp * L.Wp)) return bad(s, "layer not fit for the gradient over the winners");
+        if (st.chunk < 1 || st.chunk > WG / 64 || st.n_tiles * 64 < L.Mi || (st.n_tiles - 1) * 64 >= L.Mi || st.n_items != st.n_tiles * ((L.Mo + st.chunk - 1) / st.chunk))
+          return bad(s, "work items do not cover the filters");
+        break;
+      case ST_CONV_BWD_WIN: {
+        if (net->mode != CNN_MODE_STAGES) return bad(s, "the pull over the winners is planned for the stage-launch mode only");
+        if (L.rect || !L.full_table || !win_bwd_shape_ok(L.Mi, L.K, L.S, L.Kp, L.Mo, L.Hp * L.Wp)) return bad(s, "layer not fit for the pull over the winners");
+        const int NW = conv_bwd_win_group(L.K, L.Kp), NG = L.Hp * ((L.Wp + NW - 1) / NW);
+        if (st.rows_per_wg < 1 || st.rows_per_wg > L.Mo || st.n_items != ((L.Mi + 63) / 64) * NG * st.rows_per_wg) return bad(s, "slices do not cover the output maps");
+        if ((size_t)st.rows_per_wg * NG * (L.Kp + L.K - 1) * (L.Kp * NW + L.K - 1) * L.Mi > net->mm_part_floats) return bad(s, "partial sums exceed their scratch memory");
+        if (st.layer < 1 || P.layers[st.layer - 1].kind != L_CONV) return bad(s, "no convolutional layer below");
+        break;
+      }
+      case ST_CONV_BWD_WEPI:
+        if (st.chunk < 1 || st.chunk > 64 || st.n_tiles != (L.Hi * L.Wi + st.chunk - 1) / st.chunk || st.n_items != ((L.Mi + 63) / 64) * st.n_tiles)
+          return bad(s, "work items do not cover the input maps");
+        if (s < 1 || P.stages[s - 1].kind != ST_CONV_BWD_WIN || st.rows_per_wg != P.stages[s - 1].rows_per_wg || st.tile_rows != conv_bwd_win_group(L.K, L.Kp))
+          return bad(s, "not the sums of the stage before");
+        break;
       case ST_CONV_BWD_EPI:
         if (st.rows_per_wg < 1 || st.rows_per_wg > MFMA_MAX_SLICES) return bad(s, "partial-sum planes");
         if (st.chunk < 1 || st.n_items != (L.Mi + st.chunk - 1) / st.chunk) return bad(s, "work items do not cover the input maps");
@@ -714,12 +754,24 @@ int plan(cnn* net) {
   int pending_wgrad = -1;
   auto add_wgrad = [&](int l, int barrier) {
     LayerDev& L = P.layers[l];
+    // compute units for one round of this stage's items next to those of the (short) stage launched with it
+    const int n_cu_all = net->n_cu > 0 ? net->n_cu : 256;
+    const bool after_epi = ns >= 1 && (P.stages[ns - 1].kind == ST_CONV_BWD_EPI || P.stages[ns - 1].kind == ST_CONV_BWD_WEPI);
+    const int n_cu = after_epi ? std::max(n_cu_all / 2, n_cu_all - P.stages[ns - 1].n_items) : n_cu_all;
+    if (net->use_mfma && net->mode == CNN_MODE_STAGES && !L.rect && L.full_table && win_wgrad_shape_ok(L.Mi, L.K, L.Hi, L.Wi, L.Kp, L.Hp * L.Wp)) {
+      // one work item per compute unit: 64 input maps, as many output maps as that leaves
+      Stage& s = add(ST_CONV_WGRAD_WIN, l, 0, barrier, 1);
+      s.n_tiles = (L.Mi + 63) / 64;
+      const int groups = std::max(1, std::min(L.Mo, n_cu / s.n_tiles));
+      s.chunk = std::min(WG / 64, (L.Mo + groups - 1) / groups);   // (a wavefront each)
+      s.n_items = s.n_tiles * ((L.Mo + s.chunk - 1) / s.chunk);
+      return;
+    }
     if (net->use_mfma && net->mode == CNN_MODE_STAGES && !L.rect && L.full_table &&
         mfma_wgrad_shape_ok(L.Mi, L.K, L.Mo, L.Hi, L.Wi, L.Ho, L.Wo)) {
       // wide layer, one launch per stage: the gradients as a matrix product over the output pixels.
       // Input maps per work item: about one work item per compute unit, whole column tiles of 32
       // where the kernel size allows, at most 64 column tiles, and what LDS holds.
-      const int n_cu = net->n_cu > 0 ? net->n_cu : 256;
       const int KK = L.K * L.K, HiWi = L.Hi * L.Wi, Pn = L.Ho * L.Wo;
       const int RT = (L.Mo + 31) / 32;
       const int WP = Pn + 1 + (Pn & 1);
@@ -740,8 +792,7 @@ int plan(cnn* net) {
     const int chunk_max = std::min(LDS_IN / (L.Hi * L.Wi), L.max_conn);
     // as many work items as fit one round on the compute units: the connection lists cut into
     // floor(CUs / maps) chunks
-    const int n_cu_w = net->n_cu > 0 ? net->n_cu : 256;
-    const int want_chunks = std::max(1, n_cu_w / L.Mo);
+    const int want_chunks = std::max(1, n_cu / L.Mo);
     int chunk = std::max(1, std::min(chunk_max, (L.max_conn + want_chunks - 1) / want_chunks));
     s.chunk = chunk;
     s.n_tiles = (L.max_conn + chunk - 1) / chunk;
@@ -761,6 +812,29 @@ int plan(cnn* net) {
         // pull deltas into layer l-1 (reads the old weights of layer l) ...
         const bool with_pending = pending_wgrad >= 0;
         if (with_pending) { add_wgrad(pending_wgrad, 0); pending_wgrad = -1; }
+        if (net->use_mfma && net->mode == CNN_MODE_STAGES && !L.rect && L.full_table && win_bwd_shape_ok(L.Mi, L.K, L.S, L.Kp, L.Mo, L.Hp * L.Wp)) {
+          // wide layer, one launch per stage: the winners' terms only, a lane per input map; the contraction over the output maps
+          // split so that there is about one work item per compute unit, as far as the scratch memory goes
+          const int n_cu = net->n_cu > 0 ? net->n_cu : 256;
+          const int NW = conv_bwd_win_group(L.K, L.Kp), NG = L.Hp * ((L.Wp + NW - 1) / NW), MC = (L.Mi + 63) / 64;
+          const size_t region = (size_t)NG * (L.Kp + L.K - 1) * (L.Kp * NW + L.K - 1) * L.Mi;
+          int KS = (int)std::min<size_t>(std::max(1, std::min(n_cu / (MC * NG), L.Mo / 32)), net->mm_part_floats / region);
+          if (KS >= 1) {
+            const int per = (L.Mo + KS - 1) / KS;
+            KS = (L.Mo + per - 1) / per;
+            Stage& s = add(ST_CONV_BWD_WIN, l, MC * NG * KS, 1, 1);
+            s.rows_per_wg = KS;
+            const int Pin = L.Hi * L.Wi;
+            Stage& e = add(ST_CONV_BWD_WEPI, l, 0, 0, 1);
+            e.rows_per_wg = KS;
+            e.tile_rows = NW;
+            e.chunk = std::min(64, std::max(16, Pin * MC / 64));
+            e.n_tiles = (Pin + e.chunk - 1) / e.chunk;
+            e.n_items = MC * e.n_tiles;
+            add_wgrad(l, 1);
+            continue;
+          }
+        }
         if (net->use_mfma && net->mode == CNN_MODE_STAGES && !L.rect && L.full_table &&
             mfma_bwd_shape_ok(L.Mi, L.K, L.S, L.Mo, L.Hi, L.Wi)) {
           // wide layer, one launch per stage (the persistent kernel does not hold this stage kind:
@@ -777,14 +851,14 @@ int plan(cnn* net) {
           if (IC >= 1) {
             Stage& s = add(ST_CONV_BWD_MFMA, l, RT * KS, 1, 1);
             s.n_tiles = KS; s.chunk = IC; s.rows_per_wg = KS;
-            add_wgrad(l, 0);
             // input maps per work item of the second stage: up to two passes of the lanes over their pixels, but at
             // least 16 items (the weight adjustment that shares the interval leaves few compute units idle)
             const int Pin2 = L.Hi * L.Wi;
             const int mpb = std::max(1, std::min({2 * WG / Pin2, (L.Mi + 15) / 16, L.Mi}));
-            Stage& e = add(ST_CONV_BWD_EPI, l, (L.Mi + mpb - 1) / mpb, 1, 1);
+            Stage& e = add(ST_CONV_BWD_EPI, l, (L.Mi + mpb - 1) / mpb, 0, 1);
             e.rows_per_wg = KS;
             e.chunk = mpb;
+            add_wgrad(l, 1);
             continue;
           }
         }
@@ -1023,9 +1097,10 @@ int build_stage_graph(cnn* net, int which, int images, const RunArgs& a0) {
           continue;
         }
       }
-      const void* fn = stage_kernel(st.kind);
+      int threads = 0;
+      const void* fn = stage_kernel(st, P.layers[st.layer], &threads);
       if (!fn) return give_up(hipErrorInvalidValue, "graph node (unknown stage)");
-      hipError_t e = add(fn, (unsigned)st.n_items, WG, params);
+      hipError_t e = add(fn, (unsigned)st.n_items, (unsigned)threads, params);
       if (e != hipSuccess) return give_up(e, "graph node (stage)");
     }
   }
@@ -1139,7 +1214,7 @@ int run(cnn* net, const RunArgs& a0) {
                                        net->d_status, b, &done));
         if (done) { ++s; continue; }
       }
-      HIP_TRY(net, launch_stage(st.kind, st.n_items, net->stream, net->d_prog, s, net->d_status, b));
+      HIP_TRY(net, launch_stage(st, P.layers[st.layer], net->stream, net->d_prog, s, net->d_status, b));
     }
   }
   return CNN_OK;
@@ -1436,7 +1511,7 @@ int cnn_workspace_bytes(const char* arch, size_t* bytes) {
 
 static int plan_to_text(const ProgramDev& P, char* buf, size_t n) {
   static const char* names[] = {"?", "frontend", "conv_fwd", "fc_fwd", "head", "fc_bwd", "conv_bwd", "conv_wgrad", "conv_mfma", "conv_epi",
-                                "conv_bwd_mfma", "conv_bwd_epi", "conv_wgrad_mfma"};
+                                "conv_bwd_mfma", "conv_bwd_epi", "conv_wgrad_mfma", "conv_wgrad_win", "conv_bwd_win", "conv_bwd_wepi"};
   std::string out;
   char line[256];
   for (int s = 0; s < P.n_stages; ++s) {

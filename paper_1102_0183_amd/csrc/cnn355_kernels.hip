@@ -9,28 +9,9 @@
 // weight-adjusting phases of Sec. 3.2 - 3.4.
 #include <hip/hip_runtime.h>
 
-#if defined(__HIP_DEVICE_COMPILE__)
-#define CNN_GLOBAL __attribute__((address_space(1)))
-#endif
-#include "cnn355_dev.h"
+#include "cnn355_stage.h"
 
 namespace cnn355 {
-
-typedef CNN_GLOBAL float gfloat;  // a float in device (global) memory
-
-// Scaled hyperbolic tangent of Sec. 4, constants as printed.
-#define ACT_A 1.7159f
-#define ACT_B 0.6666f
-__device__ __forceinline__ float act_f(float a) { return ACT_A * tanhf(ACT_B * a); }
-// Its derivative A B (1 - tanh^2(B a)) = 4 A B z / (1 + z)^2 with z = e^{-2B|a|}, from the sum a the unit
-// received (the forward pass stores it wherever a delta can arrive: at the pooling winners and at the hidden
-// fully connected units).  Written in terms of the output, A B - (B/A) y^2, the two terms cancel to 1e-3 of
-// themselves at a saturated unit and fp32 keeps only 1e-4 of the result; here nothing cancels.
-__device__ __forceinline__ float dact_pre_f(float a) {
-  const float z = expf(-2.0f * ACT_B * fabsf(a));
-  const float r = 1.0f / (1.0f + z);
-  return (4.0f * ACT_A * ACT_B) * z * r * r;
-}
 
 // Optional fine-grained timestamps inside work items (development aid; compiled out unless
 // CNN355_STAMPS is defined): workgroup 0 records 100 MHz ticks at numbered points.
@@ -40,15 +21,6 @@ __device__ unsigned long long g_dbg[64];
 #else
 #define DBG(i) do { } while (0)
 #endif
-
-struct Ctx {
-  const gfloat* image;
-  gfloat* probs_out;
-  gfloat* grad_out;
-  int label;
-  int train;  // this image is trained on (0 for forward-only calls and for rejected labels)
-  float lr;
-};
 
 // Sum of n_terms partial sums for each of n_out outputs, parts[k * n_out + o]: up to 64 lanes share an output
 // (lane g adds the terms g, g + G, ... in that order, the G sums are then added across the lanes in a fixed
@@ -66,11 +38,6 @@ __device__ __forceinline__ float sum_terms(const float* parts, int n_terms, int 
   if (o < n_out && g == 0) res[o] = s;
   __syncthreads();
   return tid < n_out ? res[tid] : 0.f;
-}
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
 }
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
@@ -1331,6 +1298,10 @@ __device__ void conv_bwd_epi_item(const LayerDev& L, const LayerDev& Lp, const S
   }
 }
 
+}  // namespace cnn355
+#include "cnn355_winners.h"
+namespace cnn355 {
+
 // ------------------------------------------------------------------------------------------
 // Dispatch of one work item of one stage.  KIND is a compile-time constant in the per-stage
 // kernels (so each holds only its own code) and comes from a switch in the persistent kernel.
@@ -1368,6 +1339,10 @@ __device__ __forceinline__ void run_item(const ProgramDev& P, const Stage& st, i
     conv_bwd_epi_item(L, P.layers[st.layer - 1], st, item);
   } else if constexpr (KIND == ST_CONV_WGRAD_MFMA) {
     conv_wgrad_mfma_item(L, st, item, in, ctx, lds);
+  } else if constexpr (KIND == ST_CONV_BWD_WEPI) {
+    conv_bwd_wepi_item(L, P.layers[st.layer - 1], st, item, lds);
+  } else if constexpr (KIND == ST_CONV_WGRAD_WIN) {
+    conv_wgrad_win_item(L, st, item, in, ctx, lds);
   }
 }
 
@@ -1406,39 +1381,11 @@ __device__ __forceinline__ void run_stage_items(const ProgramDev& P, const Stage
   }
 }
 
-__device__ __forceinline__ Ctx make_ctx(const ProgramDev& P, const RunArgs& a, long long t,
-                                        StatusDev* status) {
-  Ctx c;
-  if (a.call) {   // a node of a replayed graph: the call's arguments lie in device memory
-    const CNN_GLOBAL CallArgs& q = *a.call;
-    const long long tq = q.t0 + a.t_local;
-    c.image = q.images + tq * q.image_stride;
-    c.probs_out = q.probs_out ? q.probs_out + tq * P.n_classes : nullptr;
-    c.grad_out = nullptr;
-    c.label = q.labels[tq];
-    c.lr = q.lr;
-    c.train = q.train;
-  } else {
-  c.image = a.images + t * a.image_stride;
-  c.probs_out = a.probs_out ? a.probs_out + t * P.n_classes : nullptr;
-  c.grad_out = a.grad_out;
-  c.label = a.labels ? a.labels[t] : a.label_imm;
-  c.lr = a.lr;
-  c.train = a.train;
-  }
-  if (a.train && (c.label < 0 || c.label >= P.n_classes)) {
-    // a label outside the classes: the image is skipped and the host is told
-    c.train = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) status->bad_label = 1u;
-  }
-  return c;
-}
-
 // ---- one launch per stage: grid = n_items of the stage -------------------------------------
 #define STAGE_KERNEL(name, KIND)                                                             \
   __global__ void __launch_bounds__(WG) name(const ProgramDev* __restrict__ P, int s,        \
                                              StatusDev* status, RunArgs a) {                 \
-    __shared__ float lds[LDS_FLOATS];                                                        \
+    __shared__ __align__(16) float lds[LDS_FLOATS];                                                     \
     const Ctx ctx = make_ctx(*P, a, 0, status);                                              \
     const Stage& st = P->stages[s];                                                          \
     if (st.train_only && !ctx.train) return;                                                 \
@@ -1456,13 +1403,15 @@ STAGE_KERNEL(k_conv_epi, ST_CONV_EPI)
 STAGE_KERNEL(k_conv_bwd_mfma, ST_CONV_BWD_MFMA)
 STAGE_KERNEL(k_conv_bwd_epi, ST_CONV_BWD_EPI)
 STAGE_KERNEL(k_conv_wgrad_mfma, ST_CONV_WGRAD_MFMA)
+STAGE_KERNEL(k_conv_wgrad_win, ST_CONV_WGRAD_WIN)
+STAGE_KERNEL(k_conv_bwd_wepi, ST_CONV_BWD_WEPI)
 
 // Two consecutive stages that the plan declares independent (no barrier between them: a layer's weight
 // adjustment next to the stage that follows its pull) in one launch: the first stage's items, then the second's.
 // A launch costs some 4 us however little it does, so a step of 10 to 13 stages gains what a launch costs.
 template <int KA, int KB>
 __global__ void __launch_bounds__(WG) k_pair(const ProgramDev* __restrict__ P, int s, StatusDev* status, RunArgs a) {
-  __shared__ float lds[LDS_FLOATS];
+  __shared__ __align__(16) float lds[LDS_FLOATS];
   const Ctx ctx = make_ctx(*P, a, 0, status);
   const Stage& sa = P->stages[s];
   const int n_a = sa.n_items;
@@ -1587,7 +1536,7 @@ __device__ bool xcd_barrier(StatusDev* status, unsigned int epoch, const BarCtx&
 template <bool MM>
 __global__ void __launch_bounds__(WG) k_persistent(const ProgramDev* __restrict__ P,
                                                    StatusDev* status, RunArgs a) {
-  __shared__ float lds[LDS_FLOATS];
+  __shared__ __align__(16) float lds[LDS_FLOATS];
   __shared__ int s_ok;
   __shared__ BarCtx s_bc;
   unsigned int n_barriers = 0;
@@ -1637,26 +1586,53 @@ __global__ void __launch_bounds__(WG) k_persistent(const ProgramDev* __restrict_
 }
 
 // ---- host-side launchers (called from the C ABI translation unit) ---------------------------
-hipError_t launch_stage(int kind, int n_items, hipStream_t stream, const ProgramDev* d_prog, int s,
-                        StatusDev* d_status, const RunArgs& a) {
-  if (n_items <= 0) return hipSuccess;
-  dim3 grid(n_items), block(WG);
-  switch (kind) {
-    case ST_FRONTEND: hipLaunchKernelGGL(k_frontend, grid, block, 0, stream, d_prog, s, d_status, a); break;
-    case ST_CONV_FWD: hipLaunchKernelGGL(k_conv_fwd, grid, block, 0, stream, d_prog, s, d_status, a); break;
-    case ST_FC_FWD: hipLaunchKernelGGL(k_fc_fwd, grid, block, 0, stream, d_prog, s, d_status, a); break;
-    case ST_HEAD: hipLaunchKernelGGL(k_head, grid, block, 0, stream, d_prog, s, d_status, a); break;
-    case ST_FC_BWD: hipLaunchKernelGGL(k_fc_bwd, grid, block, 0, stream, d_prog, s, d_status, a); break;
-    case ST_CONV_BWD: hipLaunchKernelGGL(k_conv_bwd, grid, block, 0, stream, d_prog, s, d_status, a); break;
-    case ST_CONV_WGRAD: hipLaunchKernelGGL(k_conv_wgrad, grid, block, 0, stream, d_prog, s, d_status, a); break;
-    case ST_CONV_FWD_MFMA: hipLaunchKernelGGL(k_conv_fwd_mfma, grid, block, 0, stream, d_prog, s, d_status, a); break;
-    case ST_CONV_EPI: hipLaunchKernelGGL(k_conv_epi, grid, block, 0, stream, d_prog, s, d_status, a); break;
-    case ST_CONV_BWD_MFMA: hipLaunchKernelGGL(k_conv_bwd_mfma, grid, block, 0, stream, d_prog, s, d_status, a); break;
-    case ST_CONV_BWD_EPI: hipLaunchKernelGGL(k_conv_bwd_epi, grid, block, 0, stream, d_prog, s, d_status, a); break;
-    case ST_CONV_WGRAD_MFMA: hipLaunchKernelGGL(k_conv_wgrad_mfma, grid, block, 0, stream, d_prog, s, d_status, a); break;
-    default: return hipErrorInvalidValue;
+const void* conv_bwd_win_kernel(int K, int KP, int* threads);
+
+// the kernel of a stage (with the threads of its workgroup), and of two stages in one launch (null: none compiled)
+const void* stage_kernel(const Stage& st, const LayerDev& L, int* threads) {
+  *threads = WG;
+  switch (st.kind) {
+    case ST_FRONTEND: return (const void*)k_frontend;
+    case ST_CONV_FWD: return (const void*)k_conv_fwd;
+    case ST_FC_FWD: return (const void*)k_fc_fwd;
+    case ST_HEAD: return (const void*)k_head;
+    case ST_FC_BWD: return (const void*)k_fc_bwd;
+    case ST_CONV_BWD: return (const void*)k_conv_bwd;
+    case ST_CONV_WGRAD: return (const void*)k_conv_wgrad;
+    case ST_CONV_FWD_MFMA: return (const void*)k_conv_fwd_mfma;
+    case ST_CONV_EPI: return (const void*)k_conv_epi;
+    case ST_CONV_BWD_MFMA: return (const void*)k_conv_bwd_mfma;
+    case ST_CONV_BWD_EPI: return (const void*)k_conv_bwd_epi;
+    case ST_CONV_WGRAD_MFMA: return (const void*)k_conv_wgrad_mfma;
+    case ST_CONV_WGRAD_WIN: return (const void*)k_conv_wgrad_win;
+    case ST_CONV_BWD_WEPI: return (const void*)k_conv_bwd_wepi;
+    case ST_CONV_BWD_WIN: return conv_bwd_win_kernel(L.K, L.Kp, threads);
+    default: return nullptr;
   }
-  return hipGetLastError();
+}
+const void* stage_pair_kernel(int kind_a, int kind_b) {
+#define PAIR(KA, KB) if (kind_a == KA && kind_b == KB) return (const void*)k_pair<KA, KB>;
+  PAIR(ST_CONV_BWD_EPI, ST_CONV_WGRAD)
+  PAIR(ST_CONV_BWD_EPI, ST_CONV_WGRAD_MFMA)
+  PAIR(ST_CONV_BWD_EPI, ST_CONV_WGRAD_WIN)
+  PAIR(ST_CONV_BWD_WEPI, ST_CONV_WGRAD)
+  PAIR(ST_CONV_BWD_WEPI, ST_CONV_WGRAD_MFMA)
+  PAIR(ST_CONV_BWD_WEPI, ST_CONV_WGRAD_WIN)
+  PAIR(ST_CONV_WGRAD, ST_CONV_WGRAD)
+  PAIR(ST_CONV_WGRAD, ST_CONV_BWD)
+#undef PAIR
+  return nullptr;
+}
+
+hipError_t launch_stage(const Stage& st, const LayerDev& L, hipStream_t stream, const ProgramDev* d_prog, int s,
+                        StatusDev* d_status, const RunArgs& a) {
+  if (st.n_items <= 0) return hipSuccess;
+  int threads = 0;
+  const void* k = stage_kernel(st, L, &threads);
+  if (!k) return hipErrorInvalidValue;
+  RunArgs args = a;
+  void* params[] = {(void*)&d_prog, (void*)&s, (void*)&d_status, (void*)&args};
+  return hipLaunchKernel(k, dim3(st.n_items), dim3(threads), params, 0, stream);
 }
 
 // ---- the stage launches of several images as one graph ----------------------------------------------------
@@ -1675,53 +1651,18 @@ hipError_t launch_call_set(hipStream_t stream, CallArgs* d_call, const CallArgs&
   return hipGetLastError();
 }
 const void* call_advance_kernel() { return (const void*)k_call_advance; }
-// the kernel of a stage kind, and of two kinds in one launch (null: none compiled)
-const void* stage_kernel(int kind) {
-  switch (kind) {
-    case ST_FRONTEND: return (const void*)k_frontend;
-    case ST_CONV_FWD: return (const void*)k_conv_fwd;
-    case ST_FC_FWD: return (const void*)k_fc_fwd;
-    case ST_HEAD: return (const void*)k_head;
-    case ST_FC_BWD: return (const void*)k_fc_bwd;
-    case ST_CONV_BWD: return (const void*)k_conv_bwd;
-    case ST_CONV_WGRAD: return (const void*)k_conv_wgrad;
-    case ST_CONV_FWD_MFMA: return (const void*)k_conv_fwd_mfma;
-    case ST_CONV_EPI: return (const void*)k_conv_epi;
-    case ST_CONV_BWD_MFMA: return (const void*)k_conv_bwd_mfma;
-    case ST_CONV_BWD_EPI: return (const void*)k_conv_bwd_epi;
-    case ST_CONV_WGRAD_MFMA: return (const void*)k_conv_wgrad_mfma;
-    default: return nullptr;
-  }
-}
-const void* stage_pair_kernel(int kind_a, int kind_b) {
-#define PAIR(KA, KB) if (kind_a == KA && kind_b == KB) return (const void*)k_pair<KA, KB>;
-  PAIR(ST_CONV_WGRAD, ST_CONV_BWD_EPI)
-  PAIR(ST_CONV_WGRAD_MFMA, ST_CONV_BWD_EPI)
-  PAIR(ST_CONV_WGRAD, ST_CONV_WGRAD)
-  PAIR(ST_CONV_WGRAD, ST_CONV_BWD)
-#undef PAIR
-  return nullptr;
-}
-
 // Stages s and s + 1 of kinds kind_a and kind_b in one launch; *done = false when no kernel is compiled for the pair
 // (the caller then launches them one after the other).
 hipError_t launch_stage_pair(int kind_a, int n_a, int kind_b, int n_b, hipStream_t stream, const ProgramDev* d_prog,
                              int s, StatusDev* d_status, const RunArgs& a, bool* done) {
   *done = false;
   if (n_a <= 0 || n_b <= 0) return hipSuccess;
-  dim3 grid(n_a + n_b), block(WG);
-#define PAIR(KA, KB)                                                                              \
-  if (kind_a == KA && kind_b == KB) {                                                             \
-    hipLaunchKernelGGL((k_pair<KA, KB>), grid, block, 0, stream, d_prog, s, d_status, a);         \
-    *done = true;                                                                                 \
-    return hipGetLastError();                                                                     \
-  }
-  PAIR(ST_CONV_WGRAD, ST_CONV_BWD_EPI)
-  PAIR(ST_CONV_WGRAD_MFMA, ST_CONV_BWD_EPI)
-  PAIR(ST_CONV_WGRAD, ST_CONV_WGRAD)
-  PAIR(ST_CONV_WGRAD, ST_CONV_BWD)
-#undef PAIR
-  return hipSuccess;
+  const void* k = stage_pair_kernel(kind_a, kind_b);
+  if (!k) return hipSuccess;
+  *done = true;
+  RunArgs args = a;
+  void* params[] = {(void*)&d_prog, (void*)&s, (void*)&d_status, (void*)&args};
+  return hipLaunchKernel(k, dim3(n_a + n_b), dim3(WG), params, 0, stream);
 }
 
 hipError_t launch_frontend_batch(hipStream_t stream, const ProgramDev* d_prog, const float* d_images,

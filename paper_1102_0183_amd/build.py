@@ -12,7 +12,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libcnn355.so")
 SOURCES = ["cnn355_kernels.hip", "cnn355_winners.hip", "cnn355_flow.hip", "cnn355_batch.hip", "cnn355_deform.hip", "cnn355_api.hip"]
 HEADERS = [os.path.join(CSRC, "cnn355_dev.h"), os.path.join(CSRC, "cnn355_flowspec.h"),
-           os.path.join(CSRC, "cnn355_stage.h"), os.path.join(CSRC, "cnn355_winners.h"),
+           os.path.join(CSRC, "cnn355_stage.h"), os.path.join(CSRC, "cnn355_first.h"), os.path.join(CSRC, "cnn355_winners.h"),
            os.path.join(HERE, "..", "include", "cnn355.h")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-FP32 instructions are switched off on purpose: some of their forms have given wrong

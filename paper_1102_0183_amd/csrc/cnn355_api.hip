@@ -201,6 +201,22 @@ bool mfma_wgrad_shape_ok(int Mi, int K, int Mo, int Hi, int Wi, int Ho, int Wo) 
   // (measured: below some 300 000 weights the vector kernel, which visits the winners only, is as fast)
   return Mo >= 64 && cols >= 256 && Mo * cols >= 300000 && P >= 4 && 32 * (P + 2) + P + (long long)Hi * Wi + 64 <= LDS_FLOATS;
 }
+// A layer of many output maps on few input maps (the first layer): its product with activation and pooling in one stage
+// (cnn355_first.h), from two tiles of 32 maps on (k_conv_fwd has an item per map there: 126 maps of 8 x 8 7.3 us, 5.4 so;
+// 300 of 46 x 46 33.9, 9.4).  A contraction of 256 and more is cut into slices instead.  LDS floats of a work item of 32 maps
+// and `rows` conv rows.
+long long conv_fwd_mx_floats(const LayerDev& L, int rows) {
+  const int Kd = L.Mi * L.K * L.K, P = rows * L.Wo;
+  return 32LL * ((Kd + 27) / 32 * 32 + 4) + ((Kd + 3) & ~3) + (long long)L.Mi * ((rows - 1) * (L.S + 1) + L.K) * L.Wi + 64LL * (P | 1);
+}
+bool conv_fwd_mx_ok(const LayerDev& L) {
+  return !L.rect && L.full_table && L.Mo >= 64 && L.Mi <= 8 && L.Mi * L.K * L.K < 256 && conv_fwd_mx_floats(L, L.Kp) <= LDS_FLOATS;
+}
+// Its gradients: the whole input and the winners of JG output maps in LDS, at least a wavefront a map.
+bool conv_wgrad_first_ok(const LayerDev& L, int JG) {
+  const long long RP = L.Wi + ((L.K - L.Wi) % 32 + 32) % 32, MP = L.Hi * RP + ((L.K * L.K - L.Hi * RP) % 32 + 32) % 32;
+  return conv_fwd_mx_ok(L) && JG >= 1 && JG <= WG / 64 && L.Mi * MP + 2LL * JG * L.Hp * L.Wp <= LDS_FLOATS;
+}
 // The same over the pooling winners, a lane per input map (cnn355_winners.h).  64 input maps lie in LDS pixel by pixel;
 // below 32 input maps most lanes idle, below 9 winners a map the matrix product multiplies few zeros and stays (300C4 with
 // its four winners: 11 us either way), without pooling there are none to skip (126 maps -> 208C4: 62.7 us an image with
@@ -572,6 +588,18 @@ int check_plan(cnn* net) {
         if (st.chunk < 1 || st.chunk > WG / 64 || st.n_tiles * 64 < L.Mi || (st.n_tiles - 1) * 64 >= L.Mi || st.n_items != st.n_tiles * ((L.Mo + st.chunk - 1) / st.chunk))
           return bad(s, "work items do not cover the filters");
         break;
+      case ST_CONV_FWD_MX:
+        if (net->mode != CNN_MODE_STAGES) return bad(s, "planned for the stage-launch mode only");
+        if (!conv_fwd_mx_ok(L) || st.tile_rows < L.Kp || st.tile_rows % L.Kp || conv_fwd_mx_floats(L, st.tile_rows) > LDS_FLOATS)
+          return bad(s, "row band not fit for the matrix-core kernel");
+        if (st.n_tiles * st.tile_rows < L.Ho || (st.n_tiles - 1) * st.tile_rows >= L.Ho || st.n_items != ((L.Mo + 31) / 32) * st.n_tiles)
+          return bad(s, "row bands do not cover the maps");
+        break;
+      case ST_CONV_WGRAD_FIRST:
+        if (net->mode != CNN_MODE_STAGES) return bad(s, "planned for the stage-launch mode only");
+        if (!conv_wgrad_first_ok(L, st.chunk)) return bad(s, "layer not fit for the gradients of a first layer");
+        if (st.n_items != (L.Mo + st.chunk - 1) / st.chunk) return bad(s, "work items do not cover the maps");
+        break;
       case ST_CONV_BWD_WIN: {
         if (net->mode != CNN_MODE_STAGES) return bad(s, "the pull over the winners is planned for the stage-launch mode only");
         if (L.rect || !L.full_table || !win_bwd_shape_ok(L.Mi, L.K, L.S, L.Kp, L.Mo, L.Hp * L.Wp)) return bad(s, "layer not fit for the pull over the winners");
@@ -734,6 +762,15 @@ int plan(cnn* net) {
       Stage& e = add(ST_CONV_EPI, l, (L.Mo + mp - 1) / mp, 1, 0);
       e.rows_per_wg = KS;
       e.chunk = mp;
+    } else if (L.kind == L_CONV && net->use_mfma && net->mode == CNN_MODE_STAGES && conv_fwd_mx_ok(L)) {
+      // the fewest rows a band that leave one round of the compute units, as far as LDS goes
+      const int n_cu = net->n_cu > 0 ? net->n_cu : 256, RT = (L.Mo + 31) / 32;
+      int rows = L.Kp;
+      while (RT * ((L.Ho + rows - 1) / rows) > n_cu && rows + L.Kp <= L.Ho && conv_fwd_mx_floats(L, rows + L.Kp) <= LDS_FLOATS) rows += L.Kp;
+      Stage& s = add(ST_CONV_FWD_MX, l, 0, 1, 0);
+      s.tile_rows = rows;
+      s.n_tiles = (L.Ho + rows - 1) / rows;
+      s.n_items = RT * s.n_tiles;
     } else if (L.kind == L_CONV) {
       Stage& s = add(ST_CONV_FWD, l, 0, 1, 0);
       int rc = plan_conv_fwd(L, s, net->n_cu > 0 ? net->n_cu : 256, &net->err);
@@ -786,6 +823,12 @@ int plan(cnn* net) {
       s.chunk = ic;
       s.n_tiles = (L.Mi + ic - 1) / ic;
       s.n_items = RT * s.n_tiles;
+      return;
+    }
+    if (net->use_mfma && net->mode == CNN_MODE_STAGES && conv_wgrad_first_ok(L, (L.Mo + n_cu - 1) / n_cu)) {
+      Stage& s = add(ST_CONV_WGRAD_FIRST, l, 0, barrier, 1);
+      s.chunk = (L.Mo + n_cu - 1) / n_cu;   // one round of the compute units
+      s.n_items = (L.Mo + s.chunk - 1) / s.chunk;
       return;
     }
     Stage& s = add(ST_CONV_WGRAD, l, 0, barrier, 1);
@@ -1511,7 +1554,7 @@ int cnn_workspace_bytes(const char* arch, size_t* bytes) {
 
 static int plan_to_text(const ProgramDev& P, char* buf, size_t n) {
   static const char* names[] = {"?", "frontend", "conv_fwd", "fc_fwd", "head", "fc_bwd", "conv_bwd", "conv_wgrad", "conv_mfma", "conv_epi",
-                                "conv_bwd_mfma", "conv_bwd_epi", "conv_wgrad_mfma", "conv_wgrad_win", "conv_bwd_win", "conv_bwd_wepi"};
+                                "conv_bwd_mfma", "conv_bwd_epi", "conv_wgrad_mfma", "conv_wgrad_win", "conv_bwd_win", "conv_bwd_wepi", "conv_fwd_mx", "conv_wgrad_first"};
   std::string out;
   char line[256];
   for (int s = 0; s < P.n_stages; ++s) {

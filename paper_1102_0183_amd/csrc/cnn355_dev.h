@@ -83,6 +83,8 @@ enum StageKind : int {
   ST_CONV_WGRAD_MFMA = 12, // weight gradients of a wide layer as a matrix product over the output pixels, and the adjustment
   ST_CONV_WGRAD_WIN = 13,  // the same over the pooling winners only, a lane per input map (cnn355_winners.h)
   ST_CONV_BWD_WIN = 14,    // delta pull through a wide layer over the pooling winners: partial sums
+  ST_CONV_FWD_MX = 16,     // FP of a wide layer on few input maps on the matrix cores, pooling included (cnn355_first.h)
+  ST_CONV_WGRAD_FIRST = 17, // weight gradients of such a layer over the pooling winners, the whole input in LDS
   ST_CONV_BWD_WEPI = 15,   // ... then: their sum, times the activation derivative of the layer below
 };
 constexpr int MFMA_MAX_SLICES = 64;  // partial-sum slices (splits of the contraction) per layer

@@ -1299,6 +1299,7 @@ __device__ void conv_bwd_epi_item(const LayerDev& L, const LayerDev& Lp, const S
 }
 
 }  // namespace cnn355
+#include "cnn355_first.h"
 #include "cnn355_winners.h"
 namespace cnn355 {
 
@@ -1339,6 +1340,10 @@ __device__ __forceinline__ void run_item(const ProgramDev& P, const Stage& st, i
     conv_bwd_epi_item(L, P.layers[st.layer - 1], st, item);
   } else if constexpr (KIND == ST_CONV_WGRAD_MFMA) {
     conv_wgrad_mfma_item(L, st, item, in, ctx, lds);
+  } else if constexpr (KIND == ST_CONV_FWD_MX) {
+    conv_fwd_mx_item(L, st, item, in, lds);
+  } else if constexpr (KIND == ST_CONV_WGRAD_FIRST) {
+    conv_wgrad_first_item(L, st, item, in, ctx, lds);
   } else if constexpr (KIND == ST_CONV_BWD_WEPI) {
     conv_bwd_wepi_item(L, P.layers[st.layer - 1], st, item, lds);
   } else if constexpr (KIND == ST_CONV_WGRAD_WIN) {
@@ -1404,6 +1409,8 @@ STAGE_KERNEL(k_conv_bwd_mfma, ST_CONV_BWD_MFMA)
 STAGE_KERNEL(k_conv_bwd_epi, ST_CONV_BWD_EPI)
 STAGE_KERNEL(k_conv_wgrad_mfma, ST_CONV_WGRAD_MFMA)
 STAGE_KERNEL(k_conv_wgrad_win, ST_CONV_WGRAD_WIN)
+STAGE_KERNEL(k_conv_fwd_mx, ST_CONV_FWD_MX)
+STAGE_KERNEL(k_conv_wgrad_first, ST_CONV_WGRAD_FIRST)
 STAGE_KERNEL(k_conv_bwd_wepi, ST_CONV_BWD_WEPI)
 
 // Two consecutive stages that the plan declares independent (no barrier between them: a layer's weight
@@ -1605,6 +1612,8 @@ const void* stage_kernel(const Stage& st, const LayerDev& L, int* threads) {
     case ST_CONV_BWD_EPI: return (const void*)k_conv_bwd_epi;
     case ST_CONV_WGRAD_MFMA: return (const void*)k_conv_wgrad_mfma;
     case ST_CONV_WGRAD_WIN: return (const void*)k_conv_wgrad_win;
+    case ST_CONV_FWD_MX: return (const void*)k_conv_fwd_mx;
+    case ST_CONV_WGRAD_FIRST: return (const void*)k_conv_wgrad_first;
     case ST_CONV_BWD_WEPI: return (const void*)k_conv_bwd_wepi;
     case ST_CONV_BWD_WIN: return conv_bwd_win_kernel(L.K, L.Kp, threads);
     default: return nullptr;
@@ -1619,6 +1628,7 @@ const void* stage_pair_kernel(int kind_a, int kind_b) {
   PAIR(ST_CONV_BWD_WEPI, ST_CONV_WGRAD_MFMA)
   PAIR(ST_CONV_BWD_WEPI, ST_CONV_WGRAD_WIN)
   PAIR(ST_CONV_WGRAD, ST_CONV_WGRAD)
+  PAIR(ST_CONV_WGRAD, ST_CONV_WGRAD_FIRST)
   PAIR(ST_CONV_WGRAD, ST_CONV_BWD)
 #undef PAIR
   return nullptr;

@@ -193,6 +193,14 @@ bool mfma_bwd_shape_ok(int Mi, int K, int S, int Mo, int Hi, int Wi) {
   const long long Kd = (long long)Mo * K * K, P = (long long)Hi * Wi;
   return S == 0 && Mi >= 32 && Kd >= 256 && P >= 16 && P <= MAX_TILE_PIX && (P + 31) / 32 <= (WG / 64) * 4;
 }
+// Maps of a chunk of such a product's slice of `per` maps: half of the slice, so that the second half is fetched behind the
+// first one's arithmetic, as far as half of LDS goes (0: not even one).
+int mfma_chunk(int per, int KK, int map) {
+  // (a short slice in one: its arithmetic would not cover a second fetch)
+  int ic = (long long)per * (map + 32 * KK) <= 8192 ? per : (per + 1) / 2;
+  while (ic > 0 && !mfma_chunk_fits(ic, KK, map)) --ic;
+  return ic;
+}
 // Weight gradients of such a layer as a matrix product over the output pixels: rows = output maps,
 // columns = (input map, tap); the deltas of 32 maps over the whole output map must fit in LDS next
 // to at least one input map.
@@ -548,9 +556,8 @@ int check_plan(cnn* net) {
       case ST_CONV_FWD_MFMA: {
         const int KK = L.K * L.K, HiWi = L.Hi * L.Wi, Pn = L.Ho * L.Wo;
         const int NT = (Pn + 31) / 32, waves = WG / 64, KW = NT >= waves ? 1 : waves / NT;
-        const int WP = st.chunk * KK + 1 + ((st.chunk * KK) & 1);
         if (L.rect || !L.full_table || !mfma_shape_ok(L.Mi, L.K, L.Mo, L.Ho, L.Wo)) return bad(s, "layer not fit for the matrix-core kernel");
-        if (st.chunk < 1 || (long long)st.chunk * HiWi + 32LL * WP + (long long)st.chunk * KK > LDS_FLOATS) return bad(s, "chunk exceeds LDS");
+        if (!mfma_chunk_fits(st.chunk, KK, HiWi)) return bad(s, "chunk exceeds LDS");
         if (st.n_tiles < 1 || st.n_tiles > L.Mi || st.n_items != ((L.Mo + 31) / 32) * st.n_tiles) return bad(s, "slices do not cover the input maps");
         if (st.rows_per_wg != st.n_tiles || st.rows_per_wg > MFMA_MAX_SLICES) return bad(s, "too many partial-sum planes");
         if (KW > 1 && (long long)KW * NT * 1024 > LDS_FLOATS) return bad(s, "k splits do not fit LDS");
@@ -560,10 +567,9 @@ int check_plan(cnn* net) {
       case ST_CONV_BWD_MFMA: {
         const int KK = L.K * L.K, HWd = (L.Hi + L.K - 1) * (L.Wi + L.K - 1), Pn = L.Hi * L.Wi;
         const int NT = (Pn + 31) / 32, waves = WG / 64, KW = NT >= waves ? 1 : waves / NT;
-        const int WP = st.chunk * KK + 1 + ((st.chunk * KK) & 1);
         if (net->mode != CNN_MODE_STAGES) return bad(s, "the matrix-core pull is planned for the stage-launch mode only");
         if (L.rect || !L.full_table || !mfma_bwd_shape_ok(L.Mi, L.K, L.S, L.Mo, L.Hi, L.Wi)) return bad(s, "layer not fit for the matrix-core pull");
-        if (st.chunk < 1 || (long long)st.chunk * HWd + 32LL * WP + (long long)st.chunk * KK > LDS_FLOATS) return bad(s, "chunk exceeds LDS");
+        if (!mfma_chunk_fits(st.chunk, KK, HWd)) return bad(s, "chunk exceeds LDS");
         if (st.n_tiles < 1 || st.n_tiles > L.Mo || st.n_items != ((L.Mi + 31) / 32) * st.n_tiles) return bad(s, "slices do not cover the output maps");
         if (st.rows_per_wg != st.n_tiles || st.rows_per_wg > MFMA_MAX_SLICES) return bad(s, "too many partial-sum planes");
         if (KW > 1 && (long long)KW * NT * 1024 > LDS_FLOATS) return bad(s, "k splits do not fit LDS");
@@ -737,7 +743,10 @@ int plan(cnn* net) {
   if (fe) add(ST_FRONTEND, 0, (net->fe_n * A[0].h * A[0].w + WG - 1) / WG, 1, 0);
   for (int l = 0; l < nl; ++l) {  // forward, bottom up
     LayerDev& L = P.layers[l];
-    if (L.kind == L_CONV && net->use_mfma && !L.rect && L.full_table && mfma_shape_ok(L.Mi, L.K, L.Mo, L.Ho, L.Wo)) {
+    const bool wide = L.kind == L_CONV && net->use_mfma && !L.rect && L.full_table && mfma_shape_ok(L.Mi, L.K, L.Mo, L.Ho, L.Wo);
+    if (wide && L.Hi * L.Wi + 33 * L.K * L.K + 2 > LDS_FLOATS - 64)
+      return fail(&net->err, CNN_E_SHAPE, "an input map does not fit the LDS staging area of the matrix-core kernel");
+    if (wide && mfma_chunk_fits(1, L.K * L.K, L.Hi * L.Wi)) {   // (a larger map: the vector kernel, band by band)
       // wide layer: implicit GEMM on the matrix cores, the contraction split over workgroups, then
       // a second stage that adds the partial sums and does what follows the sum
       const int n_cu = net->n_cu > 0 ? net->n_cu : 256;
@@ -749,8 +758,7 @@ int plan(cnn* net) {
       int KS = std::max(1, std::min({n_cu / RT, L.Mi, MFMA_MAX_SLICES}));
       const int per = (L.Mi + KS - 1) / KS;
       KS = (L.Mi + per - 1) / per;
-      const int IC = std::min(per, (LDS_FLOATS - 64) / (HiWi + 33 * KK + 2));
-      if (IC < 1) return fail(&net->err, CNN_E_SHAPE, "an input map does not fit the LDS staging area of the matrix-core kernel");
+      const int IC = mfma_chunk(per, KK, HiWi);
       Stage& s = add(ST_CONV_FWD_MFMA, l, RT * KS, 1, 0);
       s.n_tiles = KS; s.chunk = IC; s.rows_per_wg = KS;
       // maps per work item of the second stage, side by side in its lanes: as many as leave every map its
@@ -890,7 +898,7 @@ int plan(cnn* net) {
           int KS = std::max(1, std::min({n_cu / RT, L.Mo, MFMA_MAX_SLICES}));
           const int per = (L.Mo + KS - 1) / KS;
           KS = (L.Mo + per - 1) / per;
-          const int IC = std::min(per, (LDS_FLOATS - 64) / (HWd + 33 * KK + 2));
+          const int IC = mfma_chunk(per, KK, HWd);
           if (IC >= 1) {
             Stage& s = add(ST_CONV_BWD_MFMA, l, RT * KS, 1, 1);
             s.n_tiles = KS; s.chunk = IC; s.rows_per_wg = KS;

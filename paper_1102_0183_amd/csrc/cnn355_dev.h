@@ -87,6 +87,23 @@ enum StageKind : int {
   ST_CONV_WGRAD_FIRST = 17, // weight gradients of such a layer over the pooling winners, the whole input in LDS
   ST_CONV_BWD_WEPI = 15,   // ... then: their sum, times the activation derivative of the layer below
 };
+// LDS of a matrix-core work item, in floats: the places of the taps, then two halves of staged maps and filter rows each
+constexpr int MFMA_KOFF = 544;                          // taps of a chunk, in eights, at most
+constexpr int MFMA_HALF = (LDS_FLOATS - MFMA_KOFF) / 2;  // maps and filter rows of a chunk at most
+struct MfmaLds {
+  int koff, in, pitch, half;   // the table; the maps of a half; floats between filter rows; a half
+};
+#if defined(__HIP__)
+__host__ __device__
+#endif
+constexpr MfmaLds mfma_lds(int IC, int KK, int HiWi) {
+  // rows a multiple of four floats apart, an odd multiple: 128-bit reads of eight rows lie in different banks
+  const int taps = (IC * KK + 7) / 8 * 8, in = (IC * HiWi + 3) / 4 * 4, pitch = taps + 4;
+  return MfmaLds{taps, in, pitch, in + 32 * pitch};
+}
+constexpr bool mfma_chunk_fits(int IC, int KK, int HiWi) {
+  return IC >= 1 && (long long)IC * KK <= MFMA_KOFF && (long long)IC * HiWi + 32LL * (IC * KK + 12) <= MFMA_HALF;
+}
 constexpr int MFMA_MAX_SLICES = 64;  // partial-sum slices (splits of the contraction) per layer
 
 struct Stage {

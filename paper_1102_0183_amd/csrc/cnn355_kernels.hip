@@ -321,16 +321,26 @@ __device__ void conv_fwd_item(const LayerDev& L, const Stage& st, int item,
 // p = output pixel: W is the layer's filter block as it lies in memory (row j holds Mi*K*K
 // contiguous floats), X is never formed: X[k][p] = in_i[(y(S+1)+ky) Wi + x(S+1)+kx] is the
 // sum of an offset that depends on k only and one that depends on p only.
-// Work item = (tile of 32 output maps, slice of the input maps).  The slice's input maps and
-// the 32 x (maps*K*K) block of filters are staged through LDS chunk by chunk; each wavefront
+// Work item = (tile of 32 output maps, slice of the input maps).  The slice is cut into chunks of input maps: the
+// next one is on its way in registers while the present one, in the other half of LDS, is multiplied.  Each wavefront
 // owns one (or several) tiles of 32 pixels, and when there are fewer pixel tiles than
 // wavefronts the spare ones split the chunk's k range.  v_mfma_f32_32x32x2_f32: lane l feeds
-// A[l%32][l/32] and B[l/32][l%32], two k per instruction, 16 accumulators per lane.
+// A[l%32][l/32] and B[l/32][l%32], two k per instruction, 16 accumulators per lane.  Filters and
+// places of the taps lie in LDS in the order four instructions take them, 128 bits a lane.
 // The partial sums of every (slice, k split) go to their own plane of mm_part; ST_CONV_EPI
 // adds the planes in a fixed order (no atomics: results do not depend on timing).
+// 500C4 on 300 maps of 23 x 23 (256 items): 25.1 us, 33.5 without the overlap, with clamped single-word operands and an
+// integer division for every word staged, and with a fourth of its 13 pixel tiles on one SIMD; 13 us at the matrix cores' rate, the
+// rest operands from LDS.  300C2 and 300C4 8.4 -> 7.8 and 6.5 -> 6.1, the pull through 300C2 10.3 -> 8.6.
 // ------------------------------------------------------------------------------------------
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4w __attribute__((ext_vector_type(4)));
+typedef float v4wu __attribute__((ext_vector_type(4), aligned(4)));
+typedef int v4i __attribute__((ext_vector_type(4)));
 constexpr int MM_TPW = 4;  // pixel tiles one wavefront can carry (64 accumulators)
+
+// place of tap k of a row of filters (or of the table of places) in LDS: eight taps, those of even k first
+__device__ __forceinline__ int mm_place(int k) { return (k & ~7) + ((k & 1) << 2) + ((k >> 1) & 3); }
 
 // BWD = false: FP, rows = output maps, contraction over (input map, tap), staged maps = the
 // layer's inputs.  BWD = true: the delta pull of Sec. 3.3 as FP's mirror image (skipping factor 0
@@ -339,9 +349,11 @@ constexpr int MM_TPW = 4;  // pixel tiles one wavefront can carry (64 accumulato
 //   g_i[r][c] = sum_j sum_{ky,kx} D_j[r + K-1-ky][c + K-1-kx] w_{j,i}[ky][kx]
 // has the same operand pattern in[koff(k) + pbase(p)] as FP; the weights are used as they lie
 // (the tap order is turned round in koff instead).  One plane of partial sums per work item.
-template <bool BWD>
-__device__ void conv_mfma_item(const LayerDev& L, const Stage& st, int item, const gfloat* in, float* lds) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+// OVERLAP: a whole chunk is on its way in registers (else it is staged a few words at a time between two chunks'
+// arithmetic: with four tiles a wavefront, and in the persistent kernel, there are no registers for it).
+template <bool BWD, int TPW, bool OVERLAP>
+__device__ __forceinline__ void conv_mfma_tiles(const LayerDev& L, const Stage& st, int item, const gfloat* in, float* lds) {
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int lrow = lane & 31, lk = lane >> 5;
   const int KS = st.n_tiles;
   const int jt = item / KS, ks = item - jt * KS;
@@ -354,159 +366,222 @@ __device__ void conv_mfma_item(const LayerDev& L, const Stage& st, int item, con
   const int per = (Mi + KS - 1) / KS;
   const int i_lo = ks * per, i_hi = min(Mi, i_lo + per);
   const int IC = st.chunk;
-  const int WP = IC * KK + 1 + ((IC * KK) & 1);   // odd row pitch: the 32 rows of a column lie in 32 banks
+  const MfmaLds Z = mfma_lds(IC, KK, HiWi);
+  const int WP = Z.pitch;
   const int NT = (P + 31) >> 5;
   constexpr int WAVES = WG / 64;
   const int NTw = min(NT, WAVES);
-  const int KW = (NT >= WAVES) ? 1 : WAVES / NT;
-  const int kw = (NT >= WAVES) ? 0 : wave / NT;
-  const int tw = (NT >= WAVES) ? wave : wave - kw * NT;
-  const bool wave_on = kw < KW;
+  // Pixel tiles from F on are shared: KW wavefronts split the k range of one.  With up to half as many tiles as wavefronts all
+  // of them; with more, what is left of whole rounds over the four SIMDs (wavefront w runs on SIMD w mod 4).
+  const int F = NT >= WAVES ? NT : NT <= WAVES / 2 ? 0 : NT & ~3;
+  const int KW = F < NT ? (WAVES - F) / (NT - F) : 1;
+  const int kw = wave < F ? 0 : F ? (wave - F) % KW : wave / NT;
+  const int tw = wave < F ? wave : F ? F + (wave - F) / KW : wave - kw * NT;
+  const bool wave_on = tw < NT && kw < KW;
+  const int kw_n = wave < F ? 1 : KW;   // (of this wavefront's tile)
+  constexpr int UNROLL = TPW == 1 ? 2 : 1;
+  int* koff = (int*)lds;   // [IC*KK, whole eights] offset of k inside the staged maps
 
-  float* lds_in = lds;                         // [IC][Hi*Wi]
-  float* lds_w = lds + IC * HiWi;              // [32][WP]
-  int* koff = (int*)(lds_w + 32 * WP);         // [IC*KK] offset of k inside the staged maps
-
+  const float by_KK = 1.f / KK, by_K = 1.f / K;   // (quotients of whole numbers below 2^16 by those below 256, taken half a step off: exact)
   for (int x = tid; x < IC * KK; x += WG) {
-    const int c = x / KK, t = x - c * KK;
-    const int ky = t / K, kx = t - ky * K;
-    koff[x] = BWD ? c * HiWi + (K - 1 - ky) * Wi + (K - 1 - kx) : c * HiWi + ky * Wi + kx;
+    const int c = (int)((x + 0.5f) * by_KK), t = x - c * KK;
+    const int ky = (int)((t + 0.5f) * by_K), kx = t - ky * K;
+    koff[mm_place(x)] = BWD ? c * HiWi + (K - 1 - ky) * Wi + (K - 1 - kx) : c * HiWi + ky * Wi + kx;
   }
-  int pbase[MM_TPW];
+  int pbase[TPW];
 #pragma unroll
-  for (int t = 0; t < MM_TPW; ++t) {
+  for (int t = 0; t < TPW; ++t) {
     const int p = (tw + t * NTw) * 32 + lrow;
-    const int y = p / Wo, x = p - y * Wo;
+    const int y = (int)((p + 0.5f) / Wo), x = p - y * Wo;
     pbase[t] = (p < P) ? (y * Wi + x) * stride : 0;
   }
-  v16f acc[MM_TPW];
+  v16f acc[TPW];
 #pragma unroll
-  for (int t = 0; t < MM_TPW; ++t)
+  for (int t = 0; t < TPW; ++t)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
   const int n_my_tiles = wave_on ? ((NT - tw + NTw - 1) / NTw) : 0;   // 1 unless there are more than 16 pixel tiles
 
-  for (int ic0 = i_lo; ic0 < i_hi; ic0 += IC) {
-    const int n_ic = min(IC, i_hi - ic0);
-    const int kc = n_ic * KK;
-    if constexpr (!BWD) {  // stage the chunk, eight loads in flight per lane: the inputs (one contiguous block) ...
-      const gfloat* src = in + (size_t)ic0 * HiWi;
-      const int n_in = n_ic * HiWi;
-      for (int x0 = 0; x0 < n_in; x0 += 8 * WG) {
-        float v[8];
+  // ---- staging: a chunk's words in registers, then in LDS --------------------------------
+  // FP: the inputs are one contiguous block (16 bytes a lane), a filter row is a run of kc floats (32 lanes a row).
+  // BWD: the filters w_{j,i} of output map j and the 32 input maps of this tile are one run of 32 KK floats (units of 64
+  // lanes); the deltas go to their winners' places.
+  // (rounds of loads in flight together: most of a chunk; a full half of LDS would be 5 and 18 of them)
+  constexpr int VI = OVERLAP && !BWD ? 3 : 1, VD = OVERLAP && BWD ? 4 : 1, VW = OVERLAP ? 8 : 4;
+  v4w vi[VI];
+  float vt = 0.f, vw[VW], vd[VD];
+  int vyx[VD];
+  const int r_st = tid >> 5, xl = tid & 31;          // FP: row and place in it of this thread's filter words
+  const int n_rows = min(32, Mo - j0), run = n_rows * KK, S64 = (run + 63) >> 6, HWp = L.Hp * L.Wp;
+  const float by_S64 = 1.f / S64, by_HW = 1.f / HWp;
+  const bool row_ok = j0 + r_st < Mo;
+  auto fetch_in = [&](int ic0, int n_ic, int u0) {
+    const gfloat* src = in + (size_t)ic0 * HiWi;
+    const int n_in = n_ic * HiWi;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = src[min(x0 + u * WG + tid, n_in - 1)];
+    for (int u = 0; u < VI; ++u)
+      if (((u0 + u) * WG + tid) * 4 + 4 <= n_in) vi[u] = *(const CNN_GLOBAL v4wu*)(src + (unsigned)((u0 + u) * WG + tid) * 4u);
+    if (u0 == 0) vt = src[min((n_in & ~3) + (tid & 3), n_in - 1)];   // the last words when they do not fill 16 bytes
+  };
+  auto commit_in = [&](float* lds_in, int n_ic, int u0) {
+    const int n_in = n_ic * HiWi;
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (x0 + u * WG + tid < n_in) lds_in[x0 + u * WG + tid] = v[u];
-      }
-      // ... and the 32 filter rows (one contiguous run of kc floats each; 32 lanes per row)
-      const int r = tid >> 5, xl = tid & 31;
-      const bool row_ok = j0 + r < Mo;
-      const gfloat* wr = L.w + ((size_t)min(j0 + r, Mo - 1) * Mi + ic0) * KK;
-      for (int x0 = 0; x0 < kc; x0 += 8 * 32) {
-        float v[8];
+    for (int u = 0; u < VI; ++u)
+      if (((u0 + u) * WG + tid) * 4 + 4 <= n_in) *(v4w*)(lds_in + ((u0 + u) * WG + tid) * 4) = vi[u];
+    if (u0 == 0 && tid < (n_in & 3)) lds_in[(n_in & ~3) + tid] = vt;
+  };
+  auto fetch_w = [&](int ic0, int n_ic, int u0) {
+    if constexpr (!BWD) {
+      const int kc = n_ic * KK;
+      const gfloat* wr = L.w + ((size_t)min(j0 + r_st, Mo - 1) * Mi + ic0) * KK;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = wr[min(x0 + u * 32 + xl, kc - 1)];
+      for (int u = 0; u < VW; ++u)
+        if ((u0 + u) * 32 + xl < kc) vw[u] = wr[(u0 + u) * 32 + xl];
+    } else {
+      const int units = n_ic * S64;
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (x0 + u * 32 + xl < kc) lds_w[r * WP + x0 + u * 32 + xl] = row_ok ? v[u] : 0.f;
+      for (int u = 0; u < VW; ++u)
+        if ((u0 + u) * WAVES < units) {
+          const int unit = min(wave + (u0 + u) * WAVES, units - 1), jj = __builtin_amdgcn_readfirstlane((int)((unit + 0.5f) * by_S64));
+          const gfloat* wj = L.w + ((size_t)(ic0 + jj) * Mo + j0) * KK + (unit - jj * S64) * 64;
+          if ((unit - jj * S64) * 64 + lane < run) vw[u] = wj[lane];
+        }
+    }
+  };
+  auto commit_w = [&](float* lds_w, int n_ic, int u0) {
+    if constexpr (!BWD) {
+      const int kc = n_ic * KK;
+#pragma unroll
+      for (int u = 0; u < VW; ++u) {
+        const int k = (u0 + u) * 32 + xl;
+        if (k < kc) lds_w[r_st * WP + mm_place(k)] = row_ok ? vw[u] : 0.f;
       }
     } else {
-      // the filters w_{j,i} of the chunk's output maps j and the 32 input maps i of this tile: for
-      // one j they are 32 * KK consecutive floats (i runs fastest after the tap)
-      const int n_rows = min(32, Mo - j0);
-      const int run = n_rows * KK, tot = n_ic * run;
-      for (int x0 = 0; x0 < tot; x0 += 8 * WG) {
-        float v[8];
-        int d[8];
+      const int units = n_ic * S64;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int x = min(x0 + u * WG + tid, tot - 1);
-          const int jj = x / run, rem = x - jj * run;
-          const int r = rem / KK, t = rem - r * KK;
-          v[u] = L.w[((size_t)(ic0 + jj) * Mo + j0) * KK + rem];
-          d[u] = r * WP + jj * KK + t;
+      for (int u = 0; u < VW; ++u) {
+        const int unit = wave + (u0 + u) * WAVES;
+        if (unit < units) {
+          const int jj = __builtin_amdgcn_readfirstlane((int)((unit + 0.5f) * by_S64)), rem = (unit - jj * S64) * 64 + lane, r = (int)((rem + 0.5f) * by_KK);
+          if (rem < run) lds_w[r * WP + mm_place(jj * KK + rem - r * KK)] = vw[u];
         }
-        if (x0 == 0) {  // the zero fill overlaps the first batch of loads
-          for (int x = tid; x < n_ic * HiWi; x += WG) lds_in[x] = 0.f;
-          if (n_rows < 32)
-            for (int x = tid; x < (32 - n_rows) * WP; x += WG) lds_w[n_rows * WP + x] = 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (x0 + u * WG + tid < tot) lds_w[d[u]] = v[u];
-      }
-      __syncthreads();
-      // the chunk's deltas, each to its winner's place inside the zeros
-      const int HW = L.Hp * L.Wp, ntot = n_ic * HW;
-      for (int x0 = 0; x0 < ntot; x0 += 4 * WG) {
-        float dv[4];
-        int yx[4], cc[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int x = min(x0 + u * WG + tid, ntot - 1);
-          cc[u] = x / HW;
-          const size_t o = (size_t)(ic0 + cc[u]) * HW + (x - cc[u] * HW);
-          yx[u] = L.argyx[o];
-          dv[u] = L.delta[o];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (x0 + u * WG + tid < ntot)
-            lds_in[cc[u] * HiWi + ((yx[u] >> 16) + K - 1) * Wi + (yx[u] & 0xffff) + K - 1] = dv[u];
       }
     }
+  };
+  auto fetch_d = [&](int ic0, int n_ic, int u0) {
+    const int ntot = n_ic * HWp;
+#pragma unroll
+    for (int u = 0; u < VD; ++u)
+      if ((u0 + u) * WG < ntot) {
+        const size_t o = (size_t)ic0 * HWp + min((u0 + u) * WG + tid, ntot - 1);
+        vyx[u] = L.argyx[o];
+        vd[u] = L.delta[o];
+      }
+  };
+  auto commit_d = [&](float* lds_in, int n_ic, int u0) {
+    const int ntot = n_ic * HWp;
+#pragma unroll
+    for (int u = 0; u < VD; ++u) {
+      const int x = (u0 + u) * WG + tid;
+      if (x < ntot) lds_in[(int)((x + 0.5f) * by_HW) * HiWi + ((vyx[u] >> 16) + K - 1) * Wi + (vyx[u] & 0xffff) + K - 1] = vd[u];
+    }
+  };
+  // the loads of a chunk (what the registers hold of it), and the rest with its way into LDS
+  auto fetch = [&](int ic0) {
+    const int n_ic = min(IC, i_hi - ic0);
+    if constexpr (OVERLAP) {
+      if constexpr (BWD) fetch_d(ic0, n_ic, 0);
+      else fetch_in(ic0, n_ic, 0);
+      fetch_w(ic0, n_ic, 0);
+    }
+  };
+  auto clear = [&](float* half, int ic0) {   // BWD: the zeros the deltas are put into, and the rows of filters there are not
+    const int n_ic = min(IC, i_hi - ic0);
+    for (int x = tid; x < n_ic * HiWi; x += WG) half[x] = 0.f;
+    if (n_rows < 32)
+      for (int x = tid; x < (32 - n_rows) * WP; x += WG) half[Z.in + n_rows * WP + x] = 0.f;
+  };
+  auto commit = [&](float* half, int ic0) {
+    const int n_ic = min(IC, i_hi - ic0);
+    const int rw = BWD ? (n_ic * S64 + WAVES - 1) / WAVES : (n_ic * KK + 31) / 32;
+    if constexpr (OVERLAP) {
+      if constexpr (BWD) commit_d(half, n_ic, 0);
+      else commit_in(half, n_ic, 0);
+      commit_w(half + Z.in, n_ic, 0);
+    }
+    if constexpr (!BWD) {
+      for (int u = OVERLAP ? VI : 0; u * WG * 4 < n_ic * HiWi; u += VI) { fetch_in(ic0, n_ic, u); commit_in(half, n_ic, u); }
+    } else {
+      for (int u = OVERLAP ? VD : 0; u * WG < n_ic * HWp; u += VD) { fetch_d(ic0, n_ic, u); commit_d(half, n_ic, u); }
+    }
+    for (int u = OVERLAP ? VW : 0; u < rw; u += VW) { fetch_w(ic0, n_ic, u); commit_w(half + Z.in, n_ic, u); }
+  };
+
+  float* half = lds + Z.koff;
+  float* other = half + Z.half;
+  fetch(i_lo);
+  if constexpr (BWD) {
+    clear(half, i_lo);
     __syncthreads();
+  }
+  commit(half, i_lo);
+  __syncthreads();
+  for (int ic0 = i_lo; ic0 < i_hi; ic0 += IC) {
+    const int kc = min(IC, i_hi - ic0) * KK;
+    const bool more = ic0 + IC < i_hi;
+    if (more) {
+      fetch(ic0 + IC);
+      if constexpr (BWD) clear(other, ic0 + IC);
+    }
     if (wave_on) {
-      // this wavefront's share of the chunk's k range (even bounds: two k per instruction);
-      // four instructions' operands are fetched from LDS together
-      const int kper = (((kc + KW - 1) / KW) + 1) & ~1;
-      const int k_lo = kw * kper, k_hi = min(kc, k_lo + kper);
-      for (int kk = k_lo; kk < k_hi; kk += 8) {
-        float a[4];
-        int ko[4];
+      // this wavefront's share of the chunk's k range, four instructions at a time
+      const float* lds_in = half;
+      const float* wa = half + Z.in + lrow * WP + lk * 4;
+      const int* ko_at = koff + lk * 4;
+      const int kper = ((kc + kw_n - 1) / kw_n + 7) & ~7;
+      const int k_lo = min(kw * kper, kc), k_hi = min(kc, k_lo + kper), k_full = k_lo + ((k_hi - k_lo) & ~7);
+#pragma unroll UNROLL
+      for (int kk = k_lo; kk < k_full; kk += 8) {
+        const v4w a = *(const v4w*)(wa + kk);
+        const v4i ko = *(const v4i*)(ko_at + kk);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int k = kk + 2 * u + lk;
-          a[u] = (k < k_hi) ? lds_w[lrow * WP + min(k, kc - 1)] : 0.f;
-          ko[u] = koff[min(k, kc - 1)];
-        }
-#pragma unroll
-        for (int t = 0; t < MM_TPW; ++t)
-          if (t < n_my_tiles) {
-            float b[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) b[u] = lds_in[ko[u] + pbase[t]];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u], b[u], acc[t], 0, 0, 0);
+        for (int t = 0; t < TPW; ++t)
+          if (TPW == 1 || t < n_my_tiles) {
+            const float* x = lds_in + pbase[t];
+            const float b0 = x[ko.x], b1 = x[ko.y], b2 = x[ko.z], b3 = x[ko.w];
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b0, acc[t], 0, 0, 0);
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b1, acc[t], 0, 0, 0);
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b2, acc[t], 0, 0, 0);
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b3, acc[t], 0, 0, 0);
           }
       }
+      for (int kk = k_full; kk < k_hi; kk += 2) {   // what is left over: fewer than eight
+        const int k = min(kk + lk, kc - 1);
+        const float a = kk + lk < k_hi ? half[Z.in + lrow * WP + mm_place(k)] : 0.f;
+        const int ko = koff[mm_place(k)];
+#pragma unroll
+        for (int t = 0; t < TPW; ++t)
+          if (TPW == 1 || t < n_my_tiles) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, lds_in[ko + pbase[t]], acc[t], 0, 0, 0);
+      }
+    }
+    if (more) {
+      if constexpr (BWD) __syncthreads();
+      commit(other, ic0 + IC);
     }
     __syncthreads();
+    float* t = half; half = other; other = t;
   }
   // the k splits inside the workgroup are added here (through LDS, in a fixed order), so that one
   // work item leaves one plane of partial sums
   gfloat* plane = L.mm_part + (size_t)ks * Mo * P;
-  if (KW > 1) {
-    float* red = lds;  // [KW][NT][32 rows][32 pixels]
-    if (wave_on) {
+  if (KW > 1 && tw >= F && wave_on) {
+    float* red = lds;  // [KW][tiles from F on][32 rows][32 pixels]
 #pragma unroll
-      for (int v = 0; v < 16; ++v)
-        red[((kw * NT + tw) * 32 + (v >> 2) * 8 + lk * 4 + (v & 3)) * 32 + lrow] = acc[0][v];
-    }
-    __syncthreads();
-    for (int x = tid; x < NT * 1024; x += WG) {
-      const int t = x >> 10, row = (x >> 5) & 31, col = x & 31;
-      float sum = 0.f;
-      for (int q = 0; q < KW; ++q) sum += red[((q * NT + t) * 32 + row) * 32 + col];
-      const int p = t * 32 + col, j = j0 + row;
-      if (p < P && j < Mo) plane[(size_t)j * P + p] = sum;
-    }
-    __syncthreads();
+    for (int v = 0; v < 16; ++v)
+      red[((kw * (NT - F) + tw - F) * 32 + (v >> 2) * 8 + lk * 4 + (v & 3)) * 32 + lrow] = acc[0][v];
   } else if (wave_on) {
 #pragma unroll
-    for (int t = 0; t < MM_TPW; ++t)
+    for (int t = 0; t < TPW; ++t)
       if (t < n_my_tiles) {
         const int p = (tw + t * NTw) * 32 + lrow;
 #pragma unroll
@@ -516,7 +591,20 @@ __device__ void conv_mfma_item(const LayerDev& L, const Stage& st, int item, con
         }
       }
   }
+  if (KW > 1) {
+    const float* red = lds;
+    __syncthreads();
+    for (int x = tid; x < (NT - F) * 1024; x += WG) {
+      const int t = x >> 10, row = (x >> 5) & 31, col = x & 31;
+      float sum = 0.f;
+      for (int q = 0; q < KW; ++q) sum += red[((q * (NT - F) + t) * 32 + row) * 32 + col];
+      const int p = (F + t) * 32 + col, j = j0 + row;
+      if (p < P && j < Mo) plane[(size_t)j * P + p] = sum;
+    }
+    __syncthreads();
+  }
 }
+__host__ __device__ __forceinline__ bool mfma_one_tile(int P) { return P <= (WG / 64) * 32; }   // a wavefront each
 
 // Second half of the matrix-core forward pass.  Work item = output map j: add the planes of
 // partial sums (lane groups share the planes, eight loads in flight per lane, fixed order), bias,
@@ -1330,12 +1418,8 @@ __device__ __forceinline__ void run_item(const ProgramDev& P, const Stage& st, i
     conv_bwd_item(L, P.layers[st.layer - 1], st, item, lds);
   } else if constexpr (KIND == ST_CONV_WGRAD) {
     conv_wgrad_item(L, st, item, in, ctx, lds);
-  } else if constexpr (KIND == ST_CONV_FWD_MFMA) {
-    conv_mfma_item<false>(L, st, item, in, lds);
   } else if constexpr (KIND == ST_CONV_EPI) {
     conv_epi_item(L, st, item, lds);
-  } else if constexpr (KIND == ST_CONV_BWD_MFMA) {
-    conv_mfma_item<true>(L, st, item, in, lds);
   } else if constexpr (KIND == ST_CONV_BWD_EPI) {
     conv_bwd_epi_item(L, P.layers[st.layer - 1], st, item);
   } else if constexpr (KIND == ST_CONV_WGRAD_MFMA) {
@@ -1365,7 +1449,15 @@ __device__ __forceinline__ void run_stage_items(const ProgramDev& P, const Stage
     switch (st.kind) {
 #define RUN_KIND(KIND) \
       case KIND: for (int item = first; item < st.n_items; item += step) run_item<KIND>(P, st, item, ctx, status, lds); return;
-      RUN_KIND(ST_CONV_FWD_MFMA)
+      case ST_CONV_FWD_MFMA: {
+        const LayerDev& L = P.layers[st.layer];
+        const gfloat* in = L.in_is_image ? ctx.image : L.in;
+        for (int item = first; item < st.n_items; item += step) {
+          if (mfma_one_tile(L.Ho * L.Wo)) conv_mfma_tiles<false, 1, false>(L, st, item, in, lds);
+          else conv_mfma_tiles<false, MM_TPW, false>(L, st, item, in, lds);
+        }
+        return;
+      }
       RUN_KIND(ST_CONV_EPI)
 #undef RUN_KIND
       default: break;
@@ -1403,15 +1495,24 @@ STAGE_KERNEL(k_head, ST_HEAD)
 STAGE_KERNEL(k_fc_bwd, ST_FC_BWD)
 STAGE_KERNEL(k_conv_bwd, ST_CONV_BWD)
 STAGE_KERNEL(k_conv_wgrad, ST_CONV_WGRAD)
-STAGE_KERNEL(k_conv_fwd_mfma, ST_CONV_FWD_MFMA)
 STAGE_KERNEL(k_conv_epi, ST_CONV_EPI)
-STAGE_KERNEL(k_conv_bwd_mfma, ST_CONV_BWD_MFMA)
 STAGE_KERNEL(k_conv_bwd_epi, ST_CONV_BWD_EPI)
 STAGE_KERNEL(k_conv_wgrad_mfma, ST_CONV_WGRAD_MFMA)
 STAGE_KERNEL(k_conv_wgrad_win, ST_CONV_WGRAD_WIN)
 STAGE_KERNEL(k_conv_fwd_mx, ST_CONV_FWD_MX)
 STAGE_KERNEL(k_conv_wgrad_first, ST_CONV_WGRAD_FIRST)
 STAGE_KERNEL(k_conv_bwd_wepi, ST_CONV_BWD_WEPI)
+
+// (the tiles a wavefront has are of the kernel, not of the call: four tiles' accumulators would cost the others their registers)
+template <bool BWD, int TPW>
+__global__ void __launch_bounds__(WG) k_conv_mfma(const ProgramDev* __restrict__ P, int s, StatusDev* status, RunArgs a) {
+  __shared__ __align__(16) float lds[LDS_FLOATS];
+  const Ctx ctx = make_ctx(*P, a, 0, status);
+  const Stage& st = P->stages[s];
+  if (st.train_only && !ctx.train) return;
+  const LayerDev& L = P->layers[st.layer];
+  conv_mfma_tiles<BWD, TPW, TPW == 1>(L, st, blockIdx.x, L.in_is_image ? ctx.image : L.in, lds);
+}
 
 // Two consecutive stages that the plan declares independent (no barrier between them: a layer's weight
 // adjustment next to the stage that follows its pull) in one launch: the first stage's items, then the second's.
@@ -1606,9 +1707,11 @@ const void* stage_kernel(const Stage& st, const LayerDev& L, int* threads) {
     case ST_FC_BWD: return (const void*)k_fc_bwd;
     case ST_CONV_BWD: return (const void*)k_conv_bwd;
     case ST_CONV_WGRAD: return (const void*)k_conv_wgrad;
-    case ST_CONV_FWD_MFMA: return (const void*)k_conv_fwd_mfma;
+    case ST_CONV_FWD_MFMA:
+      return mfma_one_tile(L.Ho * L.Wo) ? (const void*)k_conv_mfma<false, 1> : (const void*)k_conv_mfma<false, MM_TPW>;
     case ST_CONV_EPI: return (const void*)k_conv_epi;
-    case ST_CONV_BWD_MFMA: return (const void*)k_conv_bwd_mfma;
+    case ST_CONV_BWD_MFMA:
+      return mfma_one_tile(L.Hi * L.Wi) ? (const void*)k_conv_mfma<true, 1> : (const void*)k_conv_mfma<true, MM_TPW>;
     case ST_CONV_BWD_EPI: return (const void*)k_conv_bwd_epi;
     case ST_CONV_WGRAD_MFMA: return (const void*)k_conv_wgrad_mfma;
     case ST_CONV_WGRAD_WIN: return (const void*)k_conv_wgrad_win;

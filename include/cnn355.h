@@ -55,7 +55,9 @@ enum {
                              fully connected layers and a network whose per-workgroup share
                              fits the LDS (cnn_mode_supported tells).  Weights in the
                              workspace are read at the start of a call and written back at
-                             its end.                                                       */
+                             its end.  Forward calls of one to three images run as the
+                             launches of their stages, which start sooner (sums in the
+                             order of CNN_MODE_STAGES: the same to rounding).               */
 };
 
 /* output units for cnn_set_output_units */

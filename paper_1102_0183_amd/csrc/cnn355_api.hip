@@ -595,7 +595,7 @@ int check_plan(cnn* net) {
           return bad(s, "work items do not cover the filters");
         break;
       case ST_CONV_FWD_MX:
-        if (net->mode != CNN_MODE_STAGES) return bad(s, "planned for the stage-launch mode only");
+        if (net->mode == CNN_MODE_PERSISTENT) return bad(s, "not in the persistent kernel");
         if (!conv_fwd_mx_ok(L) || st.tile_rows < L.Kp || st.tile_rows % L.Kp || conv_fwd_mx_floats(L, st.tile_rows) > LDS_FLOATS)
           return bad(s, "row band not fit for the matrix-core kernel");
         if (st.n_tiles * st.tile_rows < L.Ho || (st.n_tiles - 1) * st.tile_rows >= L.Ho || st.n_items != ((L.Mo + 31) / 32) * st.n_tiles)
@@ -770,7 +770,7 @@ int plan(cnn* net) {
       Stage& e = add(ST_CONV_EPI, l, (L.Mo + mp - 1) / mp, 1, 0);
       e.rows_per_wg = KS;
       e.chunk = mp;
-    } else if (L.kind == L_CONV && net->use_mfma && net->mode == CNN_MODE_STAGES && conv_fwd_mx_ok(L)) {
+    } else if (L.kind == L_CONV && net->use_mfma && net->mode != CNN_MODE_PERSISTENT && conv_fwd_mx_ok(L)) {
       // the fewest rows a band that leave one round of the compute units, as far as LDS goes
       const int n_cu = net->n_cu > 0 ? net->n_cu : 256, RT = (L.Mo + 31) / 32;
       int rows = L.Kp;
@@ -940,7 +940,10 @@ int plan(cnn* net) {
   int rc = check_plan(net);
   if (rc) return rc;
   plan_flow(net);
-  if (net->mode == CNN_MODE_RESIDENT && !net->flow_ok) net->mode = CNN_MODE_PERSISTENT;
+  if (net->mode == CNN_MODE_RESIDENT && !net->flow_ok) {   // (its stages are other ones)
+    net->mode = CNN_MODE_PERSISTENT;
+    return plan(net);
+  }
   return CNN_OK;
 }
 
@@ -1177,12 +1180,23 @@ static hipError_t launch_resident_of(cnn* net, int grid, size_t lds_bytes, const
   return hipModuleLaunchCooperativeKernel(net->special_func, (unsigned)grid, 1, 1, WG, 1, 1, (unsigned)lds_bytes, net->stream, params);
 }
 
+// Does a forward call of so few images take the launches of its stages in resident mode too?  A cooperative launch costs some
+// 25 us beside its kernel's work, and the kernel loads a rank's weights first; a stage costs some 6 us an image.  Measured, us
+// (resident, stages): one image of the digits net 35, 24, two 44, 48; with the kernel that reads its plan, two of
+// 100 maps a layer (7 launches) 90, 80, three 116, 121; three of 30 to 50 maps (5 launches) 103, 92.
+bool forward_by_stages(const cnn* net, unsigned long long n) {
+  int launches = 0;
+  for (int s = 0; s < net->prog.n_stages; ++s) launches += net->prog.stages[s].train_only ? 0 : 1;
+  const bool literal = net->flow_static_id > 0 || net->special_active;
+  return n <= (literal ? 1u : launches > 5 ? 2u : 3u);
+}
+
 int run(cnn* net, const RunArgs& a0) {
   RunArgs a = a0;
   a.spin_limit = net->spin_limit;
   a.barrier_kind = net->barrier_kind;
   const ProgramDev& P = net->prog;
-  if (net->mode == CNN_MODE_RESIDENT) {
+  if (net->mode == CNN_MODE_RESIDENT && (a.train || !forward_by_stages(net, (unsigned long long)a.n_images))) {
     const unsigned long long n = (unsigned long long)a.n_images;
     if (n >= (1ull << 31)) return fail(&net->err, CNN_E_ARG, "too many images in one call");
     if (((net->epoch + n) >> 32) != (net->epoch >> 32)) {
@@ -1193,7 +1207,8 @@ int run(cnn* net, const RunArgs& a0) {
     }
     const int grid = net->flow.G * net->flow.stride;
     const size_t lds_bytes = (size_t)net->flow.lds_floats * sizeof(float);
-    HIP_TRY(net, launch_reset_status(net->stream, net->d_status, 0));
+    // (no launch clears the abort flag first: it is clear unless a call before this one gave up, whose error the next
+    // synchronising call returns; until then the weights are undefined and the calls in between leave early)
     if (!P.has_frontend) {
       a.epoch_base = (unsigned int)net->epoch;
       net->epoch += n;

@@ -572,7 +572,8 @@ __device__ __forceinline__ void conv_mfma_tiles(const LayerDev& L, const Stage& 
     float* t = half; half = other; other = t;
   }
   // the k splits inside the workgroup are added here (through LDS, in a fixed order), so that one
-  // work item leaves one plane of partial sums
+  // work item leaves one plane of partial sums (streamed past the L2, whose dirty lines the end of a kernel waits
+  // for: 300C2 and 300C4 two thirds of a microsecond each)
   gfloat* plane = L.mm_part + (size_t)ks * Mo * P;
   if (KW > 1 && tw >= F && wave_on) {
     float* red = lds;  // [KW][tiles from F on][32 rows][32 pixels]
@@ -587,7 +588,7 @@ __device__ __forceinline__ void conv_mfma_tiles(const LayerDev& L, const Stage& 
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int j = j0 + (v >> 2) * 8 + lk * 4 + (v & 3);
-          if (p < P && j < Mo) plane[(size_t)j * P + p] = acc[t][v];
+          if (p < P && j < Mo) __builtin_nontemporal_store(acc[t][v], &plane[(size_t)j * P + p]);
         }
       }
   }
@@ -599,7 +600,7 @@ __device__ __forceinline__ void conv_mfma_tiles(const LayerDev& L, const Stage& 
       float sum = 0.f;
       for (int q = 0; q < KW; ++q) sum += red[((q * (NT - F) + t) * 32 + row) * 32 + col];
       const int p = (F + t) * 32 + col, j = j0 + row;
-      if (p < P && j < Mo) plane[(size_t)j * P + p] = sum;
+      if (p < P && j < Mo) __builtin_nontemporal_store(sum, &plane[(size_t)j * P + p]);
     }
     __syncthreads();
   }
@@ -705,7 +706,7 @@ __device__ void fc_fwd_item(const LayerDev& L, const Stage& st, int item,
     for (int m = lane; m < n_in; m += lpr) s = fmaf(wr[m], v[m], s);
   }
   s = wave_sum(s);
-  float* part = lds + LDS_IN + LDS_AUX + LDS_AUX2;
+  float* part = lds;
   if ((tid & 63) == 0) part[tid >> 6] = s;
   __syncthreads();
   if (tid < rpw) {
@@ -876,8 +877,8 @@ __device__ void fc_bwd_item(const LayerDev& L, const LayerDev* Lp, const Stage& 
   const int ks = tid >> cml, cm = tid & (CM - 1);
   const int m = item * CM + cm;
   const int N = L.n_out, n_in = L.n_in;
-  float* dl = lds + LDS_IN;
-  float* part = lds + LDS_IN + LDS_AUX + LDS_AUX2;
+  float* dl = lds + WG;
+  float* part = lds;
   // every global load this item needs is issued before the first wait: this column's first FB
   // weights (rows ks, ks + KS, ...), its input, and the layer's deltas
   constexpr int FB = 4;
@@ -1479,10 +1480,12 @@ __device__ __forceinline__ void run_stage_items(const ProgramDev& P, const Stage
 }
 
 // ---- one launch per stage: grid = n_items of the stage -------------------------------------
-#define STAGE_KERNEL(name, KIND)                                                             \
+// (a kernel holds the LDS its items use: two of the fully connected stages' workgroups share a compute unit)
+#define STAGE_KERNEL(name, KIND) STAGE_KERNEL_LDS(name, KIND, LDS_FLOATS)
+#define STAGE_KERNEL_LDS(name, KIND, FLOATS)                                                 \
   __global__ void __launch_bounds__(WG) name(const ProgramDev* __restrict__ P, int s,        \
                                              StatusDev* status, RunArgs a) {                 \
-    __shared__ __align__(16) float lds[LDS_FLOATS];                                                     \
+    __shared__ __align__(16) float lds[FLOATS];                                                     \
     const Ctx ctx = make_ctx(*P, a, 0, status);                                              \
     const Stage& st = P->stages[s];                                                          \
     if (st.train_only && !ctx.train) return;                                                 \
@@ -1490,9 +1493,9 @@ __device__ __forceinline__ void run_stage_items(const ProgramDev& P, const Stage
   }
 STAGE_KERNEL(k_frontend, ST_FRONTEND)
 STAGE_KERNEL(k_conv_fwd, ST_CONV_FWD)
-STAGE_KERNEL(k_fc_fwd, ST_FC_FWD)
+STAGE_KERNEL_LDS(k_fc_fwd, ST_FC_FWD, WG / 64)
 STAGE_KERNEL(k_head, ST_HEAD)
-STAGE_KERNEL(k_fc_bwd, ST_FC_BWD)
+STAGE_KERNEL_LDS(k_fc_bwd, ST_FC_BWD, WG + MAX_FC_OUT)
 STAGE_KERNEL(k_conv_bwd, ST_CONV_BWD)
 STAGE_KERNEL(k_conv_wgrad, ST_CONV_WGRAD)
 STAGE_KERNEL(k_conv_epi, ST_CONV_EPI)

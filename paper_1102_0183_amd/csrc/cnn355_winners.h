@@ -257,59 +257,78 @@ __device__ void conv_bwd_wepi_item(const LayerDev& L, const LayerDev& Lp, const 
   const int Mi = L.Mi, Wi = L.Wi, P = L.Hi * Wi;
   const int c = item / st.n_tiles, p0 = (item - c * st.n_tiles) * PB, np = min(PB, P - p0);
   const int i0 = c * 64, n = min(64, Mi - i0);
-  // The terms of a pixel (its regions row by row, the slices of each) lie NG * R rows of Mi floats and less apart: a lane works out
-  // the row of a term.  Those of all the wavefront's pixels are in flight together: one pixel after the other, each region by
-  // itself, the loads of 23 x 23 pixels waited some five times (with the adjustment beside them 19.5 us, 16.9 so).
-  constexpr int PU = 64 / WAVES, TU = 16, TB = 4;   // pixels of a wavefront, terms of one of them in flight, terms under one branch
-  const float by_KS = 1.f / KS;                     // (quotients of whole numbers below 2^16, taken half a step off: exact)
-  float s[PU];
-  int first[PU], terms[PU], across[PU], t_max = 0;
-#pragma unroll
-  for (int u = 0; u < PU; ++u) {
-    const int q = wave + u * WAVES, p = p0 + min(q, np - 1), y = p / Wi, x = p - y * Wi;
-    const int wy_lo = max(0, (y - RH + KP) / KP), wy_hi = min(L.Hp - 1, y / KP);   // (y - RH + 1 rounded up; y - RH + KP >= 0 or the maximum takes 0)
-    const int gx_lo = max(0, (x - RW + KP * NW) / (KP * NW));
-    int gx_hi = min(GX - 1, x / (KP * NW));
-    if (gx_hi == GX - 1 && x - gx_hi * KP * NW >= (Wp - gx_hi * NW) * KP + K - 1) --gx_hi;   // (the last group may be short)
-    s[u] = 0.f;
-    across[u] = max(0, gx_hi - gx_lo + 1);   // (two at most: a group is at least K - 1 pixels wide)
-    terms[u] = q < np ? across[u] * max(0, wy_hi - wy_lo + 1) * KS : 0;
-    first[u] = (wy_lo * GX + gx_lo) * R + (y - wy_lo * KP) * RW + x - gx_lo * KP * NW;
-    t_max = max(t_max, terms[u]);
-  }
-  const gfloat* src = L.mm_part + i0 + min(lane, n - 1);
-  for (int b = 0; b < t_max; b += 64) {
-    int row[PU];
-    const int reg = (int)((b + lane + 0.5f) * by_KS), k = b + lane - reg * KS;
+  if (PB <= WAVES) {   // a pixel a wavefront: its regions one by one, in the fewest instructions (300C3 on 10 x 10: with the
+                       // adjustment 9.9 us, 13.5 in the form below, whose code takes longer to come than the loads it saves)
+    if (wave < np) {
+      const int y = (p0 + wave) / Wi, x = (p0 + wave) - y * Wi;
+      const int wy_lo = max(0, (y - RH + KP) / KP), wy_hi = min(L.Hp - 1, y / KP);   // (y - RH + 1 rounded up; y - RH + KP >= 0 or the maximum takes 0)
+      const int gx_lo = max(0, (x - RW + KP * NW) / (KP * NW)), gx_hi = min(GX - 1, x / (KP * NW));
+      float s = 0.f;
+      for (int wy = wy_lo; wy <= wy_hi; ++wy)
+        for (int gx = gx_lo; gx <= gx_hi; ++gx) {
+          const int col = x - gx * KP * NW;
+          if (col >= min(NW, Wp - gx * NW) * KP + K - 1) continue;
+          const gfloat* src = L.mm_part + ((size_t)(wy * GX + gx) * R + (y - wy * KP) * RW + col) * Mi + i0 + min(lane, n - 1);
+#pragma unroll 8
+          for (int k = 0; k < KS; ++k) s += src[(size_t)k * NG * R * Mi];
+        }
+      lds[wave * 65 + lane] = s;
+    }
+  } else {
+    // The terms of a pixel (its regions row by row, the slices of each) lie NG * R rows of Mi floats and less apart: a lane works out
+    // the row of a term.  Those of all the wavefront's pixels are in flight together: one pixel after the other, each region by
+    // itself, the loads of 23 x 23 pixels waited some five times (with the adjustment beside them 19.5 us, 16.9 so).
+    constexpr int PU = 64 / WAVES, TU = 16, TB = 4;   // pixels of a wavefront, terms of one of them in flight, terms under one branch
+    const float by_KS = 1.f / KS;                     // (quotients of whole numbers below 2^16, taken half a step off: exact)
+    float s[PU];
+    int first[PU], terms[PU], across[PU], t_max = 0;
 #pragma unroll
     for (int u = 0; u < PU; ++u) {
-      const int wy = across[u] == 2 ? reg >> 1 : reg, gx = across[u] == 2 ? reg & 1 : 0;
-      row[u] = first[u] + wy * (GX * R - KP * RW) + gx * (R - KP * NW) + k * NG * R;
+      const int q = wave + u * WAVES, p = p0 + min(q, np - 1), y = p / Wi, x = p - y * Wi;
+      const int wy_lo = max(0, (y - RH + KP) / KP), wy_hi = min(L.Hp - 1, y / KP);  
+      const int gx_lo = max(0, (x - RW + KP * NW) / (KP * NW));
+      int gx_hi = min(GX - 1, x / (KP * NW));
+      if (gx_hi == GX - 1 && x - gx_hi * KP * NW >= (Wp - gx_hi * NW) * KP + K - 1) --gx_hi;   // (the last group may be short)
+      s[u] = 0.f;
+      across[u] = max(0, gx_hi - gx_lo + 1);   // (two at most: a group is at least K - 1 pixels wide)
+      terms[u] = q < np ? across[u] * max(0, wy_hi - wy_lo + 1) * KS : 0;
+      first[u] = (wy_lo * GX + gx_lo) * R + (y - wy_lo * KP) * RW + x - gx_lo * KP * NW;
+      t_max = max(t_max, terms[u]);
     }
-    for (int t0 = 0; t0 < 64 && b + t0 < t_max; t0 += TU) {
-      float v[PU][TU];
+    const gfloat* src = L.mm_part + i0 + min(lane, n - 1);
+    for (int b = 0; b < t_max; b += 64) {
+      int row[PU];
+      const int reg = (int)((b + lane + 0.5f) * by_KS), k = b + lane - reg * KS;
 #pragma unroll
-      for (int u = 0; u < PU; ++u)
+      for (int u = 0; u < PU; ++u) {
+        const int wy = across[u] == 2 ? reg >> 1 : reg, gx = across[u] == 2 ? reg & 1 : 0;
+        row[u] = first[u] + wy * (GX * R - KP * RW) + gx * (R - KP * NW) + k * NG * R;
+      }
+      for (int t0 = 0; t0 < 64 && b + t0 < t_max; t0 += TU) {
+        float v[PU][TU];
 #pragma unroll
-        for (int t = 0; t < TU; t += TB)
-          if (b + t0 + t < terms[u]) {
+        for (int u = 0; u < PU; ++u)
 #pragma unroll
-            for (int c = t; c < t + TB; ++c)
-              v[u][c] = src[(size_t)__builtin_amdgcn_readlane(row[u], min(t0 + c, terms[u] - 1 - b)) * Mi];
-          }
+          for (int t = 0; t < TU; t += TB)
+            if (b + t0 + t < terms[u]) {
 #pragma unroll
-      for (int u = 0; u < PU; ++u)
+              for (int c = t; c < t + TB; ++c)
+                v[u][c] = src[(size_t)__builtin_amdgcn_readlane(row[u], min(t0 + c, terms[u] - 1 - b)) * Mi];
+            }
 #pragma unroll
-        for (int t = 0; t < TU; t += TB)
-          if (b + t0 + t < terms[u]) {
+        for (int u = 0; u < PU; ++u)
 #pragma unroll
-            for (int c = t; c < t + TB; ++c) s[u] += b + t0 + c < terms[u] ? v[u][c] : 0.f;
-          }
+          for (int t = 0; t < TU; t += TB)
+            if (b + t0 + t < terms[u]) {
+#pragma unroll
+              for (int c = t; c < t + TB; ++c) s[u] += b + t0 + c < terms[u] ? v[u][c] : 0.f;
+            }
+      }
     }
+#pragma unroll
+    for (int u = 0; u < PU; ++u)
+      if (wave + u * WAVES < np) lds[(wave + u * WAVES) * 65 + lane] = s[u];
   }
-#pragma unroll
-  for (int u = 0; u < PU; ++u)
-    if (wave + u * WAVES < np) lds[(wave + u * WAVES) * 65 + lane] = s[u];
   __syncthreads();
   for (int m = wave; m < n; m += WAVES)
     if (lane < np) {

@@ -1068,6 +1068,27 @@ int rebuild(cnn* net) {
   return upload(net);
 }
 
+// Plan for another mode and hand the stage list to the device where it is another one (else nothing is waited for, as long
+// as no graph of launches is kept); weights, tables and everything else there stay.  A plan that fails leaves the handle as it was.
+int replan(cnn* net, int mode) {
+  const int old_mode = net->mode;
+  const ProgramDev before = net->prog;
+  net->mode = mode;
+  const int rc = plan(net);
+  if (rc) {
+    const std::string why = net->err;
+    net->mode = old_mode;
+    (void)plan(net);
+    net->err = why;
+    return rc;
+  }
+  if (std::memcmp(&before, &net->prog, sizeof before) == 0) return CNN_OK;
+  HIP_TRY(net, hipStreamSynchronize(net->stream));
+  HIP_TRY(net, hipMemcpy(net->d_prog, &net->prog, sizeof(ProgramDev), hipMemcpyHostToDevice));
+  HIP_TRY(net, hipMemcpy(net->d_flow_ptrs, &net->flow_ptrs, sizeof(FlowPtrs), hipMemcpyHostToDevice));
+  return CNN_OK;
+}
+
 int check_status(cnn* net) {
   StatusDev s;
   HIP_TRY(net, hipMemcpy(&s, net->d_status, sizeof(s), hipMemcpyDeviceToHost));
@@ -1240,9 +1261,15 @@ int run(cnn* net, const RunArgs& a0) {
     return CNN_OK;
   }
   if (net->mode == CNN_MODE_PERSISTENT) {
-    HIP_TRY(net, launch_reset_status(net->stream, net->d_status, 0));
     bool mm = false;
-    for (int s = 0; s < P.n_stages; ++s) mm = mm || P.stages[s].kind >= ST_CONV_FWD_MFMA;
+    for (int s = 0; s < P.n_stages; ++s) {
+      const int kind = P.stages[s].kind;
+      const bool matrix = kind == ST_CONV_FWD_MFMA || kind == ST_CONV_EPI;
+      // (the kernel would pass over a stage it does not hold)
+      if (kind > ST_CONV_WGRAD && !matrix) return fail(&net->err, CNN_E_STATE, "internal: stage " + std::to_string(s) + " is not in the persistent kernel");
+      mm = mm || matrix;
+    }
+    HIP_TRY(net, launch_reset_status(net->stream, net->d_status, 0));
     HIP_TRY(net, launch_persistent(persistent_grid(net, a.train), mm, net->stream, net->d_prog, net->d_status, a));
     return CNN_OK;
   }
@@ -1756,20 +1783,9 @@ int cnn_set_mode(cnn_t* net, int mode) {
     return fail(&net->err, CNN_E_ARG, "unknown mode");
   if (mode != CNN_MODE_STAGES && !net->coop_ok) return fail(&net->err, CNN_E_STATE, "device does not support cooperative launches");
   if (mode == CNN_MODE_RESIDENT && !net->flow_ok) return fail(&net->err, CNN_E_STATE, net->flow_why);
-  const bool replan = (mode == CNN_MODE_STAGES) != (net->mode == CNN_MODE_STAGES);
-  if (replan) HIP_TRY(net, hipStreamSynchronize(net->stream));
-  const int old_mode = net->mode;
-  net->mode = mode;
-  if (replan) {
-    // the stage-launch mode pulls the deltas of wide layers on the matrix cores, the other modes do
-    // not: the stage list differs; weights, tables and everything else on the device stay
-    int rc = plan(net);
-    if (rc) { net->mode = old_mode; return rc; }
-    net->mode = mode;
-    HIP_TRY(net, hipMemcpy(net->d_prog, &net->prog, sizeof(ProgramDev), hipMemcpyHostToDevice));
-      HIP_TRY(net, hipMemcpy(net->d_flow_ptrs, &net->flow_ptrs, sizeof(FlowPtrs), hipMemcpyHostToDevice));
-  }
-  return CNN_OK;
+  // every mode has a stage list of its own: the pull and the gradients over the winners and the matrix-core pull are
+  // planned for the stage launches only, the first layer's matrix-core product for all but the persistent kernel
+  return mode == net->mode ? CNN_OK : replan(net, mode);
 }
 
 int cnn_mode_supported(cnn_t* net, int mode) {
@@ -2038,8 +2054,9 @@ int cnn_set_team(cnn_t* net, int n_ranks, int xcd_stride) {
   if (net->d_flow_ptrs)
     HIP_TRY(net, hipMemcpy(net->d_flow_ptrs, &net->flow_ptrs, sizeof(FlowPtrs), hipMemcpyHostToDevice));
   if (net->mode == CNN_MODE_RESIDENT && !net->flow_ok) {
-    net->mode = CNN_MODE_PERSISTENT;
-    return fail(&net->err, CNN_E_STATE, net->flow_why);
+    const std::string why = net->flow_why;
+    const int rc = replan(net, CNN_MODE_PERSISTENT);
+    return rc ? rc : fail(&net->err, CNN_E_STATE, why);
   }
   return CNN_OK;
 }

@@ -584,7 +584,7 @@ int check_plan(cnn* net) {
         if (L.rect || !L.full_table || !mfma_wgrad_shape_ok(L.Mi, L.K, L.Mo, L.Hi, L.Wi, L.Ho, L.Wo)) return bad(s, "layer not fit for the matrix-core gradient");
         if (st.chunk < 1 || (long long)st.chunk * L.Hi * L.Wi + 32LL * WP + Pn > LDS_FLOATS) return bad(s, "chunk exceeds LDS");
         if (NT > 4 * waves) return bad(s, "too many column tiles");
-        if (KW * NT * 1024 > LDS_FLOATS) return bad(s, "k splits do not fit LDS");
+        if (KW > 1 && KW * NT * 1024 > LDS_FLOATS) return bad(s, "k splits do not fit LDS");
         if (st.n_tiles * st.chunk < L.Mi || (st.n_tiles - 1) * st.chunk >= L.Mi || st.n_items != ((L.Mo + 31) / 32) * st.n_tiles) return bad(s, "chunks do not cover the input maps");
         break;
       }

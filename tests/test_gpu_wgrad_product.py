@@ -14,6 +14,7 @@ CASES = [
     ("1x12x12-130C3-257C3-MP4-9N-3N", "one map over; a column tile not filled"),
     ("1x9x9-300C3-300C4-MP2-9N-3N", "four winners a map"),
     ("2x9x9-700C4-1900C2-MP5-8N-3N", "several column tiles a wavefront"),
+    ("1x24x24-518C1-MP2-518C5-MP4-10N-3N", "41 column tiles"),
 ]
 
 

@@ -1,0 +1,58 @@
+"""Host logic of the stage planner (no GPU): networks of wide layers -- up to 600 maps, kernels up to 7 x 7 -- are all
+planned, and the work items of every stage cover their layer."""
+import random
+import re
+
+import pytest
+
+from paper_1102_0183_amd import binding
+
+
+def random_wide_arch(rng):
+    h = rng.randint(8, 60)
+    w = h if rng.random() < 0.6 else rng.randint(8, 60)
+    s = "%dx%dx%d" % (rng.randint(1, 4), h, w)
+    for _ in range(rng.randint(1, 4)):
+        k, skip = rng.randint(1, min(7, h, w)), rng.choice([0, 0, 0, 1, 2])
+        h, w = (h - k) // (skip + 1) + 1, (w - k) // (skip + 1) + 1
+        s += "-%dC%d%s" % (round(2 * 300 ** rng.random()), k, "S%d" % skip if skip else "")
+        if rng.random() < 0.7:
+            pool = rng.choice([q for q in range(1, 8) if h % q == 0 and w % q == 0])
+            s += "-MP%d" % pool
+            h, w = h // pool, w // pool
+        if min(h, w) < 2:
+            break
+    return s + "".join("-%dN" % rng.randint(2, 500) for _ in range(rng.randint(0, 2))) + "-%dN" % rng.randint(2, 10)
+
+
+def stages(arch):
+    out = []
+    for line in binding.plan_text(arch).splitlines():
+        name = line.split()[1]
+        out.append((name, {k: int(v) for k, v in re.findall(r"(\w+)=(-?\d+)", line)}))
+    return out
+
+
+def check(arch):
+    layers = [i for i in binding.arch_info(arch) if i["kind"] != binding.LAYER_POOL]
+    for name, f in stages(arch):
+        if name == "conv_wgrad_mfma":
+            below, layer = layers[f["layer"]], layers[f["layer"] + 1]
+            assert (f["tiles"] - 1) * f["chunk"] < below["maps"] <= f["tiles"] * f["chunk"], (arch, f)
+            assert f["items"] == -(-layer["maps"] // 32) * f["tiles"], (arch, f)
+            # column tiles of 32 weights, four to a wavefront at most
+            assert -(-min(f["chunk"], below["maps"]) * layer["K"] ** 2 // 32) <= 64, (arch, f)
+
+
+@pytest.mark.parametrize("arch", ["1x28x28-431C6-274C7-500N-3N", "1x24x24-518C1-MP2-518C5-MP4-10N-3N",
+                                  "1x43x43-389C6-MP2-427C6-10N-10N"])
+def test_gradient_products_of_more_than_35_column_tiles_are_planned(arch):
+    check(arch)
+    K = binding.arch_info(arch)[3 if "MP2" in arch else 2]["K"]
+    assert any(n == "conv_wgrad_mfma" and f["chunk"] * K * K > 35 * 32 for n, f in stages(arch)), arch
+
+
+def test_random_wide_architectures_are_planned():
+    rng = random.Random(1102)
+    for _ in range(4000):
+        check(random_wide_arch(rng))

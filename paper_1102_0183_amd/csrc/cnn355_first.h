@@ -24,7 +24,7 @@ __device__ void conv_fwd_mx_item(const LayerDev& L, const Stage& st, int item, c
   const int j0 = jt * FIRST_MAPS;
   const int K = L.K, KK = K * K, Kd = L.Mi * KK, Mo = L.Mo, Wi = L.Wi, Wo = L.Wo, stride = L.S + 1, Kp = L.Kp;
   const int y0 = band * st.tile_rows, rows = min(st.tile_rows, L.Ho - y0), P = rows * Wo;
-  const int in_rows = (rows - 1) * stride + K, map_sz = in_rows * Wi, Kd4 = (Kd + 3) & ~3;
+  const int in_rows = (rows - 1) * stride + K, map_sz = in_rows * Wi, Kd4 = (Kd + 3) & ~3, Kd1 = Kd & ~3;
   const int WP = first_pitch(Kd), PP = P | 1;
 
   float* lds_w = lds;                          // [32][WP] filters, zero from Kd on
@@ -57,7 +57,11 @@ __device__ void conv_fwd_mx_item(const LayerDev& L, const Stage& st, int item, c
     const float* wa = lds_w + (half * 16 + lr) * WP + lk;
     v4acc acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 6
-    for (int k = 0; k < Kd4; k += 4) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[k], xb[koff[k + lk]], acc, 0, 0, 0);
+    for (int k = 0; k < Kd1; k += 4) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[k], xb[koff[k + lk]], acc, 0, 0, 0);
+    if (Kd1 < Kd4) {   // the last taps, filled up with zeros on both sides (an infinite pixel times a weight of zero is no zero)
+      const float x = xb[koff[Kd1 + lk]];
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[Kd1], Kd1 + lk < Kd ? x : 0.f, acc, 0, 0, 0);
+    }
     if (p < P) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) lds_pre[(half * 16 + lk * 4 + v) * PP + p] = acc[v];

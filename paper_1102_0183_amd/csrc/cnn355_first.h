@@ -116,7 +116,7 @@ __host__ __device__ constexpr int first_map_pitch(int Hi, int Wi, int K) {
 // up to 64 winners (deltas and places in the lanes of d and off): a read and a multiply-add per winner and group of 64 weights
 template <int G>
 __device__ __forceinline__ void first_groups(const float* in, float d, int off, int nq, const int (&at)[3], float (&acc)[3][2]) {
-  constexpr int B = G == 1 ? 8 : 4;   // winners whose reads are in flight together (those past the end have a delta of zero)
+  constexpr int B = G == 1 ? 8 : 4;   // winners whose reads are in flight together (past the end: the last one with a delta of zero)
   for (int q = 0; q < nq; q += B) {
     float v[B][G];
 #pragma unroll
@@ -206,8 +206,8 @@ __device__ void conv_wgrad_first_item(const LayerDev& L, const Stage& st, int it
     const int* of = lds_off + jl * HW;
     for (int q0 = q_lo; q0 < q_hi; q0 += 64) {
       const int nq = min(64, q_hi - q0);
-      const float d = lane < nq ? dl[q0 + lane] : 0.f;   // (past the end: a delta of zero at the first field)
-      const int off = lane < nq ? of[q0 + lane] : 0;
+      const float d = lane < nq ? dl[q0 + lane] : 0.f;   // (past the end: a delta of zero at the field of the last winner, which is read anyway)
+      const int off = of[q0 + min(lane, nq - 1)];
       dsum += d;
       switch (G) {   // (a loop for every number of groups: a branch a group would wait for every read by itself)
         case 1: first_groups<1>(lds_in, d, off, nq, at, acc); break;

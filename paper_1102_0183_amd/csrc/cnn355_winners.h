@@ -164,8 +164,8 @@ __device__ void conv_wgrad_win(const LayerDev& L, const Stage& st, int item, con
   for (int q0 = q_lo; q0 < (on ? q_hi : 0); q0 += 64) {
     const int nq = min(64, q_hi - q0);
     float d = dq;
-    int off = ((yx >> 16) * Wi + (yx & 0xffff)) * stride * WIN_PITCH;
-    if (lane >= nq) { d = 0.f; off = 0; }   // (winners past the end: a delta of zero at pixel 0)
+    const int off = ((yx >> 16) * Wi + (yx & 0xffff)) * stride * WIN_PITCH;
+    if (lane >= nq) d = 0.f;   // (past the end: a delta of zero at the field of a later winner of the map, or its last one)
     const size_t o = (size_t)j * HW + min(q0 + 64 + lane, HW - 1);   // the next block of winners
     dq = L.delta[o];
     yx = L.argyx[o];

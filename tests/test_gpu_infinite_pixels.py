@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_1102_0183_amd import binding
-from tests.parity_helpers import TOL_ACT, build_pair, rel_err, to_dev
+from tests.parity_helpers import TOL_ACT, build_pair, layer_bounds, rel_err, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -28,4 +28,35 @@ def test_an_infinite_pixel_saturates_the_units_above_it(arch, stage, sign):
     for l in range(1, o.num_layers):
         assert np.isfinite(o.activation(l)).all() and rel_err(g.activation(l), o.activation(l)) <= TOL_ACT, l
     assert np.abs(probs.cpu().numpy() - np.asarray(want).ravel()).max() <= TOL_ACT
+    g.close()
+
+
+@pytest.mark.parametrize("arch,stage", [("3x29x29-96C5-MP5-10N-3N", "conv_wgrad_first"),    # 64 weights and 11 more, 25 winners
+                                        ("2x22x30-65C7-MP4-10N-3N", "conv_wgrad_first"),    # 64 and 34, 24 winners
+                                        ("33x16x16-130C3-MP2-10N-3N", "conv_wgrad_win")])   # 49 winners in shares of eight
+def test_an_infinite_pixel_reaches_the_gradients_of_the_winners_that_see_it(arch, stage):
+    """The corner is seen by the first field alone: maps whose first winner is elsewhere keep all their gradients."""
+    print("case", arch, flush=True)
+    g, o = build_pair(arch=arch, seed=len(arch))
+    g.set_mode(binding.MODE_STAGES)
+    assert any(stage in line and "layer=0 " in line for line in g.plan_text().splitlines())
+    info = o.layer_info(0)
+    rng = np.random.default_rng(2)
+    img = (rng.random((info["maps"], info["h"], info["w"]), dtype=np.float32) * 2 - 1).astype(np.float32)
+    img[0, 0, 0] = np.inf
+    grad = g.debug_gradients(to_dev(img).view(-1), 1)
+    want, _ = o.gradients(img, 1)
+    # (the oracle's sums run over all pixels: its weights of the corner are zero times infinity in every map)
+    layer, skip = o.layer_info(1), o.layer_info(1)["S"] + 1
+    corner = layer_bounds(o)[0][0] + layer["maps"] + np.arange(layer["maps"]) * info["maps"] * layer["K"] * layer["Kx"]
+    assert np.isnan(want[corner]).all() and np.isfinite(np.delete(want, corner)).all()
+    Kp, delta, winner = o.layer_info(2)["K"], o.delta(1), o.argmax(2)
+    with np.errstate(invalid="ignore"):
+        for j in range(layer["maps"]):
+            want[corner[j]] = sum(delta[j, y * Kp + w // Kp, x * Kp + w % Kp] * img[0, (y * Kp + w // Kp) * skip, (x * Kp + w % Kp) * skip].astype(np.float64)
+                                  for (y, x), w in np.ndenumerate(winner[j]))
+    finite = np.isfinite(want)
+    assert 0.2 < np.mean(finite[corner]) < 0.8      # (a winner in the corner has a delta of 0, times infinity)
+    np.testing.assert_array_equal(np.isfinite(grad), finite)
+    assert rel_err(grad[finite], want[finite]) <= TOL_ACT
     g.close()

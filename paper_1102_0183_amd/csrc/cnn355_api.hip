@@ -193,12 +193,16 @@ bool mfma_bwd_shape_ok(int Mi, int K, int S, int Mo, int Hi, int Wi) {
   const long long Kd = (long long)Mo * K * K, P = (long long)Hi * Wi;
   return S == 0 && Mi >= 32 && Kd >= 256 && P >= 16 && P <= MAX_TILE_PIX && (P + 31) / 32 <= (WG / 64) * 4;
 }
-// Maps of a chunk of such a product's slice of `per` maps: half of the slice, so that the second half is fetched behind the
-// first one's arithmetic, as far as half of LDS goes (0: not even one).
-int mfma_chunk(int per, int KK, int map) {
+// Buffers in LDS of such a product (cnn355_dev.h) over pixels P, and the maps of a chunk of its slice of `per` maps: with two
+// buffers half of the slice, so that the second half is fetched behind the first one's arithmetic, as far as they go (0: not
+// even one).
+int mfma_buffers(int mode, int P, int KK, int map) {
+  return mode != CNN_MODE_PERSISTENT && P <= MFMA_ONE_TILE && mfma_chunk_fits(1, KK, map, 2) ? 2 : 1;
+}
+int mfma_chunk(int per, int KK, int map, int buffers) {
   // (a short slice in one: its arithmetic would not cover a second fetch)
-  int ic = (long long)per * (map + 32 * KK) <= 8192 ? per : (per + 1) / 2;
-  while (ic > 0 && !mfma_chunk_fits(ic, KK, map)) --ic;
+  int ic = buffers == 1 || (long long)per * (map + 32 * KK) <= 8192 ? per : (per + 1) / 2;
+  while (ic > 0 && !mfma_chunk_fits(ic, KK, map, buffers)) --ic;
   return ic;
 }
 // Weight gradients of such a layer as a matrix product over the output pixels: rows = output maps,
@@ -557,7 +561,7 @@ int check_plan(cnn* net) {
         const int KK = L.K * L.K, HiWi = L.Hi * L.Wi, Pn = L.Ho * L.Wo;
         const int NT = (Pn + 31) / 32, waves = WG / 64, KW = NT >= waves ? 1 : waves / NT;
         if (L.rect || !L.full_table || !mfma_shape_ok(L.Mi, L.K, L.Mo, L.Ho, L.Wo)) return bad(s, "layer not fit for the matrix-core kernel");
-        if (!mfma_chunk_fits(st.chunk, KK, HiWi)) return bad(s, "chunk exceeds LDS");
+        if (st.tile_rows != mfma_buffers(net->mode, Pn, KK, HiWi) || !mfma_chunk_fits(st.chunk, KK, HiWi, st.tile_rows)) return bad(s, "chunk exceeds LDS");
         if (st.n_tiles < 1 || st.n_tiles > L.Mi || st.n_items != ((L.Mo + 31) / 32) * st.n_tiles) return bad(s, "slices do not cover the input maps");
         if (st.rows_per_wg != st.n_tiles || st.rows_per_wg > MFMA_MAX_SLICES) return bad(s, "too many partial-sum planes");
         if (KW > 1 && (long long)KW * NT * 1024 > LDS_FLOATS) return bad(s, "k splits do not fit LDS");
@@ -569,7 +573,7 @@ int check_plan(cnn* net) {
         const int NT = (Pn + 31) / 32, waves = WG / 64, KW = NT >= waves ? 1 : waves / NT;
         if (net->mode != CNN_MODE_STAGES) return bad(s, "the matrix-core pull is planned for the stage-launch mode only");
         if (L.rect || !L.full_table || !mfma_bwd_shape_ok(L.Mi, L.K, L.S, L.Mo, L.Hi, L.Wi)) return bad(s, "layer not fit for the matrix-core pull");
-        if (!mfma_chunk_fits(st.chunk, KK, HWd)) return bad(s, "chunk exceeds LDS");
+        if (st.tile_rows != mfma_buffers(net->mode, Pn, KK, HWd) || !mfma_chunk_fits(st.chunk, KK, HWd, st.tile_rows)) return bad(s, "chunk exceeds LDS");
         if (st.n_tiles < 1 || st.n_tiles > L.Mo || st.n_items != ((L.Mi + 31) / 32) * st.n_tiles) return bad(s, "slices do not cover the output maps");
         if (st.rows_per_wg != st.n_tiles || st.rows_per_wg > MFMA_MAX_SLICES) return bad(s, "too many partial-sum planes");
         if (KW > 1 && (long long)KW * NT * 1024 > LDS_FLOATS) return bad(s, "k splits do not fit LDS");
@@ -746,7 +750,15 @@ int plan(cnn* net) {
     const bool wide = L.kind == L_CONV && net->use_mfma && !L.rect && L.full_table && mfma_shape_ok(L.Mi, L.K, L.Mo, L.Ho, L.Wo);
     if (wide && L.Hi * L.Wi + 33 * L.K * L.K + 2 > LDS_FLOATS - 64)
       return fail(&net->err, CNN_E_SHAPE, "an input map does not fit the LDS staging area of the matrix-core kernel");
-    if (wide && mfma_chunk_fits(1, L.K * L.K, L.Hi * L.Wi)) {   // (a larger map: the vector kernel, band by band)
+    // (a map or kernel of which half of LDS holds none, on few input maps: the product has nine work items at most, and the
+    // vector kernel one for every output map and band of rows.  Measured, us an image forward, product and vector kernel:
+    // 73C24S1 on one map of 46 x 102 (3 items) 59 and 38, 76C20S2 on three of 85 x 171 (9) 112 and 104, but 74C25S2 on four of
+    // 31 x 164 (12) 43 and 45, 247C21S2 on three of 121 x 121 (24) 154 and 206)
+    Stage by_band{};
+    std::string why;
+    const bool few = wide && !mfma_chunk_fits(1, L.K * L.K, L.Hi * L.Wi, 2) && (L.Mo + 31) / 32 * L.Mi <= 9 &&
+                     plan_conv_fwd(L, by_band, net->n_cu > 0 ? net->n_cu : 256, &why) == CNN_OK;
+    if (wide && !few) {
       // wide layer: implicit GEMM on the matrix cores, the contraction split over workgroups, then
       // a second stage that adds the partial sums and does what follows the sum
       const int n_cu = net->n_cu > 0 ? net->n_cu : 256;
@@ -758,8 +770,9 @@ int plan(cnn* net) {
       int KS = std::max(1, std::min({n_cu / RT, L.Mi, MFMA_MAX_SLICES}));
       const int per = (L.Mi + KS - 1) / KS;
       KS = (L.Mi + per - 1) / per;
-      const int IC = mfma_chunk(per, KK, HiWi);
+      const int buffers = mfma_buffers(net->mode, P, KK, HiWi), IC = mfma_chunk(per, KK, HiWi, buffers);
       Stage& s = add(ST_CONV_FWD_MFMA, l, RT * KS, 1, 0);
+      s.tile_rows = buffers;
       s.n_tiles = KS; s.chunk = IC; s.rows_per_wg = KS;
       // maps per work item of the second stage, side by side in its lanes: as many as leave every map its
       // lane groups (one per 8 planes, at most 4), and at least what brings the items down to one round of
@@ -899,9 +912,10 @@ int plan(cnn* net) {
           int KS = std::max(1, std::min({n_cu / RT, L.Mo, MFMA_MAX_SLICES}));
           const int per = (L.Mo + KS - 1) / KS;
           KS = (L.Mo + per - 1) / per;
-          const int IC = mfma_chunk(per, KK, HWd);
+          const int buffers = mfma_buffers(net->mode, L.Hi * L.Wi, KK, HWd), IC = mfma_chunk(per, KK, HWd, buffers);
           if (IC >= 1) {
             Stage& s = add(ST_CONV_BWD_MFMA, l, RT * KS, 1, 1);
+            s.tile_rows = buffers;
             s.n_tiles = KS; s.chunk = IC; s.rows_per_wg = KS;
             // input maps per work item of the second stage: up to two passes of the lanes over their pixels, but at
             // least 16 items (the weight adjustment that shares the interval leaves few compute units idle)

@@ -87,11 +87,15 @@ enum StageKind : int {
   ST_CONV_WGRAD_FIRST = 17, // weight gradients of such a layer over the pooling winners, the whole input in LDS
   ST_CONV_BWD_WEPI = 15,   // ... then: their sum, times the activation derivative of the layer below
 };
-// LDS of a matrix-core work item, in floats: the places of the taps, then two halves of staged maps and filter rows each
-constexpr int MFMA_KOFF = 544;                          // taps of a chunk, in eights, at most
-constexpr int MFMA_HALF = (LDS_FLOATS - MFMA_KOFF) / 2;  // maps and filter rows of a chunk at most
+// LDS of a matrix-core work item, in floats: the places of the taps, then one or two buffers of staged maps and filter rows
+// each.  Two of them, each with a chunk, where a wavefront has one pixel tile at most (Stage::tile_rows = 2); one, with all
+// the LDS there is, in the persistent kernel, for larger maps and for maps and kernels of which half of the LDS holds none.
+constexpr int MFMA_KOFF = 544;                          // taps of a chunk, in eights, at most (two buffers)
+constexpr int MFMA_HALF = (LDS_FLOATS - MFMA_KOFF) / 2;  // maps and filter rows of a chunk at most (two buffers)
+constexpr int MFMA_LDS = LDS_FLOATS + 512;              // one buffer (what the whole eights of taps and fours of pixels take)
+constexpr int MFMA_ONE_TILE = (WG / 64) * 32;           // pixels of a map of which every wavefront has one tile at most
 struct MfmaLds {
-  int koff, in, pitch, half;   // the table; the maps of a half; floats between filter rows; a half
+  int koff, in, pitch, half;   // the table; the maps of a buffer; floats between filter rows; a buffer
 };
 #if defined(__HIP__)
 __host__ __device__
@@ -101,8 +105,10 @@ constexpr MfmaLds mfma_lds(int IC, int KK, int HiWi) {
   const int taps = (IC * KK + 7) / 8 * 8, in = (IC * HiWi + 3) / 4 * 4, pitch = taps + 4;
   return MfmaLds{taps, in, pitch, in + 32 * pitch};
 }
-constexpr bool mfma_chunk_fits(int IC, int KK, int HiWi) {
-  return IC >= 1 && (long long)IC * KK <= MFMA_KOFF && (long long)IC * HiWi + 32LL * (IC * KK + 12) <= MFMA_HALF;
+constexpr bool mfma_chunk_fits(int IC, int KK, int HiWi, int buffers) {
+  if (IC < 1 || (long long)IC * (HiWi + KK) > MFMA_LDS) return false;
+  const MfmaLds Z = mfma_lds(IC, KK, HiWi);
+  return buffers == 2 ? Z.koff <= MFMA_KOFF && Z.half <= MFMA_HALF : Z.koff + Z.half <= MFMA_LDS;
 }
 constexpr int MFMA_MAX_SLICES = 64;  // partial-sum slices (splits of the contraction) per layer
 
@@ -113,7 +119,7 @@ struct Stage {
   int barrier_after;  // persistent mode: all workgroups must finish this stage before the next starts
   int train_only;     // skipped by forward-only calls
   // tiling parameters (meaning depends on kind)
-  int tile_rows;      // CONV_FWD: conv rows per tile (multiple of Kp)
+  int tile_rows;      // CONV_FWD: conv rows per tile (multiple of Kp); CONV_FWD_MFMA / CONV_BWD_MFMA: buffers in LDS
   int n_tiles;        // CONV_FWD / CONV_BWD: tiles per map; CONV_WGRAD: connection chunks per output map
   int chunk;          // maps staged per pass (CONV_FWD: input maps, CONV_BWD: output maps, CONV_WGRAD: input maps)
   int tw_log2;        // log2 of the lane group width used when staging one map; CONV_BWD: log2 of the pixel tile

@@ -321,8 +321,8 @@ __device__ void conv_fwd_item(const LayerDev& L, const Stage& st, int item,
 // p = output pixel: W is the layer's filter block as it lies in memory (row j holds Mi*K*K
 // contiguous floats), X is never formed: X[k][p] = in_i[(y(S+1)+ky) Wi + x(S+1)+kx] is the
 // sum of an offset that depends on k only and one that depends on p only.
-// Work item = (tile of 32 output maps, slice of the input maps).  The slice is cut into chunks of input maps: the
-// next one is on its way in registers while the present one, in the other half of LDS, is multiplied.  Each wavefront
+// Work item = (tile of 32 output maps, slice of the input maps).  The slice is cut into chunks of input maps: with two
+// buffers in LDS the next one is on its way in registers while the present one is multiplied.  Each wavefront
 // owns one (or several) tiles of 32 pixels, and when there are fewer pixel tiles than
 // wavefronts the spare ones split the chunk's k range.  v_mfma_f32_32x32x2_f32: lane l feeds
 // A[l%32][l/32] and B[l/32][l%32], two k per instruction, 16 accumulators per lane.  Filters and
@@ -349,8 +349,9 @@ __device__ __forceinline__ int mm_place(int k) { return (k & ~7) + ((k & 1) << 2
 //   g_i[r][c] = sum_j sum_{ky,kx} D_j[r + K-1-ky][c + K-1-kx] w_{j,i}[ky][kx]
 // has the same operand pattern in[koff(k) + pbase(p)] as FP; the weights are used as they lie
 // (the tap order is turned round in koff instead).  One plane of partial sums per work item.
-// OVERLAP: a whole chunk is on its way in registers (else it is staged a few words at a time between two chunks'
-// arithmetic: with four tiles a wavefront, and in the persistent kernel, there are no registers for it).
+// OVERLAP: a whole chunk is on its way in registers and two of them lie in LDS, where a wavefront has one pixel tile.  With
+// four of them, and in the persistent kernel, there are no registers for it: a chunk, in all of LDS, is staged between two
+// chunks' arithmetic.
 template <bool BWD, int TPW, bool OVERLAP>
 __device__ __forceinline__ void conv_mfma_tiles(const LayerDev& L, const Stage& st, int item, const gfloat* in, float* lds) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -407,7 +408,7 @@ __device__ __forceinline__ void conv_mfma_tiles(const LayerDev& L, const Stage& 
   // BWD: the filters w_{j,i} of output map j and the 32 input maps of this tile are one run of 32 KK floats (units of 64
   // lanes); the deltas go to their winners' places.
   // (rounds of loads in flight together: most of a chunk; a full half of LDS would be 5 and 18 of them)
-  constexpr int VI = OVERLAP && !BWD ? 3 : 1, VD = OVERLAP && BWD ? 4 : 1, VW = OVERLAP ? 8 : 4;
+  constexpr int VI = OVERLAP && !BWD ? 3 : 1, VD = BWD ? 4 : 1, VW = OVERLAP ? 8 : 4;
   v4w vi[VI];
   float vt = 0.f, vw[VW], vd[VD];
   int vyx[VD];
@@ -518,17 +519,27 @@ __device__ __forceinline__ void conv_mfma_tiles(const LayerDev& L, const Stage& 
   };
 
   float* half = lds + Z.koff;
-  float* other = half + Z.half;
-  fetch(i_lo);
-  if constexpr (BWD) {
-    clear(half, i_lo);
+  float* other = half + (OVERLAP ? Z.half : 0);
+  if constexpr (OVERLAP) {
+    fetch(i_lo);
+    if constexpr (BWD) {
+      clear(half, i_lo);
+      __syncthreads();
+    }
+    commit(half, i_lo);
     __syncthreads();
   }
-  commit(half, i_lo);
-  __syncthreads();
   for (int ic0 = i_lo; ic0 < i_hi; ic0 += IC) {
     const int kc = min(IC, i_hi - ic0) * KK;
-    const bool more = ic0 + IC < i_hi;
+    const bool more = OVERLAP && ic0 + IC < i_hi;
+    if constexpr (!OVERLAP) {
+      if constexpr (BWD) {
+        clear(half, ic0);
+        __syncthreads();
+      }
+      commit(half, ic0);
+      __syncthreads();
+    }
     if (more) {
       fetch(ic0 + IC);
       if constexpr (BWD) clear(other, ic0 + IC);
@@ -569,7 +580,7 @@ __device__ __forceinline__ void conv_mfma_tiles(const LayerDev& L, const Stage& 
       commit(other, ic0 + IC);
     }
     __syncthreads();
-    float* t = half; half = other; other = t;
+    if constexpr (OVERLAP) { float* t = half; half = other; other = t; }
   }
   // the k splits inside the workgroup are added here (through LDS, in a fixed order), so that one
   // work item leaves one plane of partial sums (streamed past the L2, whose dirty lines the end of a kernel waits
@@ -605,7 +616,6 @@ __device__ __forceinline__ void conv_mfma_tiles(const LayerDev& L, const Stage& 
     __syncthreads();
   }
 }
-__host__ __device__ __forceinline__ bool mfma_one_tile(int P) { return P <= (WG / 64) * 32; }   // a wavefront each
 
 // Second half of the matrix-core forward pass.  Work item = output map j: add the planes of
 // partial sums (lane groups share the planes, eight loads in flight per lane, fixed order), bias,
@@ -1474,7 +1484,7 @@ __device__ __forceinline__ void run_stage_items(const ProgramDev& P, const Stage
         const LayerDev& L = P.layers[st.layer];
         const gfloat* in = L.in_is_image ? ctx.image : L.in;
         for (int item = first; item < st.n_items; item += step) {
-          if (mfma_one_tile(L.Ho * L.Wo)) conv_mfma_tiles<false, 1, false>(L, st, item, in, lds);
+          if (L.Ho * L.Wo <= MFMA_ONE_TILE) conv_mfma_tiles<false, 1, false>(L, st, item, in, lds);
           else conv_mfma_tiles<false, MM_TPW, false>(L, st, item, in, lds);
         }
         return;
@@ -1529,7 +1539,7 @@ STAGE_KERNEL(k_conv_bwd_wepi, ST_CONV_BWD_WEPI)
 // (the tiles a wavefront has are of the kernel, not of the call: four tiles' accumulators would cost the others their registers)
 template <bool BWD, int TPW>
 __global__ void __launch_bounds__(WG) k_conv_mfma(const ProgramDev* __restrict__ P, int s, StatusDev* status, RunArgs a) {
-  __shared__ __align__(16) float lds[LDS_FLOATS];
+  __shared__ __align__(16) float lds[TPW == 1 ? LDS_FLOATS : MFMA_LDS];
   const Ctx ctx = make_ctx(*P, a, 0, status);
   const Stage& st = P->stages[s];
   if (st.train_only && !ctx.train) return;
@@ -1667,7 +1677,7 @@ __device__ bool xcd_barrier(StatusDev* status, unsigned int epoch, const BarCtx&
 template <bool MM>
 __global__ void __launch_bounds__(WG) k_persistent(const ProgramDev* __restrict__ P,
                                                    StatusDev* status, RunArgs a) {
-  __shared__ __align__(16) float lds[LDS_FLOATS];
+  __shared__ __align__(16) float lds[MM ? MFMA_LDS : LDS_FLOATS];
   __shared__ int s_ok;
   __shared__ BarCtx s_bc;
   unsigned int n_barriers = 0;
@@ -1731,10 +1741,10 @@ const void* stage_kernel(const Stage& st, const LayerDev& L, int* threads) {
     case ST_CONV_BWD: return (const void*)k_conv_bwd;
     case ST_CONV_WGRAD: return (const void*)k_conv_wgrad;
     case ST_CONV_FWD_MFMA:
-      return mfma_one_tile(L.Ho * L.Wo) ? (const void*)k_conv_mfma<false, 1> : (const void*)k_conv_mfma<false, MM_TPW>;
+      return st.tile_rows == 2 ? (const void*)k_conv_mfma<false, 1> : (const void*)k_conv_mfma<false, MM_TPW>;
     case ST_CONV_EPI: return (const void*)k_conv_epi;
     case ST_CONV_BWD_MFMA:
-      return mfma_one_tile(L.Hi * L.Wi) ? (const void*)k_conv_mfma<true, 1> : (const void*)k_conv_mfma<true, MM_TPW>;
+      return st.tile_rows == 2 ? (const void*)k_conv_mfma<true, 1> : (const void*)k_conv_mfma<true, MM_TPW>;
     case ST_CONV_BWD_EPI: return (const void*)k_conv_bwd_epi;
     case ST_CONV_WGRAD_MFMA: return (const void*)k_conv_wgrad_mfma;
     case ST_CONV_WGRAD_WIN: return (const void*)k_conv_wgrad_win;

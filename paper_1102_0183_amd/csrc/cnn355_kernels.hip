@@ -583,8 +583,13 @@ __device__ __forceinline__ void conv_mfma_tiles(const LayerDev& L, const Stage& 
     if constexpr (OVERLAP) { float* t = half; half = other; other = t; }
   }
   // the k splits inside the workgroup are added here (through LDS, in a fixed order), so that one
-  // work item leaves one plane of partial sums (streamed past the L2, whose dirty lines the end of a kernel waits
-  // for: 300C2 and 300C4 two thirds of a microsecond each)
+  // work item leaves one plane of partial sums (small maps: streamed past the L2, whose dirty lines the end of a kernel waits
+  // for, 300C2 and 300C4 two thirds of a microsecond each; larger ones, and those that the persistent kernel reads behind its own
+  // barrier, go through it: 96C3 on 36 x 36 59.8 us an image, 63.3 streamed, 79.2 and 83.8 in the persistent kernel)
+  auto store = [](gfloat* at, float v) {
+    if constexpr (OVERLAP) __builtin_nontemporal_store(v, at);
+    else *at = v;
+  };
   gfloat* plane = L.mm_part + (size_t)ks * Mo * P;
   if (KW > 1 && tw >= F && wave_on) {
     float* red = lds;  // [KW][tiles from F on][32 rows][32 pixels]
@@ -599,7 +604,7 @@ __device__ __forceinline__ void conv_mfma_tiles(const LayerDev& L, const Stage& 
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int j = j0 + (v >> 2) * 8 + lk * 4 + (v & 3);
-          if (p < P && j < Mo) __builtin_nontemporal_store(acc[t][v], &plane[(size_t)j * P + p]);
+          if (p < P && j < Mo) store(&plane[(size_t)j * P + p], acc[t][v]);
         }
       }
   }
@@ -611,7 +616,7 @@ __device__ __forceinline__ void conv_mfma_tiles(const LayerDev& L, const Stage& 
       float sum = 0.f;
       for (int q = 0; q < KW; ++q) sum += red[((q * (NT - F) + t) * 32 + row) * 32 + col];
       const int p = (F + t) * 32 + col, j = j0 + row;
-      if (p < P && j < Mo) __builtin_nontemporal_store(sum, &plane[(size_t)j * P + p]);
+      if (p < P && j < Mo) store(&plane[(size_t)j * P + p], sum);
     }
     __syncthreads();
   }

@@ -810,13 +810,26 @@ int plan(cnn* net) {
   // backward, top down.  The weights of a convolutional layer are adjusted one stage after the
   // deltas have been pulled through them; that adjustment shares a stage with the next pull.
   int pending_wgrad = -1;
-  auto add_wgrad = [&](int l, int barrier) {
+  const bool matrix_stages = net->use_mfma && net->mode == CNN_MODE_STAGES;
+  auto full = [&](const LayerDev& L) { return matrix_stages && !L.rect && L.full_table; };
+  auto win_wgrad = [&](const LayerDev& L) { return full(L) && win_wgrad_shape_ok(L.Mi, L.K, L.Hi, L.Wi, L.Kp, L.Hp * L.Wp); };
+  auto mfma_wgrad = [&](const LayerDev& L) { return full(L) && mfma_wgrad_shape_ok(L.Mi, L.K, L.Mo, L.Hi, L.Wi, L.Ho, L.Wo); };
+  auto win_bwd = [&](const LayerDev& L) { return full(L) && win_bwd_shape_ok(L.Mi, L.K, L.S, L.Kp, L.Mo, L.Hp * L.Wp); };
+  auto mfma_bwd = [&](const LayerDev& L) { return full(L) && mfma_bwd_shape_ok(L.Mi, L.K, L.S, L.Mo, L.Hi, L.Wi); };
+  // (shared: the stage that follows is one that the adjustment has a launch with)
+  auto add_wgrad = [&](int l, int barrier, bool shared) {
     LayerDev& L = P.layers[l];
     // compute units for one round of this stage's items next to those of the (short) stage launched with it
     const int n_cu_all = net->n_cu > 0 ? net->n_cu : 256;
     const bool after_epi = ns >= 1 && (P.stages[ns - 1].kind == ST_CONV_BWD_EPI || P.stages[ns - 1].kind == ST_CONV_BWD_WEPI);
     const int n_cu = after_epi ? std::max(n_cu_all / 2, n_cu_all - P.stages[ns - 1].n_items) : n_cu_all;
-    if (net->use_mfma && net->mode == CNN_MODE_STAGES && !L.rect && L.full_table && win_wgrad_shape_ok(L.Mi, L.K, L.Hi, L.Wi, L.Kp, L.Hp * L.Wp)) {
+    // The winners' kernel has a work item for 64 input maps and an output map: where that is half a round of the compute units or
+    // more, or the launch is another stage's as well.  Measured over 150 nets, an image's whole step against the kernels below:
+    // 0.75 to 1.00 of the time from 128 items on; fewer that share a launch 0.90 to 1.03 (5 x 5 filters beside the sums of a pull
+    // 0.98 to 1.06: not taken), with a launch of their own 1.00 to 1.03.
+    const bool after_wgrad = ns >= 1 && !P.stages[ns - 1].barrier_after && (P.stages[ns - 1].kind == ST_CONV_WGRAD || P.stages[ns - 1].kind == ST_CONV_WGRAD_WIN);
+    const bool win_pays = (L.Mi + 63) / 64 * L.Mo >= 128 || shared || after_wgrad || (after_epi && L.K <= 4);
+    if (win_wgrad(L) && win_pays) {
       // one work item per compute unit: 64 input maps, as many output maps as that leaves
       Stage& s = add(ST_CONV_WGRAD_WIN, l, 0, barrier, 1);
       s.n_tiles = (L.Mi + 63) / 64;
@@ -825,8 +838,7 @@ int plan(cnn* net) {
       s.n_items = s.n_tiles * ((L.Mo + s.chunk - 1) / s.chunk);
       return;
     }
-    if (net->use_mfma && net->mode == CNN_MODE_STAGES && !L.rect && L.full_table &&
-        mfma_wgrad_shape_ok(L.Mi, L.K, L.Mo, L.Hi, L.Wi, L.Ho, L.Wo)) {
+    if (mfma_wgrad(L)) {
       // wide layer, one launch per stage: the gradients as a matrix product over the output pixels.
       // Input maps per work item: about one work item per compute unit, whole column tiles of 32
       // where the kernel size allows, at most 64 column tiles, and what LDS holds.
@@ -846,7 +858,7 @@ int plan(cnn* net) {
       s.n_items = RT * s.n_tiles;
       return;
     }
-    if (net->use_mfma && net->mode == CNN_MODE_STAGES && conv_wgrad_first_ok(L, (L.Mo + n_cu - 1) / n_cu)) {
+    if (matrix_stages && conv_wgrad_first_ok(L, (L.Mo + n_cu - 1) / n_cu)) {
       Stage& s = add(ST_CONV_WGRAD_FIRST, l, 0, barrier, 1);
       s.chunk = (L.Mo + n_cu - 1) / n_cu;   // one round of the compute units
       s.n_items = (L.Mo + s.chunk - 1) / s.chunk;
@@ -876,8 +888,8 @@ int plan(cnn* net) {
       if (!L.in_is_image && l > 0) {
         // pull deltas into layer l-1 (reads the old weights of layer l) ...
         const bool with_pending = pending_wgrad >= 0;
-        if (with_pending) { add_wgrad(pending_wgrad, 0); pending_wgrad = -1; }
-        if (net->use_mfma && net->mode == CNN_MODE_STAGES && !L.rect && L.full_table && win_bwd_shape_ok(L.Mi, L.K, L.S, L.Kp, L.Mo, L.Hp * L.Wp)) {
+        if (with_pending) { add_wgrad(pending_wgrad, 0, !win_bwd(L) && !mfma_bwd(L)); pending_wgrad = -1; }
+        if (win_bwd(L)) {
           // wide layer, one launch per stage: the winners' terms only, a lane per input map; the contraction over the output maps
           // split so that there is about one work item per compute unit, as far as the scratch memory goes
           const int n_cu = net->n_cu > 0 ? net->n_cu : 256;
@@ -896,12 +908,11 @@ int plan(cnn* net) {
             e.chunk = std::min(64, std::max(16, Pin * MC / 64));
             e.n_tiles = (Pin + e.chunk - 1) / e.chunk;
             e.n_items = MC * e.n_tiles;
-            add_wgrad(l, 1);
+            add_wgrad(l, 1, false);
             continue;
           }
         }
-        if (net->use_mfma && net->mode == CNN_MODE_STAGES && !L.rect && L.full_table &&
-            mfma_bwd_shape_ok(L.Mi, L.K, L.S, L.Mo, L.Hi, L.Wi)) {
+        if (mfma_bwd(L)) {
           // wide layer, one launch per stage (the persistent kernel does not hold this stage kind:
           // its registers would slow every other stage): the pull as FP's mirror image on the matrix cores, the contraction over the
           // output maps split over workgroups; the second stage adds the partial sums -- the
@@ -924,7 +935,7 @@ int plan(cnn* net) {
             Stage& e = add(ST_CONV_BWD_EPI, l, (L.Mi + mpb - 1) / mpb, 0, 1);
             e.rows_per_wg = KS;
             e.chunk = mpb;
-            add_wgrad(l, 1);
+            add_wgrad(l, 1, false);
             continue;
           }
         }
@@ -943,12 +954,12 @@ int plan(cnn* net) {
         pending_wgrad = l;
       } else {
         // first trainable layer: nothing to pull; adjust it together with whatever is pending
-        if (pending_wgrad >= 0) { add_wgrad(pending_wgrad, 0); pending_wgrad = -1; }
-        add_wgrad(l, 1);
+        if (pending_wgrad >= 0) { add_wgrad(pending_wgrad, 0, win_wgrad(L) || !mfma_wgrad(L)); pending_wgrad = -1; }
+        add_wgrad(l, 1, false);
       }
     }
   }
-  if (pending_wgrad >= 0) { add_wgrad(pending_wgrad, 1); pending_wgrad = -1; }
+  if (pending_wgrad >= 0) { add_wgrad(pending_wgrad, 1, false); pending_wgrad = -1; }
   if (ns > 0) P.stages[ns - 1].barrier_after = 1;
   P.n_stages = ns;
 

@@ -33,11 +33,26 @@ def stages(arch):
     return out
 
 
+ADJUSTMENTS = ("conv_wgrad", "conv_wgrad_win", "conv_wgrad_first")
+
+
+def shares_a_launch(plan, s):
+    """With the sums of its layer's pull or an adjustment before it, or a vector pull or an adjustment behind it."""
+    before, after = plan[s - 1] if s else None, plan[s + 1] if s + 1 < len(plan) else None
+    return (before and not before[1]["barrier"] and before[0] in ADJUSTMENTS + ("conv_bwd_epi", "conv_bwd_wepi")) or \
+        (after and not plan[s][1]["barrier"] and after[0] in ADJUSTMENTS + ("conv_bwd",))
+
+
 def check(arch):
     layers = [i for i in binding.arch_info(arch) if i["kind"] != binding.LAYER_POOL]
-    for name, f in stages(arch):
+    plan = stages(arch)
+    for s, (name, f) in enumerate(plan):
+        below, layer = layers[f["layer"]], layers[f["layer"] + 1]
+        if name == "conv_wgrad_win":
+            assert f["items"] == -(-below["maps"] // 64) * -(-layer["maps"] // f["chunk"]), (arch, f)
+            # a work item for 64 input maps and an output map: half a round of them, or company
+            assert -(-below["maps"] // 64) * layer["maps"] >= 128 or shares_a_launch(plan, s), (arch, f)
         if name == "conv_wgrad_mfma":
-            below, layer = layers[f["layer"]], layers[f["layer"] + 1]
             assert (f["tiles"] - 1) * f["chunk"] < below["maps"] <= f["tiles"] * f["chunk"], (arch, f)
             assert f["items"] == -(-layer["maps"] // 32) * f["tiles"], (arch, f)
             # column tiles of 32 weights, four to a wavefront at most

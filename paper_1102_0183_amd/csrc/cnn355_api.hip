@@ -215,7 +215,8 @@ bool mfma_wgrad_shape_ok(int Mi, int K, int Mo, int Hi, int Wi, int Ho, int Wo) 
 }
 // A layer of many output maps on few input maps (the first layer): its product with activation and pooling in one stage
 // (cnn355_first.h), from two tiles of 32 maps on (k_conv_fwd has an item per map there: 126 maps of 8 x 8 7.3 us, 5.4 so;
-// 300 of 46 x 46 33.9, 9.4).  A contraction of 256 and more is cut into slices instead.  LDS floats of a work item of 32 maps
+// 300 of 46 x 46 33.9, 9.4) and up to eight input maps (measured over 23 nets with 9 to 24: 0.85 to 1.20 of the vector kernels'
+// whole step, mostly above).  A contraction of 256 and more is cut into slices instead.  LDS floats of a work item of 32 maps
 // and `rows` conv rows.
 long long conv_fwd_mx_floats(const LayerDev& L, int rows) {
   const int Kd = L.Mi * L.K * L.K, P = rows * L.Wo;
@@ -224,10 +225,28 @@ long long conv_fwd_mx_floats(const LayerDev& L, int rows) {
 bool conv_fwd_mx_ok(const LayerDev& L) {
   return !L.rect && L.full_table && L.Mo >= 64 && L.Mi <= 8 && L.Mi * L.K * L.K < 256 && conv_fwd_mx_floats(L, L.Kp) <= LDS_FLOATS;
 }
-// Its gradients: the whole input and the winners of JG output maps in LDS, at least a wavefront a map.
+// Conv rows of a work item's band: the fewest that leave one round of the compute units, as far as LDS goes; 0 where the vector
+// kernel stays the better one.  That has all maps in one round up to a map per compute unit, while a wavefront of this one
+// walks the whole contraction alone, and a lane a whole pooling window: with few items and many taps, or large windows on small
+// maps, that is the longer way.  Measured over 280 nets, forward call, what the vector kernel takes longer: 83C6 on seven maps
+// of 8 x 8 (9 items, 252 taps) -2.2 us, 69C5 on six of 18 x 18 (21 items, 150) -0.5, 87C5 on five of 22 x 22 (27, 125) +0.2, 211C7 on
+// two of 51 x 51 (105, 98) +17; over 5 x 5 windows 191C3 with 20 x 20 pixels -1.5, 157C3 with 35 x 35 +5; over 7 x 7 ones 251C5 with 28 x 28
+// -5.5, 129C7 with 42 x 42 +6.6; over 9 x 9 ones 203C6 with 18 x 18 -15, and with more maps than compute units 382C5 -3.
+int conv_fwd_mx_rows(const LayerDev& L, int n_cu) {
+  if (!conv_fwd_mx_ok(L)) return 0;
+  const int RT = (L.Mo + 31) / 32;
+  int rows = L.Kp;
+  while (RT * ((L.Ho + rows - 1) / rows) > n_cu && rows + L.Kp <= L.Ho && conv_fwd_mx_floats(L, rows + L.Kp) <= LDS_FLOATS) rows += L.Kp;
+  const int taps = L.Mi * L.K * L.K, items = RT * ((L.Ho + rows - 1) / rows), window = L.Kp * L.Kp;
+  if (L.Mo <= n_cu ? taps > 6 * items || (window > 16 && L.Mo * L.Ho * L.Wo < 4200 * window) : L.Mo <= 2 * n_cu && window > 64) return 0;
+  return rows;
+}
+// Its gradients: the whole input and the winners of JG output maps in LDS, at least a wavefront a map.  From two maps a work
+// item on, when the vector kernel takes two rounds of the compute units (42 such nets 0.9 to 3.9 us a step faster, 71 with a map an item 3.4
+// slower to 0.5 faster).
 bool conv_wgrad_first_ok(const LayerDev& L, int JG) {
   const long long RP = L.Wi + ((L.K - L.Wi) % 32 + 32) % 32, MP = L.Hi * RP + ((L.K * L.K - L.Hi * RP) % 32 + 32) % 32;
-  return conv_fwd_mx_ok(L) && JG >= 1 && JG <= WG / 64 && L.Mi * MP + 2LL * JG * L.Hp * L.Wp <= LDS_FLOATS;
+  return conv_fwd_mx_ok(L) && JG >= 2 && JG <= WG / 64 && L.Mi * MP + 2LL * JG * L.Hp * L.Wp <= LDS_FLOATS;
 }
 // The same over the pooling winners, a lane per input map (cnn355_winners.h).  64 input maps lie in LDS pixel by pixel;
 // below 32 input maps most lanes idle, below 9 winners a map the matrix product multiplies few zeros and stays (300C4 with
@@ -783,11 +802,8 @@ int plan(cnn* net) {
       Stage& e = add(ST_CONV_EPI, l, (L.Mo + mp - 1) / mp, 1, 0);
       e.rows_per_wg = KS;
       e.chunk = mp;
-    } else if (L.kind == L_CONV && net->use_mfma && net->mode != CNN_MODE_PERSISTENT && conv_fwd_mx_ok(L)) {
-      // the fewest rows a band that leave one round of the compute units, as far as LDS goes
-      const int n_cu = net->n_cu > 0 ? net->n_cu : 256, RT = (L.Mo + 31) / 32;
-      int rows = L.Kp;
-      while (RT * ((L.Ho + rows - 1) / rows) > n_cu && rows + L.Kp <= L.Ho && conv_fwd_mx_floats(L, rows + L.Kp) <= LDS_FLOATS) rows += L.Kp;
+    } else if (int rows; L.kind == L_CONV && net->use_mfma && net->mode != CNN_MODE_PERSISTENT && (rows = conv_fwd_mx_rows(L, net->n_cu > 0 ? net->n_cu : 256)) > 0) {
+      const int RT = (L.Mo + 31) / 32;
       Stage& s = add(ST_CONV_FWD_MX, l, 0, 1, 0);
       s.tile_rows = rows;
       s.n_tiles = (L.Ho + rows - 1) / rows;

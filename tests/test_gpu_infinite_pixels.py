@@ -31,9 +31,9 @@ def test_an_infinite_pixel_saturates_the_units_above_it(arch, stage, sign):
     g.close()
 
 
-@pytest.mark.parametrize("arch,stage", [("3x29x29-96C5-MP5-10N-3N", "conv_wgrad_first"),    # 64 weights and 11 more, 25 winners
-                                        ("2x22x30-65C7-MP4-10N-3N", "conv_wgrad_first"),    # 64 and 34, 24 winners
-                                        ("33x16x16-130C3-MP2-10N-3N", "conv_wgrad_win")])   # 49 winners in shares of eight
+@pytest.mark.parametrize("arch,stage", [("3x29x29-288C5-MP5-10N-3N", "conv_wgrad_first"),   # 64 weights and 11 more, 25 winners
+                                        ("2x22x30-259C7-MP4-10N-3N", "conv_wgrad_first"),   # 64 and 34, 24 winners
+                                        ("33x16x16-130C3-MP2-10N-3N", "conv_wgrad_win")])     # 49 winners in shares of eight
 def test_an_infinite_pixel_reaches_the_gradients_of_the_winners_that_see_it(arch, stage):
     """The corner is seen by the first field alone: maps whose first winner is elsewhere keep all their gradients."""
     print("case", arch, flush=True)

@@ -17,7 +17,7 @@ def _check(g, o, w0, mode):
     assert g.mode == mode
     plan = g.plan_text()
     assert ("conv_fwd_mx" in plan) == (mode != P), plan
-    assert ("conv_wgrad_first" in plan) == (mode == S), plan
+    assert ("conv_wgrad_win" in plan) == (mode == S), plan
     print("mode", mode, flush=True)
     rng = np.random.default_rng(4)
     imgs = (rng.random((5, 1, 18, 18), dtype=np.float32) * 2 - 1).astype(np.float32)

@@ -67,6 +67,17 @@ def test_gradient_products_of_more_than_35_column_tiles_are_planned(arch):
     assert any(n == "conv_wgrad_mfma" and f["chunk"] * K * K > 35 * 32 for n, f in stages(arch)), arch
 
 
+# few input maps: the vector kernels keep a layer whose product would be few items' long walks, and gradients of a map an item
+@pytest.mark.parametrize("arch,product,gradients", [
+    ("8x15x15-73C5S1-MP2-20N-5N", 0, 0), ("6x23x23-203C6-MP9-20N-5N", 0, 0), ("2x22x22-191C3-MP5-66N-8N", 0, 0),
+    ("9x14x14-100C3-MP3-20N-5N", 0, 0), ("7x22x22-382C5-MP9-20N-5N", 0, 1),
+    ("2x17x17-129C6-MP2-20N-5N", 1, 0), ("1x48x48-129C7-MP7-20N-5N", 1, 0), ("1x20x20-256C5-MP2-20N-5N", 1, 0),
+    ("1x20x20-257C5-MP2-20N-5N", 1, 1), ("3x32x32-300C3-MP2-300C2-MP2-300C4-MP2-300N-10N", 1, 1)])
+def test_which_kernels_take_a_layer_of_few_input_maps(arch, product, gradients):
+    first = [name for name, f in stages(arch) if f["layer"] == 0]
+    assert ("conv_fwd_mx" in first, "conv_wgrad_first" in first) == (bool(product), bool(gradients)), first
+
+
 def test_random_wide_architectures_are_planned():
     rng = random.Random(1102)
     for _ in range(4000):

@@ -78,6 +78,15 @@ def test_which_kernels_take_a_layer_of_few_input_maps(arch, product, gradients):
     assert ("conv_fwd_mx" in first, "conv_wgrad_first" in first) == (bool(product), bool(gradients)), first
 
 
+def test_adjustments_beside_a_pulls_sums_keep_short_lists_where_winners_are_many():
+    """Next to the sums of its layer's pull an adjustment has fewer compute units; its lists of connections stay as long as all of
+    them allow where a thread would else walk many more winners (1024 for 512 here), and get longer where it is a few."""
+    def of(arch):
+        return [f for name, f in stages(arch) if name == "conv_wgrad" and f["layer"] == 1][0]
+    assert of("3x123x123-36C7-MP3-48C8-MP1-21N-20N-2N")["chunk"] == 8     # 36 maps in 256 // 48 lists
+    assert of("1x45x41-105C2-MP1-13C5-MP2-20N-4N")["chunk"] == 8          # 105 maps in (256 - 64) // 13 lists
+
+
 def test_random_wide_architectures_are_planned():
     rng = random.Random(1102)
     for _ in range(4000):

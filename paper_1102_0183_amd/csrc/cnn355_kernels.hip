@@ -1763,11 +1763,22 @@ const void* stage_kernel(const Stage& st, const LayerDev& L, int* threads) {
 const void* stage_pair_kernel(int kind_a, int kind_b) {
 #define PAIR(KA, KB) if (kind_a == KA && kind_b == KB) return (const void*)k_pair<KA, KB>;
   // the sums of a pull and the adjustment of its layer; an adjustment and the vector pull, or the last adjustment, behind it
-#define PAIRS(KB) PAIR(ST_CONV_WGRAD, KB) PAIR(ST_CONV_WGRAD_WIN, KB) PAIR(ST_CONV_WGRAD_FIRST, KB)
-  PAIR(ST_CONV_BWD_EPI, ST_CONV_WGRAD) PAIR(ST_CONV_BWD_EPI, ST_CONV_WGRAD_MFMA) PAIR(ST_CONV_BWD_EPI, ST_CONV_WGRAD_WIN)
-  PAIR(ST_CONV_BWD_WEPI, ST_CONV_WGRAD) PAIR(ST_CONV_BWD_WEPI, ST_CONV_WGRAD_MFMA) PAIR(ST_CONV_BWD_WEPI, ST_CONV_WGRAD_WIN)
-  PAIRS(ST_CONV_BWD) PAIRS(ST_CONV_WGRAD) PAIRS(ST_CONV_WGRAD_WIN) PAIRS(ST_CONV_WGRAD_FIRST)
-#undef PAIRS
+  PAIR(ST_CONV_BWD_EPI, ST_CONV_WGRAD)
+  PAIR(ST_CONV_BWD_EPI, ST_CONV_WGRAD_MFMA)
+  PAIR(ST_CONV_BWD_EPI, ST_CONV_WGRAD_WIN)
+  PAIR(ST_CONV_BWD_WEPI, ST_CONV_WGRAD)
+  PAIR(ST_CONV_BWD_WEPI, ST_CONV_WGRAD_MFMA)
+  PAIR(ST_CONV_BWD_WEPI, ST_CONV_WGRAD_WIN)
+  PAIR(ST_CONV_WGRAD, ST_CONV_BWD)
+  PAIR(ST_CONV_WGRAD, ST_CONV_WGRAD)
+  PAIR(ST_CONV_WGRAD, ST_CONV_WGRAD_WIN)
+  PAIR(ST_CONV_WGRAD, ST_CONV_WGRAD_FIRST)
+  PAIR(ST_CONV_WGRAD_WIN, ST_CONV_BWD)
+  PAIR(ST_CONV_WGRAD_WIN, ST_CONV_WGRAD)
+  PAIR(ST_CONV_WGRAD_WIN, ST_CONV_WGRAD_WIN)
+  PAIR(ST_CONV_WGRAD_WIN, ST_CONV_WGRAD_FIRST)
+  PAIR(ST_CONV_WGRAD_FIRST, ST_CONV_BWD)
+  PAIR(ST_CONV_WGRAD_FIRST, ST_CONV_WGRAD)
 #undef PAIR
   return nullptr;
 }

@@ -55,9 +55,12 @@ enum {
                              fully connected layers and a network whose per-workgroup share
                              fits the LDS (cnn_mode_supported tells).  Weights in the
                              workspace are read at the start of a call and written back at
-                             its end.  Forward calls of one to three images run as the
-                             launches of their stages, which start sooner (sums in the
-                             order of CNN_MODE_STAGES: the same to rounding).               */
+                             its end.  Forward calls of few images run as the launches of
+                             their stages, which start sooner: one image where the library
+                             (or cnn_load_resident_code) has a kernel for the network, else
+                             two, and three where a forward pass has at most five stages.
+                             Their sums are those of CNN_MODE_STAGES: a longer call's agree
+                             with them to rounding, not bit for bit.                        */
 };
 
 /* output units for cnn_set_output_units */

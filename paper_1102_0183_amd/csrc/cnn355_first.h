@@ -15,7 +15,7 @@ constexpr int first_pitch(int taps) { return (taps + 27) / 32 * 32 + 4; }
 // Work item = (32 output maps, band of conv rows): the rows of the input maps under the band and the filters of the maps
 // lie in LDS; a wavefront computes 16 maps by 16 pixels at a time (v_mfma_f32_16x16x4_f32, four taps an instruction), the
 // sums pass through LDS to 32 lanes a map for tanh, pooling and the arg-max (index of the first maximum).
-// 300C6S1 on 2 x 96 x 96: 9.4 us, 33.9 with a lane per pixel (two LDS reads a multiply-add, 900 items of one map); bound by the
+// 300C6S1 on 2 x 96 x 96, in a kernel trace: 10.1 us, 34.0 with a lane per pixel (two LDS reads a multiply-add, 900 items of one map); bound by the
 // latency of its three steps (operands, product, epilogue), not by the 0.6 us of arithmetic.
 __device__ void conv_fwd_mx_item(const LayerDev& L, const Stage& st, int item, const gfloat* in, float* lds) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -107,8 +107,8 @@ __device__ void conv_fwd_mx_item(const LayerDev& L, const Stage& st, int item, c
 // wavefronts share a map's winners, a lane is a weight.  A group of 64 weights takes a winner at a time (place and delta are
 // scalars), the r weights left over 64 / r winners.  The rows of the input have a pitch of K beyond a multiple of 32 floats and
 // the maps one of K * K, so that the K * K taps of a winner lie in as many banks.
-// 300C6S1 on 2 x 96 x 96 with 529 winners: 11.8 us, 20.4 with a workgroup per map (two rounds of them, three LDS reads a term);
-// 300C3 on 3 x 32 x 32 6.5, 10.7; the smallest images as before (5 us). Issue of the readlanes and reads bounds the large one.
+// 300C6S1 on 2 x 96 x 96 with 529 winners, in a kernel trace: 12.9 us, 21.6 with a workgroup per map (two rounds of them, three LDS
+// reads a term); 300C3 on 3 x 32 x 32 7.8, 11.6.  Issue of the readlanes and reads bounds the large one.
 __host__ __device__ constexpr int first_row_pitch(int Wi, int K) { return Wi + ((K - Wi) % 32 + 32) % 32; }
 __host__ __device__ constexpr int first_map_pitch(int Hi, int Wi, int K) {
   return Hi * first_row_pitch(Wi, K) + ((K * K - Hi * first_row_pitch(Wi, K)) % 32 + 32) % 32;

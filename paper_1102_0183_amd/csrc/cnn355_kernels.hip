@@ -329,9 +329,10 @@ __device__ void conv_fwd_item(const LayerDev& L, const Stage& st, int item,
 // places of the taps lie in LDS in the order four instructions take them, 128 bits a lane.
 // The partial sums of every (slice, k split) go to their own plane of mm_part; ST_CONV_EPI
 // adds the planes in a fixed order (no atomics: results do not depend on timing).
-// 500C4 on 300 maps of 23 x 23 (256 items): 25.1 us, 33.5 without the overlap, with clamped single-word operands and an
-// integer division for every word staged, and with a fourth of its 13 pixel tiles on one SIMD; 13 us at the matrix cores' rate, the
-// rest operands from LDS.  300C2 and 300C4 8.4 -> 7.8 and 6.5 -> 6.1, the pull through 300C2 10.3 -> 8.6.
+// 500C4 on 300 maps of 23 x 23 (256 items), in a kernel trace: 25.8 us, 38.5 without the overlap, with clamped single-word operands and an
+// integer division for every word staged, and with a fourth of its 13 pixel tiles on one SIMD; without the matrix instructions and
+// their operands 16 us less (13 at the matrix cores' peak rate, tiles filled up).  300C2 and 300C4 11.9 -> 10.5 and 8.0 -> 7.9, the
+// pull through 300C2 14.3 -> 10.9.
 // ------------------------------------------------------------------------------------------
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4w __attribute__((ext_vector_type(4)));

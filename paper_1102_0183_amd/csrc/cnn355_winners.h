@@ -113,8 +113,8 @@ __device__ __forceinline__ float lane_value(float v, int lane) {
 // AW of a wide layer (Sec. 3.4) over the pooling winners.  Work item = (64 input maps, st.chunk <= 16 output maps).  The input
 // maps lie in LDS pixel by pixel, 64 maps side by side; a wavefront takes one output map j (or some of its winners, where
 // that gives more of the wavefronts work: one alone waits 16 clocks for a read), a lane one filter w_{j,i}: for every winner the K x K input pixels of its field, one LDS read (64 maps of a pixel) and one multiply-add
-// each, summed in C chains (500C4 on 300 maps: 16.9 us in one launch with the sums of the pull and as long without them,
-// 46.6 as a dense matrix product; the LDS reads of 14 output maps an item are 5 us of it, the rest staging, the adjustment and their waits).  The gradients then change places in LDS so that the adjustment reads and writes whole lines.
+// each, summed in C chains (500C4 on 300 maps, in a kernel trace: 16.7 us in one launch with the sums of the pull and as long without
+// them, 46.5 as a dense matrix product; the LDS reads of 14 output maps an item are 5 us of it, the rest staging, the adjustment and their waits).  The gradients then change places in LDS so that the adjustment reads and writes whole lines.
 template <int K>
 __device__ void conv_wgrad_win(const LayerDev& L, const Stage& st, int item, const gfloat* in, const Ctx& ctx, float* lds) {
   constexpr int KK = K * K, C = KK <= 9 ? 4 : 2;

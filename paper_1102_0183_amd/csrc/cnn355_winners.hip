@@ -2,7 +2,7 @@
 //
 // This file is compiled with the structurizer told to leave uniform branches alone (build.py): every wavefront branches as one on the
 // place of a winner, and only as plain jumps do the sums stay in the registers they are in (else each branch ends in
-// copies of them: twice the vector instructions, the pull through 500C4 20.7 us instead of 16.8).
+// copies of them: twice the vector instructions, the pull through 500C4 21.6 us instead of 16.1).
 #include "cnn355_winners.h"
 
 namespace cnn355 {
@@ -15,9 +15,9 @@ namespace cnn355 {
 // the delta in a scalar register, and LDS is not touched until the end.  Work item = (64 input maps, a group of
 // windows, slice of the output maps); its wavefronts share the slice, add up in LDS in a fixed order and leave one
 // region of partial sums; ST_CONV_BWD_WEPI adds the slices and the regions that overlap.
-// Pull through 500C4 on 300 maps of 23 x 23 behind 4 x 4 pooling (1/16 of 0.96 G multiply-adds): 13.5 us, 45.6 as a matrix
-// product; bound by the issue of the multiply-adds and the branches around them (7.6 us of it) and by the
-// latency of a short kernel.  Groups of windows of one slice run on one XCD, whose L2 then holds their filters: 16.8 us else.
+// Pull through 500C4 on 300 maps of 23 x 23 behind 4 x 4 pooling (1/16 of 0.96 G multiply-adds), in a kernel trace: 16.1 us, 45.9 as a
+// matrix product; bound by the issue of the multiply-adds and the branches around them (7.6 us of it) and by the
+// latency of a short kernel.  Groups of windows of one slice run on one XCD, whose L2 then holds their filters: 19.2 us else.
 // ------------------------------------------------------------------------------------------
 // acc += d * w at the K x K pixels of winner `a` (counted row by row from LO) of window `win`
 template <int K, int KP, int RW, int LO, int HI, int R>

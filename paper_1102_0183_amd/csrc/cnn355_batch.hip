@@ -264,7 +264,10 @@ __global__ void __launch_bounds__(BT) k_batch_gemm(BatchGemm g) {
 #pragma unroll
           for (int m = 0; m < MT; ++m) a[u][m] = lds_w[kr * WROW + m * TR + lrow];
 #pragma unroll
-          for (int ct = 0; ct < CT; ++ct) bv[u][ct] = *(const float*)(in_b[ct] + ko);
+          for (int ct = 0; ct < CT; ++ct) {   // (k beyond the chunk: nothing was staged there, and no number times zero is none)
+            const float t = *(const float*)(in_b[ct] + ko);
+            bv[u][ct] = k < kc ? t : 0.f;
+          }
         }
         CNN355_MAC(a, bv)
       }

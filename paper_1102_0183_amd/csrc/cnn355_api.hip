@@ -45,6 +45,13 @@ size_t batch_conv_lds_bytes(const BatchConv& g);
 int batch_conv_fit(int MT, int TR, size_t lds_bytes);
 int batch_conv_grid_x(const BatchConv& g);
 hipError_t launch_batch_conv(hipStream_t stream, const BatchConv& g);
+int batch_first_steps(int k_total);
+size_t batch_first_lds_bytes(const BatchFirst& g);
+int batch_first_fit(const BatchFirst& g);
+hipError_t launch_batch_first(hipStream_t stream, const BatchFirst& g);
+size_t batch_split_lds_bytes(const BatchSplit& g);
+int batch_split_fit(const BatchSplit& g);
+hipError_t launch_batch_split(hipStream_t stream, const BatchSplit& g);
 hipError_t launch_batch_pool(hipStream_t stream, const BatchPool& q);
 hipError_t launch_batch_outputs(hipStream_t stream, const float* sums, int n_slices, long long slice_stride, const float* bias,
                                 float* probs, long long n_images, int n_classes, int out_units);
@@ -1379,17 +1386,21 @@ namespace {
 struct BatchStep {
   BatchGemm g;
   BatchConv c;        // used instead of g when c.MT != 0
+  BatchFirst f;       // used instead of both when f.T != 0 ...
+  BatchSplit s;       // ... or s.RT != 0
   BatchPool pool;     // used when the sums come raw (g.fuse or c.fuse 0)
   BatchPack pack;
   size_t wt_off = 0;  // floats from the start of the scratch
   size_t wt_floats = 0;
-  size_t out_per_image = 0;
+  size_t out_per_image = 0;   // floats an image in the layer's buffer
+  bool split_out = false;     // outputs as split halves, for the next layer's product
+  bool raw() const { return f.T == 0 && s.RT == 0 && (c.MT ? c.fuse : g.fuse) == 0; }
 };
 struct BatchPlan {
   std::vector<BatchStep> steps;
-  size_t wt_total = 0, sums_per_image = 0, act_per_image = 0, fe_per_image = 0;
+  size_t wt_total = 0, sums_per_image = 0, act_per_image[2] = {0, 0}, fe_per_image = 0;   // (layers take the two buffers in turn)
   size_t floats(size_t batch) const {
-    return wt_total + batch * (sums_per_image + 2 * act_per_image + fe_per_image) + 4 * 64;
+    return wt_total + batch * (sums_per_image + act_per_image[0] + act_per_image[1] + fe_per_image) + 4 * 64;
   }
 };
 
@@ -1504,8 +1515,113 @@ void conv_plan(const LayerDev& L, const BatchGemm& g, size_t batch, BatchConv& c
   if (c.MT) { c.by_win_img = fast_div_of(c.win_img); c.by_wp = fast_div_of(c.Wp); }
 }
 
-// Shape of every layer's matrix product, tile choice and LDS budget.  Returns 0 or an error code.
-int batch_plan(cnn* net, size_t batch, BatchPlan& B) {
+// k_batch_split's clocks of a compute unit for a layer, fitted to 12 layers in up to 110 plans each: its workgroups share the
+// matrix pipes and LDS, and each waits for its own slabs.  The plan of the fewest clocks takes 0 to 6 % longer (of the pass
+// around the layer) than the fastest one.
+double split_clocks(const BatchSplit& t, size_t n_cb) {
+  const int S = t.TR == 32 ? 2 : 4, rows = t.RT * t.TR, cols = 4 * t.CT * t.TR, chunks = t.n_cg / t.IC;
+  const double steps = (double)chunks * (t.n_kg / S), slabs = (double)chunks * ((t.n_kg + t.slab - 1) / t.slab);
+  const double matrix = steps * t.RT * t.CT * 3 * (t.TR == 32 ? 32 : 16), lds = steps * S * (rows + cols / 4);
+  const size_t groups = (size_t)((t.Mo + rows - 1) / rows), gx = std::min(n_cb, std::max<size_t>(1, 256 * batch_split_fit(t) / groups));
+  const double side = (double)((gx * groups + 255) / 256), rounds = (double)((n_cb + gx - 1) / gx);
+  return rounds * std::max(side * (1.28 * matrix + 0.55 * lds + 263.0 * slabs + 60.0), 1.8 * matrix + 17.5 * steps + 1010.0 * slabs + 1330.0);
+}
+
+// The plan of k_batch_split for a convolutional layer behind another one: the tile, chunk and slab of the fewest clocks.  Leaves
+// t.RT = 0 where windows do not fit a block, or leave more than a quarter of it empty, and where one group of eight maps of a
+// block's images does not fit.
+double split_plan(const LayerDev& L, size_t batch, BatchSplit& out) {
+  constexpr size_t LDS = 160 * 1024;
+  BatchSplit t;
+  std::memset(&t, 0, sizeof(t));
+  out = t;
+  t.n_cg = (L.Mi + 7) / 8; t.pix = L.Hi * L.Wi; t.Wi = L.Wi; t.K = L.K; t.Kx = L.Kx; t.stride = L.S + 1; t.stride_x = L.Sx + 1;
+  t.Mo = L.Mo; t.Kp = L.Kp; t.Kpx = L.Kpx; t.Wp = L.Wp; t.win_img = L.Hp * L.Wp; t.bias = L.bias;
+  const int M = t.Kp * t.Kpx, KK = t.K * t.Kx;
+  const size_t limit = (size_t)1 << 29, in_floats = (size_t)t.n_cg * 8 * t.pix;
+  if (L.is_output || batch * in_floats >= limit || batch * (size_t)((L.Mo + 7) / 8 * 8) * t.win_img >= limit) return 0;
+  t.in_plane = (long long)batch * t.pix * 16;   // (layers of halves stay below 2^31 bytes: the kernels' offsets)
+  double best = 0;
+  // pixels from a block's first to its last, at most, by the row of windows that it starts in
+  int span_of = 0, span = 0;
+  auto pixels = [&](int wins) {
+    if (wins == span_of) return span;
+    span_of = wins; span = 0;
+    const int more_rows = wins % t.Wp == 0 ? wins / t.Wp - 1 : (wins + t.Wp - 2) / t.Wp;   // (blocks of whole rows start with one)
+    for (int y = 0; y < L.Hp; ++y) {
+      const int last = y + more_rows, rows = last / L.Hp * L.Hi + (last % L.Hp * t.Kp + t.Kp - 1) * t.stride + t.K - y * t.Kp * t.stride;
+      span = std::max(span, rows * t.Wi);
+    }
+    return span = (int)std::min<size_t>((size_t)span, batch * t.pix);
+  };
+  for (int tr : {32, 16})
+    for (int rt : {1, 2, 3, 5, 7})
+      for (int ct : {64 / tr, 32 / tr}) {
+        // The tiles that are compiled, with registers for two wavefronts a SIMD.  (Larger ones read less LDS, but one wavefront
+        // a SIMD waits alone: 300C2 of 512 images in 128 x 256 694 us of the pass, in 64 x 256 543.)
+        if (tr == 32 ? rt > 2 : rt == 2 || (rt > 3 && ct > 2)) continue;
+        const int rows = rt * tr, cols = 4 * ct * tr, S = tr == 32 ? 2 : 4, groups = (t.Mo + rows - 1) / rows;
+        if (M > cols || cols / M * M * 4 < cols * 3 || (groups > 1 && groups * rows - t.Mo >= rows / 2)) continue;
+        t.RT = rt; t.CT = ct; t.TR = tr;
+        t.wins = cols / M;
+        // whole images, or whole rows of windows, where that leaves few columns empty: fewer pixels to stage
+        if (t.wins > t.win_img && t.wins % t.win_img * 12 <= t.wins) t.wins -= t.wins % t.win_img;
+        else if (t.wins > t.Wp && t.wins % t.Wp * 24 <= t.wins) t.wins -= t.wins % t.Wp;
+        t.run_px = (pixels(t.wins) + 63) / 64 * 64;
+        const size_t n_cb = (batch * t.win_img + t.wins - 1) / t.wins;
+        for (int ic = 1; ic <= t.n_cg; ++ic) {
+          if (t.n_cg % ic) continue;
+          t.IC = ic;
+          t.n_kg = (ic * KK + S - 1) / S * S;
+          for (int part = 1; part <= 8; ++part) {   // slabs of a chunk
+            t.slab = ((t.n_kg + part - 1) / part + S - 1) / S * S;
+            if (part > 1 && t.slab < 2 * S) break;
+            const size_t lds = batch_split_lds_bytes(t);
+            if (lds > LDS) continue;
+            const double est = split_clocks(t, n_cb);
+            if (best == 0 || est < best) { best = est; out = t; }
+          }
+        }
+      }
+  if (out.RT) { out.by_win_img = fast_div_of(out.win_img); out.by_wp = fast_div_of(out.Wp); }
+  return best;
+}
+
+// The plan of k_batch_first for the first layer, and its clocks of a compute unit: the vector instructions of all windows (the
+// products of halves run beside them), or the chain of one wavefront's members.  Leaves out.T = 0 where a sum has more terms
+// than the kernel is compiled for.
+double first_plan(const LayerDev& L, size_t batch, BatchFirst& out) {
+  BatchFirst f;
+  std::memset(&f, 0, sizeof(f));
+  out = f;
+  f.Hi = L.Hi; f.Wi = L.Wi; f.K = L.K; f.Kx = L.Kx; f.stride = L.S + 1; f.stride_x = L.Sx + 1; f.Mo = L.Mo;
+  f.Kp = L.Kp; f.Kpx = L.Kpx; f.Wp = L.Wp; f.win_img = L.Hp * L.Wp; f.bias = L.bias;
+  f.by_win_img = fast_div_of(f.win_img); f.by_wp = fast_div_of(f.Wp); f.by_kpx = fast_div_of(f.Kpx);
+  f.k_total = L.Mi * L.K * L.Kx;
+  f.row = (L.Mo + 15) / 16 * 16;
+  if ((long long)L.Mi * L.Hi * L.Wi * 33 * 4 >= 1ll << 31) return 0;   // (32-bit offsets from the first of 32 windows)
+  f.H = batch_first_steps(f.k_total);
+  if (!f.H) return 0;
+  const double jobs = (double)((batch * f.win_img + 31) / 32);
+  const int M = L.Kp * L.Kpx;
+  double best = 0;
+  for (int T : {5, 2, 1})
+    for (int share = 0; share < (M >= 4 && T <= 2 ? 2 : 1); ++share) {
+      if ((T == 5 && f.H > 2) || (T == 2 && f.H > 5)) continue;   // (the registers)
+      f.T = T; f.share = share;
+      const int groups = (L.Mo + T * 32 - 1) / (T * 32);
+      const double pixels = f.H * 800.0 + 150.0, sums = T * (f.H * 50.0 + 130.0), outputs = std::min(T * 32, L.Mo) * 75.0 + 300.0;
+      const double all = jobs * groups * (M * (pixels + sums) + outputs) / 1024;
+      const double chain = share ? (M + 3) / 4 * (pixels + sums + 1200.0) + outputs / 4 + 1500.0 : M * (pixels + sums + 1200.0) + outputs;
+      const double est = 4000.0 + f.H * 300.0 + std::max(all, chain);
+      if (best == 0 || est < best) { best = est; out = f; }
+    }
+  return best;
+}
+
+// Shape of every layer's matrix product, tile choice and LDS budget.  Returns 0 or an error code.  split: convolutional layers
+// behind another one in products of halves, where their plan fits.
+int batch_plan_of(cnn* net, size_t batch, bool split, BatchPlan& B) {
   const ProgramDev& P = net->prog;
   constexpr size_t LDS_FLOATS = 20000;      // 78 KB per workgroup: two workgroups per compute unit
   constexpr size_t LDS_FLOATS_BIG = 38000;  // large input maps: one workgroup per compute unit
@@ -1590,27 +1706,79 @@ int batch_plan(cnn* net, size_t batch, BatchPlan& B) {
     std::memset(&st.c, 0, sizeof(st.c));
     if (L.kind == L_CONV) conv_plan(L, g, batch, st.c);
     const BatchConv& c = st.c;
-    const int KSl = c.MT ? c.n_slices : g.KS, fuse = c.MT ? c.fuse : g.fuse;
-    st.wt_floats = up64((size_t)g.Mi * KK * (c.MT ? (size_t)(c.Mo + c.MT * c.TR - 1) / (c.MT * c.TR) * (c.MT * c.TR) : (size_t)g.MoPad));
+    const int KSl = c.MT ? c.n_slices : g.KS;
+    std::memset(&st.s, 0, sizeof(st.s));
+    std::memset(&st.f, 0, sizeof(st.f));
+    auto old_clocks = [&](const BatchStep& t) {
+      return t.c.MT ? conv_clocks(t.c, batch, (batch * t.c.win_img + t.c.wins - 1) / t.c.wins) : gemm_clocks(t.g, batch);
+    };
+    if (split && L.kind == L_CONV && l > 0 && P.layers[l - 1].kind == L_CONV && (B.steps.back().s.RT || l == 1)) {
+      BatchStep& below = B.steps.back();
+      double est = split_plan(L, batch, st.s), old = old_clocks(st);
+      const bool with_first = !below.s.RT;
+      if (st.s.RT && with_first) {   // the first layer comes with it
+        est += first_plan(P.layers[0], batch, below.f);
+        old += old_clocks(below);
+        if (!below.f.T) st.s.RT = 0;
+      }
+      // where that is the faster form: over 216 nets of 1 to 10000 images 8 lose by it, 31 us of 14 ms together, and 6 that would
+      // gain 31 us are left as they were
+      if (0.8 * est + (with_first ? 8000.0 : 2000.0) >= old) st.s.RT = 0;
+      if (st.s.RT) {
+        below.split_out = true;
+        below.out_per_image = (size_t)st.s.n_cg * 8 * HiWi;
+        (below.s.RT ? below.s.split_out : below.f.split_out) = (int)(batch * (size_t)HiWi);
+        if (below.f.T) {
+          B.wt_total -= below.wt_floats;
+          below.wt_floats = up64((size_t)below.f.k_total * below.f.row);
+          B.wt_total += below.wt_floats;
+          below.pack.row = below.f.row;
+        }
+      } else {
+        below.f.T = 0;
+      }
+    }
+    const BatchSplit& h = st.s;
+    const int h_rows = h.RT * h.TR, h_groups = h.RT ? (h.Mo + h_rows - 1) / h_rows : 0;
+    st.wt_floats = h.RT ? up64((size_t)h_groups * h_rows * (h.n_cg / h.IC) * h.n_kg * 8) + up64((size_t)h_groups * h_rows) : up64((size_t)g.Mi * KK * (c.MT ? (size_t)(c.Mo + c.MT * c.TR - 1) / (c.MT * c.TR) * (c.MT * c.TR) : (size_t)g.MoPad));
     st.wt_off = B.wt_total;
     B.wt_total += st.wt_floats;
     BatchPack& k = st.pack;
     std::memset(&k, 0, sizeof(k));
     k.w = L.w; k.csr_ptr = L.csr_ptr; k.csr_idx = L.csr_idx;
     k.full_table = L.kind != L_CONV || L.full_table; k.Mo = g.Mo; k.K = g.K; k.Kx = g.Kx;
-    k.row = c.MT ? c.MT * c.TR : g.MoPad; k.k_total = g.Mi * KK;
+    k.row = h.RT ? h_rows : c.MT ? c.MT * c.TR : g.MoPad; k.k_total = g.Mi * KK;
+    k.Mi = g.Mi; k.n_chunks = h.RT ? h.n_cg / h.IC : 0; k.IC = h.IC; k.n_kg = h.n_kg;
     BatchPool& q = st.pool;
     std::memset(&q, 0, sizeof(q));
     q.bias = L.bias; q.Mo = g.Mo; q.Ho = Ho; q.Wo = (L.kind == L_CONV) ? L.Wo : 1; q.Kp = Kp; q.Kpx = Kpx; q.Hp = Hp; q.Wp = Wp;
     q.n_slices = KSl; q.slice_stride = c.MT ? (long long)(batch * L.Mo * L.Ho * L.Wo) : g.slice_stride; q.act = L.is_output ? 0 : 1;
     st.out_per_image = pooled ? (size_t)g.Mo * Hp * Wp : (size_t)g.Mo * g.P;
     if (c.MT) { st.c.slice_stride = q.slice_stride; st.c.out_stride = (long long)c.Mo * c.win_img; }
-    if (fuse == 0) B.sums_per_image = std::max(B.sums_per_image, up64((size_t)KSl * g.Mo * (c.MT ? c.win_img : g.P)));
+    if (h.RT) st.s.out_stride = (long long)st.out_per_image;
+    if (st.raw()) B.sums_per_image = std::max(B.sums_per_image, up64((size_t)KSl * g.Mo * (c.MT ? c.win_img : g.P)));
     // (the columns are the layer's pixels whenever fuse == 0 with pooling: pooling inside the product has fuse != 0)
-    B.act_per_image = std::max(B.act_per_image, up64(st.out_per_image));
     B.steps.push_back(st);
   }
+  size_t act[2] = {0, 0};
+  bool any = false;
+  for (size_t l = 0; l < B.steps.size(); ++l) {
+    act[l & 1] = std::max(act[l & 1], up64(B.steps[l].out_per_image));
+    any |= B.steps[l].split_out;
+  }
+  // (two buffers of the same size where every product is one of 32 bits)
+  for (size_t l = 0; l < 2; ++l) B.act_per_image[l] = any ? act[l] : std::max(act[0], act[1]);
   if (P.has_frontend) B.fe_per_image = up64((size_t)P.fe.n_filters * P.fe.H * P.fe.W);
+  return CNN_OK;
+}
+
+// Products of halves, unless the maps that fill groups of eight and tiles up take more scratch memory than 32-bit products
+// throughout: a caller whose memory was enough for a batch goes on with it.
+int batch_plan(cnn* net, size_t batch, BatchPlan& B) {
+  const int rc = batch_plan_of(net, batch, false, B);
+  if (rc) return rc;
+  BatchPlan halves;
+  if (batch_plan_of(net, batch, true, halves) == CNN_OK && halves.floats(batch) <= B.floats(batch)) B = std::move(halves);
   return CNN_OK;
 }
 
@@ -2056,7 +2224,8 @@ int cnn355_resident_plan_text(const char* arch, int fan_in, int n_ranks, int xcd
 
 // development aid, host only: the plan of the batched forward pass of `arch` at `batch` images (tables as in
 // cnn355_resident_plan_text), a line per trainable layer of "name value" pairs, then whether the output units
-// add the planes of their layer's sums and the scratch floats a call takes.
+// add the planes of their layer's sums and the scratch floats a call takes (floats_32: with 32-bit products throughout).
+// split: the layer is a product of halves (k_batch_split), its tile, chunk and slab; first: the first layer below one (k_batch_first).  The values in front of these are then those of the product that the layer has without them.
 // run: input maps (of KK terms each) of the longest running sum; gemm_run, gemm_KS: of k_batch_gemm's plan of the layer.
 int cnn355_batch_plan_text(const char* arch, int fan_in, size_t batch, char* buf, size_t n) {
   if (!arch || !buf || n == 0 || batch == 0) return fail(nullptr, CNN_E_ARG, "NULL argument or batch of 0");
@@ -2084,13 +2253,22 @@ int cnn355_batch_plan_text(const char* arch, int fan_in, size_t batch, char* buf
                          {"run", std::min(g.Mi, g.chunks_per_slice * g.IC)}, {"members", g.Kp * g.Kpx}, {"fuse", g.fuse},
                          {"lds_bytes", (long long)batch_gemm_lds_bytes(g)}});
     }
+    const BatchSplit& h = st.s;
+    f.push_back({"split", h.RT != 0});
+    f.push_back({"first", st.f.T != 0});
+    if (st.f.T) f.insert(f.end(), {{"first_T", st.f.T}, {"first_H", st.f.H}, {"first_share", st.f.share}, {"first_lds", (long long)batch_first_lds_bytes(st.f)}});
+    if (h.RT)
+      f.insert(f.end(), {{"split_RT", h.RT}, {"split_CT", h.CT}, {"split_TR", h.TR}, {"split_IC", h.IC}, {"split_kg", h.n_kg}, {"split_slab", h.slab},
+                         {"split_wins", h.wins}, {"split_px", h.run_px}, {"split_lds", (long long)batch_split_lds_bytes(h)}});
     t += "layer";
     for (const auto& kv : f) t += std::string(" ") + kv.first + " " + std::to_string(kv.second);
     t += "\n";
   }
   const BatchStep& last = B.steps.back();
-  const bool add = (last.c.MT ? last.c.fuse : last.g.fuse) == 0 && outputs_add(tmp.prog.n_classes, last.pool.n_slices);
-  t += "outputs_add " + std::to_string((int)add) + "\nfloats " + std::to_string(B.floats(batch)) + "\n";
+  const bool add = last.raw() && outputs_add(tmp.prog.n_classes, last.pool.n_slices);
+  BatchPlan B32;
+  if ((rc = batch_plan_of(&tmp, batch, false, B32))) { g_err = tmp.err; return rc; }
+  t += "outputs_add " + std::to_string((int)add) + "\nfloats " + std::to_string(B.floats(batch)) + "\nfloats_32 " + std::to_string(B32.floats(batch)) + "\n";
   if (t.size() + 1 > n) return fail(nullptr, CNN_E_ARG, "buffer too small for the plan text");
   std::memcpy(buf, t.c_str(), t.size() + 1);
   return CNN_OK;
@@ -2421,14 +2599,16 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
   const ProgramDev& P = net->prog;
   float* base = (float*)d_scratch;
   float* d_sums = base + B.wt_total;
-  float* d_act[2] = {d_sums + batch * B.sums_per_image, d_sums + batch * (B.sums_per_image + B.act_per_image)};
-  float* d_fe = d_act[1] + batch * B.act_per_image;
+  float* d_act[2] = {d_sums + batch * B.sums_per_image, d_sums + batch * (B.sums_per_image + B.act_per_image[0])};
+  float* d_fe = d_act[1] + batch * B.act_per_image[1];
   // the weights as the products read them: one [k][map] matrix per layer, from their present values
   BatchPackAll pack;
   pack.n = (int)B.steps.size();
   for (int l = 0; l < pack.n; ++l) {
     pack.l[l] = B.steps[l].pack;
     pack.l[l].wt = base + B.steps[l].wt_off;
+    const BatchSplit& h = B.steps[l].s;   // (the exponents behind the weights)
+    if (h.RT) pack.l[l].exps = (int*)(base + B.steps[l].wt_off + B.steps[l].wt_floats - up64((size_t)(h.Mo + h.RT * h.TR - 1) / (h.RT * h.TR) * (h.RT * h.TR)));
   }
   HIP_TRY(net, launch_batch_pack(net->stream, pack));
   const size_t fe_sz = P.has_frontend ? (size_t)P.fe.n_filters * P.fe.H * P.fe.W : 0;
@@ -2446,8 +2626,17 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
     for (size_t s = 0; s < B.steps.size(); ++s) {
       BatchStep& st = B.steps[s];
       float* out = d_act[cur];
-      const bool raw = (st.c.MT ? st.c.fuse : st.g.fuse) == 0;
-      if (st.c.MT) {
+      const bool raw = st.raw();
+      if (st.f.T) {
+        BatchFirst f = st.f;
+        f.in = in; f.in_stride = in_stride; f.wt = base + st.wt_off; f.out = out; f.n_win = (int)(nb * f.win_img);
+        HIP_TRY(net, launch_batch_first(net->stream, f));
+      } else if (st.s.RT) {
+        BatchSplit h = st.s;
+        h.in = (const char*)in; h.wt = (const char*)(base + st.wt_off); h.exps = pack.l[s].exps; h.out = out;
+        h.n_win = (int)(nb * h.win_img); h.n_cb = (h.n_win + h.wins - 1) / h.wins;
+        HIP_TRY(net, launch_batch_split(net->stream, h));
+      } else if (st.c.MT) {
         BatchConv c = st.c;
         c.in = in; c.in_stride = in_stride; c.wt = base + st.wt_off; c.out = raw ? d_sums : out;
         c.vec = ((uintptr_t)in & 15u) == 0 && in_stride % 4 == 0 && (c.IC * c.Hi * c.Wi) % 4 == 0 &&
@@ -2474,8 +2663,21 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
       cur ^= 1;
       if ((int)s == tap_step) {
         HIP_TRY(net, hipStreamSynchronize(net->stream));
-        HIP_TRY(net, hipMemcpy(host_tap, out, nb * st.out_per_image * sizeof(float), hipMemcpyDeviceToHost));
-        if (tap_per_image) *tap_per_image = st.out_per_image;
+        if (!st.split_out) {
+          HIP_TRY(net, hipMemcpy(host_tap, out, nb * st.out_per_image * sizeof(float), hipMemcpyDeviceToHost));
+          if (tap_per_image) *tap_per_image = st.out_per_image;
+          return CNN_OK;
+        }
+        const size_t maps = (size_t)st.pool.Mo, pixels = (size_t)st.pool.Hp * st.pool.Wp;
+        std::vector<_Float16> halves(batch * st.out_per_image * 2);
+        HIP_TRY(net, hipMemcpy(halves.data(), out, halves.size() * sizeof(_Float16), hipMemcpyDeviceToHost));
+        for (size_t b = 0; b < nb; ++b)
+          for (size_t j = 0; j < maps; ++j)
+            for (size_t w = 0; w < pixels; ++w) {
+              const _Float16* h = &halves[((j >> 3) * 2 * batch * pixels + b * pixels + w) * 8 + (j & 7)];
+              host_tap[(b * maps + j) * pixels + w] = ((float)h[0] + (float)h[batch * pixels * 8]) / (float)(1 << SPLIT_SHIFT);
+            }
+        if (tap_per_image) *tap_per_image = maps * pixels;
         return CNN_OK;
       }
     }

@@ -5,8 +5,8 @@
 // which is what the matrix cores are for.  X is never formed: its element is
 // in[b][i][(y (S+1) + ky)][(x (S+1) + kx)], read from the images staged in LDS at offset
 // koff(k) + pbase(n).  A fully connected layer is the same product with 1 x 1 maps and K = 1.
-// fp32 operands and fp32 accumulation (v_mfma_f32_32x32x2_f32): the results stay within the
-// tolerance of the one-image path.
+// fp32 operands and fp32 accumulation (v_mfma_f32_32x32x2_f32), or operands as two halves each
+// (k_batch_split, k_batch_first): the results stay within the tolerance of the one-image path.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -21,6 +21,8 @@ typedef const CNN_GLOBAL float* cgf;
 typedef CNN_GLOBAL float* gf;
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef _Float16 v4h __attribute__((ext_vector_type(4)));
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
 namespace {
 
@@ -39,6 +41,47 @@ __device__ __forceinline__ float b_act(float a) {
   p = fmaf(x2, p, -1.0f / 3.0f);
   const float small = 1.7159f * fmaf(x, x2 * p, x);
   return fabsf(x) < 0.3f ? small : big;
+}
+
+// Activation v as split halves (BatchSplit): v 2^14 is the sum of two halves to 23 bits, for activations down to 1e-6 of the
+// largest.  off: byte offset of the high half in `out`, the low one lies a plane behind it.
+__device__ __forceinline__ void put_split(CNN_GLOBAL char* out, unsigned plane, unsigned off, float v) {
+  const float x = v * (float)(1 << SPLIT_SHIFT);
+  const _Float16 h = (_Float16)x;
+  *(CNN_GLOBAL _Float16*)(out + off) = h;
+  *(CNN_GLOBAL _Float16*)(out + plane + off) = (_Float16)(x - (float)h);
+}
+// the same of four maps side by side
+__device__ __forceinline__ void put_split4(CNN_GLOBAL char* out, unsigned plane, unsigned off, const float (&v)[4]) {
+  v4h h, l;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const float x = v[u] * (float)(1 << SPLIT_SHIFT);
+    h[u] = (_Float16)x;
+    l[u] = (_Float16)(x - (float)h[u]);
+  }
+  *(CNN_GLOBAL v4h*)(out + off) = h;
+  *(CNN_GLOBAL v4h*)(out + plane + off) = l;
+}
+
+// 2 x 2 windows whose members are the four lanes of a quad: the window's largest sum of row u (of four) goes to lane q = u.
+// (The maximum of what the compiler cannot tell is no signalling NaN costs it three instructions, the statement's one; the
+// operands come from an instruction that it sees, so it is the one that waits for the matrix cores.)
+__device__ __forceinline__ float pool_quad(float a0, float a1, float a2, float a3, int q) {
+  const float x0 = __builtin_canonicalizef(a0), x1 = __builtin_canonicalizef(a1), x2 = __builtin_canonicalizef(a2), x3 = __builtin_canonicalizef(a3);
+  float r0, r1, r2, r3;
+  asm("s_nop 1\n\t"
+      "v_max_f32_dpp %0, %4, %4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %1, %5, %5 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %2, %6, %6 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %3, %7, %7 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %3, %3, %3 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
+      : "=&v"(r0), "=&v"(r1), "=&v"(r2), "=&v"(r3)
+      : "v"(x0), "v"(x1), "v"(x2), "v"(x3));
+  return fmaxf(q < 2 ? (q == 0 ? r0 : r1) : (q == 2 ? r2 : r3), -INFINITY);   // (no number at all: -inf)
 }
 
 constexpr int PRE_IN = 16;     // floats per thread a prefetched chunk may hold: staged images ...
@@ -351,7 +394,26 @@ __device__ __forceinline__ void lds_dma16(unsigned lds_byte, const CNN_GLOBAL ch
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(lds_byte)),
                "v"(off), "s"(uniform(base)) : "memory", "m0");
 }
+// N runs of 64 lanes' 16 bytes, one behind the other at either end (an instruction's offset counts for both addresses).
+// lds_byte and base come from scalar instructions.
+template <int N>
+__device__ __forceinline__ void lds_dma16_runs(unsigned lds_byte, const CNN_GLOBAL char* base, unsigned off) {
+  if constexpr (N == 1)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_byte), "v"(off), "s"(base) : "memory", "m0");
+  else if constexpr (N == 2)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024" ::"s"(lds_byte),
+                 "v"(off), "s"(base) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024\n\t"
+                 "global_load_lds_dwordx4 %1, %2 offset:2048\n\tglobal_load_lds_dwordx4 %1, %2 offset:3072" ::"s"(lds_byte),
+                 "v"(off), "s"(base) : "memory", "m0");
+}
 #pragma clang diagnostic pop
+__device__ __forceinline__ void lds_dma16_n(unsigned lds_byte, const CNN_GLOBAL char* base, unsigned off, int n) {
+  for (; n >= 4; n -= 4, lds_byte += 4096, off += 4096) lds_dma16_runs<4>(lds_byte, base, off);
+  if (n >= 2) { lds_dma16_runs<2>(lds_byte, base, off); n -= 2; lds_byte += 2048; off += 2048; }
+  if (n > 0) lds_dma16_runs<1>(lds_byte, base, off);
+}
 
 template <int MT, int TR>
 __global__ void __launch_bounds__(BT, MT * TR > 96 ? 2 : 3) k_batch_conv(BatchConv g) {
@@ -585,6 +647,522 @@ __global__ void __launch_bounds__(BT, MT * TR > 96 ? 2 : 3) k_batch_conv(BatchCo
   }
 }
 
+// ---- the first convolutional layer in front of one in products of halves ---------------------------------------
+// A wavefront takes 32 windows and walks their members one after the other, keeping the largest sums of T tiles of 32 maps in
+// registers: no sums pass between lanes, and a lane has four maps of its window side by side for a store.  A lane gathers its
+// k's pixels straight from memory (the caches serve the overlapping fields), the next member's while it works on this one, and
+// splits them into halves as put_split does; the weights are split into LDS at the start.  Nothing is staged and no wavefront
+// waits for another -- unless the windows are few: then four wavefronts share the members of 32 windows (g.share).
+// Why halves: 32-bit products leave the vector units idle (a wavefront's vector instructions wait for another one's products:
+// 103 us of products and 122 of vector work on the same SIMD took 220 together, with products of halves 62 and 122 took 148),
+// and these layers have as much of the one as of the other.  300C3 on 3 maps, 512 images: k_batch_conv 177 us, this kernel with
+// 32-bit products 146, with halves 90; 20C4 of 4096 digits 77, 51, 45.
+// Pixels that do not split (4 and larger, infinite, or all of a lane's below 2^-14 and not zero) and weights that do not (not
+// finite, or all of a row's below 2^-81) take 32-bit products, member by member.
+constexpr int first_waves(int T, int H) {   // wavefronts a SIMD, by the registers of pixels, offsets, halves and sums
+  const int regs = (H <= 4 ? 24 : 16) * H + 16 * T + 72;
+  return regs <= 124 ? 4 : regs <= 164 ? 3 : 2;
+}
+template <int T, int H>
+__global__ void __launch_bounds__(BT, first_waves(T, H)) k_batch_first(BatchFirst g) {
+  extern __shared__ __align__(16) char lds_s[];
+  constexpr int N = 8 * H, ROWS = T * 32;
+  const int tid = threadIdx.x, lane = tid & 63, lrow = lane & 31, lk = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j0 = blockIdx.y * ROWS;
+  char* lds_h = lds_s;                                   // [T][H][high, low][k / 8 mod 2][32 maps][8] halves
+  float* lds_f = (float*)(lds_h + T * H * 2048);         // [k_total][ROWS] weights
+  float* lds_b = lds_f + g.k_total * ROWS;               // [ROWS] biases
+  int* lds_e = (int*)(lds_b + ROWS);                     // [ROWS] -(e + SPLIT_SHIFT), halves are w 2^e
+  int* koff = lds_e + ROWS;                              // [16 H] byte offset of k from a member's first pixel
+  float* ex = (float*)(koff + 16 * H);                   // [4][T * 16][64] where wavefronts share
+  const int KK = g.K * g.Kx, HiWi = g.Hi * g.Wi;
+  for (int x = tid; x < 16 * H; x += BT) {
+    const int k = min(x, g.k_total - 1), c = k / KK, t = k - c * KK, ky = t / g.Kx;
+    koff[x] = (c * HiWi + ky * g.Wi + t - ky * g.Kx) * 4;
+  }
+  for (int x = tid; x < ROWS; x += BT) lds_b[x] = j0 + x < g.Mo ? g.bias[j0 + x] : 0.f;
+  for (int x0 = tid; x0 < g.k_total * ROWS; x0 += 8 * BT) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int x = x0 + u * BT, k = x / ROWS, j = j0 + x % ROWS;
+      v[u] = k < g.k_total && j < g.row ? g.wt[(long long)k * g.row + j] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (x0 + u * BT < g.k_total * ROWS) lds_f[x0 + u * BT] = v[u];
+  }
+  __syncthreads();
+  bool odd = false;
+  for (int r = tid; r < ROWS; r += BT) {
+    float most = 0.f;
+    for (int k = 0; k < g.k_total; ++k) {
+      const float v = fabsf(lds_f[k * ROWS + r]);
+      odd |= !(v < INFINITY);
+      most = fmaxf(most, v);
+    }
+    int e = 0;
+    if (most > 0.f && most < INFINITY) { frexpf(most, &e); e = 15 - e; }
+    odd |= e > 96;
+    lds_e[r] = -(e + SPLIT_SHIFT);
+  }
+  odd = __syncthreads_or(odd);
+  if (odd)
+    for (int r = tid; r < ROWS; r += BT) lds_e[r] = 0;
+  else
+    for (int x = tid; x < T * H * 64; x += BT) {         // (tile, h, k / 8 mod 2, map)
+      const int r = x & 31, l = (x >> 5) & 1, h = (x >> 6) % H, m = x / (64 * H), e = -lds_e[m * 32 + r] - SPLIT_SHIFT;
+      v8h hi, lo;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int k = h * 16 + l * 8 + i;
+        const float v = k < g.k_total ? ldexpf(lds_f[k * ROWS + m * 32 + r], e) : 0.f;
+        hi[i] = (_Float16)v;
+        lo[i] = (_Float16)(v - (float)hi[i]);
+      }
+      *(v8h*)(lds_h + ((m * H + h) * 4 + l) * 512 + r * 16) = hi;
+      *(v8h*)(lds_h + ((m * H + h) * 4 + 2 + l) * 512 + r * 16) = lo;
+    }
+  __syncthreads();
+  // a lane's k = 16 h + 8 lk + i; the offsets of long sums are read again for every member
+  constexpr bool KEEP = H <= 4;
+  int ko[KEEP ? N : 1];
+#pragma unroll
+  for (int s = 0; s < N; ++s)
+    if constexpr (KEEP) ko[s] = koff[(s >> 3) * 16 + lk * 8 + (s & 7)];
+  const int M = g.Kp * g.Kpx, n_tiles = (g.n_win + 31) >> 5, share = g.share;
+  const unsigned plane = (unsigned)g.split_out * 16u;
+  float px[N];
+  const CNN_GLOBAL char* src = nullptr;            // the first image of the wavefront's next windows
+  int at = 0;                                      // the lane's first pixel, bytes from there
+  auto aim = [&](int t) {
+    const int b0 = fast_div(t * 32, g.by_win_img), w = min(t * 32 + lrow, g.n_win - 1);
+    const int b = fast_div(w, g.by_win_img), wi = w - b * g.win_img, wy = fast_div(wi, g.by_wp), wx = wi - wy * g.Wp;
+    src = (const CNN_GLOBAL char*)(g.in + (long long)b0 * g.in_stride);
+    at = ((b - b0) * (int)g.in_stride + wy * g.Kp * g.stride * g.Wi + wx * g.Kpx * g.stride_x) * 4;
+  };
+  auto fetch = [&](int d) {   // member d's pixels
+    const int dy = fast_div(d, g.by_kpx), dx = d - dy * g.Kpx;
+    const CNN_GLOBAL char* p = src + (unsigned)((dy * g.stride * g.Wi + dx * g.stride_x) * 4);
+    int a = at;
+    asm volatile("" : "+v"(a));   // (or the sums of it and every ko are kept too)
+#pragma unroll
+    for (int s = 0; s < N; ++s) px[s] = *(const CNN_GLOBAL float*)(p + (unsigned)(a + (KEEP ? ko[KEEP ? s : 0] : koff[(s >> 3) * 16 + lk * 8 + (s & 7)])));
+  };
+  const int step = gridDim.x * (share ? 1 : 4), d_first = share ? wave : 0, d_step = share ? 4 : 1;
+  int t = share ? (int)blockIdx.x : (int)blockIdx.x * 4 + wave;
+  if (t >= n_tiles) return;                        // (sharing wavefronts leave together)
+  aim(t);
+  fetch(d_first);
+  for (; t < n_tiles; t += step) {
+    v16f best[T];
+#pragma unroll
+    for (int m = 0; m < T; ++m)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) best[m][v] = -INFINITY;
+    for (int d = d_first; d < M; d += d_step) {
+      v8h xh[H], xl[H];
+      float most = 0.f;
+#pragma unroll
+      for (int s = 0; s < N; ++s) {
+        const float x = px[s] * (float)(1 << SPLIT_SHIFT);
+        most = fmaxf(most, fabsf(px[s]));
+        xh[s >> 3][s & 7] = (_Float16)x;
+        xl[s >> 3][s & 7] = (_Float16)(x - (float)xh[s >> 3][s & 7]);
+      }
+      const bool splits = !odd && !__any(most >= 3.99f || (most < 0x1p-14f && most > 0.f));
+      if (!splits) {   // (k beyond the last one count as zero on both sides)
+#pragma unroll
+        for (int m = 0; m < T; ++m) {
+          v16f acc;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+          for (int s = 0; s < N; ++s) {
+            const int k = (s >> 3) * 16 + lk * 8 + (s & 7);
+            const float w = lds_f[min(k, g.k_total - 1) * ROWS + m * 32 + lrow];
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(k < g.k_total ? w : 0.f, k < g.k_total ? px[s] : 0.f, acc, 0, 0, 0);
+          }
+#pragma unroll
+          for (int v = 0; v < 16; ++v) best[m][v] = fmaxf(best[m][v], ldexpf(acc[v], -lds_e[m * 32 + (v >> 2) * 8 + lk * 4 + (v & 3)]));
+        }
+      }
+      const bool last = d + d_step >= M;
+      if (last && t + step < n_tiles) aim(t + step);
+      fetch(last ? d_first : d + d_step);          // (behind the last windows: once more)
+      __builtin_amdgcn_sched_barrier(0);           // (the loads are not put off until their registers are free)
+      if (!splits) continue;
+#pragma unroll
+      for (int m = 0; m < T; ++m) {
+        if (m && j0 + m * 32 >= g.Mo) break;
+        const char* w = lds_h + m * H * 2048 + lane * 16;
+        v16f acc;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+        // the small products first: they are rounded to what they are, not to the whole sum
+        v8h wh[H];
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+          wh[h] = *(const v8h*)(w + h * 2048);
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wh[h], xl[h], acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(*(const v8h*)(w + h * 2048 + 1024), xh[h], acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int h = 0; h < H; ++h) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wh[h], xh[h], acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const float sum = __builtin_canonicalizef(acc[v]);
+          asm("v_max_f32 %0, %0, %1" : "+v"(best[m][v]) : "v"(sum));   // (as in pool_quad)
+        }
+      }
+    }
+    if (share) {
+      __syncthreads();   // the last windows' have been read
+#pragma unroll
+      for (int m = 0; m < T; ++m)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) ex[(wave * T + m) * 1024 + v * 64 + lane] = best[m][v];
+      __syncthreads();
+    }
+    // element v of a lane: map (v / 4) * 8 + lk * 4 + v % 4 of the tile
+    const int w = t * 32 + lrow;
+    int lk4 = lk * 4;
+    asm volatile("" : "+v"(lk4));
+#pragma unroll
+    for (int m = 0; m < T; ++m)
+#pragma unroll
+      for (int v4 = 0; v4 < 16; v4 += 4) {
+        const int first = m * 32 + v4 * 2, row = first + lk4;
+        if (j0 + first >= g.Mo) break;
+        if (share && (m * 4 + v4 / 4) % 4 != wave) continue;
+        const bool part = j0 + first + 8 > g.Mo;
+        float sv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          float x = best[m][v4 + u];
+          if (share)
+            for (int o = 0; o < 4; ++o) x = fmaxf(x, ex[(o * T + m) * 1024 + (v4 + u) * 64 + lane]);
+          sv[u] = b_act(ldexpf(x, lds_e[row + u]) + lds_b[row + u]);
+          if (part && j0 + row + u >= g.Mo) sv[u] = 0.f;   // (maps that fill the last group of eight up)
+        }
+        if (w < g.n_win)
+          put_split4((CNN_GLOBAL char*)g.out + (size_t)((unsigned)(j0 + first) >> 3) * 2 * plane, plane, (unsigned)w * 16u + (unsigned)lk4 * 2u, sv);
+      }
+  }
+}
+
+// ---- a convolutional layer behind another one, in products of halves --------------------------------------------
+// The product of k_batch_conv on v_mfma_f32_{32x32x16,16x16x32}_f16, which take sixteen times the terms a clock: both
+// operands are split into two halves (23 bits together), a = ah + al, and ah xh + ah xl + al xh summed in 32 bits; al xl is
+// below 2^-22 of the term.  An instruction adds its terms in groups of eight to the running sum, each group's sum rounded; so a
+// running sum ends after SPLIT_RUN groups and is added to the total, which keeps the error against 64 bits below that of the
+// 32-bit products.  The layer below has split its activations already
+// (put_split), in groups of eight maps, so that a lane's eight k are one 16-byte read from LDS: k = (group of eight maps, ky,
+// kx, map of the group).
+// Error against 64 bits (2-norm, of 64 images' outputs of a layer, 32-bit products / halves): 300C4 on 300 maps 5.7e-7 /
+// 3.3e-7, 300C2 4.0 / 2.2, 40C5 on 20 2.4 / 2.2, 128C3 on 50 2.4 / 2.2; without runs 8.8, 3.8, 2.9 and 3.0.
+// Staging as in k_batch_conv: the next slab of weights (a run of the k range, packed in the order it is read) and the next
+// chunk of input maps go to the other halves of their buffers by 16-byte loads to LDS while the present ones are multiplied,
+// one barrier a slab, nothing between two column blocks.
+// Bound by the issue of instructions beside the matrix pipes (40 % busy in 300C2) and by the waits of a slab; larger tiles, one
+// wavefront a SIMD, were slower (300C2: 128 x 256 columns 694 us of the pass, 64 x 256 543).  Against k_batch_conv, under the
+// tracer: 300C2 of 512 images 743 -> 235 us (305 TFLOP/s of the layer's own sums), 300C4 234 -> 98, 40C5 of 4096 digits 184 ->
+// 80, 128C3 of 33 stereo pairs 42 (with its k_batch_pool) -> 16.
+constexpr int SPLIT_RUN = 32;
+// wavefronts a SIMD, by the registers of sums, totals and two sets of columns
+constexpr int split_waves(int RT, int CT, int TR) {
+  const int regs = 2 * RT * CT * (TR == 32 ? 16 : 4) + 16 * CT + 48;
+  return regs <= 120 ? 4 : regs <= 136 ? 3 : 2;
+}
+template <int RT, int CT, int TR>
+__global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(BatchSplit g) {
+  extern __shared__ __align__(16) char lds_s[];
+  constexpr int S = TR == 32 ? 2 : 4;              // groups of eight k an instruction takes, one per 64 / S lanes
+  constexpr int AV = TR == 32 ? 16 : 4;            // accumulator floats per lane and tile
+  constexpr int ROWS = RT * TR, COLS = 4 * CT * TR, EPS = COLS + 4;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lrow = lane & (TR - 1), lk = lane / TR;
+  const int plane = g.run_px * 16;                 // bytes of a staged plane: eight maps' high or low halves
+  const int x_bytes = g.IC * 2 * plane, slab_bytes = g.slab * ROWS * 32;
+  char* lds_x = lds_s;
+  char* lds_w = lds_x + 2 * x_bytes;
+  int* koff = (int*)(lds_w + 2 * slab_bytes);      // byte offset of a (group, tap) pair from a column's first pixel
+  int* lds_e = koff + g.n_kg;                      // [ROWS] exponents
+  float* lds_b = (float*)(lds_e + ROWS);           // [ROWS] biases
+  float* ep = lds_b + ROWS;                        // [TR][EPS] where windows are pooled through LDS
+  const unsigned x_at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds_x;
+  const unsigned w_at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds_w;
+  const int KK = g.K * g.Kx;
+  for (int x = tid; x < g.n_kg; x += BT) {         // (pairs that fill an instruction up have no weights: a pixel that is read anyway)
+    const int k = min(x, g.IC * KK - 1), c = k / KK, t = k - c * KK, ky = t / g.Kx;
+    koff[x] = c * 2 * plane + (ky * g.Wi + t - ky * g.Kx) * 16;
+  }
+  const int j0 = blockIdx.y * ROWS;
+  bool slow = false;
+  for (int x = tid; x < ROWS; x += BT) {
+    const int e = g.exps[j0 + x];
+    lds_e[x] = e;
+    lds_b[x] = j0 + x < g.Mo ? g.bias[j0 + x] : 0.f;
+    slow |= e >= SPLIT_SLOW / 2;
+  }
+  slow = __syncthreads_or(slow);
+  const int n_chunks = g.n_cg / g.IC, slabs = (g.n_kg + g.slab - 1) / g.slab, M = g.Kp * g.Kpx;
+  const int run = min(SPLIT_RUN, n_chunks * g.n_kg / 2);
+  const CNN_GLOBAL char* wt = g.wt + (long long)blockIdx.y * n_chunks * g.n_kg * ROWS * 32;
+  // Pixels of the batch that block cb reads: from the first of its first window to the last of its last.  Staged in loads of 64
+  // pixels of a plane, whose last ones may reach past the block's (into memory of the call's: its end is 64 pixels off), and of
+  // 64 units of weights; a wavefront takes a run of them.
+  int x_first = 0, x_n = 0;
+  auto aim = [&](int cb) {
+    const int w0 = cb * g.wins, w1 = min(w0 + g.wins, g.n_win) - 1;
+    const int b0 = fast_div(w0, g.by_win_img), b1 = fast_div(w1, g.by_win_img);
+    const int i0 = w0 - b0 * g.win_img, i1 = w1 - b1 * g.win_img, y0 = fast_div(i0, g.by_wp), y1 = fast_div(i1, g.by_wp);
+    x_first = b0 * g.pix + y0 * g.Kp * g.stride * g.Wi + (i0 - y0 * g.Wp) * g.Kpx * g.stride_x;
+    x_n = b1 * g.pix + ((y1 * g.Kp + g.Kp - 1) * g.stride + g.K - 1) * g.Wi + ((i1 - y1 * g.Wp) * g.Kpx + g.Kpx - 1) * g.stride_x + g.Kx - x_first;
+  };
+  auto fetch_x = [&](int chunk, int buf) {
+    const CNN_GLOBAL char* src = g.in + (long long)chunk * g.IC * 2 * g.in_plane + (long long)x_first * 16;
+    const int per = (x_n + 63) >> 6, half = (per + 1) >> 1;
+    const bool halves = g.IC == 1;   // two planes: two wavefronts each
+    const int q = halves ? (wave & 1) * half : 0, n = halves ? min(half, per - q) : per;
+    for (int p = halves ? wave >> 1 : wave; p < g.IC * 2; p += 4)
+      lds_dma16_n(x_at + (unsigned)(buf * x_bytes + p * plane + q * 1024), src + p * g.in_plane, (unsigned)(q * 64 + lane) * 16u, n);
+  };
+  auto fetch_w = [&](int at, int n, int buf) {     // n pairs from pair `at` of the group's stream
+    const int loads = n * ROWS / 32, share = (loads + 3) >> 2, q = wave * share;
+    lds_dma16_n(w_at + (unsigned)(buf * slab_bytes + q * 1024), wt, (unsigned)(at * ROWS * 32 + (q * 64 + lane) * 16), min(share, loads - q));
+  };
+
+  typedef float accv __attribute__((ext_vector_type(AV)));
+  int xb = 0, wb = 0;
+  aim(blockIdx.x);
+  fetch_x(0, 0);
+  fetch_w(0, min(g.slab, g.n_kg), 0);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  for (int cb = blockIdx.x; cb < g.n_cb; cb += gridDim.x) {
+    const bool more = cb + (int)gridDim.x < g.n_cb;
+    const int first = x_first;
+    // the first pixel of the batch that column c reads (columns that are not there: the block's first)
+    auto column = [&](int c) {
+      const int wl = c / M, d = c - wl * M, w = cb * g.wins + wl;
+      if (wl >= g.wins || w >= g.n_win) return first;
+      const int b = fast_div(w, g.by_win_img);
+      const int wi = w - b * g.win_img, wy = fast_div(wi, g.by_wp), wx = wi - wy * g.Wp, dy = d / g.Kpx, dx = d - dy * g.Kpx;
+      return b * g.pix + (wy * g.Kp + dy) * g.stride * g.Wi + (wx * g.Kpx + dx) * g.stride_x;
+    };
+    int pbase[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) pbase[ct] = (column((wave * CT + ct) * TR + lrow) - first) * 16;
+    accv acc[RT][CT], tot[RT][CT];
+#pragma unroll
+    for (int m = 0; m < RT; ++m)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int v = 0; v < AV; ++v) acc[m][ct][v] = tot[m][ct][v] = 0.f;
+    int pairs = 0;
+    for (int ch = 0; ch < n_chunks; ++ch, xb ^= 1) {
+      for (int sl = 0; sl < slabs; ++sl, wb ^= 1) {
+        // slab and chunk have arrived (every wavefront has waited for its own loads), the other halves are read no more
+        __syncthreads();
+        const int at = ch * g.n_kg + sl * g.slab, here = min(g.slab, g.n_kg - sl * g.slab);
+        const bool last = ch + 1 == n_chunks;
+        if (sl + 1 < slabs) fetch_w(at + here, min(g.slab, g.n_kg - (sl + 1) * g.slab), wb ^ 1);
+        else if (!last || more) fetch_w(last ? 0 : at + here, min(g.slab, g.n_kg), wb ^ 1);
+        if (sl == 0) {
+          if (!last) fetch_x(ch + 1, xb ^ 1);
+          else if (more) { aim(cb + gridDim.x); fetch_x(0, xb ^ 1); }
+        }
+        // A step is one instruction's k.  The operands of the next tile of maps, and at the first tile the columns of the next
+        // step, are on their way from LDS while the present tile is multiplied.
+        const char* x_b = lds_x + xb * x_bytes;
+        const char* w_b = lds_w + wb * slab_bytes + (lk * 2 * ROWS + lrow) * 16;
+        const int* ko = koff + sl * g.slab + lk;
+        const int steps = here / S;
+        v8h xh[2][CT], xl[2][CT], wh[2], wl[2];
+        auto load_x = [&](int set, int k) {
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) {
+            const char* p = x_b + (pbase[ct] + k);
+            xh[set][ct] = *(const v8h*)p;
+            xl[set][ct] = *(const v8h*)(p + plane);
+          }
+        };
+        auto load_w = [&](int set, const char* w, int m) {
+          wh[set] = *(const v8h*)(w + m * TR * 16);
+          wl[set] = *(const v8h*)(w + (ROWS + m * TR) * 16);
+        };
+        load_x(0, ko[0]);
+        load_w(0, w_b, 0);
+        int k_next = ko[steps > 1 ? S : 0];
+#define CNN355_MAC(a, x)                                                                                             \
+  _Pragma("unroll") for (int ct = 0; ct < CT; ++ct) {                                                                \
+    if constexpr (TR == 32) acc[m][ct] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, x[ct], acc[m][ct], 0, 0, 0);      \
+    else acc[m][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, x[ct], acc[m][ct], 0, 0, 0);                         \
+  }
+#define CNN355_STEP(P, st)                                                                                           \
+  {                                                                                                                  \
+    const char* w_next = w_b + (st + 1 < steps ? S * 2 * ROWS * 16 : 0);                                             \
+    _Pragma("unroll") for (int m = 0; m < RT; ++m) {                                                                 \
+      constexpr int odd = (P)*RT & 1;                                                                                \
+      const int set = (odd + m) & 1;                                                                                 \
+      if (m + 1 < RT) load_w(set ^ 1, w_b, m + 1);                                                                   \
+      else load_w(set ^ 1, w_next, 0);                                                                               \
+      if (m == 0) {                                                                                                  \
+        load_x((P) ^ 1, k_next);                                                                                     \
+        k_next = ko[min(st + 2, steps - 1) * S];                                                                     \
+      }                                                                                                              \
+      CNN355_MAC(wh[set], xh[P])                                                                                     \
+      CNN355_MAC(wh[set], xl[P])                                                                                     \
+      CNN355_MAC(wl[set], xh[P])                                                                                     \
+      __builtin_amdgcn_sched_barrier(0);                                                                             \
+    }                                                                                                                \
+    w_b = w_next;                                                                                                    \
+  }
+        for (int st = 0; st < steps; st += 2) {
+          CNN355_STEP(0, st)
+          if (st + 1 >= steps) break;
+          CNN355_STEP(1, st + 1)
+        }
+#undef CNN355_STEP
+#undef CNN355_MAC
+        pairs += here;
+        if (pairs >= run || (last && sl + 1 == slabs)) {
+          pairs = 0;
+#pragma unroll
+          for (int m = 0; m < RT; ++m)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+              for (int v = 0; v < AV; ++v) { tot[m][ct][v] += acc[m][ct][v]; acc[m][ct][v] = 0.f; }
+        }
+        // here and not behind the barrier: the wait would take in the stores of the results
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+    }
+    // element v of a lane, 32-row tiles: row (v / 4) * 8 + (lane / 32) * 4 + v % 4 of the tile, column lane % 32;
+    // 16-row tiles: row (lane / 16) * 4 + v, column lane % 16
+    // (worked out here: what depends on a row only would otherwise be kept in registers over all of the arithmetic)
+    int lk4 = lk * 4;
+    asm volatile("" : "+v"(lk4));
+    auto row_of = [&](int m, int v) { return m * TR + (TR == 32 ? (v >> 2) * 8 + lk4 + (v & 3) : lk4 + v); };
+    // the output of row r from a window's best sum times 2^-e
+    auto finish = [&](int r, float sv, int e) { return b_act(ldexpf(sv, e) + lds_b[r]); };
+    const unsigned plane_out = (unsigned)g.split_out * 16u;
+    auto store = [&](int w, int r, float out) {
+      const int j = j0 + r;
+      if (g.split_out) {   // (the last map brings the zeros that fill its group up)
+        const unsigned off = (unsigned)(j >> 3) * 2u * plane_out + (unsigned)w * 16u + (unsigned)(j & 7) * 2u;
+        put_split((CNN_GLOBAL char*)g.out, plane_out, off, out);
+        if (j == g.Mo - 1)
+          for (int u = 1; u < 8 - (j & 7); ++u) put_split((CNN_GLOBAL char*)g.out, plane_out, off + 2u * u, 0.f);
+        return;
+      }
+      const int b = fast_div(w, g.by_win_img);
+      (g.out + (long long)b * g.out_stride)[j * g.win_img + w - b * g.win_img] = out;
+    };
+    if (M == 1 || M == 4) {
+      const int q = M == 4 ? lane & 3 : 0;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        const int c = (wave * CT + ct) * TR + lrow;
+        const int w = cb * g.wins + (M == 4 ? c >> 2 : c);
+        const bool ok = w < g.n_win && (M == 4 ? c >> 2 : c) < g.wins;
+        const int b = ok ? fast_div(w, g.by_win_img) : 0, wi = ok ? w - b * g.win_img : 0;
+        const unsigned o0 = (unsigned)b * (unsigned)g.out_stride + (unsigned)wi;
+#pragma unroll
+        for (int m = 0; m < RT; ++m) {
+#pragma unroll
+          for (int v4 = 0; v4 < AV; v4 += 4) {   // four rows of a lane, eight (TR = 32) or sixteen of the tile
+            __builtin_amdgcn_sched_barrier(0);   // (fewer registers: the next rows' work stays behind this one's)
+            const int first = m * TR + v4 * 2, row = first + lk4;   // (TR = 16: v4 is 0)
+            if (j0 + first >= g.Mo) break;
+            const bool part = j0 + first + (TR == 32 ? 8 : 16) > g.Mo;
+            float sv[4];
+            if (M == 4) {
+              sv[0] = pool_quad(tot[m][ct][v4], tot[m][ct][v4 + 1], tot[m][ct][v4 + 2], tot[m][ct][v4 + 3], q);
+              sv[0] = finish(row + q, sv[0], lds_e[row + q]);
+            } else {
+#pragma unroll
+              for (int u = 0; u < 4; ++u) sv[u] = finish(row + u, tot[m][ct][v4 + u], lds_e[row + u]);
+            }
+            if (g.split_out) {   // groups of eight maps: maps behind the last one are zero
+              const unsigned off = (TR == 32 ? 0u : (unsigned)(lk4 >> 3) * 2u * plane_out) + (unsigned)w * 16u + (unsigned)(lk4 & 4) * 2u;
+              CNN_GLOBAL char* out = (CNN_GLOBAL char*)g.out + (size_t)((unsigned)(j0 + first) >> 3) * 2 * plane_out;
+              if (M == 4) {
+                if (part && j0 + row + q >= g.Mo) sv[0] = 0.f;
+                if (ok && (!part || j0 + row + q < ((g.Mo + 7) & ~7))) put_split(out, plane_out, off + (unsigned)q * 2u, sv[0]);
+              } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                  if (part && j0 + row + u >= g.Mo) sv[u] = 0.f;
+                if (ok && (!part || j0 + row < ((g.Mo + 7) & ~7))) put_split4(out, plane_out, off, sv);
+              }
+            } else if (M == 4) {
+              if (ok && j0 + row + q < g.Mo) g.out[o0 + (unsigned)(j0 + row + q) * (unsigned)g.win_img] = sv[0];
+            } else {
+#pragma unroll
+              for (int u = 0; u < 4; ++u)
+                if (ok && j0 + row + u < g.Mo) g.out[o0 + (unsigned)(j0 + row + u) * (unsigned)g.win_img] = sv[u];
+            }
+          }
+        }
+      }
+    } else {
+      // a thread's window stays its own for all rows it takes
+      const int rows = BT / g.wins, jr = tid / g.wins, wl = tid - jr * g.wins;
+      const int w = cb * g.wins + wl;
+      const bool ok = jr < rows && w < g.n_win;
+#pragma unroll
+      for (int m = 0; m < RT; ++m) {
+        __syncthreads();   // the previous tile has been read
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+          for (int v = 0; v < AV; ++v) ep[(row_of(0, v)) * EPS + (wave * CT + ct) * TR + lrow] = tot[m][ct][v];
+        __syncthreads();
+        if (ok)
+          for (int r = jr; r < TR; r += rows) {
+            if (j0 + m * TR + r >= g.Mo) break;
+            const float* win = ep + r * EPS + wl * M;
+            float best = -INFINITY;
+            for (int d = 0; d < M; ++d) best = fmaxf(best, win[d]);
+            store(w, m * TR + r, finish(m * TR + r, best, lds_e[m * TR + r]));
+          }
+      }
+    }
+    if (!slow) continue;
+    // rows with an infinite weight (infinity times both halves is no number): summed again, term by term, behind the stores above
+    __syncthreads();
+#pragma clang loop unroll(disable)
+    for (int r = 0; r < ROWS && j0 + r < g.Mo; ++r) {
+      if (lds_e[r] < SPLIT_SLOW / 2) continue;
+#pragma clang loop unroll(disable)
+      for (int wl = tid; wl < g.wins && cb * g.wins + wl < g.n_win; wl += BT) {
+        float best = -INFINITY, sum = 0.f;
+#pragma clang loop unroll(disable)
+        for (int d = 0; d < M; ++d) {
+          const int at = column(wl * M + d);
+          sum = 0.f;
+#pragma clang loop unroll(disable)
+          for (int x = 0; x < g.n_cg * KK; ++x) {
+            const int c = x / KK, t = x - c * KK, ky = t / g.Kx;
+            const CNN_GLOBAL char* xp = g.in + c * 2 * g.in_plane + (long long)(at + ky * g.Wi + t - ky * g.Kx) * 16;
+            const CNN_GLOBAL char* wp = wt + ((long long)(c / g.IC * g.n_kg + c % g.IC * KK + t) * 2 * ROWS + r) * 16;
+            const v8h xh = *(const CNN_GLOBAL v8h*)xp, xl = *(const CNN_GLOBAL v8h*)(xp + g.in_plane);
+            const v8h wh = *(const CNN_GLOBAL v8h*)wp, wl8 = *(const CNN_GLOBAL v8h*)(wp + ROWS * 16);
+            for (int i = 0; i < 8; ++i) sum = fmaf((float)wh[i] + (float)wl8[i], (float)xh[i] + (float)xl[i], sum);
+          }
+          best = fmaxf(best, sum);
+        }
+        store(cb * g.wins + wl, r, finish(r, M == 1 ? sum : best, lds_e[r] - SPLIT_SLOW));
+      }
+    }
+  }
+}
+
 // the planes of partial sums of one output, added in their order, up to eight loads in flight
 __device__ __forceinline__ float add_planes(cgf p, int n, long long stride) {
   if (n == 1) return 0.f + p[0];
@@ -654,9 +1232,95 @@ __global__ void __launch_bounds__(256) k_batch_outputs(cgf sums, int n_slices, l
 // the canonical weights are read, rows of Wt written.  Two launches a layer (clear, scatter) before: 10000 digits 38 us
 // of launches -> 5.
 constexpr int PK = 64, PJ = 32;
+// The slot of input map i in map j's row of a sparse table (the connections ascend), -1 where there is none
+__device__ __forceinline__ int table_slot(const BatchPack& q, int j, int i) {
+  int lo = q.csr_ptr[j], hi = q.csr_ptr[j + 1];
+  const int end = hi;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (q.csr_idx[mid] < i) lo = mid + 1; else hi = mid;
+  }
+  return lo < end && q.csr_idx[lo] == i ? lo : -1;
+}
+
+// Weights of k_batch_split: a wavefront finds the largest finite weight of a row, whose power of two brings the row below
+// 2^15; then the workgroup writes a piece of four rows in groups of eight k, high and low halves.  The pieces of a row find its
+// largest weight each for itself: with a workgroup to four whole rows 300 maps of 4800 weights took 45 us, so 10.
+constexpr int PACK_PIECE = 128;   // groups of eight k
+typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ void pack_split(const BatchPack& q, int* e4) {
+  const int KK = q.K * q.Kx, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int rows = (q.Mo + q.row - 1) / q.row * q.row, per_chunk = q.n_kg, total = q.n_chunks * per_chunk;
+  const int pieces = (total + PACK_PIECE - 1) / PACK_PIECE;
+  for (int job = blockIdx.x; job < rows / 4 * pieces; job += gridDim.x) {
+    const int tile = job / pieces, piece = job - tile * pieces;
+    const int jw = tile * 4 + wave;
+    float most = 0.f;
+    bool inf = false;
+    auto look = [&](float x) {
+      x = fabsf(x);
+      inf |= x == INFINITY;
+      most = fmaxf(most, x < INFINITY ? x : 0.f);
+    };
+    if (jw < q.Mo) {
+      const long long first = q.full_table ? (long long)jw * q.k_total : (long long)q.csr_ptr[jw] * KK;
+      const int n = q.full_table ? q.k_total : (q.csr_ptr[jw + 1] - q.csr_ptr[jw]) * KK;
+      const cgf w = q.w + first;
+      int x0 = 0;
+      for (; x0 + 256 <= n; x0 += 8 * 256) {
+        v4f v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (x0 + u * 256 + 256 <= n) v[u] = *(const CNN_GLOBAL v4u*)(w + x0 + u * 256 + lane * 4);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (x0 + u * 256 + 256 <= n)
+            for (int i = 0; i < 4; ++i) look(v[u][i]);
+      }
+      for (int x = (n & ~255) + lane; x < n; x += 64) look(w[x]);
+    }
+    for (int d = 32; d; d >>= 1) most = fmaxf(most, __shfl_xor(most, d));
+    int e = 0;
+    if (most > 0.f) { frexpf(most, &e); e = 15 - e; }   // (most = f 2^x, f below 1: below 2^15 then)
+    const int word = -(e + SPLIT_SHIFT) + (__any(inf) ? SPLIT_SLOW : 0);
+    __syncthreads();
+    if (lane == 0) { e4[wave] = e; q.exps[jw] = word; }
+    __syncthreads();
+    CNN_GLOBAL char* dst = (CNN_GLOBAL char*)q.wt + ((long long)(tile * 4 / q.row) * total * 2 * q.row + tile * 4 % q.row) * 16;
+    const int end = min(total, (piece + 1) * PACK_PIECE) * 4;
+    for (int u = piece * PACK_PIECE * 4 + threadIdx.x; u < end; u += 256) {
+      const int r = u & 3, x = u >> 2, ch = x / per_chunk, kg = x - ch * per_chunk, c = kg / KK, t = kg - c * KK, j = tile * 4 + r;
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int map = (ch * q.IC + c) * 8 + i;
+        v[i] = 0.f;
+        if (j < q.Mo && c < q.IC && map < q.Mi) {
+          if (q.full_table) v[i] = q.w[(long long)j * q.k_total + map * KK + t];
+          else {
+            const int slot = table_slot(q, j, map);
+            if (slot >= 0) v[i] = q.w[(long long)slot * KK + t];
+          }
+        }
+      }
+      v8h h, l;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float s = ldexpf(v[i], e4[r]);
+        h[i] = (_Float16)s;
+        l[i] = fabsf(s) < INFINITY ? (_Float16)(s - (float)h[i]) : (_Float16)0.f;
+      }
+      CNN_GLOBAL char* p = dst + ((long long)x * 2 * q.row + r) * 16;
+      *(CNN_GLOBAL v8h*)p = h;
+      *(CNN_GLOBAL v8h*)(p + q.row * 16) = l;
+    }
+  }
+}
+
 __global__ void __launch_bounds__(256) k_batch_pack(BatchPackAll all) {
   __shared__ float t[PJ][PK + 1];
   const BatchPack q = all.l[blockIdx.y];
+  if (q.exps) { pack_split(q, (int*)t); return; }
   const int KK = q.K * q.Kx, tk = (q.k_total + PK - 1) / PK;
   const int rows = (q.Mo + q.row - 1) / q.row * q.row, tiles = tk * ((rows + PJ - 1) / PJ);
   for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
@@ -669,14 +1333,9 @@ __global__ void __launch_bounds__(256) k_batch_pack(BatchPackAll all) {
       if (j < q.Mo && k < q.k_total) {
         if (q.full_table) {
           v = q.w[(long long)j * q.k_total + k];
-        } else {   // the slot of input map i among the row's connections, which ascend
-          int lo = q.csr_ptr[j], hi = q.csr_ptr[j + 1];
-          const int end = hi;
-          while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (q.csr_idx[mid] < i) lo = mid + 1; else hi = mid;
-          }
-          if (lo < end && q.csr_idx[lo] == i) v = q.w[(long long)lo * KK + (k - i * KK)];
+        } else {
+          const int slot = table_slot(q, j, i);
+          if (slot >= 0) v = q.w[(long long)slot * KK + (k - i * KK)];
         }
       }
       t[r][k - k0] = v;
@@ -772,6 +1431,76 @@ hipError_t launch_batch_conv(hipStream_t stream, const BatchConv& g) {
   }
 }
 
+// steps of 16 k that k_batch_first is compiled for, 0: more than that
+int batch_first_steps(int k_total) {
+  for (int H : {1, 2, 4, 5, 7})
+    if (k_total <= 16 * H) return H;
+  return 0;
+}
+size_t batch_first_lds_bytes(const BatchFirst& g) {
+  const size_t rows = (size_t)g.T * 32;
+  return (size_t)g.T * g.H * 2048 + (rows * g.k_total + rows * 2 + (size_t)16 * g.H + (g.share ? (size_t)4 * g.T * 1024 : 0)) * 4;
+}
+// workgroups a compute unit holds at once: registers, LDS
+int batch_first_fit(const BatchFirst& g) {
+  return std::max(1, std::min(first_waves(g.T, g.H), (int)(160 * 1024 / batch_first_lds_bytes(g))));
+}
+
+namespace {
+template <int T, int H>
+hipError_t launch_first(hipStream_t stream, const BatchFirst& g) {
+  const size_t lds_bytes = batch_first_lds_bytes(g);
+  hipError_t e = hipFuncSetAttribute((const void*)k_batch_first<T, H>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+  if (e != hipSuccess) return e;
+  const int groups = (g.Mo + T * 32 - 1) / (T * 32), wgs = (g.n_win + (g.share ? 31 : 127)) / (g.share ? 32 : 128);
+  hipLaunchKernelGGL((k_batch_first<T, H>), dim3((unsigned)std::min(wgs, std::max(1, 256 * batch_first_fit(g) / groups)), (unsigned)groups),
+                     dim3(BT), lds_bytes, stream, g);
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_batch_first(hipStream_t stream, const BatchFirst& g) {
+  if (g.n_win <= 0) return hipSuccess;
+#define CNN355_CASE(T_, H_) \
+  if (g.T == T_ && g.H == H_) return launch_first<T_, H_>(stream, g);
+  CNN355_CASE(1, 1) CNN355_CASE(2, 1) CNN355_CASE(5, 1) CNN355_CASE(1, 2) CNN355_CASE(2, 2) CNN355_CASE(5, 2)
+  CNN355_CASE(1, 4) CNN355_CASE(2, 4) CNN355_CASE(1, 5) CNN355_CASE(2, 5) CNN355_CASE(1, 7)
+#undef CNN355_CASE
+  return hipErrorInvalidValue;
+}
+
+size_t batch_split_lds_bytes(const BatchSplit& g) {
+  const int M = g.Kp * g.Kpx, rows = g.RT * g.TR, cols = 4 * g.CT * g.TR;
+  return 2 * (size_t)g.IC * 2 * g.run_px * 16 + 2 * (size_t)g.slab * rows * 32 + (size_t)g.n_kg * 4 + (size_t)rows * 8 +
+         (M == 1 || M == 4 ? 0 : (size_t)g.TR * (cols + 4) * 4);
+}
+// workgroups a compute unit holds at once: registers, LDS
+int batch_split_fit(const BatchSplit& g) {
+  return std::max(1, std::min(split_waves(g.RT, g.CT, g.TR), (int)(160 * 1024 / batch_split_lds_bytes(g))));
+}
+
+namespace {
+template <int RT, int CT, int TR>
+hipError_t launch_split(hipStream_t stream, const BatchSplit& g) {
+  const size_t lds_bytes = batch_split_lds_bytes(g);
+  hipError_t e = hipFuncSetAttribute((const void*)k_batch_split<RT, CT, TR>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+  if (e != hipSuccess) return e;
+  const int groups = (g.Mo + RT * TR - 1) / (RT * TR), gx = std::min(g.n_cb, std::max(1, 256 * batch_split_fit(g) / groups));
+  hipLaunchKernelGGL((k_batch_split<RT, CT, TR>), dim3((unsigned)gx, (unsigned)groups), dim3(BT), lds_bytes, stream, g);
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_batch_split(hipStream_t stream, const BatchSplit& g) {
+  if (g.n_win <= 0) return hipSuccess;
+#define CNN355_CASE(RT_, CT_, TR_) \
+  if (g.RT == RT_ && g.CT == CT_ && g.TR == TR_) return launch_split<RT_, CT_, TR_>(stream, g);
+  CNN355_CASE(1, 1, 32) CNN355_CASE(1, 2, 32) CNN355_CASE(2, 1, 32) CNN355_CASE(2, 2, 32)
+  CNN355_CASE(1, 2, 16) CNN355_CASE(1, 4, 16) CNN355_CASE(3, 2, 16) CNN355_CASE(3, 4, 16) CNN355_CASE(5, 2, 16) CNN355_CASE(7, 2, 16)
+#undef CNN355_CASE
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_batch_gemm(hipStream_t stream, const BatchGemm& g) {
   if (g.N <= 0) return hipSuccess;
   const size_t lds_bytes = batch_gemm_lds_bytes(g);
@@ -813,6 +1542,7 @@ hipError_t launch_batch_pack(hipStream_t stream, const BatchPackAll& all) {
   for (int l = 0; l < all.n; ++l) {
     const BatchPack& q = all.l[l];
     const long long rows = (q.Mo + q.row - 1) / q.row * (long long)q.row;
+    if (q.exps) { most = std::max(most, rows / 4 * ((q.n_chunks * q.n_kg + PACK_PIECE - 1) / PACK_PIECE)); continue; }
     most = std::max(most, (q.k_total + PK - 1) / PK * ((rows + PJ - 1) / PJ));
   }
   hipLaunchKernelGGL(k_batch_pack, dim3((unsigned)std::min(most, 4096ll), (unsigned)all.n), dim3(256), 0, stream, all);

@@ -299,6 +299,45 @@ struct BatchConv {
   int vec;                       // images and chunks start on 16 bytes: staged 16 bytes a lane
   int fuse;                      // 0: raw sums; 1: bias + scaled tanh; 2: bias only
 };
+// A convolutional layer behind another one, over a whole batch, in products of halves (k_batch_split).  Activations are
+// written by the layer below as v * 2^SPLIT_SHIFT = high + low, both halves, in groups of eight maps:
+// [group][high, low][pixel of the batch][8], so that what a block of columns reads of a group is one run; the maps that fill
+// the last group up are zero.
+constexpr int SPLIT_SHIFT = 14;         // |activation| <= 1.7159: below the largest half
+constexpr int SPLIT_SLOW = 0x4000;      // row exponent of a row with an infinite weight
+struct BatchSplit {
+  const CNN_GLOBAL char* in;
+  const CNN_GLOBAL char* wt;     // [group of RT * TR maps][chunk][n_kg][high, low][RT * TR][8] halves, w * 2^e of its row
+  const CNN_GLOBAL int* exps;    // [groups * RT * TR] -(e + SPLIT_SHIFT) of every map, or SPLIT_SLOW - (e + SPLIT_SHIFT)
+  const CNN_GLOBAL float* bias;  // [Mo]
+  CNN_GLOBAL float* out;         // as of BatchConv; split_out: as split halves
+  long long in_plane;            // bytes of a plane of the input: 16 a pixel of the batch
+  long long out_stride;          // floats an image
+  int n_cg;                      // groups of eight input maps
+  int pix, Wi, K, Kx, stride, stride_x, Mo;
+  int Kp, Kpx, Wp, win_img;      // pooling window (1 x 1: none); windows of one row of an image, of an image
+  FastDiv by_win_img, by_wp;
+  int wins, n_win, n_cb;         // windows of a column block, of the whole batch; column blocks
+  int IC, run_px;                // groups of input maps of a chunk (a divisor of n_cg); pixels a block can touch, in whole loads of 64
+  int n_kg, slab;                // (group, tap) pairs of a chunk and of a slab of weights, multiples of what an instruction takes
+  int RT, CT, TR;                // tiles of TR maps a workgroup, tiles of TR columns a wavefront
+  int split_out;                 // pixels of the output's planes; 0: as floats
+};
+// The first convolutional layer below such a one (k_batch_first): windows of the whole batch, sums of up to 16 H terms.
+struct BatchFirst {
+  const CNN_GLOBAL float* in;    // [batch] images of [Mi][Hi][Wi], in_stride floats apart
+  const CNN_GLOBAL float* wt;    // [k_total][row], row a multiple of 16
+  const CNN_GLOBAL float* bias;  // [Mo]
+  CNN_GLOBAL float* out;         // split halves
+  long long in_stride;
+  int Hi, Wi, K, Kx, stride, stride_x, Mo;
+  int Kp, Kpx, Wp, win_img;      // pooling window (1 x 1: none); windows of one row of an image, of an image
+  FastDiv by_win_img, by_wp, by_kpx;
+  int n_win, k_total, row;
+  int T, H;                      // tiles of 32 maps a workgroup (0: the layer is not planned so); steps of 16 k
+  int share;                     // 1: four wavefronts share the members of 32 windows
+  int split_out;                 // pixels of the output's planes
+};
 struct BatchPool {
   const CNN_GLOBAL float* sums;  // [batch][Mo][Ho][Wo] raw sums
   const CNN_GLOBAL float* bias;
@@ -315,6 +354,8 @@ struct BatchPack {
   const CNN_GLOBAL int* csr_idx;
   int full_table, Mo, K, Kx;     // (a fully connected layer: full, K = Kx = 1)
   int row, k_total;              // maps of a group of Wt, rows of it
+  CNN_GLOBAL int* exps;          // split halves (BatchSplit) where not null, with
+  int Mi, n_chunks, IC, n_kg;
 };
 struct BatchPackAll {
   int n;

@@ -1,0 +1,39 @@
+"""Host logic of the products of halves in the batched pass (no GPU): which layers take them, and what they take of memory,
+over the benchmark networks and seeded random ones, from one image to thousands."""
+import pytest
+
+from paper_1102_0183_amd import binding, synth
+from tests.test_batch_plan_host import ARCHS, BATCHES, LDS
+
+
+@pytest.mark.parametrize("arch", ARCHS)
+def test_products_of_halves_fit_and_take_no_more_scratch_memory(arch):
+    """A caller whose scratch memory was enough for a batch with 32-bit products goes on with it; halves only behind a layer that
+    writes them, and only before a layer that reads them."""
+    for batch in BATCHES:
+        layers, whole = binding.batch_plan(arch, batch)
+        assert whole["floats"] <= whole["floats_32"], batch
+        for l, p in enumerate(layers):
+            where = (batch, l, p)
+            if p["first"]:
+                assert l == 0 and layers[1]["split"] and p["Mi"] * p["KK"] <= 16 * p["first_H"] and p["first_lds"] <= LDS, where
+            if p["split"]:
+                below = layers[l - 1]
+                assert l > 0 and (below["split"] or below["first"]), where
+                groups = -(-p["Mi"] // 8)
+                step = 2 if p["split_TR"] == 32 else 4
+                assert groups % p["split_IC"] == 0 and p["split_lds"] <= LDS, where
+                assert p["split_kg"] == -(-p["split_IC"] * p["KK"] // step) * step and p["split_slab"] % step == 0, where
+                assert 0 < p["split_slab"] <= p["split_kg"] and p["split_px"] % 64 == 0, where
+
+
+@pytest.mark.parametrize("name,batch,layers", [("cfg2a", 4096, 2), ("cfg3", 33, 2), ("cfg4a", 512, 3), ("cfg4b", 512, 3)])
+def test_the_benchmark_networks_take_them(name, batch, layers):
+    plan, _ = binding.batch_plan(synth.WORKLOADS[name].arch, batch)
+    assert plan[0]["first"] and [p["split"] for p in plan[:layers]] == [0] + [1] * (layers - 1)
+
+
+def test_single_images_keep_the_32_bit_products():
+    """Their layers are launches and waits, whichever the kernel; measured up to 1.2 times as slow in halves."""
+    for arch in ("1x13x13-100C2-MP1-5C4S1-MP1-4N", "2x21x21-100C1-MP1-150C2S1-MP1-4N", "3x53x53-100C2-MP1-40C1S1-MP1-4N"):
+        assert not any(p["split"] or p["first"] for p in binding.batch_plan(arch, 1)[0])

@@ -1,0 +1,193 @@
+"""The batched pass's products of halves (k_batch_first, k_batch_split) at the edges of their tiles, windows, chunks and
+slabs, and on pixels and weights that do not split into halves, against the oracle or 64-bit sums."""
+import numpy as np
+import pytest
+
+from paper_1102_0183_amd import binding, synth
+from tests.parity_helpers import build_pair, to_dev
+from tests.test_gpu_batch import _check_layers, _scratch
+
+pytestmark = pytest.mark.gpu
+
+# (arch, batch, tiles of the second layer: RT, CT, TR, members of its window, several chunks, several slabs a chunk)
+TILES = [
+    ("3x22x22-33C3-MP2-16C1S1-MP1-4N", 7, 1, 1, 32, 1, True, False),
+    ("4x15x15-8C4-MP2-17C5-MP2-4N", 33, 1, 1, 32, 4, False, False),
+    ("2x30x30-70C1-MP3-17C1-MP5-4N", 7, 1, 1, 32, 25, False, False),
+    ("2x13x13-70C4-MP2-5C3-MP1-4N", 7, 1, 2, 16, 1, False, True),
+    ("3x26x26-20C5-MP2-5C4S1-MP2-4N", 7, 1, 2, 16, 4, True, False),
+    ("2x14x14-40C4-MP1-5C1S1-MP3-4N", 7, 1, 2, 16, 9, False, False),
+    ("1x28x28-20C1-MP2-17C1-MP2-4N", 600, 1, 2, 32, 4, False, False),
+    ("2x36x36-17C4-MP1-31C1-MP3-4N", 33, 1, 2, 32, 9, False, False),
+    ("2x39x39-33C1-MP1-5C1-MP1-4N", 33, 1, 4, 16, 1, False, False),
+    ("1x14x14-33C5-MP2-112C2-MP2-4N", 300, 1, 4, 16, 4, False, True),
+    ("1x38x38-70C4-MP1-16C1-MP5-4N", 33, 1, 4, 16, 25, True, False),
+    ("3x13x13-33C3-MP1-40C1S1-MP1-4N", 33, 2, 1, 32, 1, False, True),
+    ("3x28x28-8C1-MP2-100C4S1-MP2-4N", 7, 2, 1, 32, 4, False, False),
+    ("3x15x15-40C5-MP1-40C1S1-MP3-4N", 33, 2, 1, 32, 9, True, False),
+    ("3x32x32-3C5-MP1-40C1-MP1-4N", 130, 2, 2, 32, 1, False, False),
+    ("1x24x24-50C3-MP1-48C1-MP2-4N", 130, 2, 2, 32, 4, False, True),
+    ("2x10x10-20C1-MP1-40C3S1-MP2-4N", 7, 3, 2, 16, 4, False, True),
+    ("4x10x10-70C1-MP2-40C1S1-MP3-4N", 33, 3, 2, 16, 9, True, False),
+    ("3x39x39-3C2-MP2-48C2-MP1-4N", 300, 3, 4, 16, 1, False, False),
+    ("2x19x19-17C5-MP1-40C2-MP2-4N", 600, 3, 4, 16, 4, True, False),
+    ("1x17x17-3C4-MP1-150C1S1-MP1-4N", 600, 5, 2, 16, 1, False, False),
+    ("2x30x30-3C2-MP1-80C2-MP2-4N", 130, 5, 2, 16, 4, False, False),
+    ("1x39x39-17C2-MP2-100C1S1-MP1-4N", 300, 7, 2, 16, 1, False, False),
+    ("1x31x31-6C4-MP1-112C5S1-MP2-4N", 130, 7, 2, 16, 4, False, True),
+]
+
+
+@pytest.mark.parametrize("arch,batch,RT,CT,TR,members,chunks,slabs", TILES)
+def test_every_tile_of_the_products_of_halves(arch, batch, RT, CT, TR, members, chunks, slabs):
+    """Both convolutional layers of a batch, as planned (a planner that no longer picks the tile fails here first), against
+    the oracle, and the outputs with a ragged second batch against the one-image path."""
+    import torch
+    print("case", arch, batch, flush=True)
+    p = binding.batch_plan(arch, batch)[0]
+    h = p[1]
+    assert p[0]["first"] and h["split"] and (h["split_RT"], h["split_CT"], h["split_TR"]) == (RT, CT, TR), p[:2]
+    assert int(arch.split("MP")[2].split("-")[0]) ** 2 == members
+    assert (-(-p[1]["Mi"] // 8) > h["split_IC"], h["split_kg"] > h["split_slab"]) == (chunks, slabs), h
+    n = batch + batch // 2 + 1
+    g, o = build_pair(arch=arch, wscale=0.2)
+    imgs = (np.random.default_rng(6).random((n, g.image_size)) * 2 - 1).astype(np.float32)
+    d_imgs = to_dev(imgs)
+    _check_layers(g, o, d_imgs, imgs, batch, sorted({0, 1, batch // 2, batch - 1}), [0, 1])
+    probs = torch.full((n * g.num_classes,), -1.0, dtype=torch.float32, device="cuda:0")
+    g.forward_batch(d_imgs, n, probs, _scratch(g, batch), batch)
+    one = torch.empty(n * g.num_classes, dtype=torch.float32, device="cuda:0")
+    g.forward_many(d_imgs, n, one)
+    g.synchronize()
+    assert (probs - one).abs().max().item() <= 1e-5
+    g.close()
+
+
+# (arch, batch, tiles and steps of the first layer: T, H, whether wavefronts share windows)
+FIRST = [
+    ("1x11x11-8C4-MP1-112C5-MP2-4N", 7, 1, 1, 0), ("2x21x21-6C1-MP3-112C5-MP3-4N", 7, 1, 1, 1),
+    ("2x10x10-20C4-MP1-5C5-MP3-4N", 7, 1, 2, 0), ("1x16x16-33C5-MP2-112C3-MP1-4N", 7, 1, 2, 1),
+    ("2x11x11-17C5-MP1-112C3-MP5-4N", 7, 1, 4, 0), ("4x11x11-33C4-MP2-112C2-MP1-4N", 7, 1, 4, 1),
+    ("3x13x13-17C5-MP1-80C5-MP1-4N", 7, 1, 5, 0), ("3x16x16-40C5-MP2-128C2S1-MP3-4N", 7, 1, 5, 1),
+    ("4x11x11-50C5-MP1-128C2-MP2-4N", 7, 1, 7, 0), ("4x18x18-50C5-MP2-48C2-MP2-4N", 33, 1, 7, 1),
+    ("2x28x28-33C2-MP1-48C3S1-MP1-4N", 33, 2, 1, 0), ("1x39x39-33C4-MP2-5C4-MP3-4N", 33, 2, 1, 1),
+    ("2x31x31-33C4-MP1-16C3-MP1-4N", 33, 2, 2, 0), ("2x29x29-33C3-MP3-48C4-MP1-4N", 130, 2, 2, 1),
+    ("2x17x17-33C5-MP1-48C4-MP2-4N", 130, 2, 4, 0), ("2x34x34-33C5-MP2-80C2-MP1-4N", 33, 2, 4, 1),
+    ("3x18x18-33C5-MP1-31C3-MP3-4N", 130, 2, 5, 0), ("3x22x22-40C5-MP3-40C5-MP1-4N", 300, 2, 5, 1),
+    ("3x14x14-70C1-MP1-5C5-MP5-4N", 130, 5, 1, 0), ("2x29x29-70C3-MP1-31C3-MP1-4N", 33, 5, 2, 0),
+]
+
+
+@pytest.mark.parametrize("arch,batch,T,H,share", FIRST)
+def test_every_tile_of_the_first_layer(arch, batch, T, H, share):
+    """The first layer as planned against the oracle, its images as they are, a thousandth and a thousand times them (products of
+    halves, the same of small halves, 32-bit products).  Tolerance: the parity bar, and the rounding of a sum of k terms of 0.2 times
+    the images' scale, k 2^-24 of them, under the activation's slope of 1.15."""
+    print("case", arch, batch, flush=True)
+    p = binding.batch_plan(arch, batch)[0][0]
+    assert p["first"] and (p["first_T"], p["first_H"], p["first_share"]) == (T, H, share), p
+    g, o = build_pair(arch=arch, wscale=0.2)
+    imgs = (np.random.default_rng(7).random((batch, g.image_size)) * 2 - 1).astype(np.float32)
+    k = int(arch.split("x")[0]) * int(arch.split("C")[1].split("-")[0].split("S")[0]) ** 2
+    for scale in (1.0, 1e-3, 1e3):
+        x = (imgs * np.float32(scale)).astype(np.float32)
+        got = g.debug_forward_batch_layer(to_dev(x), batch, 0, _scratch(g, batch)).astype(np.float64)
+        for i in sorted({0, batch // 2, batch - 1}):
+            o.forward(x[i])
+            want = np.asarray(o.activation(2), dtype=np.float64).ravel()
+            assert np.abs(got[i] - want).max() <= max(1e-5 * np.abs(want).max(), 1.15 * k * 0.2 * scale * 2.0 ** -24), (scale, i)
+    g.close()
+
+
+def test_every_tile_is_reached():
+    assert {t[2:5] for t in TILES} == {(1, 1, 32), (1, 2, 32), (2, 1, 32), (2, 2, 32), (1, 2, 16), (1, 4, 16), (3, 2, 16), (3, 4, 16),
+                                      (5, 2, 16), (7, 2, 16)}
+    assert {t[2:4] for t in FIRST} == {(1, 1), (2, 1), (5, 1), (1, 2), (2, 2), (5, 2), (1, 4), (2, 4), (1, 5), (2, 5), (1, 7)}
+
+
+def _layer(x, w, b, pool):
+    """Convolution, largest of the numbers of a window (none: -inf) and activation in 64 bits; w [M][Mi][K][K]."""
+    n, _, h, _ = x.shape
+    M, Mi, K, _ = w.shape
+    ho = h - K + 1
+    y = np.zeros((n, M, ho, ho))
+    with np.errstate(all="ignore"):
+        for i in range(Mi):
+            for ky in range(K):
+                for kx in range(K):
+                    y += w[None, :, i, ky, kx, None, None] * x[:, None, i, ky:ky + ho, kx:kx + ho]
+        q = ho // pool
+        y = y.reshape(n, M, q, pool, q, pool).transpose(0, 1, 2, 4, 3, 5).reshape(n, M, q, q, -1)
+        y = np.fmax.reduce(y, axis=-1)
+        y = np.where(np.isnan(y), -np.inf, y) + b[None, :, None, None]
+        return 1.7159 * np.tanh(0.6666 * y)
+
+
+M1, M2, SIDE = 36, 44, 26
+ARCH = "2x%dx%d-%dC3-MP2-%dC3-MP2-4N" % (SIDE, SIDE, M1, M2)
+
+
+def _net(edit=None, seed=3):
+    """The network (weights in canonical order: a layer's biases, then its connections) and its layers' parameters in 64 bits."""
+    g = binding.Cnn(ARCH)
+    w = ((np.random.default_rng(seed).random(g.num_weights) - 0.5) * 0.4).astype(np.float32)
+    n1, n2 = M1 * 2 * 9, M2 * M1 * 9
+    shapes = [(M1,), (M1, 2, 3, 3), (M2,), (M2, M1, 3, 3)]
+    at = np.cumsum([0, M1, n1, M2, n2])
+    b1, w1, b2, w2 = [w[at[k]:at[k + 1]].reshape(shapes[k]) for k in range(4)]
+    if edit is not None:
+        edit(w1, w2)
+    g.set_weights(w)
+    return (g,) + tuple(p.astype(np.float64) for p in (w1, b1, w2, b2))
+
+
+def _check(g, w1, b1, w2, b2, imgs):
+    n = len(imgs)
+    p = binding.batch_plan(ARCH, n)[0]
+    assert p[0]["first"] and p[1]["split"]
+    d = to_dev(imgs.reshape(n, -1))
+    scratch = _scratch(g, n)
+    first = g.debug_forward_batch_layer(d, n, 0, scratch).reshape(n, M1, 12, 12)
+    want = _layer(imgs.astype(np.float64), w1, b1, 2)
+    assert np.array_equal(np.isnan(first), np.isnan(want))
+    assert np.nanmax(np.abs(first - want)) <= 1e-5 * 1.7159
+    second = g.debug_forward_batch_layer(d, n, 1, scratch).reshape(n, M2, 5, 5)
+    want = _layer(first.astype(np.float64), w2, b2, 2)      # (from the first layer's outputs as they are)
+    assert np.array_equal(np.isnan(second), np.isnan(want))
+    assert np.nanmax(np.abs(second - want)) <= 1e-5 * 1.7159
+    g.close()
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 1e30, -7.0, 3.98, 4.0, 65504.0, 1e-30])
+def test_pixels_that_do_not_split(value):
+    """Single pixels, and a whole image, of every kind that leaves the products of halves, beside images that do not."""
+    imgs = (np.random.default_rng(11).random((40, 2, SIDE, SIDE)) * 2 - 1).astype(np.float32)
+    imgs[3, 0, 7, 9] = value
+    imgs[17, 1, 0, 0] = value
+    imgs[39, 1, SIDE - 1, SIDE - 1] = value
+    imgs[20] = value
+    _check(*_net(), imgs)
+
+
+def test_small_and_empty_images():
+    imgs = (np.random.default_rng(12).random((40, 2, SIDE, SIDE)) * 2 - 1).astype(np.float32)
+    imgs[1] = 0
+    imgs[2] *= 1e-6
+    imgs[3, :, 5:, :] = 0
+    imgs[4, :, :10] *= 1e-5
+    _check(*_net(), imgs)
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 1e30, 1e-30, 0.0])
+def test_weights_that_do_not_split(value):
+    """One weight, and a whole row, of either layer."""
+    imgs = (np.random.default_rng(13).random((40, 2, SIDE, SIDE)) * 2 - 1).astype(np.float32)
+
+    def edit(w1, w2):
+        w1[3, 1, 2, 0] = value
+        w2[5, M1 - 1, 2, 1] = value
+        w2[M2 - 1, 0, 0, 0] = value
+        if not np.isinf(value):
+            w1[M1 - 1] = value
+            w2[11] = value
+    _check(*_net(edit), imgs)

@@ -52,6 +52,7 @@ hipError_t launch_batch_first(hipStream_t stream, const BatchFirst& g);
 size_t batch_split_lds_bytes(const BatchSplit& g);
 int batch_split_fit(const BatchSplit& g);
 hipError_t launch_batch_split(hipStream_t stream, const BatchSplit& g);
+hipError_t launch_batch_tail(hipStream_t stream, const BatchTail& g);
 hipError_t launch_batch_pool(hipStream_t stream, const BatchPool& q);
 hipError_t launch_batch_outputs(hipStream_t stream, const float* sums, int n_slices, long long slice_stride, const float* bias,
                                 float* probs, long long n_images, int n_classes, int out_units);
@@ -1394,10 +1395,11 @@ struct BatchStep {
   size_t wt_floats = 0;
   size_t out_per_image = 0;   // floats an image in the layer's buffer
   bool split_out = false;     // outputs as split halves, for the next layer's product
-  bool raw() const { return f.T == 0 && s.RT == 0 && (c.MT ? c.fuse : g.fuse) == 0; }
+  bool raw() const { return s.RT ? s.raw : f.T == 0 && (c.MT ? c.fuse : g.fuse) == 0; }
 };
 struct BatchPlan {
   std::vector<BatchStep> steps;
+  bool tail = false;   // the last two layers are k_batch_tail's (the first of them up to its sums)
   size_t wt_total = 0, sums_per_image = 0, act_per_image[2] = {0, 0}, fe_per_image = 0;   // (layers take the two buffers in turn)
   size_t floats(size_t batch) const {
     return wt_total + batch * (sums_per_image + act_per_image[0] + act_per_image[1] + fe_per_image) + 4 * 64;
@@ -1519,10 +1521,10 @@ void conv_plan(const LayerDev& L, const BatchGemm& g, size_t batch, BatchConv& c
 // matrix pipes and LDS, and each waits for its own slabs.  The plan of the fewest clocks takes 0 to 6 % longer (of the pass
 // around the layer) than the fastest one.
 double split_clocks(const BatchSplit& t, size_t n_cb) {
-  const int S = t.TR == 32 ? 2 : 4, rows = t.RT * t.TR, cols = 4 * t.CT * t.TR, chunks = t.n_cg / t.IC;
+  const int S = t.TR == 32 ? 2 : 4, rows = t.RT * t.TR, cols = 4 * t.CT * t.TR, chunks = t.cps, slices = (t.n_cg / t.IC + t.cps - 1) / t.cps;
   const double steps = (double)chunks * (t.n_kg / S), slabs = (double)chunks * ((t.n_kg + t.slab - 1) / t.slab);
   const double matrix = steps * t.RT * t.CT * 3 * (t.TR == 32 ? 32 : 16), lds = steps * S * (rows + cols / 4);
-  const size_t groups = (size_t)((t.Mo + rows - 1) / rows), gx = std::min(n_cb, std::max<size_t>(1, 256 * batch_split_fit(t) / groups));
+  const size_t groups = (size_t)((t.Mo + rows - 1) / rows) * slices, gx = std::min(n_cb, std::max<size_t>(1, 256 * batch_split_fit(t) / groups));
   const double side = (double)((gx * groups + 255) / 256), rounds = (double)((n_cb + gx - 1) / gx);
   return rounds * std::max(side * (1.28 * matrix + 0.55 * lds + 263.0 * slabs + 60.0), 1.8 * matrix + 17.5 * steps + 1010.0 * slabs + 1330.0);
 }
@@ -1572,6 +1574,7 @@ double split_plan(const LayerDev& L, size_t batch, BatchSplit& out) {
         for (int ic = 1; ic <= t.n_cg; ++ic) {
           if (t.n_cg % ic) continue;
           t.IC = ic;
+          t.cps = t.n_cg / ic;
           t.n_kg = (ic * KK + S - 1) / S * S;
           for (int part = 1; part <= 8; ++part) {   // slabs of a chunk
             t.slab = ((t.n_kg + part - 1) / part + S - 1) / S * S;
@@ -1585,6 +1588,56 @@ double split_plan(const LayerDev& L, size_t batch, BatchSplit& out) {
       }
   if (out.RT) { out.by_win_img = fast_div_of(out.win_img); out.by_wp = fast_div_of(out.Wp); }
   return best;
+}
+
+// (group of maps, tap) pairs of a row that a workgroup of k_batch_pack turns into halves at a time.  Every piece of a row reads
+// the whole row for its scale.
+int split_piece(const BatchSplit& t) {
+  const int rows = t.RT * t.TR, tiles = (t.Mo + rows - 1) / rows * rows / 4, total = t.n_cg / t.IC * t.n_kg, pieces = std::max(1, 512 / tiles);
+  return std::max(128, (total + pieces - 1) / pieces);
+}
+
+// The plan of k_batch_split for a fully connected layer behind a layer of `maps` maps of `pix` pixels: as split_plan, and slices of
+// the k range, at most as many as the 32-bit product has.
+double fc_plan(const LayerDev& L, int maps, int pix, size_t batch, int most_slices, BatchSplit& out) {
+  constexpr size_t LDS = 160 * 1024;
+  BatchSplit t;
+  std::memset(&t, 0, sizeof(t));
+  out = t;
+  t.fc = 1; t.n_cg = (maps + 7) / 8 * pix; t.pix = pix; t.by_pix = fast_div_of(pix); t.Wi = t.K = t.Kx = t.stride = t.stride_x = 1;
+  t.Mo = L.n_out; t.Kp = t.Kpx = t.Wp = t.win_img = 1; t.bias = L.bias;
+  const size_t limit = (size_t)1 << 29, in_floats = (size_t)t.n_cg * 8;
+  // (weights that the L2 caches do not hold are read from memory once more for every piece: 600 rows of 134480 took 1.4 times as long)
+  if (L.is_output || (size_t)L.n_out * maps * pix > (size_t)1 << 23 || batch * in_floats >= limit || batch * (size_t)(L.n_out + 7) >= limit) return 0;
+  t.in_plane = (long long)batch * pix * 16;
+  t.slice_stride = (long long)(batch * (size_t)L.n_out);
+  double best = 0;
+  for (int tr : {32, 16})
+    for (int rt : {1, 2, 3, 5, 7})
+      for (int ct : {64 / tr, 32 / tr}) {
+        if (tr == 32 ? rt > 2 : rt == 2 || (rt > 3 && ct > 2)) continue;
+        const int rows = rt * tr, cols = 4 * ct * tr, S = tr == 32 ? 2 : 4, groups = (t.Mo + rows - 1) / rows;
+        if (groups > 1 && groups * rows - t.Mo >= rows / 2) continue;
+        t.RT = rt; t.CT = ct; t.TR = tr; t.wins = t.run_px = cols;
+        const size_t n_cb = (batch + cols - 1) / cols;
+        for (int ic = 1; ic <= std::min(t.n_cg, 48); ++ic) {
+          if (t.n_cg % ic) continue;
+          t.IC = ic;
+          t.n_kg = t.slab = (ic + S - 1) / S * S;
+          if (batch_split_lds_bytes(t) > LDS) break;
+          const int chunks = t.n_cg / ic;
+          for (int slices = 1; slices <= std::min(most_slices, chunks); slices *= 2) {
+            t.cps = (chunks + slices - 1) / slices;
+            t.raw = (chunks + t.cps - 1) / t.cps > 1;
+            const double est = split_clocks(t, n_cb) + (t.raw ? 1500.0 : 0.0);
+            if (best == 0 || est < best) { best = est; out = t; }
+          }
+        }
+      }
+  if (out.RT == 0) return 0;
+  out.by_win_img = out.by_wp = fast_div_of(1);
+  const int total = out.n_cg / out.IC * out.n_kg, piece = split_piece(out);
+  return best + 4.0 * L.n_out * maps * pix * ((total + piece - 1) / piece) / 1200.0;   // (a row is read once a piece)
 }
 
 // The plan of k_batch_first for the first layer, and its clocks of a compute unit: the vector instructions of all windows (the
@@ -1706,7 +1759,7 @@ int batch_plan_of(cnn* net, size_t batch, bool split, BatchPlan& B) {
     std::memset(&st.c, 0, sizeof(st.c));
     if (L.kind == L_CONV) conv_plan(L, g, batch, st.c);
     const BatchConv& c = st.c;
-    const int KSl = c.MT ? c.n_slices : g.KS;
+    int KSl = c.MT ? c.n_slices : g.KS;
     std::memset(&st.s, 0, sizeof(st.s));
     std::memset(&st.f, 0, sizeof(st.f));
     auto old_clocks = [&](const BatchStep& t) {
@@ -1738,6 +1791,19 @@ int batch_plan_of(cnn* net, size_t batch, bool split, BatchPlan& B) {
         below.f.T = 0;
       }
     }
+    if (split && L.kind != L_CONV && l > 0 && B.steps.back().s.RT) {
+      BatchStep& below = B.steps.back();
+      const LayerDev& prev = P.layers[l - 1];
+      const int maps = prev.kind == L_CONV ? prev.Mo : prev.n_out, pix = prev.kind == L_CONV ? prev.Hp * prev.Wp : 1;
+      const double est = below.raw() ? 0.0 : fc_plan(L, maps, pix, batch, g.KS, st.s);
+      if (st.s.RT == 0 || 0.8 * est + 2000.0 >= gemm_clocks(g, batch)) std::memset(&st.s, 0, sizeof(st.s));
+      else {
+        st.s.drop = g.fuse == 0;
+        below.split_out = true;
+        below.out_per_image = (size_t)st.s.n_cg * 8;
+        below.s.split_out = (int)(batch * (size_t)pix);
+      }
+    }
     const BatchSplit& h = st.s;
     const int h_rows = h.RT * h.TR, h_groups = h.RT ? (h.Mo + h_rows - 1) / h_rows : 0;
     st.wt_floats = h.RT ? up64((size_t)h_groups * h_rows * (h.n_cg / h.IC) * h.n_kg * 8) + up64((size_t)h_groups * h_rows) : up64((size_t)g.Mi * KK * (c.MT ? (size_t)(c.Mo + c.MT * c.TR - 1) / (c.MT * c.TR) * (c.MT * c.TR) : (size_t)g.MoPad));
@@ -1748,7 +1814,13 @@ int batch_plan_of(cnn* net, size_t batch, bool split, BatchPlan& B) {
     k.w = L.w; k.csr_ptr = L.csr_ptr; k.csr_idx = L.csr_idx;
     k.full_table = L.kind != L_CONV || L.full_table; k.Mo = g.Mo; k.K = g.K; k.Kx = g.Kx;
     k.row = h.RT ? h_rows : c.MT ? c.MT * c.TR : g.MoPad; k.k_total = g.Mi * KK;
-    k.Mi = g.Mi; k.n_chunks = h.RT ? h.n_cg / h.IC : 0; k.IC = h.IC; k.n_kg = h.n_kg;
+    k.Mi = g.Mi; k.n_chunks = h.RT ? h.n_cg / h.IC : 0; k.n_kg = h.n_kg; k.piece = h.RT ? split_piece(h) : 0; k.per_chunk = h.fc ? h.IC : h.IC * KK;
+    if (h.fc) {   // inputs are (map, pixel): a map's pixels are the taps of its kernel
+      const LayerDev& prev = P.layers[l - 1];
+      k.Mi = prev.kind == L_CONV ? prev.Mo : prev.n_out;
+      k.K = prev.kind == L_CONV ? prev.Hp : 1; k.Kx = prev.kind == L_CONV ? prev.Wp : 1;
+    }
+    if (h.RT) KSl = (h.n_cg / h.IC + h.cps - 1) / h.cps;
     BatchPool& q = st.pool;
     std::memset(&q, 0, sizeof(q));
     q.bias = L.bias; q.Mo = g.Mo; q.Ho = Ho; q.Wo = (L.kind == L_CONV) ? L.Wo : 1; q.Kp = Kp; q.Kpx = Kpx; q.Hp = Hp; q.Wp = Wp;
@@ -1756,9 +1828,14 @@ int batch_plan_of(cnn* net, size_t batch, bool split, BatchPlan& B) {
     st.out_per_image = pooled ? (size_t)g.Mo * Hp * Wp : (size_t)g.Mo * g.P;
     if (c.MT) { st.c.slice_stride = q.slice_stride; st.c.out_stride = (long long)c.Mo * c.win_img; }
     if (h.RT) st.s.out_stride = (long long)st.out_per_image;
+    if (h.fc) q.slice_stride = h.slice_stride;
     if (st.raw()) B.sums_per_image = std::max(B.sums_per_image, up64((size_t)KSl * g.Mo * (c.MT ? c.win_img : g.P)));
     // (the columns are the layer's pixels whenever fuse == 0 with pooling: pooling inside the product has fuse != 0)
     B.steps.push_back(st);
+  }
+  if (P.n_layers > 1 && P.layers[P.n_layers - 2].kind != L_CONV) {
+    const LayerDev &hidden = P.layers[P.n_layers - 2], &out = P.layers[P.n_layers - 1];
+    B.tail = out.is_output && out.kind != L_CONV && hidden.n_out <= TAIL_HIDDEN && out.n_out <= TAIL_OUT && hidden.n_out * out.n_out <= TAIL_WEIGHTS;
   }
   size_t act[2] = {0, 0};
   bool any = false;
@@ -2255,11 +2332,12 @@ int cnn355_batch_plan_text(const char* arch, int fan_in, size_t batch, char* buf
     }
     const BatchSplit& h = st.s;
     f.push_back({"split", h.RT != 0});
+    f.push_back({"split_fc", h.fc && h.RT});
     f.push_back({"first", st.f.T != 0});
     if (st.f.T) f.insert(f.end(), {{"first_T", st.f.T}, {"first_H", st.f.H}, {"first_share", st.f.share}, {"first_lds", (long long)batch_first_lds_bytes(st.f)}});
     if (h.RT)
       f.insert(f.end(), {{"split_RT", h.RT}, {"split_CT", h.CT}, {"split_TR", h.TR}, {"split_IC", h.IC}, {"split_kg", h.n_kg}, {"split_slab", h.slab},
-                         {"split_wins", h.wins}, {"split_px", h.run_px}, {"split_lds", (long long)batch_split_lds_bytes(h)}});
+                         {"split_slices", (h.n_cg / h.IC + h.cps - 1) / h.cps}, {"split_wins", h.wins}, {"split_px", h.run_px}, {"split_lds", (long long)batch_split_lds_bytes(h)}});
     t += "layer";
     for (const auto& kv : f) t += std::string(" ") + kv.first + " " + std::to_string(kv.second);
     t += "\n";
@@ -2268,7 +2346,7 @@ int cnn355_batch_plan_text(const char* arch, int fan_in, size_t batch, char* buf
   const bool add = last.raw() && outputs_add(tmp.prog.n_classes, last.pool.n_slices);
   BatchPlan B32;
   if ((rc = batch_plan_of(&tmp, batch, false, B32))) { g_err = tmp.err; return rc; }
-  t += "outputs_add " + std::to_string((int)add) + "\nfloats " + std::to_string(B.floats(batch)) + "\nfloats_32 " + std::to_string(B32.floats(batch)) + "\n";
+  t += "tail " + std::to_string((int)B.tail) + "\noutputs_add " + std::to_string((int)add) + "\nfloats " + std::to_string(B.floats(batch)) + "\nfloats_32 " + std::to_string(B32.floats(batch)) + "\n";
   if (t.size() + 1 > n) return fail(nullptr, CNN_E_ARG, "buffer too small for the plan text");
   std::memcpy(buf, t.c_str(), t.size() + 1);
   return CNN_OK;
@@ -2622,6 +2700,7 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
       in_stride = (long long)fe_sz;
     }
     int cur = 0;
+    bool done = false;
     const BatchPool* last_raw = nullptr;
     for (size_t s = 0; s < B.steps.size(); ++s) {
       BatchStep& st = B.steps[s];
@@ -2635,6 +2714,7 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
         BatchSplit h = st.s;
         h.in = (const char*)in; h.wt = (const char*)(base + st.wt_off); h.exps = pack.l[s].exps; h.out = out;
         h.n_win = (int)(nb * h.win_img); h.n_cb = (h.n_win + h.wins - 1) / h.wins;
+        if (h.raw) h.out = d_sums;
         HIP_TRY(net, launch_batch_split(net->stream, h));
       } else if (st.c.MT) {
         BatchConv c = st.c;
@@ -2653,10 +2733,22 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
         in = d_sums;
         break;
       }
-      if (raw) {
+      const bool tail = B.tail && s + 2 == B.steps.size() && tap_step < 0;
+      const bool add = tail && raw && st.pool.n_slices <= TAIL_SLICES;   // the planes are the last launch's too
+      if (raw && !add) {
         BatchPool q = st.pool;
         q.sums = d_sums; q.out = out; q.total = (long long)nb * q.Mo * q.Hp * q.Wp;
         HIP_TRY(net, launch_batch_pool(net->stream, q));
+      }
+      if (tail) {
+        const LayerDev& L = P.layers[P.n_layers - 1];
+        BatchTail t;
+        t.in = add ? d_sums : out; t.bias_h = add ? st.pool.bias : nullptr; t.w = L.w; t.bias = L.bias; t.out = d_probs + t0 * P.n_classes;
+        t.n = (long long)nb; t.slice_stride = st.pool.slice_stride; t.n_slices = add ? st.pool.n_slices : 1;
+        t.n_hidden = L.n_in; t.n_out = L.n_out; t.out_units = net->out_units; t.drop = B.steps.back().raw();
+        HIP_TRY(net, launch_batch_tail(net->stream, t));
+        done = true;
+        break;
       }
       in = out;
       in_stride = (long long)st.out_per_image;
@@ -2681,6 +2773,7 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
         return CNN_OK;
       }
     }
+    if (done) continue;
     HIP_TRY(net, launch_batch_outputs(net->stream, in, last_raw ? last_raw->n_slices : 1, last_raw ? last_raw->slice_stride : 0,
                                       last_raw ? (const float*)last_raw->bias : nullptr, d_probs + t0 * P.n_classes, (long long)nb,
                                       P.n_classes, net->out_units));

@@ -869,13 +869,17 @@ __global__ void __launch_bounds__(BT, first_waves(T, H)) k_batch_first(BatchFirs
 // wavefront a SIMD, were slower (300C2: 128 x 256 columns 694 us of the pass, 64 x 256 543).  Against k_batch_conv, under the
 // tracer: 300C2 of 512 images 743 -> 235 us (305 TFLOP/s of the layer's own sums), 300C4 234 -> 98, 40C5 of 4096 digits 184 ->
 // 80, 128C3 of 33 stereo pairs 42 (with its k_batch_pool) -> 16.
+// FC: a fully connected layer behind such a layer.  A column is an image, and a lane of a staging load fetches an image's eight
+// maps at one pixel (16 bytes a line of memory; neighbouring pixels follow in the same chunk and meet it in the caches); the k
+// range in slices where the images are few.  Against k_batch_gemm and its k_batch_pool: 150N of 4096 digits 30 us -> 14.3, 300N of
+// 512 images 27 -> 14.2, 100N of 33 stereo pairs 21.5 -> 8.4.
 constexpr int SPLIT_RUN = 32;
 // wavefronts a SIMD, by the registers of sums, totals and two sets of columns
 constexpr int split_waves(int RT, int CT, int TR) {
   const int regs = 2 * RT * CT * (TR == 32 ? 16 : 4) + 16 * CT + 48;
   return regs <= 120 ? 4 : regs <= 136 ? 3 : 2;
 }
-template <int RT, int CT, int TR>
+template <int RT, int CT, int TR, bool FC>
 __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(BatchSplit g) {
   extern __shared__ __align__(16) char lds_s[];
   constexpr int S = TR == 32 ? 2 : 4;              // groups of eight k an instruction takes, one per 64 / S lanes
@@ -894,7 +898,7 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
   float* ep = lds_b + ROWS;                        // [TR][EPS] where windows are pooled through LDS
   const unsigned x_at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds_x;
   const unsigned w_at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds_w;
-  const int KK = g.K * g.Kx;
+  const int KK = FC ? 1 : g.K * g.Kx;
   for (int x = tid; x < g.n_kg; x += BT) {         // (pairs that fill an instruction up have no weights: a pixel that is read anyway)
     const int k = min(x, g.IC * KK - 1), c = k / KK, t = k - c * KK, ky = t / g.Kx;
     koff[x] = c * 2 * plane + (ky * g.Wi + t - ky * g.Kx) * 16;
@@ -908,7 +912,8 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
     slow |= e >= SPLIT_SLOW / 2;
   }
   slow = __syncthreads_or(slow);
-  const int n_chunks = g.n_cg / g.IC, slabs = (g.n_kg + g.slab - 1) / g.slab, M = g.Kp * g.Kpx;
+  const int n_chunks = g.n_cg / g.IC, ch_first = FC ? blockIdx.z * g.cps : 0, ch_end = FC ? min(n_chunks, ch_first + g.cps) : n_chunks;
+  const int slabs = (g.n_kg + g.slab - 1) / g.slab, M = FC ? 1 : g.Kp * g.Kpx;
   const int run = min(SPLIT_RUN, n_chunks * g.n_kg / 2);
   const CNN_GLOBAL char* wt = g.wt + (long long)blockIdx.y * n_chunks * g.n_kg * ROWS * 32;
   // Pixels of the batch that block cb reads: from the first of its first window to the last of its last.  Staged in loads of 64
@@ -916,13 +921,27 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
   // 64 units of weights; a wavefront takes a run of them.
   int x_first = 0, x_n = 0;
   auto aim = [&](int cb) {
+    if constexpr (FC) {
+      x_first = cb * COLS * g.pix;
+      return;
+    }
     const int w0 = cb * g.wins, w1 = min(w0 + g.wins, g.n_win) - 1;
     const int b0 = fast_div(w0, g.by_win_img), b1 = fast_div(w1, g.by_win_img);
     const int i0 = w0 - b0 * g.win_img, i1 = w1 - b1 * g.win_img, y0 = fast_div(i0, g.by_wp), y1 = fast_div(i1, g.by_wp);
     x_first = b0 * g.pix + y0 * g.Kp * g.stride * g.Wi + (i0 - y0 * g.Wp) * g.Kpx * g.stride_x;
     x_n = b1 * g.pix + ((y1 * g.Kp + g.Kp - 1) * g.stride + g.K - 1) * g.Wi + ((i1 - y1 * g.Wp) * g.Kpx + g.Kpx - 1) * g.stride_x + g.Kx - x_first;
   };
+  unsigned image[FC ? COLS / 64 : 1];              // FC: the lane's images of a block, bytes from the first one
   auto fetch_x = [&](int chunk, int buf) {
+    if constexpr (FC) {
+      for (int p = wave; p < g.IC * 2; p += 4) {
+        const int vg = chunk * g.IC + (p >> 1), cg = fast_div(vg, g.by_pix);
+        const CNN_GLOBAL char* src = g.in + (long long)(cg * 2 + (p & 1)) * g.in_plane + (long long)(x_first + vg - cg * g.pix) * 16;
+#pragma unroll
+        for (int q = 0; q < COLS / 64; ++q) lds_dma16_runs<1>(x_at + (unsigned)(buf * x_bytes + p * plane + q * 1024), src, image[q]);
+      }
+      return;
+    }
     const CNN_GLOBAL char* src = g.in + (long long)chunk * g.IC * 2 * g.in_plane + (long long)x_first * 16;
     const int per = (x_n + 63) >> 6, half = (per + 1) >> 1;
     const bool halves = g.IC == 1;   // two planes: two wavefronts each
@@ -937,9 +956,14 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
 
   typedef float accv __attribute__((ext_vector_type(AV)));
   int xb = 0, wb = 0;
+  auto aim_lanes = [&](int cb) {                   // (behind the last image: that one)
+#pragma unroll
+    for (int q = 0; q < COLS / 64; ++q) image[q] = (unsigned)(min(q * 64 + lane, g.n_win - 1 - cb * COLS) * g.pix * 16);
+  };
+  if constexpr (FC) aim_lanes(blockIdx.x);
   aim(blockIdx.x);
-  fetch_x(0, 0);
-  fetch_w(0, min(g.slab, g.n_kg), 0);
+  fetch_x(ch_first, 0);
+  fetch_w(ch_first * g.n_kg, min(g.slab, g.n_kg), 0);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   for (int cb = blockIdx.x; cb < g.n_cb; cb += gridDim.x) {
     const bool more = cb + (int)gridDim.x < g.n_cb;
@@ -954,7 +978,10 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
     };
     int pbase[CT];
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) pbase[ct] = (column((wave * CT + ct) * TR + lrow) - first) * 16;
+    for (int ct = 0; ct < CT; ++ct) {
+      const int c = (wave * CT + ct) * TR + lrow;
+      pbase[ct] = (FC ? c : column(c) - first) * 16;
+    }
     accv acc[RT][CT], tot[RT][CT];
 #pragma unroll
     for (int m = 0; m < RT; ++m)
@@ -963,17 +990,21 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
 #pragma unroll
         for (int v = 0; v < AV; ++v) acc[m][ct][v] = tot[m][ct][v] = 0.f;
     int pairs = 0;
-    for (int ch = 0; ch < n_chunks; ++ch, xb ^= 1) {
+    for (int ch = ch_first; ch < ch_end; ++ch, xb ^= 1) {
       for (int sl = 0; sl < slabs; ++sl, wb ^= 1) {
         // slab and chunk have arrived (every wavefront has waited for its own loads), the other halves are read no more
         __syncthreads();
         const int at = ch * g.n_kg + sl * g.slab, here = min(g.slab, g.n_kg - sl * g.slab);
-        const bool last = ch + 1 == n_chunks;
+        const bool last = ch + 1 == ch_end;
         if (sl + 1 < slabs) fetch_w(at + here, min(g.slab, g.n_kg - (sl + 1) * g.slab), wb ^ 1);
-        else if (!last || more) fetch_w(last ? 0 : at + here, min(g.slab, g.n_kg), wb ^ 1);
+        else if (!last || more) fetch_w(last ? ch_first * g.n_kg : at + here, min(g.slab, g.n_kg), wb ^ 1);
         if (sl == 0) {
           if (!last) fetch_x(ch + 1, xb ^ 1);
-          else if (more) { aim(cb + gridDim.x); fetch_x(0, xb ^ 1); }
+          else if (more) {
+            if constexpr (FC) aim_lanes(cb + gridDim.x);
+            aim(cb + gridDim.x);
+            fetch_x(ch_first, xb ^ 1);
+          }
         }
         // A step is one instruction's k.  The operands of the next tile of maps, and at the first tile the columns of the next
         // step, are on their way from LDS while the present tile is multiplied.
@@ -1049,7 +1080,15 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
     asm volatile("" : "+v"(lk4));
     auto row_of = [&](int m, int v) { return m * TR + (TR == 32 ? (v >> 2) * 8 + lk4 + (v & 3) : lk4 + v); };
     // the output of row r from a window's best sum times 2^-e
-    auto finish = [&](int r, float sv, int e) { return b_act(ldexpf(sv, e) + lds_b[r]); };
+    auto finish = [&](int r, float sv, int e) {
+      sv = ldexpf(sv, e);
+      if constexpr (FC)
+        if (g.raw) return sv;
+      if constexpr (FC)
+        if (g.drop) sv = fmaxf(sv, -INFINITY);
+      return b_act(sv + lds_b[r]);
+    };
+    const gf out_z = FC ? g.out + (long long)blockIdx.z * g.slice_stride : g.out;
     const unsigned plane_out = (unsigned)g.split_out * 16u;
     auto store = [&](int w, int r, float out) {
       const int j = j0 + r;
@@ -1061,7 +1100,7 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
         return;
       }
       const int b = fast_div(w, g.by_win_img);
-      (g.out + (long long)b * g.out_stride)[j * g.win_img + w - b * g.win_img] = out;
+      (out_z + (long long)b * g.out_stride)[j * g.win_img + w - b * g.win_img] = out;
     };
     if (M == 1 || M == 4) {
       const int q = M == 4 ? lane & 3 : 0;
@@ -1101,11 +1140,11 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
                 if (ok && (!part || j0 + row < ((g.Mo + 7) & ~7))) put_split4(out, plane_out, off, sv);
               }
             } else if (M == 4) {
-              if (ok && j0 + row + q < g.Mo) g.out[o0 + (unsigned)(j0 + row + q) * (unsigned)g.win_img] = sv[0];
+              if (ok && j0 + row + q < g.Mo) out_z[o0 + (unsigned)(j0 + row + q) * (unsigned)g.win_img] = sv[0];
             } else {
 #pragma unroll
               for (int u = 0; u < 4; ++u)
-                if (ok && j0 + row + u < g.Mo) g.out[o0 + (unsigned)(j0 + row + u) * (unsigned)g.win_img] = sv[u];
+                if (ok && j0 + row + u < g.Mo) out_z[o0 + (unsigned)(j0 + row + u) * (unsigned)g.win_img] = sv[u];
             }
           }
         }
@@ -1147,9 +1186,10 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
           const int at = column(wl * M + d);
           sum = 0.f;
 #pragma clang loop unroll(disable)
-          for (int x = 0; x < g.n_cg * KK; ++x) {
-            const int c = x / KK, t = x - c * KK, ky = t / g.Kx;
-            const CNN_GLOBAL char* xp = g.in + c * 2 * g.in_plane + (long long)(at + ky * g.Wi + t - ky * g.Kx) * 16;
+          for (int x = ch_first * g.IC * KK; x < ch_end * g.IC * KK; ++x) {
+            const int c = x / KK, t = x - c * KK, ky = t / g.Kx, cg = FC ? fast_div(c, g.by_pix) : c;
+            const int px = FC ? c - cg * g.pix : ky * g.Wi + t - ky * g.Kx;
+            const CNN_GLOBAL char* xp = g.in + cg * 2 * g.in_plane + (long long)(at + px) * 16;
             const CNN_GLOBAL char* wp = wt + ((long long)(c / g.IC * g.n_kg + c % g.IC * KK + t) * 2 * ROWS + r) * 16;
             const v8h xh = *(const CNN_GLOBAL v8h*)xp, xl = *(const CNN_GLOBAL v8h*)(xp + g.in_plane);
             const v8h wh = *(const CNN_GLOBAL v8h*)wp, wl8 = *(const CNN_GLOBAL v8h*)(wp + ROWS * 16);
@@ -1227,6 +1267,110 @@ __global__ void __launch_bounds__(256) k_batch_outputs(cgf sums, int n_slices, l
   for (int k = 0; k < n_classes; ++k) o[k] = expf(v[k] - mx) / z;
 }
 
+// The last hidden layer's units (planes of sums added up, bias, scaled tanh, where they come as sums), the output layer and its
+// units: a wavefront an image, 64 U hidden neurons' places, the output layer's weights in LDS.  One launch for k_batch_pool,
+// k_batch_gemm, k_batch_pool and k_batch_outputs: 4096 digits 27.5 us -> 8.6, 512 images of 300 neurons 28 -> 9.7, 33 of 100 19 ->
+// 6.2.  Bound by the latency of its loads, which are under way together: the weights, and four planes of the wavefront's first
+// image (one after the other: 12.8, 20 and 8.5 us).
+template <int U>
+__global__ void __launch_bounds__(256) k_batch_tail(BatchTail g) {
+  extern __shared__ float lds[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n_w = g.n_out * g.n_hidden;
+  float* lds_b = lds + n_w;
+  float h[U], bias_h[U];
+  auto load = [&](long long b) {
+    const cgf p = g.in + b * g.n_hidden;
+    unsigned at[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) { at[u] = (unsigned)min(u * 64 + lane, g.n_hidden - 1); h[u] = 0.f; }
+    constexpr int Q = U > 8 ? 2 : 4;
+    int s = 0;
+    for (; s + Q <= g.n_slices; s += Q) {
+      float t[Q][U];
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int u = 0; u < U; ++u) t[q][u] = (p + (s + q) * g.slice_stride)[at[u]];
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int u = 0; u < U; ++u) h[u] += t[q][u];
+    }
+    for (; s < g.n_slices; ++s)
+#pragma unroll
+      for (int u = 0; u < U; ++u) h[u] += (p + s * g.slice_stride)[at[u]];
+  };
+  long long b = (long long)blockIdx.x * 4 + wave;
+#pragma unroll
+  for (int u = 0; u < U; ++u) bias_h[u] = g.bias_h ? g.bias_h[min(u * 64 + lane, g.n_hidden - 1)] : 0.f;
+  if (b < g.n) load(b);
+  int x = threadIdx.x;
+  for (; x + 1792 < n_w; x += 2048) {
+    float t[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t[u] = g.w[x + u * 256];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) lds[x + u * 256] = t[u];
+  }
+  float t[7];
+#pragma unroll
+  for (int u = 0; u < 7; ++u) t[u] = g.w[min(x + u * 256, n_w - 1)];
+#pragma unroll
+  for (int u = 0; u < 7; ++u)
+    if (x + u * 256 < n_w) lds[x + u * 256] = t[u];
+  if (threadIdx.x < g.n_out) lds_b[threadIdx.x] = g.bias[threadIdx.x];
+  __syncthreads();
+  int top = 32;                                    // lanes that hold outputs, halved
+  while (top > 1 && top >= g.n_out) top >>= 1;
+  for (; b < g.n; b += (long long)gridDim.x * 4) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (g.bias_h) h[u] = b_act(fmaxf(h[u], -INFINITY) + bias_h[u]);
+      if (u * 64 + lane >= g.n_hidden) h[u] = 0.f;
+    }
+    float mine = -INFINITY;
+    for (int k0 = 0; k0 < g.n_out; k0 += 8) {      // eight outputs' sums, halved over the lanes until lane 8 c + i has a part of sum c
+      float s[8];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const float* w = lds + min(k0 + c, g.n_out - 1) * g.n_hidden;
+        s[c] = 0.f;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const float v = w[min(u * 64 + lane, g.n_hidden - 1)];
+          s[c] = fmaf(h[u], u * 64 + lane < g.n_hidden ? v : 0.f, s[c]);
+        }
+      }
+#pragma unroll
+      for (int d = 4; d; d >>= 1) {
+        const bool up = lane & (d * 8);
+#pragma unroll
+        for (int c = 0; c < d; ++c) {
+          const float keep = up ? s[c + d] : s[c], give = up ? s[c] : s[c + d];
+          s[c] = keep + __shfl_xor(give, d * 8);
+        }
+      }
+#pragma unroll
+      for (int d = 4; d; d >>= 1) s[0] += __shfl_xor(s[0], d);
+      const float v = __shfl(s[0], (lane & 7) * 8);
+      if (lane >> 3 == k0 >> 3 && lane < g.n_out) mine = (g.drop ? fmaxf(v, -INFINITY) : v) + lds_b[lane];
+    }
+    float out = 0.f;
+    if (g.out_units == 1) out = b_act(mine);
+    else {
+      float most = mine;
+      for (int d = top; d; d >>= 1) most = fmaxf(most, __shfl_xor(most, d));
+      const float e = lane < g.n_out ? expf(mine - most) : 0.f;
+      float z = e;
+      for (int d = top; d; d >>= 1) z += __shfl_xor(z, d);
+      out = e / z;
+    }
+    if (lane < g.n_out) g.out[b * g.n_out + lane] = out;
+    if (b + (long long)gridDim.x * 4 < g.n) load(b + (long long)gridDim.x * 4);
+  }
+}
+
 // Wt[group of `row` maps][k][map] of every layer (blockIdx.y) from the canonical weights: k = (input map, ky, kx), j =
 // output map; absent connections and the padding maps are zero.  Tiles of 64 k x 32 maps, turned round in LDS: rows of
 // the canonical weights are read, rows of Wt written.  Two launches a layer (clear, scatter) before: 10000 digits 38 us
@@ -1246,12 +1390,11 @@ __device__ __forceinline__ int table_slot(const BatchPack& q, int j, int i) {
 // Weights of k_batch_split: a wavefront finds the largest finite weight of a row, whose power of two brings the row below
 // 2^15; then the workgroup writes a piece of four rows in groups of eight k, high and low halves.  The pieces of a row find its
 // largest weight each for itself: with a workgroup to four whole rows 300 maps of 4800 weights took 45 us, so 10.
-constexpr int PACK_PIECE = 128;   // groups of eight k
 typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));
 __device__ void pack_split(const BatchPack& q, int* e4) {
   const int KK = q.K * q.Kx, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int rows = (q.Mo + q.row - 1) / q.row * q.row, per_chunk = q.n_kg, total = q.n_chunks * per_chunk;
-  const int pieces = (total + PACK_PIECE - 1) / PACK_PIECE;
+  const int rows = (q.Mo + q.row - 1) / q.row * q.row, total = q.n_chunks * q.n_kg;
+  const int pieces = (total + q.piece - 1) / q.piece;
   for (int job = blockIdx.x; job < rows / 4 * pieces; job += gridDim.x) {
     const int tile = job / pieces, piece = job - tile * pieces;
     const int jw = tile * 4 + wave;
@@ -1287,15 +1430,15 @@ __device__ void pack_split(const BatchPack& q, int* e4) {
     if (lane == 0) { e4[wave] = e; q.exps[jw] = word; }
     __syncthreads();
     CNN_GLOBAL char* dst = (CNN_GLOBAL char*)q.wt + ((long long)(tile * 4 / q.row) * total * 2 * q.row + tile * 4 % q.row) * 16;
-    const int end = min(total, (piece + 1) * PACK_PIECE) * 4;
-    for (int u = piece * PACK_PIECE * 4 + threadIdx.x; u < end; u += 256) {
-      const int r = u & 3, x = u >> 2, ch = x / per_chunk, kg = x - ch * per_chunk, c = kg / KK, t = kg - c * KK, j = tile * 4 + r;
+    const int end = min(total, (piece + 1) * q.piece) * 4;
+    for (int u = piece * q.piece * 4 + threadIdx.x; u < end; u += 256) {
+      const int r = u & 3, x = u >> 2, ch = x / q.n_kg, kg = x - ch * q.n_kg, at = ch * q.per_chunk + kg, c = at / KK, t = at - c * KK, j = tile * 4 + r;
       float v[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const int map = (ch * q.IC + c) * 8 + i;
+        const int map = c * 8 + i;
         v[i] = 0.f;
-        if (j < q.Mo && c < q.IC && map < q.Mi) {
+        if (j < q.Mo && kg < q.per_chunk && map < q.Mi) {
           if (q.full_table) v[i] = q.w[(long long)j * q.k_total + map * KK + t];
           else {
             const int slot = table_slot(q, j, map);
@@ -1327,18 +1470,24 @@ __global__ void __launch_bounds__(256) k_batch_pack(BatchPackAll all) {
     const int j0 = tile / tk * PJ, k0 = tile % tk * PK;
     const int k = k0 + (threadIdx.x & (PK - 1));
     const int i = k / KK;
-    for (int r = threadIdx.x / PK; r < PJ; r += 256 / PK) {
-      const int j = j0 + r;
-      float v = 0.f;
-      if (j < q.Mo && k < q.k_total) {
-        if (q.full_table) {
-          v = q.w[(long long)j * q.k_total + k];
-        } else {
-          const int slot = table_slot(q, j, i);
-          if (slot >= 0) v = q.w[(long long)slot * KK + (k - i * KK)];
-        }
+    if (q.full_table) {   // (a tile's loads under way together: a pass over 148000 x 600 weights 458 us, 498 with a loop of loads)
+      float v[PJ * PK / 256];
+      const int r0 = threadIdx.x / PK;
+#pragma unroll
+      for (int u = 0; u < PJ * PK / 256; ++u) {
+        const int j = j0 + r0 + u * (256 / PK);
+        v[u] = q.w[(long long)min(j, q.Mo - 1) * q.k_total + min(k, q.k_total - 1)];
       }
-      t[r][k - k0] = v;
+#pragma unroll
+      for (int u = 0; u < PJ * PK / 256; ++u) {
+        const int r = r0 + u * (256 / PK);
+        t[r][k - k0] = j0 + r < q.Mo && k < q.k_total ? v[u] : 0.f;
+      }
+    } else {
+      for (int r = threadIdx.x / PK; r < PJ; r += 256 / PK) {
+        const int j = j0 + r, slot = j < q.Mo && k < q.k_total ? table_slot(q, j, i) : -1;
+        t[r][k - k0] = slot >= 0 ? q.w[(long long)slot * KK + (k - i * KK)] : 0.f;
+      }
     }
     __syncthreads();
     const int j = j0 + (threadIdx.x & (PJ - 1));
@@ -1480,13 +1629,14 @@ int batch_split_fit(const BatchSplit& g) {
 }
 
 namespace {
-template <int RT, int CT, int TR>
+template <int RT, int CT, int TR, bool FC>
 hipError_t launch_split(hipStream_t stream, const BatchSplit& g) {
   const size_t lds_bytes = batch_split_lds_bytes(g);
-  hipError_t e = hipFuncSetAttribute((const void*)k_batch_split<RT, CT, TR>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+  hipError_t e = hipFuncSetAttribute((const void*)k_batch_split<RT, CT, TR, FC>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
   if (e != hipSuccess) return e;
-  const int groups = (g.Mo + RT * TR - 1) / (RT * TR), gx = std::min(g.n_cb, std::max(1, 256 * batch_split_fit(g) / groups));
-  hipLaunchKernelGGL((k_batch_split<RT, CT, TR>), dim3((unsigned)gx, (unsigned)groups), dim3(BT), lds_bytes, stream, g);
+  const int groups = (g.Mo + RT * TR - 1) / (RT * TR), slices = (g.n_cg / g.IC + g.cps - 1) / g.cps;
+  const int gx = std::min(g.n_cb, std::max(1, 256 * batch_split_fit(g) / (groups * slices)));
+  hipLaunchKernelGGL((k_batch_split<RT, CT, TR, FC>), dim3((unsigned)gx, (unsigned)groups, (unsigned)slices), dim3(BT), lds_bytes, stream, g);
   return hipGetLastError();
 }
 }  // namespace
@@ -1494,7 +1644,7 @@ hipError_t launch_split(hipStream_t stream, const BatchSplit& g) {
 hipError_t launch_batch_split(hipStream_t stream, const BatchSplit& g) {
   if (g.n_win <= 0) return hipSuccess;
 #define CNN355_CASE(RT_, CT_, TR_) \
-  if (g.RT == RT_ && g.CT == CT_ && g.TR == TR_) return launch_split<RT_, CT_, TR_>(stream, g);
+  if (g.RT == RT_ && g.CT == CT_ && g.TR == TR_) return g.fc ? launch_split<RT_, CT_, TR_, true>(stream, g) : launch_split<RT_, CT_, TR_, false>(stream, g);
   CNN355_CASE(1, 1, 32) CNN355_CASE(1, 2, 32) CNN355_CASE(2, 1, 32) CNN355_CASE(2, 2, 32)
   CNN355_CASE(1, 2, 16) CNN355_CASE(1, 4, 16) CNN355_CASE(3, 2, 16) CNN355_CASE(3, 4, 16) CNN355_CASE(5, 2, 16) CNN355_CASE(7, 2, 16)
 #undef CNN355_CASE
@@ -1529,6 +1679,17 @@ hipError_t launch_batch_pool(hipStream_t stream, const BatchPool& q) {
   return hipGetLastError();
 }
 
+hipError_t launch_batch_tail(hipStream_t stream, const BatchTail& g) {
+  if (g.n <= 0) return hipSuccess;
+  const size_t lds_bytes = ((size_t)g.n_out * g.n_hidden + g.n_out) * sizeof(float);
+  const dim3 grid((unsigned)std::min<long long>((g.n + 3) / 4, 1024));
+#define CNN355_CASE(U_) \
+  if (g.n_hidden <= 64 * U_) { hipLaunchKernelGGL(k_batch_tail<U_>, grid, dim3(256), lds_bytes, stream, g); return hipGetLastError(); }
+  CNN355_CASE(1) CNN355_CASE(2) CNN355_CASE(3) CNN355_CASE(5) CNN355_CASE(8) CNN355_CASE(16)
+#undef CNN355_CASE
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_batch_outputs(hipStream_t stream, const float* sums, int n_slices, long long slice_stride, const float* bias,
                                 float* probs, long long n_images, int n_classes, int out_units) {
   if (n_images <= 0) return hipSuccess;
@@ -1542,7 +1703,7 @@ hipError_t launch_batch_pack(hipStream_t stream, const BatchPackAll& all) {
   for (int l = 0; l < all.n; ++l) {
     const BatchPack& q = all.l[l];
     const long long rows = (q.Mo + q.row - 1) / q.row * (long long)q.row;
-    if (q.exps) { most = std::max(most, rows / 4 * ((q.n_chunks * q.n_kg + PACK_PIECE - 1) / PACK_PIECE)); continue; }
+    if (q.exps) { most = std::max(most, rows / 4 * ((q.n_chunks * q.n_kg + q.piece - 1) / q.piece)); continue; }
     most = std::max(most, (q.k_total + PK - 1) / PK * ((rows + PJ - 1) / PJ));
   }
   hipLaunchKernelGGL(k_batch_pack, dim3((unsigned)std::min(most, 4096ll), (unsigned)all.n), dim3(256), 0, stream, all);

@@ -322,7 +322,26 @@ struct BatchSplit {
   int n_kg, slab;                // (group, tap) pairs of a chunk and of a slab of weights, multiples of what an instruction takes
   int RT, CT, TR;                // tiles of TR maps a workgroup, tiles of TR columns a wavefront
   int split_out;                 // pixels of the output's planes; 0: as floats
+  // A fully connected layer (fc): the columns are images, a group of eight maps at each of its pix pixels is a group of its own
+  // with one tap (n_cg counts those, run_px is the images of a block).
+  int fc;
+  FastDiv by_pix;
+  int drop;                      // sums that are no number count as -inf (as where the 32-bit product's planes are added)
+  int cps, raw;                  // chunks of a slice of the k range, one per blockIdx.z; raw: sums without bias and activation,
+  long long slice_stride;        //   a plane for every slice, slice_stride floats apart
 };
+// The last two fully connected layers of a batch (k_batch_tail).
+struct BatchTail {
+  const CNN_GLOBAL float* in;    // [n_slices] planes, slice_stride floats apart, of the hidden units' sums [n][n_hidden], or their outputs
+  const CNN_GLOBAL float* bias_h; // null: outputs
+  const CNN_GLOBAL float* w;     // [n_out][n_hidden]
+  const CNN_GLOBAL float* bias;
+  CNN_GLOBAL float* out;         // [n][n_out]
+  long long n, slice_stride;
+  int n_slices, n_hidden, n_out, out_units, drop;   // drop: of the output layer, as BatchSplit's
+};
+constexpr int TAIL_HIDDEN = 1024, TAIL_OUT = 64, TAIL_WEIGHTS = 12288;   // what k_batch_tail takes
+constexpr int TAIL_SLICES = 32;   // planes that it adds (25 of 33 images' 100 neurons: 6.2 us, 9.2 with a launch of their own)
 // The first convolutional layer below such a one (k_batch_first): windows of the whole batch, sums of up to 16 H terms.
 struct BatchFirst {
   const CNN_GLOBAL float* in;    // [batch] images of [Mi][Hi][Wi], in_stride floats apart
@@ -355,7 +374,8 @@ struct BatchPack {
   int full_table, Mo, K, Kx;     // (a fully connected layer: full, K = Kx = 1)
   int row, k_total;              // maps of a group of Wt, rows of it
   CNN_GLOBAL int* exps;          // split halves (BatchSplit) where not null, with
-  int Mi, n_chunks, IC, n_kg;
+  int Mi, n_chunks, per_chunk, n_kg;   // (group of maps, tap) pairs of a chunk, and with those that fill an instruction up
+  int piece;                           // pairs that a workgroup writes at a time
 };
 struct BatchPackAll {
   int n;

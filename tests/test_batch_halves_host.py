@@ -20,6 +20,10 @@ def test_products_of_halves_fit_and_take_no_more_scratch_memory(arch):
             if p["split"]:
                 below = layers[l - 1]
                 assert l > 0 and (below["split"] or below["first"]), where
+                if p["split_fc"]:   # (behind a layer of p["Mi"] outputs: maps of its pixels)
+                    assert not p["conv"] and l + 1 < len(layers) and p["split_slab"] == p["split_kg"] and p["split_IC"] <= p["Mi"], where
+                    assert p["split_slices"] <= max(1, p["gemm_KS"]) and p["split_lds"] <= LDS, where
+                    continue
                 groups = -(-p["Mi"] // 8)
                 step = 2 if p["split_TR"] == 32 else 4
                 assert groups % p["split_IC"] == 0 and p["split_lds"] <= LDS, where
@@ -27,10 +31,22 @@ def test_products_of_halves_fit_and_take_no_more_scratch_memory(arch):
                 assert 0 < p["split_slab"] <= p["split_kg"] and p["split_px"] % 64 == 0, where
 
 
-@pytest.mark.parametrize("name,batch,layers", [("cfg2a", 4096, 2), ("cfg3", 33, 2), ("cfg4a", 512, 3), ("cfg4b", 512, 3)])
+@pytest.mark.parametrize("name,batch,layers", [("cfg2a", 4096, 3), ("cfg3", 33, 3), ("cfg4a", 512, 4), ("cfg4b", 512, 4)])
 def test_the_benchmark_networks_take_them(name, batch, layers):
-    plan, _ = binding.batch_plan(synth.WORKLOADS[name].arch, batch)
-    assert plan[0]["first"] and [p["split"] for p in plan[:layers]] == [0] + [1] * (layers - 1)
+    plan, whole = binding.batch_plan(synth.WORKLOADS[name].arch, batch)
+    assert whole["tail"] and plan[0]["first"] and [p["split"] for p in plan[:layers]] == [0] + [1] * (layers - 1)
+
+
+def test_which_last_layers_are_one_launch():
+    """Up to 1024 hidden neurons, 64 outputs and 48 KB of weights between them, behind a hidden layer."""
+    for hidden, classes, one in ((1024, 12, 1), (1025, 4, 0), (192, 64, 1), (100, 65, 0), (1024, 13, 0)):
+        assert binding.batch_plan("1x9x9-4C2-MP2-%dN-%dN" % (hidden, classes), 33)[1]["tail"] == one
+    assert binding.batch_plan("1x9x9-4C2-MP2-10N", 33)[1]["tail"] == 0
+
+
+def test_rows_of_many_inputs_keep_the_32_bit_products():
+    """Each piece of a row that is turned into halves reads the row for its scale: 1.4 times as slow at 134480 inputs."""
+    assert not binding.batch_plan("3x43x43-17C1-MP1-80C3-MP1-600N-12N", 33)[0][2]["split"]
 
 
 def test_single_images_keep_the_32_bit_products():

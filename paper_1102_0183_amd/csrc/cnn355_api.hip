@@ -8,6 +8,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -295,6 +296,8 @@ struct Carver {
 
 }  // namespace
 
+struct BatchKept;
+
 struct cnn {
   std::vector<ArchLayer> arch;
   std::vector<int> dev_of_arch;  // arch layer -> index in prog.layers (pool -> its conv), -1 for input
@@ -319,6 +322,8 @@ struct cnn {
   int* d_fe_src = nullptr;
   float* d_fe_out = nullptr;
   float* d_fe_batch = nullptr;  // resident mode: front-end outputs of FE_BATCH images at a time
+  std::shared_ptr<const BatchKept> batch_kept;   // the plan of the last batched forward call
+  std::mutex batch_kept_lock;
   float* d_mm_part = nullptr;   // partial sums of the matrix-core forward pass (one layer at a time)
   size_t mm_part_floats = 0;
   int use_mfma = 1;
@@ -1859,8 +1864,40 @@ int batch_plan(cnn* net, size_t batch, BatchPlan& B) {
   return CNN_OK;
 }
 
+// The plan of a handle for a batch.  The last one is kept, with all that it was made from, and taken again while that is the same:
+// making it takes 11 to 42 us of the host's time, which a single call waits for.
+int batch_plan(cnn* net, size_t batch, std::shared_ptr<const BatchKept>& out);
+
 }  // namespace
 
+struct BatchKept {
+  size_t batch;
+  int has_frontend, n_filters, fe_h, fe_w;
+  std::vector<LayerDev> layers;
+  BatchPlan plan;
+  bool made_for(const ProgramDev& P, size_t n) const {
+    return n == batch && P.has_frontend == has_frontend && P.fe.n_filters == n_filters && P.fe.H == fe_h && P.fe.W == fe_w &&
+           (size_t)P.n_layers == layers.size() && std::memcmp(layers.data(), P.layers, layers.size() * sizeof(LayerDev)) == 0;
+  }
+};
+
+namespace {
+int batch_plan(cnn* net, size_t batch, std::shared_ptr<const BatchKept>& out) {
+  const ProgramDev& P = net->prog;
+  std::lock_guard<std::mutex> hold(net->batch_kept_lock);
+  if (!net->batch_kept || !net->batch_kept->made_for(P, batch)) {
+    auto made = std::make_shared<BatchKept>();
+    const int rc = batch_plan(net, batch, made->plan);
+    if (rc) return rc;
+    made->batch = batch;
+    made->has_frontend = P.has_frontend; made->n_filters = P.fe.n_filters; made->fe_h = P.fe.H; made->fe_w = P.fe.W;
+    made->layers.assign(P.layers, P.layers + P.n_layers);
+    net->batch_kept = std::move(made);
+  }
+  out = net->batch_kept;
+  return CNN_OK;
+}
+}  // namespace
 
 extern "C" {
 
@@ -2591,10 +2628,10 @@ const char* cnn_last_error(const cnn_t* net) { return net ? net->err.c_str() : g
 
 int cnn_forward_batch_scratch_bytes(cnn_t* net, size_t batch, size_t* bytes) {
   if (!net || !bytes || batch == 0) return fail(net ? &net->err : nullptr, CNN_E_ARG, "NULL argument or batch of 0");
-  BatchPlan B;
-  int rc = batch_plan(net, batch, B);
+  std::shared_ptr<const BatchKept> kept;
+  int rc = batch_plan(net, batch, kept);
   if (rc) return rc;
-  *bytes = B.floats(batch) * sizeof(float);
+  *bytes = kept->plan.floats(batch) * sizeof(float);
   return CNN_OK;
 }
 
@@ -2658,9 +2695,10 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
   if (n == 0) return CNN_OK;
   if (!d_images || (!d_probs && tap_step < 0) || !d_scratch || batch == 0) return fail(&net->err, CNN_E_ARG, "NULL argument or batch of 0");
   if (((uintptr_t)d_scratch & 255u) != 0) return fail(&net->err, CNN_E_ARG, "scratch must be 256-byte aligned");
-  BatchPlan B;
-  int rc = batch_plan(net, batch, B);
+  std::shared_ptr<const BatchKept> kept;
+  int rc = batch_plan(net, batch, kept);
   if (rc) return rc;
+  const BatchPlan& B = kept->plan;
   for (const BatchStep& st : B.steps) {
     const unsigned long long lim = (1ull << 31) - 256;
     const unsigned long long b = batch;
@@ -2703,7 +2741,7 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
     bool done = false;
     const BatchPool* last_raw = nullptr;
     for (size_t s = 0; s < B.steps.size(); ++s) {
-      BatchStep& st = B.steps[s];
+      const BatchStep& st = B.steps[s];
       float* out = d_act[cur];
       const bool raw = st.raw();
       if (st.f.T) {

@@ -112,3 +112,35 @@ def test_weights_of_hidden_layers_that_do_not_split(value):
             continue
         assert np.nanmax(np.abs(x[l] - y)) <= 1e-5 * 1.7159, l
     g.close()
+
+
+def test_a_handle_plans_again_when_its_batch_table_or_filters_change():
+    """A handle keeps the plan of its last batched call: after every change its outputs are those of a handle that never had
+    another one."""
+    from paper_1102_0183_amd import synth
+    arch, table = "2x20x20-17C3-MP2-40C4-MP2-33N-4N", synth.random_table(40, 17, 5, 7)
+    filters = (np.random.default_rng(1).random((2, 5, 5)) - 0.5).astype(np.float32)
+
+    def run(g, batch, n=40):
+        w = ((np.random.default_rng(5).random(g.num_weights) - 0.5) * 0.2).astype(np.float32)
+        g.set_weights(w)
+        imgs = (np.random.default_rng(6).random((n, g.image_size)) * 2 - 1).astype(np.float32)
+        return _outputs(g, to_dev(imgs), n, batch)
+
+    steps = [("batch", 33), ("batch", 7), ("batch", 33), ("table", 33), ("units", 33), ("front", 33), ("batch", 1)]
+    kept = binding.Cnn(arch)
+    done = set()
+    for what, batch in steps:
+        done.add(what)
+        fresh = binding.Cnn(arch)
+        for g in (kept, fresh):
+            if "table" in done and (g is fresh or what == "table"):
+                g.set_connection_table(1, table)
+            if "units" in done and (g is fresh or what == "units"):
+                g.set_output_units(binding.OUTPUT_TANH_SQERR)
+            if "front" in done and (g is fresh or what == "front"):
+                g.set_fixed_frontend(filters, np.zeros(2, dtype=np.int32), 1)
+        got, want = run(kept, batch), run(fresh, batch)
+        assert np.array_equal(got, want), (what, batch)
+        fresh.close()
+    kept.close()

@@ -504,6 +504,7 @@ def main():
             best = min(event_ms(torch, lambda: net.forward_batch(src, n_stream, d_probs, scratch, fbatch)) for _ in range(3))
             assert torch.isfinite(d_probs).all()
             inf, nc, _ = shapes_of(net)
+            # (the method's own sums; the pass multiplies split halves, so their share of the fp32 peak may exceed 1)
             tf = fwd_flop(layer_work(inf, nc)) * n_stream / (best * 1e-3) / 1e12
             extra[key + "_forward_batch_images_per_s"] = round(n_stream / (best * 1e-3), 1)
             extra[key + "_forward_batch_tflops"] = round(tf, 2)

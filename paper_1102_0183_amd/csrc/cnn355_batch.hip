@@ -656,7 +656,7 @@ __global__ void __launch_bounds__(BT, MT * TR > 96 ? 2 : 3) k_batch_conv(BatchCo
 // Why halves: 32-bit products leave the vector units idle (a wavefront's vector instructions wait for another one's products:
 // 103 us of products and 122 of vector work on the same SIMD took 220 together, with products of halves 62 and 122 took 148),
 // and these layers have as much of the one as of the other.  300C3 on 3 maps, 512 images: k_batch_conv 177 us, this kernel with
-// 32-bit products 146, with halves 90; 20C4 of 4096 digits 77, 51, 45.
+// 32-bit products 146, with halves 90 (105 in a trace of whole passes); 20C4 of 4096 digits 77, 51, 45.
 // Pixels that do not split (4 and larger, infinite, or all of a lane's below 2^-14 and not zero) and weights that do not (not
 // finite, or all of a row's below 2^-81) take 32-bit products, member by member.
 constexpr int first_waves(int T, int H) {   // wavefronts a SIMD, by the registers of pixels, offsets, halves and sums
@@ -868,7 +868,8 @@ __global__ void __launch_bounds__(BT, first_waves(T, H)) k_batch_first(BatchFirs
 // Bound by the issue of instructions beside the matrix pipes (40 % busy in 300C2) and by the waits of a slab; larger tiles, one
 // wavefront a SIMD, were slower (300C2: 128 x 256 columns 694 us of the pass, 64 x 256 543).  Against k_batch_conv, under the
 // tracer: 300C2 of 512 images 743 -> 235 us (305 TFLOP/s of the layer's own sums), 300C4 234 -> 98, 40C5 of 4096 digits 184 ->
-// 80, 128C3 of 33 stereo pairs 42 (with its k_batch_pool) -> 16.
+// 80, 128C3 of 33 stereo pairs 42 (with its k_batch_pool) -> 16.  (In a trace of whole passes, hidden layers in this kernel too:
+// 300C2 262, 300C4 112, 40C5 81, 128C3 16.)
 // FC: a fully connected layer behind such a layer.  A column is an image, and a lane of a staging load fetches an image's eight
 // maps at one pixel (16 bytes a line of memory; neighbouring pixels follow in the same chunk and meet it in the caches); the k
 // range in slices where the images are few.  Against k_batch_gemm and its k_batch_pool: 150N of 4096 digits 30 us -> 14.3, 300N of

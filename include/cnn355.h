@@ -166,7 +166,7 @@ int cnn_set_weights(cnn_t* net, const float* host_src, size_t n);
  * weight, Sec. 4, so their images are independent).  Every layer becomes one matrix product over
  * the whole batch on the matrix cores, fp32 in and out; results agree with cnn_forward_many to
  * rounding (other summation order), whatever the mode of the handle.
- *   cnn_forward_batch_scratch_bytes: device memory the call needs for `batch` images in flight
+ *   cnn_forward_batch_scratch_bytes: device memory that is enough for `batch` images in flight
  *     (re-packed weights, the layer outputs of one batch); the caller allocates it.
  *   cnn_forward_batch: d_images [n][cnn_image_size], d_probs [n][cnn_num_classes] (probabilities, or
  *     the outputs with CNN_OUTPUT_TANH_SQERR), both device memory; d_scratch: device memory,

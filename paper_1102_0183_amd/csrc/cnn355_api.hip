@@ -1409,6 +1409,7 @@ struct BatchPlan {
   size_t floats(size_t batch) const {
     return wt_total + batch * (sums_per_image + act_per_image[0] + act_per_image[1] + fe_per_image) + 4 * 64;
   }
+  size_t asked = 0;    // floats that a caller is asked for
 };
 
 size_t up64(size_t x) { return (x + 63) / 64 * 64; }
@@ -1855,12 +1856,16 @@ int batch_plan_of(cnn* net, size_t batch, bool split, BatchPlan& B) {
 }
 
 // Products of halves, unless the maps that fill groups of eight and tiles up take more scratch memory than 32-bit products
-// throughout: a caller whose memory was enough for a batch goes on with it.
+// throughout: a caller whose memory was enough for a batch goes on with it.  The caller is asked for what the latter take:
+// fewer images may run in 32-bit products where more run in halves (60 digits 1 M floats, 100 digits 0.6 M), and a program
+// with memory for its batch calls with what remains of a set.
 int batch_plan(cnn* net, size_t batch, BatchPlan& B) {
   const int rc = batch_plan_of(net, batch, false, B);
   if (rc) return rc;
+  const size_t asked = B.floats(batch);
   BatchPlan halves;
-  if (batch_plan_of(net, batch, true, halves) == CNN_OK && halves.floats(batch) <= B.floats(batch)) B = std::move(halves);
+  if (batch_plan_of(net, batch, true, halves) == CNN_OK && halves.floats(batch) <= asked) B = std::move(halves);
+  B.asked = asked;
   return CNN_OK;
 }
 
@@ -2338,7 +2343,8 @@ int cnn355_resident_plan_text(const char* arch, int fan_in, int n_ranks, int xcd
 
 // development aid, host only: the plan of the batched forward pass of `arch` at `batch` images (tables as in
 // cnn355_resident_plan_text), a line per trainable layer of "name value" pairs, then whether the output units
-// add the planes of their layer's sums and the scratch floats a call takes (floats_32: with 32-bit products throughout).
+// add the planes of their layer's sums and the scratch floats a call takes (floats_32: with 32-bit products throughout, which
+// is what a caller is asked for).
 // split: the layer is a product of halves (k_batch_split), its tile, chunk and slab; first: the first layer below one (k_batch_first).  The values in front of these are then those of the product that the layer has without them.
 // run: input maps (of KK terms each) of the longest running sum; gemm_run, gemm_KS: of k_batch_gemm's plan of the layer.
 int cnn355_batch_plan_text(const char* arch, int fan_in, size_t batch, char* buf, size_t n) {
@@ -2381,9 +2387,7 @@ int cnn355_batch_plan_text(const char* arch, int fan_in, size_t batch, char* buf
   }
   const BatchStep& last = B.steps.back();
   const bool add = last.raw() && outputs_add(tmp.prog.n_classes, last.pool.n_slices);
-  BatchPlan B32;
-  if ((rc = batch_plan_of(&tmp, batch, false, B32))) { g_err = tmp.err; return rc; }
-  t += "tail " + std::to_string((int)B.tail) + "\noutputs_add " + std::to_string((int)add) + "\nfloats " + std::to_string(B.floats(batch)) + "\nfloats_32 " + std::to_string(B32.floats(batch)) + "\n";
+  t += "tail " + std::to_string((int)B.tail) + "\noutputs_add " + std::to_string((int)add) + "\nfloats " + std::to_string(B.floats(batch)) + "\nfloats_32 " + std::to_string(B.asked) + "\n";
   if (t.size() + 1 > n) return fail(nullptr, CNN_E_ARG, "buffer too small for the plan text");
   std::memcpy(buf, t.c_str(), t.size() + 1);
   return CNN_OK;
@@ -2631,7 +2635,7 @@ int cnn_forward_batch_scratch_bytes(cnn_t* net, size_t batch, size_t* bytes) {
   std::shared_ptr<const BatchKept> kept;
   int rc = batch_plan(net, batch, kept);
   if (rc) return rc;
-  *bytes = kept->plan.floats(batch) * sizeof(float);
+  *bytes = kept->plan.asked * sizeof(float);
   return CNN_OK;
 }
 

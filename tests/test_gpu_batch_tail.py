@@ -144,3 +144,22 @@ def test_a_handle_plans_again_when_its_batch_table_or_filters_change():
         assert np.array_equal(got, want), (what, batch)
         fresh.close()
     kept.close()
+
+
+@pytest.mark.parametrize("arch,most,batches", [("1x29x29-20C4-MP2-40C5-MP3-150N-10N", 100, (88, 60, 1)),
+                                               ("2x48x48-50C5-MP2-128C3-MP4-100N-5N", 33, (7, 1))])
+def test_scratch_memory_for_a_batch_is_enough_for_what_remains_of_a_set(arch, most, batches):
+    """Fewer images may run in 32-bit products, which take more memory, where more run in halves."""
+    import torch
+    g, _ = build_pair(arch=arch)
+    scratch = _scratch(g, most)
+    d_imgs = to_dev((np.random.default_rng(3).random((most, g.image_size)) * 2 - 1).astype(np.float32))
+    assert any(not binding.batch_plan(arch, b)[0][1]["split"] for b in batches) and binding.batch_plan(arch, most)[0][1]["split"]
+    one = torch.empty(most * g.num_classes, dtype=torch.float32, device="cuda:0")
+    g.forward_many(d_imgs, most, one)
+    for batch in batches:
+        probs = torch.empty(batch * g.num_classes, dtype=torch.float32, device="cuda:0")
+        g.forward_batch(d_imgs[:batch], batch, probs, scratch, batch)
+        g.synchronize()
+        assert (probs - one[:len(probs)]).abs().max().item() <= 1e-5
+    g.close()

@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <cstdint>
 
 #define CNN_GLOBAL __attribute__((address_space(1)))
@@ -908,14 +909,15 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
   bool slow = false;
   for (int x = tid; x < ROWS; x += BT) {
     const int e = g.exps[j0 + x];
-    lds_e[x] = e;
+    const bool inf = e >= SPLIT_SLOW / 2;
+    lds_e[x] = inf ? e - SPLIT_SLOW : e;
     lds_b[x] = j0 + x < g.Mo ? g.bias[j0 + x] : 0.f;
-    slow |= e >= SPLIT_SLOW / 2;
+    slow |= inf;
   }
-  slow = __syncthreads_or(slow);
+  slow = __builtin_amdgcn_readfirstlane(__syncthreads_or(slow));
   const int n_chunks = g.n_cg / g.IC, ch_first = FC ? blockIdx.z * g.cps : 0, ch_end = FC ? min(n_chunks, ch_first + g.cps) : n_chunks;
   const int slabs = (g.n_kg + g.slab - 1) / g.slab, M = FC ? 1 : g.Kp * g.Kpx;
-  const int run = min(SPLIT_RUN, n_chunks * g.n_kg / 2);
+  const int longest = min(SPLIT_RUN, n_chunks * g.n_kg / 2);
   const CNN_GLOBAL char* wt = g.wt + (long long)blockIdx.y * n_chunks * g.n_kg * ROWS * 32;
   // Pixels of the batch that block cb reads: from the first of its first window to the last of its last.  Staged in loads of 64
   // pixels of a plane, whose last ones may reach past the block's (into memory of the call's: its end is 64 pixels off), and of
@@ -955,80 +957,110 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
     lds_dma16_n(w_at + (unsigned)(buf * slab_bytes + q * 1024), wt, (unsigned)(at * ROWS * 32 + (q * 64 + lane) * 16), min(share, loads - q));
   };
 
-  typedef float accv __attribute__((ext_vector_type(AV)));
-  int xb = 0, wb = 0;
-  auto aim_lanes = [&](int cb) {                   // (behind the last image: that one)
+  // CAREFUL: a group with an infinite weight, in products of 32 bits.  Code of its own: as a branch of the step loop it cost the
+  // products of halves 2 % (30 registers).  An infinity in every 97th weight, 4096 digits: 440 us a call (180 without; 35600 with
+  // the sums of such rows by a thread an output), 512 images of 300 maps a layer: 1420 (510; 214000).
+  auto run = [&](auto careful) {
+    constexpr bool CAREFUL = decltype(careful)::value;
+    typedef float accv __attribute__((ext_vector_type(AV)));
+    int xb = 0, wb = 0;
+    auto aim_lanes = [&](int cb) {                   // (behind the last image: that one)
 #pragma unroll
-    for (int q = 0; q < COLS / 64; ++q) image[q] = (unsigned)(min(q * 64 + lane, g.n_win - 1 - cb * COLS) * g.pix * 16);
-  };
-  if constexpr (FC) aim_lanes(blockIdx.x);
-  aim(blockIdx.x);
-  fetch_x(ch_first, 0);
-  fetch_w(ch_first * g.n_kg, min(g.slab, g.n_kg), 0);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  for (int cb = blockIdx.x; cb < g.n_cb; cb += gridDim.x) {
-    const bool more = cb + (int)gridDim.x < g.n_cb;
-    const int first = x_first;
-    // the first pixel of the batch that column c reads (columns that are not there: the block's first)
-    auto column = [&](int c) {
-      const int wl = c / M, d = c - wl * M, w = cb * g.wins + wl;
-      if (wl >= g.wins || w >= g.n_win) return first;
-      const int b = fast_div(w, g.by_win_img);
-      const int wi = w - b * g.win_img, wy = fast_div(wi, g.by_wp), wx = wi - wy * g.Wp, dy = d / g.Kpx, dx = d - dy * g.Kpx;
-      return b * g.pix + (wy * g.Kp + dy) * g.stride * g.Wi + (wx * g.Kpx + dx) * g.stride_x;
+      for (int q = 0; q < COLS / 64; ++q) image[q] = (unsigned)(min(q * 64 + lane, g.n_win - 1 - cb * COLS) * g.pix * 16);
     };
-    int pbase[CT];
+    if constexpr (FC) aim_lanes(blockIdx.x);
+    aim(blockIdx.x);
+    fetch_x(ch_first, 0);
+    fetch_w(ch_first * g.n_kg, min(g.slab, g.n_kg), 0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    for (int cb = blockIdx.x; cb < g.n_cb; cb += gridDim.x) {
+      const bool more = cb + (int)gridDim.x < g.n_cb;
+      const int first = x_first;
+      // the first pixel of the batch that column c reads (columns that are not there: the block's first)
+      auto column = [&](int c) {
+        const int wl = c / M, d = c - wl * M, w = cb * g.wins + wl;
+        if (wl >= g.wins || w >= g.n_win) return first;
+        const int b = fast_div(w, g.by_win_img);
+        const int wi = w - b * g.win_img, wy = fast_div(wi, g.by_wp), wx = wi - wy * g.Wp, dy = d / g.Kpx, dx = d - dy * g.Kpx;
+        return b * g.pix + (wy * g.Kp + dy) * g.stride * g.Wi + (wx * g.Kpx + dx) * g.stride_x;
+      };
+      int pbase[CT];
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-      const int c = (wave * CT + ct) * TR + lrow;
-      pbase[ct] = (FC ? c : column(c) - first) * 16;
-    }
-    accv acc[RT][CT], tot[RT][CT];
+      for (int ct = 0; ct < CT; ++ct) {
+        const int c = (wave * CT + ct) * TR + lrow;
+        pbase[ct] = (FC ? c : column(c) - first) * 16;
+      }
+      accv acc[RT][CT], tot[RT][CT];
 #pragma unroll
-    for (int m = 0; m < RT; ++m)
+      for (int m = 0; m < RT; ++m)
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct)
+        for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-        for (int v = 0; v < AV; ++v) acc[m][ct][v] = tot[m][ct][v] = 0.f;
-    int pairs = 0;
-    for (int ch = ch_first; ch < ch_end; ++ch, xb ^= 1) {
-      for (int sl = 0; sl < slabs; ++sl, wb ^= 1) {
-        // slab and chunk have arrived (every wavefront has waited for its own loads), the other halves are read no more
-        __syncthreads();
-        const int at = ch * g.n_kg + sl * g.slab, here = min(g.slab, g.n_kg - sl * g.slab);
-        const bool last = ch + 1 == ch_end;
-        if (sl + 1 < slabs) fetch_w(at + here, min(g.slab, g.n_kg - (sl + 1) * g.slab), wb ^ 1);
-        else if (!last || more) fetch_w(last ? ch_first * g.n_kg : at + here, min(g.slab, g.n_kg), wb ^ 1);
-        if (sl == 0) {
-          if (!last) fetch_x(ch + 1, xb ^ 1);
-          else if (more) {
-            if constexpr (FC) aim_lanes(cb + gridDim.x);
-            aim(cb + gridDim.x);
-            fetch_x(ch_first, xb ^ 1);
+          for (int v = 0; v < AV; ++v) acc[m][ct][v] = tot[m][ct][v] = 0.f;
+      int pairs = 0;
+      for (int ch = ch_first; ch < ch_end; ++ch, xb ^= 1) {
+        for (int sl = 0; sl < slabs; ++sl, wb ^= 1) {
+          // slab and chunk have arrived (every wavefront has waited for its own loads), the other halves are read no more
+          __syncthreads();
+          const int at = ch * g.n_kg + sl * g.slab, here = min(g.slab, g.n_kg - sl * g.slab);
+          const bool last = ch + 1 == ch_end;
+          if (sl + 1 < slabs) fetch_w(at + here, min(g.slab, g.n_kg - (sl + 1) * g.slab), wb ^ 1);
+          else if (!last || more) fetch_w(last ? ch_first * g.n_kg : at + here, min(g.slab, g.n_kg), wb ^ 1);
+          if (sl == 0) {
+            if (!last) fetch_x(ch + 1, xb ^ 1);
+            else if (more) {
+              if constexpr (FC) aim_lanes(cb + gridDim.x);
+              aim(cb + gridDim.x);
+              fetch_x(ch_first, xb ^ 1);
+            }
           }
-        }
-        // A step is one instruction's k.  The operands of the next tile of maps, and at the first tile the columns of the next
-        // step, are on their way from LDS while the present tile is multiplied.
-        const char* x_b = lds_x + xb * x_bytes;
-        const char* w_b = lds_w + wb * slab_bytes + (lk * 2 * ROWS + lrow) * 16;
-        const int* ko = koff + sl * g.slab + lk;
-        const int steps = here / S;
-        v8h xh[2][CT], xl[2][CT], wh[2], wl[2];
-        auto load_x = [&](int set, int k) {
+          // A step is one instruction's k.  The operands of the next tile of maps, and at the first tile the columns of the next
+          // step, are on their way from LDS while the present tile is multiplied.
+          const char* x_b = lds_x + xb * x_bytes;
+          const char* w_b = lds_w + wb * slab_bytes + (lk * 2 * ROWS + lrow) * 16;
+          const int* ko = koff + sl * g.slab + lk;
+          const int steps = here / S;
+          if constexpr (CAREFUL) {   // (infinity times either half of zero, or of signs that differ, is no number: halves are put together first)
+#pragma clang loop unroll(disable)
+            for (int st = 0; st < steps; ++st) {
 #pragma unroll
-          for (int ct = 0; ct < CT; ++ct) {
-            const char* p = x_b + (pbase[ct] + k);
-            xh[set][ct] = *(const v8h*)p;
-            xl[set][ct] = *(const v8h*)(p + plane);
-          }
-        };
-        auto load_w = [&](int set, const char* w, int m) {
-          wh[set] = *(const v8h*)(w + m * TR * 16);
-          wl[set] = *(const v8h*)(w + (ROWS + m * TR) * 16);
-        };
-        load_x(0, ko[0]);
-        load_w(0, w_b, 0);
-        int k_next = ko[steps > 1 ? S : 0];
+              for (int ct = 0; ct < CT; ++ct) {
+                const char* p = x_b + (pbase[ct] + ko[st * S]);
+                const v8h ph = *(const v8h*)p, pl = *(const v8h*)(p + plane);
+                float x[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) x[i] = (float)ph[i] + (float)pl[i];
+#pragma unroll
+                for (int m = 0; m < RT; ++m) {
+                  const char* w = w_b + (st * S * 2 * ROWS + m * TR) * 16;
+                  const v8h qh = *(const v8h*)w, ql = *(const v8h*)(w + ROWS * 16);
+#pragma unroll
+                  for (int i = 0; i < 8; ++i) {
+                    const float wi = (float)qh[i] + (float)ql[i];
+                    if constexpr (TR == 32) acc[m][ct] = __builtin_amdgcn_mfma_f32_32x32x2f32(wi, x[i], acc[m][ct], 0, 0, 0);
+                    else acc[m][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(wi, x[i], acc[m][ct], 0, 0, 0);
+                  }
+                  __builtin_amdgcn_sched_barrier(0);
+                }
+              }
+            }
+          } else {
+            v8h xh[2][CT], xl[2][CT], wh[2], wl[2];
+            auto load_x = [&](int set, int k) {
+#pragma unroll
+              for (int ct = 0; ct < CT; ++ct) {
+                const char* p = x_b + (pbase[ct] + k);
+                xh[set][ct] = *(const v8h*)p;
+                xl[set][ct] = *(const v8h*)(p + plane);
+              }
+            };
+            auto load_w = [&](int set, const char* w, int m) {
+              wh[set] = *(const v8h*)(w + m * TR * 16);
+              wl[set] = *(const v8h*)(w + (ROWS + m * TR) * 16);
+            };
+            load_x(0, ko[0]);
+            load_w(0, w_b, 0);
+            int k_next = ko[steps > 1 ? S : 0];
 #define CNN355_MAC(a, x)                                                                                             \
   _Pragma("unroll") for (int ct = 0; ct < CT; ++ct) {                                                                \
     if constexpr (TR == 32) acc[m][ct] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, x[ct], acc[m][ct], 0, 0, 0);      \
@@ -1053,155 +1085,131 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
     }                                                                                                                \
     w_b = w_next;                                                                                                    \
   }
-        for (int st = 0; st < steps; st += 2) {
-          CNN355_STEP(0, st)
-          if (st + 1 >= steps) break;
-          CNN355_STEP(1, st + 1)
-        }
+            for (int st = 0; st < steps; st += 2) {
+              CNN355_STEP(0, st)
+              if (st + 1 >= steps) break;
+              CNN355_STEP(1, st + 1)
+            }
+          }
 #undef CNN355_STEP
 #undef CNN355_MAC
-        pairs += here;
-        if (pairs >= run || (last && sl + 1 == slabs)) {
-          pairs = 0;
+          pairs += here;
+          if (pairs >= longest || (last && sl + 1 == slabs)) {
+            pairs = 0;
 #pragma unroll
-          for (int m = 0; m < RT; ++m)
+            for (int m = 0; m < RT; ++m)
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
+              for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-              for (int v = 0; v < AV; ++v) { tot[m][ct][v] += acc[m][ct][v]; acc[m][ct][v] = 0.f; }
+                for (int v = 0; v < AV; ++v) { tot[m][ct][v] += acc[m][ct][v]; acc[m][ct][v] = 0.f; }
+          }
+          // here and not behind the barrier: the wait would take in the stores of the results
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
-        // here and not behind the barrier: the wait would take in the stores of the results
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       }
-    }
-    // element v of a lane, 32-row tiles: row (v / 4) * 8 + (lane / 32) * 4 + v % 4 of the tile, column lane % 32;
-    // 16-row tiles: row (lane / 16) * 4 + v, column lane % 16
-    // (worked out here: what depends on a row only would otherwise be kept in registers over all of the arithmetic)
-    int lk4 = lk * 4;
-    asm volatile("" : "+v"(lk4));
-    auto row_of = [&](int m, int v) { return m * TR + (TR == 32 ? (v >> 2) * 8 + lk4 + (v & 3) : lk4 + v); };
-    // the output of row r from a window's best sum times 2^-e
-    auto finish = [&](int r, float sv, int e) {
-      sv = ldexpf(sv, e);
-      if constexpr (FC)
-        if (g.raw) return sv;
-      if constexpr (FC)
-        if (g.drop) sv = fmaxf(sv, -INFINITY);
-      return b_act(sv + lds_b[r]);
-    };
-    const gf out_z = FC ? g.out + (long long)blockIdx.z * g.slice_stride : g.out;
-    const unsigned plane_out = (unsigned)g.split_out * 16u;
-    auto store = [&](int w, int r, float out) {
-      const int j = j0 + r;
-      if (g.split_out) {   // (the last map brings the zeros that fill its group up)
-        const unsigned off = (unsigned)(j >> 3) * 2u * plane_out + (unsigned)w * 16u + (unsigned)(j & 7) * 2u;
-        put_split((CNN_GLOBAL char*)g.out, plane_out, off, out);
-        if (j == g.Mo - 1)
-          for (int u = 1; u < 8 - (j & 7); ++u) put_split((CNN_GLOBAL char*)g.out, plane_out, off + 2u * u, 0.f);
-        return;
-      }
-      const int b = fast_div(w, g.by_win_img);
-      (out_z + (long long)b * g.out_stride)[j * g.win_img + w - b * g.win_img] = out;
-    };
-    if (M == 1 || M == 4) {
-      const int q = M == 4 ? lane & 3 : 0;
+      // element v of a lane, 32-row tiles: row (v / 4) * 8 + (lane / 32) * 4 + v % 4 of the tile, column lane % 32;
+      // 16-row tiles: row (lane / 16) * 4 + v, column lane % 16
+      // (worked out here: what depends on a row only would otherwise be kept in registers over all of the arithmetic)
+      int lk4 = lk * 4;
+      asm volatile("" : "+v"(lk4));
+      auto row_of = [&](int m, int v) { return m * TR + (TR == 32 ? (v >> 2) * 8 + lk4 + (v & 3) : lk4 + v); };
+      // the output of row r from a window's best sum times 2^-e
+      auto finish = [&](int r, float sv, int e) {
+        sv = ldexpf(sv, e);
+        if constexpr (FC)
+          if (g.raw) return sv;
+        if constexpr (FC)
+          if (g.drop) sv = fmaxf(sv, -INFINITY);
+        return b_act(sv + lds_b[r]);
+      };
+      const gf out_z = FC ? g.out + (long long)blockIdx.z * g.slice_stride : g.out;
+      const unsigned plane_out = (unsigned)g.split_out * 16u;
+      auto store = [&](int w, int r, float out) {
+        const int j = j0 + r;
+        if (g.split_out) {   // (the last map brings the zeros that fill its group up)
+          const unsigned off = (unsigned)(j >> 3) * 2u * plane_out + (unsigned)w * 16u + (unsigned)(j & 7) * 2u;
+          put_split((CNN_GLOBAL char*)g.out, plane_out, off, out);
+          if (j == g.Mo - 1)
+            for (int u = 1; u < 8 - (j & 7); ++u) put_split((CNN_GLOBAL char*)g.out, plane_out, off + 2u * u, 0.f);
+          return;
+        }
+        const int b = fast_div(w, g.by_win_img);
+        (out_z + (long long)b * g.out_stride)[j * g.win_img + w - b * g.win_img] = out;
+      };
+      if (M == 1 || M == 4) {
+        const int q = M == 4 ? lane & 3 : 0;
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        const int c = (wave * CT + ct) * TR + lrow;
-        const int w = cb * g.wins + (M == 4 ? c >> 2 : c);
-        const bool ok = w < g.n_win && (M == 4 ? c >> 2 : c) < g.wins;
-        const int b = ok ? fast_div(w, g.by_win_img) : 0, wi = ok ? w - b * g.win_img : 0;
-        const unsigned o0 = (unsigned)b * (unsigned)g.out_stride + (unsigned)wi;
+        for (int ct = 0; ct < CT; ++ct) {
+          const int c = (wave * CT + ct) * TR + lrow;
+          const int w = cb * g.wins + (M == 4 ? c >> 2 : c);
+          const bool ok = w < g.n_win && (M == 4 ? c >> 2 : c) < g.wins;
+          const int b = ok ? fast_div(w, g.by_win_img) : 0, wi = ok ? w - b * g.win_img : 0;
+          const unsigned o0 = (unsigned)b * (unsigned)g.out_stride + (unsigned)wi;
 #pragma unroll
-        for (int m = 0; m < RT; ++m) {
+          for (int m = 0; m < RT; ++m) {
 #pragma unroll
-          for (int v4 = 0; v4 < AV; v4 += 4) {   // four rows of a lane, eight (TR = 32) or sixteen of the tile
-            __builtin_amdgcn_sched_barrier(0);   // (fewer registers: the next rows' work stays behind this one's)
-            const int first = m * TR + v4 * 2, row = first + lk4;   // (TR = 16: v4 is 0)
-            if (j0 + first >= g.Mo) break;
-            const bool part = j0 + first + (TR == 32 ? 8 : 16) > g.Mo;
-            float sv[4];
-            if (M == 4) {
-              sv[0] = pool_quad(tot[m][ct][v4], tot[m][ct][v4 + 1], tot[m][ct][v4 + 2], tot[m][ct][v4 + 3], q);
-              sv[0] = finish(row + q, sv[0], lds_e[row + q]);
-            } else {
-#pragma unroll
-              for (int u = 0; u < 4; ++u) sv[u] = finish(row + u, tot[m][ct][v4 + u], lds_e[row + u]);
-            }
-            if (g.split_out) {   // groups of eight maps: maps behind the last one are zero
-              const unsigned off = (TR == 32 ? 0u : (unsigned)(lk4 >> 3) * 2u * plane_out) + (unsigned)w * 16u + (unsigned)(lk4 & 4) * 2u;
-              CNN_GLOBAL char* out = (CNN_GLOBAL char*)g.out + (size_t)((unsigned)(j0 + first) >> 3) * 2 * plane_out;
+            for (int v4 = 0; v4 < AV; v4 += 4) {   // four rows of a lane, eight (TR = 32) or sixteen of the tile
+              __builtin_amdgcn_sched_barrier(0);   // (fewer registers: the next rows' work stays behind this one's)
+              const int first = m * TR + v4 * 2, row = first + lk4;   // (TR = 16: v4 is 0)
+              if (j0 + first >= g.Mo) break;
+              const bool part = j0 + first + (TR == 32 ? 8 : 16) > g.Mo;
+              float sv[4];
               if (M == 4) {
-                if (part && j0 + row + q >= g.Mo) sv[0] = 0.f;
-                if (ok && (!part || j0 + row + q < ((g.Mo + 7) & ~7))) put_split(out, plane_out, off + (unsigned)q * 2u, sv[0]);
+                sv[0] = pool_quad(tot[m][ct][v4], tot[m][ct][v4 + 1], tot[m][ct][v4 + 2], tot[m][ct][v4 + 3], q);
+                sv[0] = finish(row + q, sv[0], lds_e[row + q]);
+              } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) sv[u] = finish(row + u, tot[m][ct][v4 + u], lds_e[row + u]);
+              }
+              if (g.split_out) {   // groups of eight maps: maps behind the last one are zero
+                const unsigned off = (TR == 32 ? 0u : (unsigned)(lk4 >> 3) * 2u * plane_out) + (unsigned)w * 16u + (unsigned)(lk4 & 4) * 2u;
+                CNN_GLOBAL char* out = (CNN_GLOBAL char*)g.out + (size_t)((unsigned)(j0 + first) >> 3) * 2 * plane_out;
+                if (M == 4) {
+                  if (part && j0 + row + q >= g.Mo) sv[0] = 0.f;
+                  if (ok && (!part || j0 + row + q < ((g.Mo + 7) & ~7))) put_split(out, plane_out, off + (unsigned)q * 2u, sv[0]);
+                } else {
+#pragma unroll
+                  for (int u = 0; u < 4; ++u)
+                    if (part && j0 + row + u >= g.Mo) sv[u] = 0.f;
+                  if (ok && (!part || j0 + row < ((g.Mo + 7) & ~7))) put_split4(out, plane_out, off, sv);
+                }
+              } else if (M == 4) {
+                if (ok && j0 + row + q < g.Mo) out_z[o0 + (unsigned)(j0 + row + q) * (unsigned)g.win_img] = sv[0];
               } else {
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                  if (part && j0 + row + u >= g.Mo) sv[u] = 0.f;
-                if (ok && (!part || j0 + row < ((g.Mo + 7) & ~7))) put_split4(out, plane_out, off, sv);
+                  if (ok && j0 + row + u < g.Mo) out_z[o0 + (unsigned)(j0 + row + u) * (unsigned)g.win_img] = sv[u];
               }
-            } else if (M == 4) {
-              if (ok && j0 + row + q < g.Mo) out_z[o0 + (unsigned)(j0 + row + q) * (unsigned)g.win_img] = sv[0];
-            } else {
-#pragma unroll
-              for (int u = 0; u < 4; ++u)
-                if (ok && j0 + row + u < g.Mo) out_z[o0 + (unsigned)(j0 + row + u) * (unsigned)g.win_img] = sv[u];
             }
           }
         }
-      }
-    } else {
-      // a thread's window stays its own for all rows it takes
-      const int rows = BT / g.wins, jr = tid / g.wins, wl = tid - jr * g.wins;
-      const int w = cb * g.wins + wl;
-      const bool ok = jr < rows && w < g.n_win;
+      } else {
+        // a thread's window stays its own for all rows it takes
+        const int rows = BT / g.wins, jr = tid / g.wins, wl = tid - jr * g.wins;
+        const int w = cb * g.wins + wl;
+        const bool ok = jr < rows && w < g.n_win;
 #pragma unroll
-      for (int m = 0; m < RT; ++m) {
-        __syncthreads();   // the previous tile has been read
+        for (int m = 0; m < RT; ++m) {
+          __syncthreads();   // the previous tile has been read
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
+          for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-          for (int v = 0; v < AV; ++v) ep[(row_of(0, v)) * EPS + (wave * CT + ct) * TR + lrow] = tot[m][ct][v];
-        __syncthreads();
-        if (ok)
-          for (int r = jr; r < TR; r += rows) {
-            if (j0 + m * TR + r >= g.Mo) break;
-            const float* win = ep + r * EPS + wl * M;
-            float best = -INFINITY;
-            for (int d = 0; d < M; ++d) best = fmaxf(best, win[d]);
-            store(w, m * TR + r, finish(m * TR + r, best, lds_e[m * TR + r]));
-          }
-      }
-    }
-    if (!slow) continue;
-    // rows with an infinite weight (infinity times both halves is no number): summed again, term by term, behind the stores above
-    __syncthreads();
-#pragma clang loop unroll(disable)
-    for (int r = 0; r < ROWS && j0 + r < g.Mo; ++r) {
-      if (lds_e[r] < SPLIT_SLOW / 2) continue;
-#pragma clang loop unroll(disable)
-      for (int wl = tid; wl < g.wins && cb * g.wins + wl < g.n_win; wl += BT) {
-        float best = -INFINITY, sum = 0.f;
-#pragma clang loop unroll(disable)
-        for (int d = 0; d < M; ++d) {
-          const int at = column(wl * M + d);
-          sum = 0.f;
-#pragma clang loop unroll(disable)
-          for (int x = ch_first * g.IC * KK; x < ch_end * g.IC * KK; ++x) {
-            const int c = x / KK, t = x - c * KK, ky = t / g.Kx, cg = FC ? fast_div(c, g.by_pix) : c;
-            const int px = FC ? c - cg * g.pix : ky * g.Wi + t - ky * g.Kx;
-            const CNN_GLOBAL char* xp = g.in + cg * 2 * g.in_plane + (long long)(at + px) * 16;
-            const CNN_GLOBAL char* wp = wt + ((long long)(c / g.IC * g.n_kg + c % g.IC * KK + t) * 2 * ROWS + r) * 16;
-            const v8h xh = *(const CNN_GLOBAL v8h*)xp, xl = *(const CNN_GLOBAL v8h*)(xp + g.in_plane);
-            const v8h wh = *(const CNN_GLOBAL v8h*)wp, wl8 = *(const CNN_GLOBAL v8h*)(wp + ROWS * 16);
-            for (int i = 0; i < 8; ++i) sum = fmaf((float)wh[i] + (float)wl8[i], (float)xh[i] + (float)xl[i], sum);
-          }
-          best = fmaxf(best, sum);
+            for (int v = 0; v < AV; ++v) ep[(row_of(0, v)) * EPS + (wave * CT + ct) * TR + lrow] = tot[m][ct][v];
+          __syncthreads();
+          if (ok)
+            for (int r = jr; r < TR; r += rows) {
+              if (j0 + m * TR + r >= g.Mo) break;
+              const float* win = ep + r * EPS + wl * M;
+              float best = -INFINITY;
+              for (int d = 0; d < M; ++d) best = fmaxf(best, win[d]);
+              store(w, m * TR + r, finish(m * TR + r, best, lds_e[m * TR + r]));
+            }
         }
-        store(cb * g.wins + wl, r, finish(r, M == 1 ? sum : best, lds_e[r] - SPLIT_SLOW));
       }
     }
-  }
+  };
+  if (slow) run(std::true_type{});
+  else run(std::false_type{});
 }
 
 // the planes of partial sums of one output, added in their order, up to eight loads in flight

@@ -191,3 +191,28 @@ def test_weights_that_do_not_split(value):
             w1[M1 - 1] = value
             w2[11] = value
     _check(*_net(edit), imgs)
+
+
+def test_infinite_weights_take_no_longer_than_products_in_32_bits():
+    """A network that has diverged: an infinity in most rows.  A product of halves is three instructions at sixteen times the
+    rate of one in 32 bits, so 16 / 3 times as long, and 16 with all that is done around it; summed by a thread an output: 387."""
+    import torch
+    arch, n = "3x32x32-300C3-MP2-300C2-MP2-300C4-MP2-300N-10N", 256
+    assert [p["split"] for p in binding.batch_plan(arch, n)[0][1:3]] == [1, 1]
+    g = binding.Cnn(arch)
+    d = to_dev((np.random.default_rng(15).random((n, g.image_size)) * 2 - 1).astype(np.float32))
+    probs, scratch = torch.empty(n * g.num_classes, dtype=torch.float32, device="cuda:0"), _scratch(g, n)
+    w = ((np.random.default_rng(16).random(g.num_weights) - 0.5) * 0.1).astype(np.float32)
+    us = []
+    for value in (0.01, np.inf):
+        w[::97] = value
+        g.set_weights(w)
+        ends = [torch.cuda.Event(enable_timing=True) for _ in range(8)]
+        for e in ends:
+            g.forward_batch(d, n, probs, scratch, n)
+            e.record()
+        g.synchronize()
+        us.append(min(a.elapsed_time(b) for a, b in zip(ends, ends[1:])) * 1e3)
+    print("us a call without and with infinite weights", us, flush=True)
+    assert us[1] <= 16 * us[0], us
+    g.close()

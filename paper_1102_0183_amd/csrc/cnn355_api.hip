@@ -1399,7 +1399,8 @@ struct BatchStep {
   size_t wt_off = 0;  // floats from the start of the scratch
   size_t wt_floats = 0;
   size_t out_per_image = 0;   // floats an image in the layer's buffer
-  bool split_out = false;     // outputs as split halves, for the next layer's product
+  bool split_out = false;     // outputs as split halves, for the next layer's product, and their marks behind them
+  size_t halves_per_image = 0;   // floats an image of the halves
   bool raw() const { return s.RT ? s.raw : f.T == 0 && (c.MT ? c.fuse : g.fuse) == 0; }
 };
 struct BatchPlan {
@@ -1678,6 +1679,15 @@ double first_plan(const LayerDev& L, size_t batch, BatchFirst& out) {
   return best;
 }
 
+// The buffer of a layer that writes halves of `eights` groups of eight maps of `pix` pixels for `s`: the halves, and their marks.
+void marked(BatchStep& below, BatchSplit& s, size_t eights, size_t pix) {
+  const int rows = below.f.T ? below.f.T * 32 : below.s.RT * below.s.TR;
+  s.in_groups = (int)((eights * 8 + rows - 1) / rows);
+  s.by_eights = fast_div_of(rows / 8);
+  below.halves_per_image = eights * 8 * pix;
+  below.out_per_image = below.halves_per_image + (s.in_groups * pix + 3) / 4;
+}
+
 // Shape of every layer's matrix product, tile choice and LDS budget.  Returns 0 or an error code.  split: convolutional layers
 // behind another one in products of halves, where their plan fits.
 int batch_plan_of(cnn* net, size_t batch, bool split, BatchPlan& B) {
@@ -1785,7 +1795,7 @@ int batch_plan_of(cnn* net, size_t batch, bool split, BatchPlan& B) {
       if (0.8 * est + (with_first ? 8000.0 : 2000.0) >= old) st.s.RT = 0;
       if (st.s.RT) {
         below.split_out = true;
-        below.out_per_image = (size_t)st.s.n_cg * 8 * HiWi;
+        marked(below, st.s, (size_t)st.s.n_cg, (size_t)HiWi);
         (below.s.RT ? below.s.split_out : below.f.split_out) = (int)(batch * (size_t)HiWi);
         if (below.f.T) {
           B.wt_total -= below.wt_floats;
@@ -1806,13 +1816,13 @@ int batch_plan_of(cnn* net, size_t batch, bool split, BatchPlan& B) {
       else {
         st.s.drop = g.fuse == 0;
         below.split_out = true;
-        below.out_per_image = (size_t)st.s.n_cg * 8;
+        marked(below, st.s, (size_t)st.s.n_cg / pix, (size_t)pix);
         below.s.split_out = (int)(batch * (size_t)pix);
       }
     }
     const BatchSplit& h = st.s;
     const int h_rows = h.RT * h.TR, h_groups = h.RT ? (h.Mo + h_rows - 1) / h_rows : 0;
-    st.wt_floats = h.RT ? up64((size_t)h_groups * h_rows * (h.n_cg / h.IC) * h.n_kg * 8) + up64((size_t)h_groups * h_rows) : up64((size_t)g.Mi * KK * (c.MT ? (size_t)(c.Mo + c.MT * c.TR - 1) / (c.MT * c.TR) * (c.MT * c.TR) : (size_t)g.MoPad));
+    st.wt_floats = h.RT ? up64((size_t)h_groups * h_rows * (h.n_cg / h.IC) * h.n_kg * 8) + up64((size_t)h_groups * h_rows + 1) : up64((size_t)g.Mi * KK * (c.MT ? (size_t)(c.Mo + c.MT * c.TR - 1) / (c.MT * c.TR) * (c.MT * c.TR) : (size_t)g.MoPad));
     st.wt_off = B.wt_total;
     B.wt_total += st.wt_floats;
     BatchPack& k = st.pack;
@@ -2727,8 +2737,11 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
   for (int l = 0; l < pack.n; ++l) {
     pack.l[l] = B.steps[l].pack;
     pack.l[l].wt = base + B.steps[l].wt_off;
-    const BatchSplit& h = B.steps[l].s;   // (the exponents behind the weights)
-    if (h.RT) pack.l[l].exps = (int*)(base + B.steps[l].wt_off + B.steps[l].wt_floats - up64((size_t)(h.Mo + h.RT * h.TR - 1) / (h.RT * h.TR) * (h.RT * h.TR)));
+    const BatchSplit& h = B.steps[l].s;
+    if (!h.RT) continue;
+    const size_t rows = (size_t)(h.Mo + h.RT * h.TR - 1) / (h.RT * h.TR) * (h.RT * h.TR);
+    pack.l[l].exps = (int*)(base + B.steps[l].wt_off + B.steps[l].wt_floats - up64(rows + 1));   // (behind the weights)
+    pack.l[l].any = pack.l[l].exps + rows;
   }
   HIP_TRY(net, launch_batch_pack(net->stream, pack));
   const size_t fe_sz = P.has_frontend ? (size_t)P.fe.n_filters * P.fe.H * P.fe.W : 0;
@@ -2744,18 +2757,22 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
     int cur = 0;
     bool done = false;
     const BatchPool* last_raw = nullptr;
+    SplitMarks in_marks = {nullptr, nullptr};
     for (size_t s = 0; s < B.steps.size(); ++s) {
       const BatchStep& st = B.steps[s];
       float* out = d_act[cur];
       const bool raw = st.raw();
+      SplitMarks marks = {nullptr, nullptr};   // of the halves that this layer writes
+      if (st.split_out) marks = {(unsigned char*)(out + batch * st.halves_per_image), pack.l[s + 1].any};
       if (st.f.T) {
         BatchFirst f = st.f;
-        f.in = in; f.in_stride = in_stride; f.wt = base + st.wt_off; f.out = out; f.n_win = (int)(nb * f.win_img);
+        f.in = in; f.in_stride = in_stride; f.wt = base + st.wt_off; f.out = out; f.n_win = (int)(nb * f.win_img); f.out_marks = marks;
         HIP_TRY(net, launch_batch_first(net->stream, f));
       } else if (st.s.RT) {
         BatchSplit h = st.s;
         h.in = (const char*)in; h.wt = (const char*)(base + st.wt_off); h.exps = pack.l[s].exps; h.out = out;
         h.n_win = (int)(nb * h.win_img); h.n_cb = (h.n_win + h.wins - 1) / h.wins;
+        h.in_marks = in_marks; h.out_marks = marks;
         if (h.raw) h.out = d_sums;
         HIP_TRY(net, launch_batch_split(net->stream, h));
       } else if (st.c.MT) {
@@ -2794,6 +2811,7 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
       }
       in = out;
       in_stride = (long long)st.out_per_image;
+      in_marks = marks;
       cur ^= 1;
       if ((int)s == tap_step) {
         HIP_TRY(net, hipStreamSynchronize(net->stream));
@@ -2803,13 +2821,20 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
           return CNN_OK;
         }
         const size_t maps = (size_t)st.pool.Mo, pixels = (size_t)st.pool.Hp * st.pool.Wp;
-        std::vector<_Float16> halves(batch * st.out_per_image * 2);
-        HIP_TRY(net, hipMemcpy(halves.data(), out, halves.size() * sizeof(_Float16), hipMemcpyDeviceToHost));
+        const BatchSplit& reader = B.steps[s + 1].s;
+        const size_t eights = st.f.T ? st.f.T * 4 : st.s.RT * st.s.TR / 8;
+        std::vector<unsigned short> halves(batch * st.halves_per_image * 2);
+        std::vector<unsigned char> whole(reader.in_groups * batch * pixels);
+        HIP_TRY(net, hipMemcpy(halves.data(), out, halves.size() * sizeof(halves[0]), hipMemcpyDeviceToHost));
+        HIP_TRY(net, hipMemcpy(whole.data(), (const void*)marks.at, whole.size(), hipMemcpyDeviceToHost));
         for (size_t b = 0; b < nb; ++b)
           for (size_t j = 0; j < maps; ++j)
             for (size_t w = 0; w < pixels; ++w) {
-              const _Float16* h = &halves[((j >> 3) * 2 * batch * pixels + b * pixels + w) * 8 + (j & 7)];
-              host_tap[(b * maps + j) * pixels + w] = ((float)h[0] + (float)h[batch * pixels * 8]) / (float)(1 << SPLIT_SHIFT);
+              const unsigned short* h = &halves[((j >> 3) * 2 * batch * pixels + b * pixels + w) * 8 + (j & 7)];
+              const unsigned short high = h[0], low = h[batch * pixels * 8];
+              float& v = host_tap[(b * maps + j) * pixels + w];
+              if (whole[((j >> 3) / eights * batch + b) * pixels + w]) v = __builtin_bit_cast(float, (unsigned)high << 16 | low);
+              else v = ((float)__builtin_bit_cast(_Float16, high) + (float)__builtin_bit_cast(_Float16, low)) / (float)(1 << SPLIT_SHIFT);
             }
         if (tap_per_image) *tap_per_image = maps * pixels;
         return CNN_OK;

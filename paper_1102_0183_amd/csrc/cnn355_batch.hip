@@ -44,8 +44,7 @@ __device__ __forceinline__ float b_act(float a) {
   return fabsf(x) < 0.3f ? small : big;
 }
 
-// Activation v as split halves (BatchSplit): v 2^14 is the sum of two halves to 23 bits, for activations down to 1e-6 of the
-// largest.  off: byte offset of the high half in `out`, the low one lies a plane behind it.
+// Activation v as split halves (BatchSplit).  off: byte offset of the high half in `out`, the low one lies a plane behind it.
 __device__ __forceinline__ void put_split(CNN_GLOBAL char* out, unsigned plane, unsigned off, float v) {
   const float x = v * (float)(1 << SPLIT_SHIFT);
   const _Float16 h = (_Float16)x;
@@ -63,6 +62,34 @@ __device__ __forceinline__ void put_split4(CNN_GLOBAL char* out, unsigned plane,
   }
   *(CNN_GLOBAL v4h*)(out + off) = h;
   *(CNN_GLOBAL v4h*)(out + plane + off) = l;
+}
+
+// Activation v as it is, in the place of its halves (SplitMarks)
+__device__ __forceinline__ void put_whole(CNN_GLOBAL char* out, unsigned plane, unsigned off, float v) {
+  const unsigned b = __float_as_uint(v);
+  *(CNN_GLOBAL _Float16*)(out + off) = __builtin_bit_cast(_Float16, (unsigned short)(b >> 16));
+  *(CNN_GLOBAL _Float16*)(out + plane + off) = __builtin_bit_cast(_Float16, (unsigned short)b);
+}
+__device__ __forceinline__ void put_whole4(CNN_GLOBAL char* out, unsigned plane, unsigned off, const float (&v)[4]) {
+  v4h h, l;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const unsigned b = __float_as_uint(v[u]);
+    h[u] = __builtin_bit_cast(_Float16, (unsigned short)(b >> 16));
+    l[u] = __builtin_bit_cast(_Float16, (unsigned short)b);
+  }
+  *(CNN_GLOBAL v4h*)(out + off) = h;
+  *(CNN_GLOBAL v4h*)(out + plane + off) = l;
+}
+// the activation that is stored in these halves, times 2^14
+__device__ __forceinline__ float whole_of(_Float16 high, _Float16 low) {
+  const unsigned b = (unsigned)__builtin_bit_cast(unsigned short, high) << 16 | __builtin_bit_cast(unsigned short, low);
+  return __uint_as_float(b) * (float)(1 << SPLIT_SHIFT);
+}
+
+// (21600 wavefronts that all store the word took 750 us)
+__device__ __forceinline__ void mark_any(const SplitMarks& m) {
+  if (__hip_atomic_load(m.any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) __hip_atomic_store(m.any, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // 2 x 2 windows whose members are the four lanes of a quad: the window's largest sum of row u (of four) goes to lane q = u.
@@ -677,6 +704,7 @@ __global__ void __launch_bounds__(BT, first_waves(T, H)) k_batch_first(BatchFirs
   int* lds_e = (int*)(lds_b + ROWS);                     // [ROWS] -(e + SPLIT_SHIFT), halves are w 2^e
   int* koff = lds_e + ROWS;                              // [16 H] byte offset of k from a member's first pixel
   float* ex = (float*)(koff + 16 * H);                   // [4][T * 16][64] where wavefronts share
+  float* all_most = ex + 4 * T * 1024;                   // [4][32] of the same
   const int KK = g.K * g.Kx, HiWi = g.Hi * g.Wi;
   for (int x = tid; x < 16 * H; x += BT) {
     const int k = min(x, g.k_total - 1), c = k / KK, t = k - c * KK, ky = t / g.Kx;
@@ -830,26 +858,63 @@ __global__ void __launch_bounds__(BT, first_waves(T, H)) k_batch_first(BatchFirs
     const int w = t * 32 + lrow;
     int lk4 = lk * 4;
     asm volatile("" : "+v"(lk4));
+    // the outputs of four maps of a lane
+    auto outputs = [&](int m, int v4, int row, float sum, float (&sv)[4]) {
+      const bool part = j0 + m * 32 + v4 * 2 + 8 > g.Mo;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        float x = u ? best[m][v4 + u] : sum;
+        if (share)
+          for (int o = 0; o < 4; ++o) x = fmaxf(x, ex[(o * T + m) * 1024 + (v4 + u) * 64 + lane]);
+        sv[u] = b_act(ldexpf(x, lds_e[row + u]) + lds_b[row + u]);
+        if (part && j0 + row + u >= g.Mo) sv[u] = 0.f;   // (maps that fill the last group of eight up)
+      }
+    };
+    auto out_of = [&](int first) { return (CNN_GLOBAL char*)g.out + (size_t)((unsigned)(j0 + first) >> 3) * 2 * plane; };
+    float most = 0.f;
 #pragma unroll
     for (int m = 0; m < T; ++m)
 #pragma unroll
       for (int v4 = 0; v4 < 16; v4 += 4) {
-        const int first = m * 32 + v4 * 2, row = first + lk4;
+        const int first = m * 32 + v4 * 2;
         if (j0 + first >= g.Mo) break;
         if (share && (m * 4 + v4 / 4) % 4 != wave) continue;
-        const bool part = j0 + first + 8 > g.Mo;
         float sv[4];
+        outputs(m, v4, first + lk4, best[m][v4], sv);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          float x = best[m][v4 + u];
-          if (share)
-            for (int o = 0; o < 4; ++o) x = fmaxf(x, ex[(o * T + m) * 1024 + (v4 + u) * 64 + lane]);
-          sv[u] = b_act(ldexpf(x, lds_e[row + u]) + lds_b[row + u]);
-          if (part && j0 + row + u >= g.Mo) sv[u] = 0.f;   // (maps that fill the last group of eight up)
-        }
-        if (w < g.n_win)
-          put_split4((CNN_GLOBAL char*)g.out + (size_t)((unsigned)(j0 + first) >> 3) * 2 * plane, plane, (unsigned)w * 16u + (unsigned)lk4 * 2u, sv);
+        for (int u = 0; u < 4; ++u) most = fmaxf(most, fabsf(sv[u]));
+        if (w < g.n_win) put_split4(out_of(first), plane, (unsigned)w * 16u + (unsigned)lk4 * 2u, sv);
       }
+    if (share) {   // (the wavefronts have the window's maps between them)
+      most = fmaxf(most, __shfl_xor(most, 32));
+      if (lane < 32) all_most[wave * 32 + lane] = most;
+      __syncthreads();
+      for (int o = 0; o < 4; ++o) most = fmaxf(most, all_most[o * 32 + lrow]);
+    }
+    unsigned long long small = __ballot(!(most >= SPLIT_TINY));
+    small &= small >> 32;
+    bool tiny = false;
+    if (__builtin_expect(small != 0, 0)) {
+      most = fmaxf(most, __shfl_xor(most, 32));
+      tiny = w < g.n_win && most < SPLIT_TINY;
+      if (!__any(tiny && most > 0.f)) tiny = false;   // (zeros are halves, and floats)
+      else {                                          // once more: these are stored as they are
+        if (lane == 0) mark_any(g.out_marks);
+#pragma unroll
+        for (int m = 0; m < T; ++m)
+#pragma unroll
+          for (int v4 = 0; v4 < 16; v4 += 4) {
+            const int first = m * 32 + v4 * 2;
+            if (j0 + first >= g.Mo) break;
+            if (share && (m * 4 + v4 / 4) % 4 != wave) continue;
+            float sum = best[m][v4], sv[4];
+            asm volatile("" : "+v"(lk4), "+v"(sum));   // (or what is worked out above is kept in registers for here)
+            outputs(m, v4, first + lk4, sum, sv);
+            if (tiny) put_whole4(out_of(first), plane, (unsigned)w * 16u + (unsigned)lk4 * 2u, sv);
+          }
+      }
+    }
+    if (w < g.n_win && lane < 32) g.out_marks.at[(size_t)blockIdx.y * (unsigned)g.split_out + (unsigned)w] = tiny;
   }
 }
 
@@ -861,6 +926,9 @@ __global__ void __launch_bounds__(BT, first_waves(T, H)) k_batch_first(BatchFirs
 // 32-bit products.  The layer below has split its activations already
 // (put_split), in groups of eight maps, so that a lane's eight k are one 16-byte read from LDS: k = (group of eight maps, ky,
 // kx, map of the group).
+// What a workgroup writes of a window is stored as floats where all of it is tiny (SplitMarks): the largest output is kept along
+// with the stores, and the stores are done again where it is.  40C5 of 4096 digits 81.3 -> 83.1 us with it, the first layer's 20C4
+// 46.1 -> 46.9, 100N of 33 stereo pairs 8.4 -> 9.2 (it waits for the word that says whether there is such a window).
 // Error against 64 bits (2-norm, of 64 images' outputs of a layer, 32-bit products / halves): 300C4 on 300 maps 5.7e-7 /
 // 3.3e-7, 300C2 4.0 / 2.2, 40C5 on 20 2.4 / 2.2, 128C3 on 50 2.4 / 2.2; without runs 8.8, 3.8, 2.9 and 3.0.
 // Staging as in k_batch_conv: the next slab of weights (a run of the k range, packed in the order it is read) and the next
@@ -887,9 +955,9 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
   constexpr int S = TR == 32 ? 2 : 4;              // groups of eight k an instruction takes, one per 64 / S lanes
   constexpr int AV = TR == 32 ? 16 : 4;            // accumulator floats per lane and tile
   constexpr int ROWS = RT * TR, COLS = 4 * CT * TR, EPS = COLS + 4;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lrow = lane & (TR - 1), lk = lane / TR;
+  int tid = threadIdx.x, lane = tid & 63;
+  int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int lrow = lane & (TR - 1), lk = lane / TR;
   const int plane = g.run_px * 16;                 // bytes of a staged plane: eight maps' high or low halves
   const int x_bytes = g.IC * 2 * plane, slab_bytes = g.slab * ROWS * 32;
   char* lds_x = lds_s;
@@ -898,8 +966,10 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
   int* lds_e = koff + g.n_kg;                      // [ROWS] exponents
   float* lds_b = (float*)(lds_e + ROWS);           // [ROWS] biases
   float* ep = lds_b + ROWS;                        // [TR][EPS] where windows are pooled through LDS
+  unsigned* w_most = (unsigned*)(ep + TR * EPS);   // [wins] the largest output of each, of the same
   const unsigned x_at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds_x;
   const unsigned w_at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds_w;
+  const int any_marks = __builtin_amdgcn_readfirstlane(*g.in_marks.any);   // (asked for first: what it waits for comes from memory)
   const int KK = FC ? 1 : g.K * g.Kx;
   for (int x = tid; x < g.n_kg; x += BT) {         // (pairs that fill an instruction up have no weights: a pixel that is read anyway)
     const int k = min(x, g.IC * KK - 1), c = k / KK, t = k - c * KK, ky = t / g.Kx;
@@ -915,6 +985,7 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
     slow |= inf;
   }
   slow = __builtin_amdgcn_readfirstlane(__syncthreads_or(slow));
+  const bool marked = any_marks != 0;
   const int n_chunks = g.n_cg / g.IC, ch_first = FC ? blockIdx.z * g.cps : 0, ch_end = FC ? min(n_chunks, ch_first + g.cps) : n_chunks;
   const int slabs = (g.n_kg + g.slab - 1) / g.slab, M = FC ? 1 : g.Kp * g.Kpx;
   const int longest = min(SPLIT_RUN, n_chunks * g.n_kg / 2);
@@ -957,24 +1028,41 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
     lds_dma16_n(w_at + (unsigned)(buf * slab_bytes + q * 1024), wt, (unsigned)(at * ROWS * 32 + (q * 64 + lane) * 16), min(share, loads - q));
   };
 
-  // CAREFUL: a group with an infinite weight, in products of 32 bits.  Code of its own: as a branch of the step loop it cost the
-  // products of halves 2 % (30 registers).  An infinity in every 97th weight, 4096 digits: 440 us a call (180 without; 35600 with
-  // the sums of such rows by a thread an output), 512 images of 300 maps a layer: 1420 (510; 214000).
+  typedef float accv __attribute__((ext_vector_type(AV)));
+  auto aim_lanes = [&](int cb) {                   // (behind the last image: that one)
+#pragma unroll
+    for (int q = 0; q < COLS / 64; ++q) image[q] = (unsigned)(min(q * 64 + lane, g.n_win - 1 - cb * COLS) * g.pix * 16);
+  };
+  auto start = [&](int cb, int xb, int wb) {       // the first chunk and slab of a block
+    if constexpr (FC) aim_lanes(cb);
+    aim(cb);
+    fetch_x(ch_first, xb);
+    fetch_w(ch_first * g.n_kg, min(g.slab, g.n_kg), wb);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  };
+  auto all_halves = [&](int cb) {                  // of what a block reads
+    aim(cb);
+    const int n_px = FC ? min(COLS, g.n_win - cb * COLS) * g.pix : x_n;
+    bool found = false;
+    for (int m = 0; m < g.in_groups; ++m) {
+      const CNN_GLOBAL unsigned char* marks = g.in_marks.at + (g.in_plane >> 4) * m + x_first;
+      for (int x = tid; x < n_px; x += BT) found |= marks[x] != 0;
+    }
+    return __builtin_amdgcn_readfirstlane(__syncthreads_or(found)) == 0;
+  };
   auto run = [&](auto careful) {
     constexpr bool CAREFUL = decltype(careful)::value;
-    typedef float accv __attribute__((ext_vector_type(AV)));
+    // (what the lanes need is worked out once more: kept from the products of halves it cost those registers)
+    if constexpr (CAREFUL) asm volatile("" : "+v"(tid), "+v"(lane), "+v"(lrow), "+v"(lk), "+s"(wave));
     int xb = 0, wb = 0;
-    auto aim_lanes = [&](int cb) {                   // (behind the last image: that one)
-#pragma unroll
-      for (int q = 0; q < COLS / 64; ++q) image[q] = (unsigned)(min(q * 64 + lane, g.n_win - 1 - cb * COLS) * g.pix * 16);
-    };
-    if constexpr (FC) aim_lanes(blockIdx.x);
-    aim(blockIdx.x);
-    fetch_x(ch_first, 0);
-    fetch_w(ch_first * g.n_kg, min(g.slab, g.n_kg), 0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if constexpr (!CAREFUL) start(blockIdx.x, 0, 0);
     for (int cb = blockIdx.x; cb < g.n_cb; cb += gridDim.x) {
-      const bool more = cb + (int)gridDim.x < g.n_cb;
+      if constexpr (CAREFUL) {
+        if (!slow && all_halves(cb)) continue;
+        __syncthreads();   // what is staged has been read
+        start(cb, xb, wb);
+      }
+      const bool more = !CAREFUL && cb + (int)gridDim.x < g.n_cb;
       const int first = x_first;
       // the first pixel of the batch that column c reads (columns that are not there: the block's first)
       auto column = [&](int c) {
@@ -1023,25 +1111,35 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
           if constexpr (CAREFUL) {   // (infinity times either half of zero, or of signs that differ, is no number: halves are put together first)
 #pragma clang loop unroll(disable)
             for (int st = 0; st < steps; ++st) {
+              const int k = ko[st * S], c = k / (2 * plane), vg = ch * g.IC + c, eight = FC ? fast_div(vg, g.by_pix) : vg;
+              float x[CT][8];
 #pragma unroll
               for (int ct = 0; ct < CT; ++ct) {
-                const char* p = x_b + (pbase[ct] + ko[st * S]);
+                const char* p = x_b + (pbase[ct] + k);
                 const v8h ph = *(const v8h*)p, pl = *(const v8h*)(p + plane);
-                float x[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) x[i] = (float)ph[i] + (float)pl[i];
-#pragma unroll
-                for (int m = 0; m < RT; ++m) {
-                  const char* w = w_b + (st * S * 2 * ROWS + m * TR) * 16;
-                  const v8h qh = *(const v8h*)w, ql = *(const v8h*)(w + ROWS * 16);
-#pragma unroll
-                  for (int i = 0; i < 8; ++i) {
-                    const float wi = (float)qh[i] + (float)ql[i];
-                    if constexpr (TR == 32) acc[m][ct] = __builtin_amdgcn_mfma_f32_32x32x2f32(wi, x[i], acc[m][ct], 0, 0, 0);
-                    else acc[m][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(wi, x[i], acc[m][ct], 0, 0, 0);
-                  }
-                  __builtin_amdgcn_sched_barrier(0);
+                bool whole = false;
+                if (marked) {
+                  const int px = FC ? min(cb * COLS + (pbase[ct] >> 4), g.n_win - 1) * g.pix + vg - eight * g.pix
+                                    : first + ((pbase[ct] + k - c * 2 * plane) >> 4);
+                  whole = g.in_marks.at[(g.in_plane >> 4) * fast_div(eight, g.by_eights) + px] != 0;
                 }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) x[ct][i] = whole ? whole_of(ph[i], pl[i]) : (float)ph[i] + (float)pl[i];
+              }
+#pragma unroll
+              for (int m = 0; m < RT; ++m) {
+                const char* w = w_b + (st * S * 2 * ROWS + m * TR) * 16;
+                const v8h qh = *(const v8h*)w, ql = *(const v8h*)(w + ROWS * 16);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                  const float wi = (float)qh[i] + (float)ql[i];
+#pragma unroll
+                  for (int ct = 0; ct < CT; ++ct) {
+                    if constexpr (TR == 32) acc[m][ct] = __builtin_amdgcn_mfma_f32_32x32x2f32(wi, x[ct][i], acc[m][ct], 0, 0, 0);
+                    else acc[m][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(wi, x[ct][i], acc[m][ct], 0, 0, 0);
+                  }
+                }
+                __builtin_amdgcn_sched_barrier(0);   // (fewer registers)
               }
             }
           } else {
@@ -1124,11 +1222,13 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
       };
       const gf out_z = FC ? g.out + (long long)blockIdx.z * g.slice_stride : g.out;
       const unsigned plane_out = (unsigned)g.split_out * 16u;
-      auto store = [&](int w, int r, float out) {
+      CNN_GLOBAL unsigned char* marks = g.out_marks.at + (size_t)blockIdx.y * (unsigned)g.split_out;
+      auto store = [&](int w, int r, float out, bool whole) {
         const int j = j0 + r;
         if (g.split_out) {   // (the last map brings the zeros that fill its group up)
           const unsigned off = (unsigned)(j >> 3) * 2u * plane_out + (unsigned)w * 16u + (unsigned)(j & 7) * 2u;
-          put_split((CNN_GLOBAL char*)g.out, plane_out, off, out);
+          if (whole) put_whole((CNN_GLOBAL char*)g.out, plane_out, off, out);
+          else put_split((CNN_GLOBAL char*)g.out, plane_out, off, out);
           if (j == g.Mo - 1)
             for (int u = 1; u < 8 - (j & 7); ++u) put_split((CNN_GLOBAL char*)g.out, plane_out, off + 2u * u, 0.f);
           return;
@@ -1143,73 +1243,164 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
           const int c = (wave * CT + ct) * TR + lrow;
           const int w = cb * g.wins + (M == 4 ? c >> 2 : c);
           const bool ok = w < g.n_win && (M == 4 ? c >> 2 : c) < g.wins;
-          const int b = ok ? fast_div(w, g.by_win_img) : 0, wi = ok ? w - b * g.win_img : 0;
-          const unsigned o0 = (unsigned)b * (unsigned)g.out_stride + (unsigned)wi;
+          // the sums of four rows of a lane, eight (TR = 32) or sixteen of the tile, as outputs (M == 4: the one of row + q)
+          auto outputs = [&](int m, int v4, int row, float sum, float (&sv)[4]) {
+            if (M == 4) {
+              sv[0] = pool_quad(sum, tot[m][ct][v4 + 1], tot[m][ct][v4 + 2], tot[m][ct][v4 + 3], q);
+              sv[0] = finish(row + q, sv[0], lds_e[row + q]);
+            } else {
 #pragma unroll
-          for (int m = 0; m < RT; ++m) {
+              for (int u = 0; u < 4; ++u) sv[u] = finish(row + u, u ? tot[m][ct][v4 + u] : sum, lds_e[row + u]);
+            }
+          };
+          if (!g.split_out) {
+            const int b = ok ? fast_div(w, g.by_win_img) : 0, wi = ok ? w - b * g.win_img : 0;
+            const unsigned o0 = (unsigned)b * (unsigned)g.out_stride + (unsigned)wi;
 #pragma unroll
-            for (int v4 = 0; v4 < AV; v4 += 4) {   // four rows of a lane, eight (TR = 32) or sixteen of the tile
-              __builtin_amdgcn_sched_barrier(0);   // (fewer registers: the next rows' work stays behind this one's)
-              const int first = m * TR + v4 * 2, row = first + lk4;   // (TR = 16: v4 is 0)
-              if (j0 + first >= g.Mo) break;
-              const bool part = j0 + first + (TR == 32 ? 8 : 16) > g.Mo;
-              float sv[4];
-              if (M == 4) {
-                sv[0] = pool_quad(tot[m][ct][v4], tot[m][ct][v4 + 1], tot[m][ct][v4 + 2], tot[m][ct][v4 + 3], q);
-                sv[0] = finish(row + q, sv[0], lds_e[row + q]);
-              } else {
+            for (int m = 0; m < RT; ++m) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) sv[u] = finish(row + u, tot[m][ct][v4 + u], lds_e[row + u]);
-              }
-              if (g.split_out) {   // groups of eight maps: maps behind the last one are zero
-                const unsigned off = (TR == 32 ? 0u : (unsigned)(lk4 >> 3) * 2u * plane_out) + (unsigned)w * 16u + (unsigned)(lk4 & 4) * 2u;
-                CNN_GLOBAL char* out = (CNN_GLOBAL char*)g.out + (size_t)((unsigned)(j0 + first) >> 3) * 2 * plane_out;
+              for (int v4 = 0; v4 < AV; v4 += 4) {
+                __builtin_amdgcn_sched_barrier(0);   // (fewer registers: the next rows' work stays behind this one's)
+                const int first = m * TR + v4 * 2, row = first + lk4;   // (TR = 16: v4 is 0)
+                if (j0 + first >= g.Mo) break;
+                float sv[4];
+                outputs(m, v4, row, tot[m][ct][v4], sv);
                 if (M == 4) {
-                  if (part && j0 + row + q >= g.Mo) sv[0] = 0.f;
-                  if (ok && (!part || j0 + row + q < ((g.Mo + 7) & ~7))) put_split(out, plane_out, off + (unsigned)q * 2u, sv[0]);
+                  if (ok && j0 + row + q < g.Mo) out_z[o0 + (unsigned)(j0 + row + q) * (unsigned)g.win_img] = sv[0];
                 } else {
 #pragma unroll
                   for (int u = 0; u < 4; ++u)
-                    if (part && j0 + row + u >= g.Mo) sv[u] = 0.f;
-                  if (ok && (!part || j0 + row < ((g.Mo + 7) & ~7))) put_split4(out, plane_out, off, sv);
+                    if (ok && j0 + row + u < g.Mo) out_z[o0 + (unsigned)(j0 + row + u) * (unsigned)g.win_img] = sv[u];
                 }
-              } else if (M == 4) {
-                if (ok && j0 + row + q < g.Mo) out_z[o0 + (unsigned)(j0 + row + q) * (unsigned)g.win_img] = sv[0];
+              }
+            }
+            continue;
+          }
+          // groups of eight maps: maps behind the last one are zero
+          auto eights = [&](int m, int v4, float (&sv)[4]) {
+            const int row = m * TR + v4 * 2 + lk4;
+            const bool part = j0 + m * TR + v4 * 2 + (TR == 32 ? 8 : 16) > g.Mo;
+            if (M == 4) {
+              if (part && j0 + row + q >= g.Mo) sv[0] = 0.f;
+              return !part || j0 + row + q < ((g.Mo + 7) & ~7);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (part && j0 + row + u >= g.Mo) sv[u] = 0.f;
+            return !part || j0 + row < ((g.Mo + 7) & ~7);
+          };
+          auto off_of = [&]() { return (TR == 32 ? 0u : (unsigned)(lk4 >> 3) * 2u * plane_out) + (unsigned)w * 16u + (unsigned)(lk4 & 4) * 2u; };
+          auto out_of = [&](int first) { return (CNN_GLOBAL char*)g.out + (size_t)((unsigned)(j0 + first) >> 3) * 2 * plane_out; };
+          float most = 0.f;
+#pragma unroll
+          for (int m = 0; m < RT; ++m) {
+#pragma unroll
+            for (int v4 = 0; v4 < AV; v4 += 4) {
+              __builtin_amdgcn_sched_barrier(0);
+              const int first = m * TR + v4 * 2;
+              if (j0 + first >= g.Mo) break;
+              float sv[4];
+              outputs(m, v4, first + lk4, tot[m][ct][v4], sv);
+              const bool there = eights(m, v4, sv);
+              if (M == 4) {
+                most = fmaxf(most, fabsf(sv[0]));
+                if (ok && there) put_split(out_of(first), plane_out, off_of() + (unsigned)q * 2u, sv[0]);
               } else {
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                  if (ok && j0 + row + u < g.Mo) out_z[o0 + (unsigned)(j0 + row + u) * (unsigned)g.win_img] = sv[u];
+                for (int u = 0; u < 4; ++u) most = fmaxf(most, fabsf(sv[u]));
+                if (ok && there) put_split4(out_of(first), plane_out, off_of(), sv);
               }
             }
           }
+          unsigned long long small = __ballot(ok && !(most >= SPLIT_TINY));   // the lanes of a window
+          if (M == 4) { small &= small >> 1; small &= small >> 2; small &= 0x1111111111111111ull; }
+          for (int d = 32; d >= TR; d >>= 1) small &= small >> d;
+          bool tiny = false;
+          if (__builtin_expect(small != 0, 0)) {
+            if (M == 4) { most = fmaxf(most, __shfl_xor(most, 1)); most = fmaxf(most, __shfl_xor(most, 2)); }
+            for (int d = 32; d >= TR; d >>= 1) most = fmaxf(most, __shfl_xor(most, d));
+            tiny = ok && most < SPLIT_TINY;
+            if (!__any(tiny && most > 0.f)) tiny = false;   // (zeros are halves, and floats)
+            else {                                          // once more: these are stored as they are
+              if (lane == 0) mark_any(g.out_marks);
+#pragma unroll
+              for (int m = 0; m < RT; ++m)
+#pragma unroll
+                for (int v4 = 0; v4 < AV; v4 += 4) {
+                  const int first = m * TR + v4 * 2;
+                  if (j0 + first >= g.Mo) break;
+                  float sum = tot[m][ct][v4], sv[4];
+                  asm volatile("" : "+v"(lk4), "+v"(sum));   // (or what is worked out above is kept in registers for here)
+                  outputs(m, v4, first + lk4, sum, sv);
+                  const bool there = eights(m, v4, sv);
+                  if (!tiny || !there) continue;
+                  if (M == 4) put_whole(out_of(first), plane_out, off_of() + (unsigned)q * 2u, sv[0]);
+                  else put_whole4(out_of(first), plane_out, off_of(), sv);
+                }
+            }
+          }
+          if (ok && lane < TR && q == 0) marks[w] = tiny;
         }
       } else {
         // a thread's window stays its own for all rows it takes
         const int rows = BT / g.wins, jr = tid / g.wins, wl = tid - jr * g.wins;
         const int w = cb * g.wins + wl;
         const bool ok = jr < rows && w < g.n_win;
+        auto tiles = [&](auto whole, bool mine) {
+          float most = 0.f;
 #pragma unroll
-        for (int m = 0; m < RT; ++m) {
-          __syncthreads();   // the previous tile has been read
+          for (int m = 0; m < RT; ++m) {
+            __syncthreads();   // the previous tile has been read
 #pragma unroll
-          for (int ct = 0; ct < CT; ++ct)
+            for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-            for (int v = 0; v < AV; ++v) ep[(row_of(0, v)) * EPS + (wave * CT + ct) * TR + lrow] = tot[m][ct][v];
-          __syncthreads();
-          if (ok)
-            for (int r = jr; r < TR; r += rows) {
-              if (j0 + m * TR + r >= g.Mo) break;
-              const float* win = ep + r * EPS + wl * M;
-              float best = -INFINITY;
-              for (int d = 0; d < M; ++d) best = fmaxf(best, win[d]);
-              store(w, m * TR + r, finish(m * TR + r, best, lds_e[m * TR + r]));
-            }
+              for (int v = 0; v < AV; ++v) ep[(row_of(0, v)) * EPS + (wave * CT + ct) * TR + lrow] = tot[m][ct][v];
+            __syncthreads();
+            if (mine)
+              for (int r = jr; r < TR; r += rows) {
+                if (j0 + m * TR + r >= g.Mo) break;
+                const float* win = ep + r * EPS + wl * M;
+                float best = -INFINITY;
+                for (int d = 0; d < M; ++d) best = fmaxf(best, win[d]);
+                const float out = finish(m * TR + r, best, lds_e[m * TR + r]);
+                most = fmaxf(most, fabsf(out));
+                store(w, m * TR + r, out, whole);
+              }
+          }
+          return most;
+        };
+        if (tid < g.wins) w_most[tid] = 0;
+        const float most = tiles(std::false_type{}, ok);
+        if (!g.split_out) continue;
+        if (ok) atomicMax(&w_most[wl], __float_as_uint(most));
+        __syncthreads();
+        bool any = false;
+        for (int x = lane; x < g.wins; x += 64) {   // (every wavefront looks at all of them)
+          const float v = __uint_as_float(w_most[x]);
+          any |= v > 0.f && v < SPLIT_TINY;
+        }
+        any = __any(any);
+        if (wave == 0)
+          for (int x = lane; x < g.wins && cb * g.wins + x < g.n_win; x += 64) marks[cb * g.wins + x] = any && __uint_as_float(w_most[x]) < SPLIT_TINY;
+        if (__builtin_expect(any, 0)) {             // once more: these are stored as they are
+          if (tid == 0) mark_any(g.out_marks);
+          tiles(std::true_type{}, ok && __uint_as_float(w_most[min(wl, g.wins - 1)]) < SPLIT_TINY);
         }
       }
     }
   };
-  if (slow) run(std::true_type{});
-  else run(std::false_type{});
+  // Products in 32 bits for a group with an infinite weight, and, behind those of halves, for blocks that read values that are no
+  // halves (not in front of them where no block of the workgroup's is without).  Code of its own: as a branch of the step loop it
+  // cost the products of halves 2 % (30 registers), as one of a block 3 to 6 %.  4096 digits: 175 us a call in halves; with an
+  // infinity in every 97th weight 418 (35600 with the sums of such rows by a thread an output), with all weights 1e-7 of that 452;
+  // 512 images of 300 maps a layer 500, 1490 (214000) and 1560.
+  bool halves = !slow;
+  if (halves && marked) {
+    halves = false;
+    for (int cb = blockIdx.x; cb < g.n_cb && !halves; cb += gridDim.x) halves = all_halves(cb);
+  }
+  if (halves) run(std::false_type{});
+  if (slow || marked) run(std::true_type{});
 }
 
 // the planes of partial sums of one output, added in their order, up to eight loads in flight
@@ -1404,6 +1595,7 @@ __device__ void pack_split(const BatchPack& q, int* e4) {
   const int KK = q.K * q.Kx, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int rows = (q.Mo + q.row - 1) / q.row * q.row, total = q.n_chunks * q.n_kg;
   const int pieces = (total + q.piece - 1) / q.piece;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *q.any = 0;
   for (int job = blockIdx.x; job < rows / 4 * pieces; job += gridDim.x) {
     const int tile = job / pieces, piece = job - tile * pieces;
     const int jw = tile * 4 + wave;
@@ -1597,7 +1789,7 @@ int batch_first_steps(int k_total) {
 }
 size_t batch_first_lds_bytes(const BatchFirst& g) {
   const size_t rows = (size_t)g.T * 32;
-  return (size_t)g.T * g.H * 2048 + (rows * g.k_total + rows * 2 + (size_t)16 * g.H + (g.share ? (size_t)4 * g.T * 1024 : 0)) * 4;
+  return (size_t)g.T * g.H * 2048 + (rows * g.k_total + rows * 2 + (size_t)16 * g.H + (g.share ? (size_t)4 * g.T * 1024 + 128 : 0)) * 4;
 }
 // workgroups a compute unit holds at once: registers, LDS
 int batch_first_fit(const BatchFirst& g) {
@@ -1630,7 +1822,7 @@ hipError_t launch_batch_first(hipStream_t stream, const BatchFirst& g) {
 size_t batch_split_lds_bytes(const BatchSplit& g) {
   const int M = g.Kp * g.Kpx, rows = g.RT * g.TR, cols = 4 * g.CT * g.TR;
   return 2 * (size_t)g.IC * 2 * g.run_px * 16 + 2 * (size_t)g.slab * rows * 32 + (size_t)g.n_kg * 4 + (size_t)rows * 8 +
-         (M == 1 || M == 4 ? 0 : (size_t)g.TR * (cols + 4) * 4);
+         (M == 1 || M == 4 ? 0 : ((size_t)g.TR * (cols + 4) + g.wins) * 4);
 }
 // workgroups a compute unit holds at once: registers, LDS
 int batch_split_fit(const BatchSplit& g) {

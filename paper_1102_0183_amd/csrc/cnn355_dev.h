@@ -302,9 +302,18 @@ struct BatchConv {
 // A convolutional layer behind another one, over a whole batch, in products of halves (k_batch_split).  Activations are
 // written by the layer below as v * 2^SPLIT_SHIFT = high + low, both halves, in groups of eight maps:
 // [group][high, low][pixel of the batch][8], so that what a block of columns reads of a group is one run; the maps that fill
-// the last group up are zero.
+// the last group up are zero.  The sum of the halves is off by at most 2^-24 of v where |v| >= 2^-16, and by 2^-39 below: where
+// all that a workgroup of the layer below writes of a pixel is smaller than SPLIT_TINY, and not zero, these values are stored
+// as they are (SplitMarks).
 constexpr int SPLIT_SHIFT = 14;         // |activation| <= 1.7159: below the largest half
 constexpr int SPLIT_SLOW = 0x4000;      // row exponent of a row with an infinite weight
+constexpr float SPLIT_TINY = 0x1p-16f;
+// Behind the halves a byte for every group of maps of a workgroup (`eights` groups of eight) and pixel of the batch: 1 where the
+// values are 32-bit floats, the upper 16 bits in the place of the high half, the lower ones in that of the low half.
+struct SplitMarks {
+  CNN_GLOBAL unsigned char* at;  // [groups][pixels of the batch]
+  CNN_GLOBAL int* any;           // not 0: there has been such a pixel in this call
+};
 struct BatchSplit {
   const CNN_GLOBAL char* in;
   const CNN_GLOBAL char* wt;     // [group of RT * TR maps][chunk][n_kg][high, low][RT * TR][8] halves, w * 2^e of its row
@@ -327,6 +336,9 @@ struct BatchSplit {
   int fc;
   FastDiv by_pix;
   int drop;                      // sums that are no number count as -inf (as where the 32-bit product's planes are added)
+  SplitMarks in_marks, out_marks;
+  int in_groups;                 // groups of in_marks
+  FastDiv by_eights;             // groups of eight maps of such a group
   int cps, raw;                  // chunks of a slice of the k range, one per blockIdx.z; raw: sums without bias and activation,
   long long slice_stride;        //   a plane for every slice, slice_stride floats apart
 };
@@ -356,6 +368,7 @@ struct BatchFirst {
   int T, H;                      // tiles of 32 maps a workgroup (0: the layer is not planned so); steps of 16 k
   int share;                     // 1: four wavefronts share the members of 32 windows
   int split_out;                 // pixels of the output's planes
+  SplitMarks out_marks;
 };
 struct BatchPool {
   const CNN_GLOBAL float* sums;  // [batch][Mo][Ho][Wo] raw sums
@@ -374,6 +387,7 @@ struct BatchPack {
   int full_table, Mo, K, Kx;     // (a fully connected layer: full, K = Kx = 1)
   int row, k_total;              // maps of a group of Wt, rows of it
   CNN_GLOBAL int* exps;          // split halves (BatchSplit) where not null, with
+  CNN_GLOBAL int* any;           // (of the marks of its input, cleared)
   int Mi, n_chunks, per_chunk, n_kg;   // (group of maps, tap) pairs of a chunk, and with those that fill an instruction up
   int piece;                           // pairs that a workgroup writes at a time
 };

@@ -322,7 +322,7 @@ struct cnn {
   int* d_fe_src = nullptr;
   float* d_fe_out = nullptr;
   float* d_fe_batch = nullptr;  // resident mode: front-end outputs of FE_BATCH images at a time
-  std::shared_ptr<const BatchKept> batch_kept;   // the plan of the last batched forward call
+  std::vector<std::shared_ptr<const BatchKept>> batch_kept;   // plans of the last batched forward calls, the last one first
   std::mutex batch_kept_lock;
   float* d_mm_part = nullptr;   // partial sums of the matrix-core forward pass (one layer at a time)
   size_t mm_part_floats = 0;
@@ -1879,8 +1879,11 @@ int batch_plan(cnn* net, size_t batch, BatchPlan& B) {
   return CNN_OK;
 }
 
-// The plan of a handle for a batch.  The last one is kept, with all that it was made from, and taken again while that is the same:
-// making it takes 11 to 42 us of the host's time, which a single call waits for.
+// The plan of a handle for a batch.  The last few are kept, with all that they were made from, and taken again while that is the
+// same: making one takes 9 to 58 us of the host's time (2.7 to 14 for 32-bit products alone), which a single call waits for.  Few,
+// and not one: a program goes back and forth between batches (training and validation sets, what remains of one), or asks for
+// another one's memory in between.  The lock is for calls that ask for memory side by side: they only read the handle otherwise.
+constexpr size_t BATCH_KEPT = 4;
 int batch_plan(cnn* net, size_t batch, std::shared_ptr<const BatchKept>& out);
 
 }  // namespace
@@ -1900,16 +1903,22 @@ namespace {
 int batch_plan(cnn* net, size_t batch, std::shared_ptr<const BatchKept>& out) {
   const ProgramDev& P = net->prog;
   std::lock_guard<std::mutex> hold(net->batch_kept_lock);
-  if (!net->batch_kept || !net->batch_kept->made_for(P, batch)) {
+  auto& kept = net->batch_kept;
+  size_t at = 0;
+  while (at < kept.size() && !kept[at]->made_for(P, batch)) ++at;
+  if (at == kept.size()) {
     auto made = std::make_shared<BatchKept>();
     const int rc = batch_plan(net, batch, made->plan);
     if (rc) return rc;
     made->batch = batch;
     made->has_frontend = P.has_frontend; made->n_filters = P.fe.n_filters; made->fe_h = P.fe.H; made->fe_w = P.fe.W;
     made->layers.assign(P.layers, P.layers + P.n_layers);
-    net->batch_kept = std::move(made);
+    if (kept.size() < BATCH_KEPT) kept.push_back(nullptr);
+    at = kept.size() - 1;
+    kept[at] = std::move(made);
   }
-  out = net->batch_kept;
+  std::rotate(kept.begin(), kept.begin() + at, kept.begin() + at + 1);
+  out = kept.front();
   return CNN_OK;
 }
 }  // namespace

@@ -1593,6 +1593,10 @@ double split_plan(const LayerDev& L, size_t batch, BatchSplit& out) {
           }
         }
       }
+  if (out.slab > SPLIT_RUN) {   // (a running sum is a slab at least)
+    const int S = out.TR == 32 ? 2 : 4, parts = (out.n_kg + SPLIT_RUN - 1) / SPLIT_RUN;
+    out.slab = ((out.n_kg + parts - 1) / parts + S - 1) / S * S;
+  }
   if (out.RT) { out.by_win_img = fast_div_of(out.win_img); out.by_wp = fast_div_of(out.Wp); }
   return best;
 }
@@ -1627,7 +1631,7 @@ double fc_plan(const LayerDev& L, int maps, int pix, size_t batch, int most_slic
         if (groups > 1 && groups * rows - t.Mo >= rows / 2) continue;
         t.RT = rt; t.CT = ct; t.TR = tr; t.wins = t.run_px = cols;
         const size_t n_cb = (batch + cols - 1) / cols;
-        for (int ic = 1; ic <= std::min(t.n_cg, 48); ++ic) {
+        for (int ic = 1; ic <= std::min(t.n_cg, SPLIT_RUN); ++ic) {   // (a chunk is a slab)
           if (t.n_cg % ic) continue;
           t.IC = ic;
           t.n_kg = t.slab = (ic + S - 1) / S * S;

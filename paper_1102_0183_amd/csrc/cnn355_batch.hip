@@ -922,15 +922,15 @@ __global__ void __launch_bounds__(BT, first_waves(T, H)) k_batch_first(BatchFirs
 // The product of k_batch_conv on v_mfma_f32_{32x32x16,16x16x32}_f16, which take sixteen times the terms a clock: both
 // operands are split into two halves (23 bits together), a = ah + al, and ah xh + ah xl + al xh summed in 32 bits; al xl is
 // below 2^-22 of the term.  An instruction adds its terms in groups of eight to the running sum, each group's sum rounded; so a
-// running sum ends after SPLIT_RUN groups and is added to the total, which keeps the error against 64 bits below that of the
-// 32-bit products.  The layer below has split its activations already
-// (put_split), in groups of eight maps, so that a lane's eight k are one 16-byte read from LDS: k = (group of eight maps, ky,
-// kx, map of the group).
+// running sum ends after whole slabs of at most SPLIT_RUN groups together and is added to the total, which keeps the error against
+// 64 bits below that of the 32-bit products.  The layer below has split its activations already (put_split), in groups of eight
+// maps, so that a lane's eight k are one 16-byte read from LDS: k = (group of eight maps, ky, kx, map of the group).
 // What a workgroup writes of a window is stored as floats where all of it is tiny (SplitMarks): the largest output is kept along
 // with the stores, and the stores are done again where it is.  40C5 of 4096 digits 81.3 -> 83.1 us with it, the first layer's 20C4
 // 46.1 -> 46.9, 100N of 33 stereo pairs 8.4 -> 9.2 (it waits for the word that says whether there is such a window).
-// Error against 64 bits (2-norm, of 64 images' outputs of a layer, 32-bit products / halves): 300C4 on 300 maps 5.7e-7 /
-// 3.3e-7, 300C2 4.0 / 2.2, 40C5 on 20 2.4 / 2.2, 128C3 on 50 2.4 / 2.2; without runs 8.8, 3.8, 2.9 and 3.0.
+// Error against 64 bits (2-norm, of a layer's outputs from the images on, 32-bit products / halves): 300C4 behind 300C2 behind
+// 300C3 10.8e-7 / 3.4e-7, 300C2 5.8 / 2.2, 40C5 behind 20C4 4.8 / 2.4, 128C3 behind 50C5 2.3 / 2.0; of 300C4 alone 5.7 / 3.3, and
+// 8.8 without runs.
 // Staging as in k_batch_conv: the next slab of weights (a run of the k range, packed in the order it is read) and the next
 // chunk of input maps go to the other halves of their buffers by 16-byte loads to LDS while the present ones are multiplied,
 // one barrier a slab, nothing between two column blocks.
@@ -943,7 +943,6 @@ __global__ void __launch_bounds__(BT, first_waves(T, H)) k_batch_first(BatchFirs
 // maps at one pixel (16 bytes a line of memory; neighbouring pixels follow in the same chunk and meet it in the caches); the k
 // range in slices where the images are few.  Against k_batch_gemm and its k_batch_pool: 150N of 4096 digits 30 us -> 14.3, 300N of
 // 512 images 27 -> 14.2, 100N of 33 stereo pairs 21.5 -> 8.4.
-constexpr int SPLIT_RUN = 32;
 // wavefronts a SIMD, by the registers of sums, totals and two sets of columns
 constexpr int split_waves(int RT, int CT, int TR) {
   const int regs = 2 * RT * CT * (TR == 32 ? 16 : 4) + 16 * CT + 48;
@@ -1192,7 +1191,7 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
 #undef CNN355_STEP
 #undef CNN355_MAC
           pairs += here;
-          if (pairs >= longest || (last && sl + 1 == slabs)) {
+          if (pairs + g.slab > longest || (last && sl + 1 == slabs)) {
             pairs = 0;
 #pragma unroll
             for (int m = 0; m < RT; ++m)

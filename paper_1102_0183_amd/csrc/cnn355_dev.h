@@ -308,6 +308,7 @@ struct BatchConv {
 constexpr int SPLIT_SHIFT = 14;         // |activation| <= 1.7159: below the largest half
 constexpr int SPLIT_SLOW = 0x4000;      // row exponent of a row with an infinite weight
 constexpr float SPLIT_TINY = 0x1p-16f;
+constexpr int SPLIT_RUN = 32;           // groups of eight terms of a running sum, and of a slab of weights, at most
 // Behind the halves a byte for every group of maps of a workgroup (`eights` groups of eight) and pixel of the batch: 1 where the
 // values are 32-bit floats, the upper 16 bits in the place of the high half, the lower ones in that of the low half.
 struct SplitMarks {

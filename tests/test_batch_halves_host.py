@@ -53,3 +53,11 @@ def test_single_images_keep_the_32_bit_products():
     """Their layers are launches and waits, whichever the kernel; measured up to 1.2 times as slow in halves."""
     for arch in ("1x13x13-100C2-MP1-5C4S1-MP1-4N", "2x21x21-100C1-MP1-150C2S1-MP1-4N", "3x53x53-100C2-MP1-40C1S1-MP1-4N"):
         assert not any(p["split"] or p["first"] for p in binding.batch_plan(arch, 1)[0])
+
+
+@pytest.mark.parametrize("arch", ARCHS)
+def test_running_sums_end_after_32_groups(arch):
+    """A running sum is whole slabs of weights, as many as are 32 groups of eight terms together, or one."""
+    for batch in BATCHES:
+        for p in binding.batch_plan(arch, batch)[0]:
+            assert not p["split"] or p["split_slab"] <= 32, (batch, p)

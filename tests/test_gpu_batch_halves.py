@@ -216,3 +216,43 @@ def test_infinite_weights_take_no_longer_than_products_in_32_bits():
     print("us a call without and with infinite weights", us, flush=True)
     assert us[1] <= 16 * us[0], us
     g.close()
+
+
+@pytest.mark.parametrize("arch,batch,errors", [
+    ("1x29x29-20C4-MP2-40C5-MP3-150N-10N", 4096, (1.1e-7, 2.7e-7, 3.0e-7)),
+    ("3x32x32-300C3-MP2-300C2-MP2-300C4-MP2-300N-10N", 512, (1.2e-7, 2.5e-7, 3.8e-7, 4.4e-7)),
+    ("2x48x48-50C5-MP2-128C3-MP4-100N-5N", 33, (1.2e-7, 2.4e-7, 3.4e-7)),
+])
+def test_errors_against_64_bits(arch, batch, errors):
+    """The layers' outputs for 24 images of a batch, from the images in 64 bits (2-norm).  Measured 1.0, 2.4, 2.6; 1.0, 2.2, 3.4,
+    3.9; 1.1, 2.0, 3.1 (e-7), in 32-bit products 1.0, 4.8, 4.6; 1.1, 5.8, 10.8, 11.2; 1.4, 2.3, 3.4: a tenth above the measured ones,
+    which is below what the running sums are off by where they do not end (2.9, 3.8 and 3.0 in the second layers)."""
+    import torch
+    import torch.nn.functional as F
+    plan = binding.batch_plan(arch, batch)[0]
+    assert plan[0]["first"] and all(p["split"] for p in plan[1:len(errors)])
+    g = binding.Cnn(arch)
+    w = ((np.random.default_rng(5).random(g.num_weights, dtype=np.float32) - np.float32(0.5)) * np.float32(0.1))
+    g.set_weights(w)
+    i0 = g.layer_info(0)
+    x = torch.rand((batch, i0["maps"], i0["h"], i0["w"]), generator=torch.Generator().manual_seed(1)) * 2 - 1
+    d, scratch = to_dev(x.numpy().reshape(batch, -1)), _scratch(g, batch)
+    h, at, l = x[:24].double(), 0, 1
+    for k, most in enumerate(errors):
+        a = g.layer_info(l)
+        n_in = h[0].numel() if a["kind"] == binding.LAYER_FC else h.shape[1] * a["K"] ** 2
+        bias, m = torch.from_numpy(w[at:at + a["maps"]]).double(), torch.from_numpy(w[at + a["maps"]:at + a["maps"] * (1 + n_in)]).double()
+        at += a["maps"] * (1 + n_in)
+        if a["kind"] == binding.LAYER_FC:
+            y = h.flatten(1) @ m.view(a["maps"], -1).T + bias
+            l += 1
+        else:
+            y = F.conv2d(h, m.view(a["maps"], h.shape[1], a["K"], a["K"]))
+            y = F.max_pool2d(y, g.layer_info(l + 1)["K"]) + bias.view(1, -1, 1, 1)
+            l += 2
+        h = 1.7159 * torch.tanh(0.6666 * y)
+        got = torch.from_numpy(np.asarray(g.debug_forward_batch_layer(d, batch, k, scratch))).double()[:24].reshape(h.shape)
+        e = ((got - h).norm() / h.norm()).item()
+        print("layer", k, "error %.2e" % e, flush=True)
+        assert e <= most, (k, e)
+    g.close()

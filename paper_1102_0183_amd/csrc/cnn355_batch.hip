@@ -761,6 +761,8 @@ __global__ void __launch_bounds__(BT, first_waves(T, H)) k_batch_first(BatchFirs
   for (int s = 0; s < N; ++s)
     if constexpr (KEEP) ko[s] = koff[(s >> 3) * 16 + lk * 8 + (s & 7)];
   const int M = g.Kp * g.Kpx, n_tiles = (g.n_win + 31) >> 5, share = g.share;
+  // the largest number of none: of several members -inf, of one member what its sum is (the largest of two is the number of them)
+  const float none = M == 1 ? __builtin_nanf("") : -INFINITY;
   const unsigned plane = (unsigned)g.split_out * 16u;
   float px[N];
   const CNN_GLOBAL char* src = nullptr;            // the first image of the wavefront's next windows
@@ -789,7 +791,11 @@ __global__ void __launch_bounds__(BT, first_waves(T, H)) k_batch_first(BatchFirs
 #pragma unroll
     for (int m = 0; m < T; ++m)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) best[m][v] = -INFINITY;
+      for (int v = 0; v < 16; ++v) {
+        float x = none;
+        asm volatile("" : "+v"(x));   // (or sixteen of them are kept in registers)
+        best[m][v] = x;
+      }
     for (int d = d_first; d < M; d += d_step) {
       v8h xh[H], xl[H];
       float most = 0.f;

@@ -256,3 +256,39 @@ def test_errors_against_64_bits(arch, batch, errors):
         print("layer", k, "error %.2e" % e, flush=True)
         assert e <= most, (k, e)
     g.close()
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("pool", ["-", "-MP1-"])
+@pytest.mark.parametrize("where", ["pixel", "weight"])
+def test_sums_that_are_no_number_stay_so_without_pooling(where, pool, value):
+    """Units of an unpooled first layer whose sums are no number, beside others, against the sums in 64 bits; a window of several
+    units leaves them out, one of one unit has nothing else."""
+    arch, n = "2x14x14-36C3%s44C3-MP2-4N" % pool, 40
+    p = binding.batch_plan(arch, n)[0]
+    assert p[0]["first"] and p[0]["members"] == 1 and p[1]["split"]
+    g = binding.Cnn(arch)
+    w = ((np.random.default_rng(17).random(g.num_weights) - 0.5) * 0.4).astype(np.float32)
+    imgs = (np.random.default_rng(18).random((n, 2, 14, 14)) * 2 - 1).astype(np.float32)
+    if where == "pixel":
+        imgs[7, 0, 5, 6], imgs[7, 1, 5, 6] = value, -value    # (infinities of either sign in a sum)
+    else:
+        w[36 + 3 * 18 + 4] = value
+        imgs[9, 0, 4:8] = 0
+    g.set_weights(w)
+    b1, w1, at = w[:36].astype(np.float64), w[36:36 + 36 * 18].reshape(36, 2, 3, 3).astype(np.float64), 36 + 36 * 18
+    b2, w2 = w[at:at + 44].astype(np.float64), w[at + 44:at + 44 + 44 * 36 * 9].reshape(44, 36, 3, 3).astype(np.float64)
+    with np.errstate(all="ignore"):
+        x = imgs.astype(np.float64)
+        first = sum(w1[None, :, i, ky, kx, None, None] * x[:, None, i, ky:ky + 12, kx:kx + 12] for i in range(2) for ky in range(3) for kx in range(3))
+        first = 1.7159 * np.tanh(0.6666 * (first + b1[None, :, None, None]))
+    assert 0 < np.isnan(first).mean() < 0.1
+    d, scratch = to_dev(imgs.reshape(n, -1)), _scratch(g, n)
+    got = np.asarray(g.debug_forward_batch_layer(d, n, 0, scratch)).reshape(first.shape)
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(first))
+    assert np.nanmax(np.abs(got - first)) <= 1e-5 * 1.7159
+    want = _layer(first, w2, b2, 2)
+    got = np.asarray(g.debug_forward_batch_layer(d, n, 1, scratch)).reshape(want.shape)
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(want))
+    assert np.nanmax(np.abs(got - want)) <= 1e-5 * 1.7159
+    g.close()

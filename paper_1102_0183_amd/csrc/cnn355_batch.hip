@@ -974,23 +974,26 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
   unsigned* w_most = (unsigned*)(ep + TR * EPS);   // [wins] the largest output of each, of the same
   const unsigned x_at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds_x;
   const unsigned w_at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds_w;
-  const int any_marks = __builtin_amdgcn_readfirstlane(*g.in_marks.any);   // (asked for first: what it waits for comes from memory)
+  // (asked for side by side, as vector loads: one after the other they are three trips to memory before anything is staged)
+  static_assert(ROWS <= BT, "a row a thread");
+  const int j0 = blockIdx.y * ROWS, row = min(tid, ROWS - 1);
+  int none = 0;
+  asm volatile("" : "+v"(none));
+  const int any_marks = g.in_marks.any[none], e_row = g.exps[j0 + row];
+  const float b_row = g.bias[min(j0 + row, g.Mo - 1)];
   const int KK = FC ? 1 : g.K * g.Kx;
   for (int x = tid; x < g.n_kg; x += BT) {         // (pairs that fill an instruction up have no weights: a pixel that is read anyway)
     const int k = min(x, g.IC * KK - 1), c = k / KK, t = k - c * KK, ky = t / g.Kx;
     koff[x] = c * 2 * plane + (ky * g.Wi + t - ky * g.Kx) * 16;
   }
-  const int j0 = blockIdx.y * ROWS;
   bool slow = false;
-  for (int x = tid; x < ROWS; x += BT) {
-    const int e = g.exps[j0 + x];
-    const bool inf = e >= SPLIT_SLOW / 2;
-    lds_e[x] = inf ? e - SPLIT_SLOW : e;
-    lds_b[x] = j0 + x < g.Mo ? g.bias[j0 + x] : 0.f;
-    slow |= inf;
+  if (tid < ROWS) {
+    slow = e_row >= SPLIT_SLOW / 2;
+    lds_e[tid] = slow ? e_row - SPLIT_SLOW : e_row;
+    lds_b[tid] = j0 + tid < g.Mo ? b_row : 0.f;
   }
   slow = __builtin_amdgcn_readfirstlane(__syncthreads_or(slow));
-  const bool marked = any_marks != 0;
+  const bool marked = __builtin_amdgcn_readfirstlane(any_marks) != 0;
   const int n_chunks = g.n_cg / g.IC, ch_first = FC ? blockIdx.z * g.cps : 0, ch_end = FC ? min(n_chunks, ch_first + g.cps) : n_chunks;
   const int slabs = (g.n_kg + g.slab - 1) / g.slab, M = FC ? 1 : g.Kp * g.Kpx;
   const int longest = min(SPLIT_RUN, n_chunks * g.n_kg / 2);

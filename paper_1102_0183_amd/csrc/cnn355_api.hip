@@ -1680,13 +1680,19 @@ double first_plan(const LayerDev& L, size_t batch, BatchFirst& out) {
       const double est = 4000.0 + f.H * 300.0 + std::max(all, chain);
       if (best == 0 || est < best) { best = est; out = f; }
     }
+  // A last group of maps takes eight more, from the one in front of it, where it would have eight or fewer.  One or two maps of a
+  // pixel are below SPLIT_TINY by chance (with weights up to 0.05 one in 3000 of a map's activations), and every such pixel makes
+  // the blocks behind that read it take 32-bit products.  424 images of 3x32x32-65C5-MP2-32C5-MP2-24C4-MP2 281 us a call, 465 with a last
+  // group of one map; 143 of 2x96x96-193C6S1-MP2-217C4-MP4 593 and 1265.
+  if (out.T && L.Mo > out.T * 32 && (L.Mo - 1) % (out.T * 32) < 8) out.shift = 8;
   return best;
 }
 
 // The buffer of a layer that writes halves of `eights` groups of eight maps of `pix` pixels for `s`: the halves, and their marks.
 void marked(BatchStep& below, BatchSplit& s, size_t eights, size_t pix) {
   const int rows = below.f.T ? below.f.T * 32 : below.s.RT * below.s.TR;
-  s.in_groups = (int)((eights * 8 + rows - 1) / rows);
+  s.in_shift = below.f.T ? below.f.shift / 8 : 0;
+  s.in_groups = (int)(((eights + s.in_shift) * 8 + rows - 1) / rows);
   s.by_eights = fast_div_of(rows / 8);
   below.halves_per_image = eights * 8 * pix;
   below.out_per_image = below.halves_per_image + (s.in_groups * pix + 3) / 4;
@@ -2400,7 +2406,7 @@ int cnn355_batch_plan_text(const char* arch, int fan_in, size_t batch, char* buf
     f.push_back({"split", h.RT != 0});
     f.push_back({"split_fc", h.fc && h.RT});
     f.push_back({"first", st.f.T != 0});
-    if (st.f.T) f.insert(f.end(), {{"first_T", st.f.T}, {"first_H", st.f.H}, {"first_share", st.f.share}, {"first_lds", (long long)batch_first_lds_bytes(st.f)}});
+    if (st.f.T) f.insert(f.end(), {{"first_T", st.f.T}, {"first_H", st.f.H}, {"first_share", st.f.share}, {"first_shift", st.f.shift}, {"first_lds", (long long)batch_first_lds_bytes(st.f)}});
     if (h.RT)
       f.insert(f.end(), {{"split_RT", h.RT}, {"split_CT", h.CT}, {"split_TR", h.TR}, {"split_IC", h.IC}, {"split_kg", h.n_kg}, {"split_slab", h.slab},
                          {"split_slices", (h.n_cg / h.IC + h.cps - 1) / h.cps}, {"split_wins", h.wins}, {"split_px", h.run_px}, {"split_lds", (long long)batch_split_lds_bytes(h)}});
@@ -2846,7 +2852,7 @@ static int forward_batch_impl(cnn_t* net, const float* d_images, size_t n, float
               const unsigned short* h = &halves[((j >> 3) * 2 * batch * pixels + b * pixels + w) * 8 + (j & 7)];
               const unsigned short high = h[0], low = h[batch * pixels * 8];
               float& v = host_tap[(b * maps + j) * pixels + w];
-              if (whole[((j >> 3) / eights * batch + b) * pixels + w]) v = __builtin_bit_cast(float, (unsigned)high << 16 | low);
+              if (whole[(((j >> 3) + reader.in_shift) / eights * batch + b) * pixels + w]) v = __builtin_bit_cast(float, (unsigned)high << 16 | low);
               else v = ((float)__builtin_bit_cast(_Float16, high) + (float)__builtin_bit_cast(_Float16, low)) / (float)(1 << SPLIT_SHIFT);
             }
         if (tap_per_image) *tap_per_image = maps * pixels;

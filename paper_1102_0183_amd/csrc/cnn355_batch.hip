@@ -697,7 +697,7 @@ __global__ void __launch_bounds__(BT, first_waves(T, H)) k_batch_first(BatchFirs
   constexpr int N = 8 * H, ROWS = T * 32;
   const int tid = threadIdx.x, lane = tid & 63, lrow = lane & 31, lk = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int j0 = blockIdx.y * ROWS;
+  const int j0 = max(0, (int)blockIdx.y * ROWS - g.shift), end = min(g.Mo, ((int)blockIdx.y + 1) * ROWS - g.shift);   // maps
   char* lds_h = lds_s;                                   // [T][H][high, low][k / 8 mod 2][32 maps][8] halves
   float* lds_f = (float*)(lds_h + T * H * 2048);         // [k_total][ROWS] weights
   float* lds_b = lds_f + g.k_total * ROWS;               // [ROWS] biases
@@ -830,7 +830,7 @@ __global__ void __launch_bounds__(BT, first_waves(T, H)) k_batch_first(BatchFirs
       if (!splits) continue;
 #pragma unroll
       for (int m = 0; m < T; ++m) {
-        if (m && j0 + m * 32 >= g.Mo) break;
+        if (m && j0 + m * 32 >= end) break;
         const char* w = lds_h + m * H * 2048 + lane * 16;
         v16f acc;
 #pragma unroll
@@ -866,14 +866,14 @@ __global__ void __launch_bounds__(BT, first_waves(T, H)) k_batch_first(BatchFirs
     asm volatile("" : "+v"(lk4));
     // the outputs of four maps of a lane
     auto outputs = [&](int m, int v4, int row, float sum, float (&sv)[4]) {
-      const bool part = j0 + m * 32 + v4 * 2 + 8 > g.Mo;
+      const bool part = j0 + m * 32 + v4 * 2 + 8 > end;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         float x = u ? best[m][v4 + u] : sum;
         if (share)
           for (int o = 0; o < 4; ++o) x = fmaxf(x, ex[(o * T + m) * 1024 + (v4 + u) * 64 + lane]);
         sv[u] = b_act(ldexpf(x, lds_e[row + u]) + lds_b[row + u]);
-        if (part && j0 + row + u >= g.Mo) sv[u] = 0.f;   // (maps that fill the last group of eight up)
+        if (part && j0 + row + u >= end) sv[u] = 0.f;   // (maps that fill the last group of eight up)
       }
     };
     auto out_of = [&](int first) { return (CNN_GLOBAL char*)g.out + (size_t)((unsigned)(j0 + first) >> 3) * 2 * plane; };
@@ -883,7 +883,7 @@ __global__ void __launch_bounds__(BT, first_waves(T, H)) k_batch_first(BatchFirs
 #pragma unroll
       for (int v4 = 0; v4 < 16; v4 += 4) {
         const int first = m * 32 + v4 * 2;
-        if (j0 + first >= g.Mo) break;
+        if (j0 + first >= end) break;
         if (share && (m * 4 + v4 / 4) % 4 != wave) continue;
         float sv[4];
         outputs(m, v4, first + lk4, best[m][v4], sv);
@@ -911,7 +911,7 @@ __global__ void __launch_bounds__(BT, first_waves(T, H)) k_batch_first(BatchFirs
 #pragma unroll
           for (int v4 = 0; v4 < 16; v4 += 4) {
             const int first = m * 32 + v4 * 2;
-            if (j0 + first >= g.Mo) break;
+            if (j0 + first >= end) break;
             if (share && (m * 4 + v4 / 4) % 4 != wave) continue;
             float sum = best[m][v4], sv[4];
             asm volatile("" : "+v"(lk4), "+v"(sum));   // (or what is worked out above is kept in registers for here)
@@ -1129,7 +1129,7 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
                 if (marked) {
                   const int px = FC ? min(cb * COLS + (pbase[ct] >> 4), g.n_win - 1) * g.pix + vg - eight * g.pix
                                     : first + ((pbase[ct] + k - c * 2 * plane) >> 4);
-                  whole = g.in_marks.at[(g.in_plane >> 4) * fast_div(eight, g.by_eights) + px] != 0;
+                  whole = g.in_marks.at[(g.in_plane >> 4) * fast_div(eight + g.in_shift, g.by_eights) + px] != 0;
                 }
 #pragma unroll
                 for (int i = 0; i < 8; ++i) x[ct][i] = whole ? whole_of(ph[i], pl[i]) : (float)ph[i] + (float)pl[i];

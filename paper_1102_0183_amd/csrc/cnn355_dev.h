@@ -339,7 +339,8 @@ struct BatchSplit {
   int drop;                      // sums that are no number count as -inf (as where the 32-bit product's planes are added)
   SplitMarks in_marks, out_marks;
   int in_groups;                 // groups of in_marks
-  FastDiv by_eights;             // groups of eight maps of such a group
+  FastDiv by_eights;             // groups of eight maps of such a group, the first one
+  int in_shift;                  //   in_shift shorter
   int cps, raw;                  // chunks of a slice of the k range, one per blockIdx.z; raw: sums without bias and activation,
   long long slice_stride;        //   a plane for every slice, slice_stride floats apart
 };
@@ -368,6 +369,7 @@ struct BatchFirst {
   int n_win, k_total, row;
   int T, H;                      // tiles of 32 maps a workgroup (0: the layer is not planned so); steps of 16 k
   int share;                     // 1: four wavefronts share the members of 32 windows
+  int shift;                     // maps that the first workgroup's tiles are short of, a multiple of eight
   int split_out;                 // pixels of the output's planes
   SplitMarks out_marks;
 };

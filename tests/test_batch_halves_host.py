@@ -61,3 +61,17 @@ def test_running_sums_end_after_32_groups(arch):
     for batch in BATCHES:
         for p in binding.batch_plan(arch, batch)[0]:
             assert not p["split"] or p["split_slab"] <= 32, (batch, p)
+
+
+@pytest.mark.parametrize("maps", range(33, 335, 5))
+def test_no_workgroup_of_the_first_layer_has_few_maps(maps):
+    """One or two maps of a pixel are all tiny by chance, which the layer behind takes for a layer of tiny activations there."""
+    for arch in ("1x29x29-%dC4-MP2-40C5-MP3-150N-10N", "3x32x32-%dC3-MP2-100C2-MP2-10N", "3x32x32-%dC5-MP2-64C5-MP2-10N", "2x96x96-%dC6S1-MP2-150C4-MP4-5N"):
+        for batch in (33, 300):
+            p = binding.batch_plan(arch % maps, batch)[0][0]
+            if not p["first"] or maps <= p["first_T"] * 32:
+                continue
+            rows = p["first_T"] * 32
+            groups = -(-maps // rows)
+            assert maps + p["first_shift"] <= groups * rows and p["first_shift"] % 8 == 0
+            assert maps - ((groups - 1) * rows - p["first_shift"]) > 8, (arch % maps, batch, p)

@@ -84,3 +84,20 @@ def test_a_layer_of_small_weights_below_one_of_large_ones(layer, scale):
     imgs = (np.random.default_rng(32).random((batch, g.image_size)) * 2 - 1).astype(np.float32)
     _check(g, o, imgs, batch, 4, [0, 64, batch - 1])
     g.close()
+
+
+@pytest.mark.parametrize("arch,batch,T,share", [("3x16x16-37C3-MP1-33C3-MP2-4N", 33, 1, 0), ("4x14x14-70C5-MP2-33C2-MP2-4N", 7, 1, 1),
+                                                ("1x15x15-197C2-MP1-80C3-MP2-4N", 130, 2, 0), ("3x17x17-200C5-MP1-48C4-MP2-4N", 300, 2, 0),
+                                                ("1x28x28-69C5-MP2-33C1-MP2-4N", 130, 2, 1), ("4x15x15-326C2-MP2-80C4-MP1-4N", 300, 5, 0)])
+def test_groups_of_maps_that_begin_eight_earlier(arch, batch, T, share):
+    """The first layer's workgroups where the last one takes eight maps from the one in front of it, some images tiny."""
+    print("case", arch, batch, flush=True)
+    p = binding.batch_plan(arch, batch)[0]
+    assert p[1]["split"] and (p[0]["first_T"], p[0]["first_share"], p[0]["first_shift"]) == (T, share, 8), p[0]
+    g, o = build_pair(arch=arch, wscale=0.1)
+    _no_biases(g, o)
+    imgs = (np.random.default_rng(33).random((batch, g.image_size)) * 2 - 1).astype(np.float32)
+    imgs[1] *= np.float32(1e-6)
+    imgs[2] *= np.float32(1e-12)
+    _check(g, o, imgs, batch, 2, [0, 1, 2, 3, batch - 1])
+    g.close()

@@ -1223,8 +1223,6 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
       auto finish = [&](int r, float sv, int e) {
         sv = ldexpf(sv, e);
         if constexpr (FC)
-          if (g.raw) return sv;
-        if constexpr (FC)
           if (g.drop) sv = fmaxf(sv, -INFINITY);
         return b_act(sv + lds_b[r]);
       };
@@ -1264,6 +1262,17 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
           if (!g.split_out) {
             const int b = ok ? fast_div(w, g.by_win_img) : 0, wi = ok ? w - b * g.win_img : 0;
             const unsigned o0 = (unsigned)b * (unsigned)g.out_stride + (unsigned)wi;
+            if constexpr (FC)
+              if (g.raw) {   // (not a branch of every output: the code jumped to and fro, a trip to memory each time)
+#pragma unroll
+                for (int m = 0; m < RT; ++m)
+#pragma unroll
+                  for (int v = 0; v < AV; ++v) {
+                    const int row = row_of(m, v);
+                    if (ok && j0 + row < g.Mo) out_z[o0 + (unsigned)(j0 + row)] = ldexpf(tot[m][ct][v], lds_e[row]);
+                  }
+                continue;
+              }
 #pragma unroll
             for (int m = 0; m < RT; ++m) {
 #pragma unroll

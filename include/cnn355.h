@@ -7,8 +7,9 @@
  * C ABI.  Pointers named d_* are DEVICE pointers (memory of the current HIP device, owned
  * by the caller); pointers named host_* are HOST pointers.  The library allocates no
  * device memory: everything it needs on the device lives in the workspace the caller
- * hands to cnn_create and must keep alive until cnn_destroy.  All arithmetic is fp32
- * (the paper's GPU precision, Sec. 4); indices are integers.
+ * hands to cnn_create and must keep alive until cnn_destroy.  Inputs, weights, sums and results
+ * are fp32 (the paper's GPU precision, Sec. 4), and so is all arithmetic but the products of the
+ * batched forward pass (cnn_forward_batch); indices are integers.
  *
  * Errors: every int-returning call gives 0 on success or one of the negative codes below;
  * nothing throws or aborts across this boundary.  Device work is asynchronous on the
@@ -165,7 +166,12 @@ int cnn_set_weights(cnn_t* net, const float* host_src, size_t n);
 /* Forward propagation of many images at once (Sec. 3.2; validation and test passes change no
  * weight, Sec. 4, so their images are independent).  Every layer becomes one matrix product over
  * the whole batch on the matrix cores, fp32 in and out; results agree with cnn_forward_many to
- * rounding (other summation order), whatever the mode of the handle.
+ * rounding, whatever the mode of the handle.  The sums have another order, and where a convolutional
+ * layer follows another one, and behind it, operands are split into two halves of 11 bits each and
+ * three of their four products are summed in fp32: an operand keeps 23 bits, or 2^-39 of the largest
+ * weight of its row, 2^-23 of the largest activation or pixel that is split with it.  What does not split
+ * (infinities, NaN, pixels of 4 and more, activations that are all tiny) takes products in fp32, with
+ * what is worked on beside it: an image's last bits may depend on the images of its batch.
  *   cnn_forward_batch_scratch_bytes: device memory that is enough for `batch` images in flight
  *     (re-packed weights, the layer outputs of one batch); the caller allocates it.
  *   cnn_forward_batch: d_images [n][cnn_image_size], d_probs [n][cnn_num_classes] (probabilities, or

@@ -302,7 +302,7 @@ struct BatchConv {
 // A convolutional layer behind another one, over a whole batch, in products of halves (k_batch_split).  Activations are
 // written by the layer below as v * 2^SPLIT_SHIFT = high + low, both halves, in groups of eight maps:
 // [group][high, low][pixel of the batch][8], so that what a block of columns reads of a group is one run; the maps that fill
-// the last group up are zero.  The sum of the halves is off by at most 2^-24 of v where |v| >= 2^-16, and by 2^-39 below: where
+// the last group up are zero.  The sum of the halves is off by at most 2^-23 of v where |v| >= 2^-16, and by 2^-39 below: where
 // all that a workgroup of the layer below writes of a pixel is smaller than SPLIT_TINY, and not zero, these values are stored
 // as they are (SplitMarks).
 constexpr int SPLIT_SHIFT = 14;         // |activation| <= 1.7159: below the largest half

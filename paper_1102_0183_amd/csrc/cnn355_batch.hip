@@ -993,7 +993,6 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
     lds_b[tid] = j0 + tid < g.Mo ? b_row : 0.f;
   }
   slow = __builtin_amdgcn_readfirstlane(__syncthreads_or(slow));
-  const bool marked = __builtin_amdgcn_readfirstlane(any_marks) != 0;
   const int n_chunks = g.n_cg / g.IC, ch_first = FC ? blockIdx.z * g.cps : 0, ch_end = FC ? min(n_chunks, ch_first + g.cps) : n_chunks;
   const int slabs = (g.n_kg + g.slab - 1) / g.slab, M = FC ? 1 : g.Kp * g.Kpx;
   const int longest = min(SPLIT_RUN, n_chunks * g.n_kg / 2);
@@ -1058,6 +1057,7 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
     }
     return __builtin_amdgcn_readfirstlane(__syncthreads_or(found)) == 0;
   };
+  bool marked = false;
   auto run = [&](auto careful) {
     constexpr bool CAREFUL = decltype(careful)::value;
     // (what the lanes need is worked out once more: kept from the products of halves it cost those registers)
@@ -1407,16 +1407,13 @@ __global__ void __launch_bounds__(BT, split_waves(RT, CT, TR)) k_batch_split(Bat
     }
   };
   // Products in 32 bits for a group with an infinite weight, and, behind those of halves, for blocks that read values that are no
-  // halves (not in front of them where no block of the workgroup's is without).  Code of its own: as a branch of the step loop it
-  // cost the products of halves 2 % (30 registers), as one of a block 3 to 6 %.  4096 digits: 175 us a call in halves; with an
-  // infinity in every 97th weight 418 (35600 with the sums of such rows by a thread an output), with all weights 1e-7 of that 452;
-  // 512 images of 300 maps a layer 500, 1490 (214000) and 1560.
-  bool halves = !slow;
-  if (halves && marked) {
-    halves = false;
-    for (int cb = blockIdx.x; cb < g.n_cb && !halves; cb += gridDim.x) halves = all_halves(cb);
-  }
-  if (halves) run(std::false_type{});
+  // halves: they are done again.  (Whether there are such values is asked for at the start and looked at here: a wait for it in
+  // front of the halves cost every launch 0.5 us, 281 images of 20C4 11C5 182 us a call and 179.5.)  Code of its own: as a branch of
+  // the step loop it cost the products of halves 2 % (30 registers), as one of a block 3 to 6 %.  4096 digits: 148 us a call in
+  // halves; with an infinity in every 97th weight 402 (35600 with the sums of such rows by a thread an output), with all weights 1e-7
+  // of that 519; 512 images of 300 maps a layer 431, 1467 (214000) and 1850.  k_batch_conv and k_batch_gemm took 292 and 1151.
+  if (!slow) run(std::false_type{});
+  marked = __builtin_amdgcn_readfirstlane(any_marks) != 0;
   if (slow || marked) run(std::true_type{});
 }
 

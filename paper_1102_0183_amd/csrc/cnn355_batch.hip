@@ -686,7 +686,8 @@ __global__ void __launch_bounds__(BT, MT * TR > 96 ? 2 : 3) k_batch_conv(BatchCo
 // and these layers have as much of the one as of the other.  300C3 on 3 maps, 512 images: k_batch_conv 177 us, this kernel with
 // 32-bit products 146, with halves 90 (105 in a trace of whole passes); 20C4 of 4096 digits 77, 51, 45.
 // Pixels that do not split (4 and larger, infinite, or all of a lane's below 2^-14 and not zero) and weights that do not (not
-// finite, or all of a row's below 2^-81) take 32-bit products, member by member.
+// finite, or all of a row's below 2^-81) take 32-bit products, member by member, for the 32 windows of a wavefront (images of 0..255:
+// 4096 digits 148 -> 162 us a call, 512 images of 300 maps a layer 431 -> 485; k_batch_conv's nets 292 and 1151).
 constexpr int first_waves(int T, int H) {   // wavefronts a SIMD, by the registers of pixels, offsets, halves and sums
   const int regs = (H <= 4 ? 24 : 16) * H + 16 * T + 72;
   return regs <= 124 ? 4 : regs <= 164 ? 3 : 2;
@@ -932,23 +933,23 @@ __global__ void __launch_bounds__(BT, first_waves(T, H)) k_batch_first(BatchFirs
 // 64 bits below that of the 32-bit products.  The layer below has split its activations already (put_split), in groups of eight
 // maps, so that a lane's eight k are one 16-byte read from LDS: k = (group of eight maps, ky, kx, map of the group).
 // What a workgroup writes of a window is stored as floats where all of it is tiny (SplitMarks): the largest output is kept along
-// with the stores, and the stores are done again where it is.  40C5 of 4096 digits 81.3 -> 83.1 us with it, the first layer's 20C4
-// 46.1 -> 46.9, 100N of 33 stereo pairs 8.4 -> 9.2 (it waits for the word that says whether there is such a window).
+// with the stores, and the stores are done again where it is.  40C5 of 4096 digits 76.8 -> 80.2 us with it, the first layer's 20C4
+// 43.6 -> 45.9, 300C2 of 512 images 225 -> 227 (one trace).
 // Error against 64 bits (2-norm, of a layer's outputs from the images on, 32-bit products / halves): 300C4 behind 300C2 behind
 // 300C3 10.8e-7 / 3.4e-7, 300C2 5.8 / 2.2, 40C5 behind 20C4 4.8 / 2.4, 128C3 behind 50C5 2.3 / 2.0; of 300C4 alone 5.7 / 3.3, and
 // 8.8 without runs.
 // Staging as in k_batch_conv: the next slab of weights (a run of the k range, packed in the order it is read) and the next
 // chunk of input maps go to the other halves of their buffers by 16-byte loads to LDS while the present ones are multiplied,
 // one barrier a slab, nothing between two column blocks.
-// Bound by the issue of instructions beside the matrix pipes (40 % busy in 300C2) and by the waits of a slab; larger tiles, one
-// wavefront a SIMD, were slower (300C2: 128 x 256 columns 694 us of the pass, 64 x 256 543).  Against k_batch_conv, under the
-// tracer: 300C2 of 512 images 743 -> 235 us (305 TFLOP/s of the layer's own sums), 300C4 234 -> 98, 40C5 of 4096 digits 184 ->
-// 80, 128C3 of 33 stereo pairs 42 (with its k_batch_pool) -> 16.  (In a trace of whole passes, hidden layers in this kernel too:
-// 300C2 262, 300C4 112, 40C5 81, 128C3 16.)
+// Matrix pipes 40 % busy in 300C2: a step's other instructions fit beside the products of two wavefronts a SIMD, what lies outside
+// the steps does not: a wait for all loads and a barrier a slab, and, a block, scalars that the compiler keeps in lanes of vector
+// registers.  Larger tiles, one wavefront a SIMD, were slower (300C2: 128 x 256 columns 694 us of the pass, 64 x 256 543).  Against
+// k_batch_conv, in traces of whole passes: 300C2 of 512 images 772 -> 227 us (318 TFLOP/s of the layer's own sums), 300C4 235 -> 89,
+// 40C5 of 4096 digits 183 -> 80, 128C3 of 33 stereo pairs 42 (with its k_batch_pool) -> 16.
 // FC: a fully connected layer behind such a layer.  A column is an image, and a lane of a staging load fetches an image's eight
 // maps at one pixel (16 bytes a line of memory; neighbouring pixels follow in the same chunk and meet it in the caches); the k
-// range in slices where the images are few.  Against k_batch_gemm and its k_batch_pool: 150N of 4096 digits 30 us -> 14.3, 300N of
-// 512 images 27 -> 14.2, 100N of 33 stereo pairs 21.5 -> 8.4.
+// range in slices where the images are few.  Against k_batch_gemm and its k_batch_pool: 150N of 4096 digits 30 us -> 13.6, 300N of
+// 512 images 27 -> 12.9, 100N of 33 stereo pairs 21.5 -> 8.0.
 // wavefronts a SIMD, by the registers of sums, totals and two sets of columns
 constexpr int split_waves(int RT, int CT, int TR) {
   const int regs = 2 * RT * CT * (TR == 32 ? 16 : 4) + 16 * CT + 48;
